@@ -38,6 +38,7 @@ namespace sk {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));  // at any element's address
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -207,15 +208,6 @@ __device__ __forceinline__ void store4(void *C, int64_t row_off, int n, int n_en
   }
 }
 
-template <int ES, bool NT>
-__device__ __forceinline__ u32x4 load_piece_vec(const void *base, int64_t off) {
-  const u32x4 SK_GLOBAL *p = (const u32x4 SK_GLOBAL *)(as_global<char>(base) + off * ES);
-  if constexpr (NT)
-    return __builtin_nontemporal_load(p);
-  else
-    return *p;
-}
-
 // The MFMA paths below require both operands to be readable in aligned 16-byte
 // pieces (FLAG_VEC_A and FLAG_VEC_B: 16-byte aligned bases and row strides, Kg
 // and, for a convolution, Cin multiples of a piece).  Everything else goes
@@ -239,15 +231,58 @@ __device__ __forceinline__ uintptr_t zero_piece_address() {
   asm volatile("" : "+v"(z));
   return z;
 }
-template <int ES, bool NT>
+template <int ES, bool ANY>
 __device__ __forceinline__ u32x4 fetch_B(const DevProblem &P, int64_t row_off, int k, bool ok, uintptr_t zeros) {
+  using piece_t = typename std::conditional<ANY, u32x4_any, u32x4>::type;
   const uintptr_t p = (uintptr_t)P.B + (uintptr_t)((row_off + k) * ES);
-  const u32x4 SK_GLOBAL *q = (const u32x4 SK_GLOBAL *)(ok ? p : zeros);
-  if constexpr (NT)
-    return __builtin_nontemporal_load(q);
-  else
-    return *q;
+  return __builtin_nontemporal_load((const piece_t SK_GLOBAL *)(ok ? p : zeros));
 }
+
+// ---- pieces at any element's address ----
+// (The hardware reads 16 bytes from any address in one instruction.)
+// Element e of the result is element e + sh of v; what would come from beyond v's ends is zero.
+template <int ES>
+__device__ __forceinline__ u32x4 shift_piece(const u32x4 &v, int sh) {
+  const int n = (sh < 0 ? -sh : sh) * (ES / 2);  // in halves
+  const bool d1 = n & 2, d2 = n & 4, gone = n >= 8;
+  const uint32_t bits = (n & 1) * 16;
+  u32x4 r = v;
+  if (__any(sh > 0)) {  // towards lower places
+    const u32x4 s = {d1 ? v[1] : v[0], d1 ? v[2] : v[1], d1 ? v[3] : v[2], d1 ? 0u : v[3]};
+    const u32x4 t = {d2 ? s[2] : s[0], d2 ? s[3] : s[1], d2 ? 0u : s[2], d2 ? 0u : s[3]};
+    const u32x4 u = {__builtin_amdgcn_alignbit(t[1], t[0], bits), __builtin_amdgcn_alignbit(t[2], t[1], bits),
+                     __builtin_amdgcn_alignbit(t[3], t[2], bits), t[3] >> bits};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = sh > 0 ? (gone ? 0u : u[i]) : r[i];
+  }
+  if (__any(sh < 0)) {  // towards higher places
+    const u32x4 s = {d1 ? 0u : v[0], d1 ? v[0] : v[1], d1 ? v[1] : v[2], d1 ? v[2] : v[3]};
+    const u32x4 t = {d2 ? 0u : s[0], d2 ? 0u : s[1], d2 ? s[0] : s[2], d2 ? s[1] : s[3]};
+    // (alignbit shifts right: by 32 - bits, written as a left shift of the pair by `bits`)
+    const u32x4 u = {t[0] << bits, bits ? __builtin_amdgcn_alignbit(t[1], t[0], 16) : t[1],
+                     bits ? __builtin_amdgcn_alignbit(t[2], t[1], 16) : t[2], bits ? __builtin_amdgcn_alignbit(t[3], t[2], 16) : t[3]};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = sh < 0 ? (gone ? 0u : u[i]) : r[i];
+  }
+  return r;
+}
+// Elements below `lo` and from `hi` on become zero.
+template <int ES>
+__device__ __forceinline__ u32x4 mask_piece(const u32x4 &v, int lo, int hi) {
+  u32x4 r = v;
+  if constexpr (ES == 4) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = (e >= lo && e < hi) ? v[e] : 0u;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t m = ((2 * e >= lo && 2 * e < hi) ? 0xffffu : 0u) | ((2 * e + 1 >= lo && 2 * e + 1 < hi) ? 0xffff0000u : 0u);
+      r[e] = v[e] & m;
+    }
+  }
+  return r;
+}
+__device__ __forceinline__ u32x4 load_any(uintptr_t p) { return *(const u32x4_any SK_GLOBAL *)p; }
 
 // n / d with d given as multiplier and shift (FastDiv), 0 <= n < 2^31.
 __device__ __forceinline__ int fast_div(int n, const uint32_t (&d)[2]) {
@@ -282,15 +317,7 @@ __device__ __forceinline__ RowA row_of(const DevProblem &P, int m) {
   return r;
 }
 
-// Channel-major convolutions (element-wise paths only).  Element strides of the image along
-// filter row, filter column and channel, and where output (m, n) lives in Y[Nb,Cout,Ho,Wo].
-struct ImageStrides {
-  int64_t sh, sw, sc;
-};
-__device__ __forceinline__ ImageStrides image_strides(const DevProblem &P) {
-  if (P.nchw) return ImageStrides{(int64_t)P.W, 1, (int64_t)P.H * P.W};
-  return ImageStrides{(int64_t)P.W * P.Cin, (int64_t)P.Cin, 1};
-}
+// Channel-major convolutions: where output (m, n) lives in Y[Nb,Cout,Ho,Wo].
 __device__ __forceinline__ int64_t nchw_out_base(const DevProblem &P, int m) {
   const int hw = P.Ho * P.Wo;
   const int b = fast_div(m, P.div_hw);
@@ -305,25 +332,12 @@ __device__ __forceinline__ void store_elem(void *C, int64_t off, float v) {
     *(uint16_t SK_GLOBAL *)c = (uint16_t)cvt_bits<DT>(v);
 }
 
-// Element k of the implicit patch row: k = (r*S + s)*Cin + c  ->  pixel (hb+r, wb+s), channel c.
-__device__ __forceinline__ bool patch_offset(const DevProblem &P, const RowA &row, int k, int64_t &off) {
-  const int tap = fast_div(k, P.div_cin);
-  const int c = k - tap * P.Cin;
-  const int r = fast_div(tap, P.div_s);
-  const int s = tap - r * P.S;
-  const int h = row.hb + r, w = row.wb + s;
-  off = row.base + ((int64_t)r * P.W + s) * P.Cin + c;
-  return (unsigned)h < (unsigned)P.H && (unsigned)w < (unsigned)P.W;
-}
-
-// Activation piece: elements k .. k+CE-1 of row `row` of A'.  Where the piece must read as
-// zero (`ok` false on entry, or the tap falls into the padding) the piece of zeros is loaded.
-template <int ES>
-__device__ __forceinline__ u32x4 fetch_A(const DevProblem &P, const RowA &row, int k, bool ok, uintptr_t zeros) {
-  int64_t off = row.base + k;
-  if (P.gather) ok = patch_offset(P, row, k, off) && ok;
+// Activation piece at element `off` of the operand; where !ok the piece of zeros.
+template <int ES, bool ANY>
+__device__ __forceinline__ u32x4 fetch_A(const DevProblem &P, int64_t off, bool ok, uintptr_t zeros) {
+  using piece_t = typename std::conditional<ANY, u32x4_any, u32x4>::type;
   const uintptr_t p = (uintptr_t)P.A + (uintptr_t)(off * ES);
-  return *(const u32x4 SK_GLOBAL *)(ok ? p : zeros);
+  return *(const piece_t SK_GLOBAL *)(ok ? p : zeros);
 }
 
 // Single elements as float, for run_generic.
@@ -526,7 +540,12 @@ struct Prefetch {
 };
 constexpr int CLAIM_LEAD = 8, ISSUE_GAP = 4;
 
-template <int DT, int RM>
+//
+// ANY: operands at any element's address, and GEMMs whose reduction length is not a multiple of a piece.  The
+// piece that would reach beyond the end of a row is read so that it ends with the row, and shifted into
+// place (shift_piece) when it is used; only the last block of a row has such pieces.  Everything else is
+// the same, so aligned operators of a plan that has others too run through this form as well.
+template <int DT, int RM, bool ANY>
 __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T, const SplitK &sp,
                                            unsigned char *lds, uint32_t *s_flag, Prefetch &pf) {
   constexpr int ES = Elem<DT>::ES;
@@ -570,6 +589,8 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
   const RowA srow = row_of(P, s_ok ? s_row : 0);
   const int s_lds = s_row * LROW + s_piece * 16;
   u32x4 ar[SPT];
+  int ar_k = 0;  // (ANY) reduction index of ar[0]
+  const bool ragged = ANY && P.Kg % CE != 0;  // some pieces end beyond their row
   // For a convolution: filter tap (g_r, g_s) and channel g_c of this thread's first piece in the
   // chunk that stage_load will fetch next, and g_off = ((g_r*W + g_s)*Cin + g_c), its distance in
   // elements from the pixel under tap (0,0).  Chunks are fetched in order (0, 1, ..., then 0 again
@@ -590,8 +611,12 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
   auto stage_load = [&](int c) {
     const int k = k0 + ((c << BPC_LOG2) * 8 + s_piece) * CE;
     if (!P.gather) {
+      ar_k = k;
 #pragma unroll
-      for (int i = 0; i < SPT; ++i) ar[i] = fetch_A<ES>(P, srow, k + i * CE, s_ok && k + i * CE < k_stop, zeros);
+      for (int i = 0; i < SPT; ++i) {
+        const int at = ANY ? min(k + i * CE, P.Kg - CE) : k + i * CE;
+        ar[i] = fetch_A<ES, ANY>(P, srow.base + at, s_ok && k + i * CE < k_stop, zeros);
+      }
       return;
     }
     if (c == 0) {
@@ -608,8 +633,7 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
     for (int i = 0; i < SPT; ++i) {
       const bool ok = s_ok && k + i * CE < k_stop && (unsigned)(srow.hb + r) < (unsigned)P.H &&
                       (unsigned)(srow.wb + t) < (unsigned)P.W;
-      const uintptr_t pa = (uintptr_t)P.A + (uintptr_t)((srow.base + off) * ES);
-      ar[i] = *(const u32x4 SK_GLOBAL *)(ok ? pa : zeros);
+      ar[i] = fetch_A<ES, ANY>(P, srow.base + off, ok, zeros);
       cc += CE;
       off += CE;
       const bool next_tap = cc >= P.Cin;
@@ -635,6 +659,13 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
   };
   auto stage_store = [&](int c) {
     unsigned char *base = lds + (c & 1) * BUF + s_lds;
+    if (ragged) {
+#pragma unroll
+      for (int i = 0; i < SPT; ++i) {
+        const int past = ar_k + (i + 1) * CE - P.Kg;  // how far the piece reaches beyond its row (a whole piece: zeros)
+        if (__any(past > 0)) ar[i] = shift_piece<ES>(ar[i], max(past, 0));
+      }
+    }
 #pragma unroll
     for (int i = 0; i < SPT; ++i) *(u32x4 *)(base + i * 16) = ar[i];
   };
@@ -673,7 +704,7 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
     const int k = k0 + p_blk * KB + piece * CE;
     const bool in = p_act && k < k_stop;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = fetch_B<ES, true>(P, wrow[j], k, in, zeros);
+    for (int j = 0; j < 4; ++j) w[j] = fetch_B<ES, ANY>(P, wrow[j], ANY ? min(k, P.Kg - CE) : k, in, zeros);
     if (++p_blk == nslots) {
       p_blk = 0;
       ++p_it;
@@ -756,6 +787,11 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
             a1[mb] = *(const u32x4 *)(abase + mb * 16 * LROW + 64);  // pieces 4..7
           }
           __builtin_amdgcn_sched_barrier(0);  // (the scheduler would sink the reads back to their uses)
+          if (ragged && k0 + (blk + 1) * KB > P.Kg) {  // the last block of the rows
+            const int past = k0 + blk * KB + (piece + 1) * CE - P.Kg;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[u][j] = shift_piece<ES>(w[u][j], max(past, 0));
+          }
           // rows 16rb..16rb+15: pieces 0..3 (x) and 4..7 (y) in MFMA lane order
           const u32x4 x0 = fix_lo(w[u][0], w[u][1]), y0 = fix_hi(w[u][0], w[u][1]);
           const u32x4 x1 = fix_lo(w[u][2], w[u][3]), y1 = fix_hi(w[u][2], w[u][3]);
@@ -1750,52 +1786,125 @@ __device__ __forceinline__ void run_generic(const DevProblem *P_mem, const sk_ti
 
 // ---------------------------------------------------------------------------
 // MFMA tiles for operands of any alignment (an image with 3 channels, an odd
-// reduction length, unaligned bases): the staging map and the LDS layout of
-// run_tile, but a 16-byte piece is put together from single elements, loaded one
-// by one, and a stage is loaded, stored to LDS and multiplied before the next
-// one is touched (the unpacked elements of one stage fill the registers that
-// the packed pieces of a ring of stages would).  Any output rectangle is
-// walked in blocks of 128 x 128; the slices of a split reduction (always a
-// single block) meet in the workspace like those of the other tile classes.
+// reduction length, unaligned bases) and for channel-major images
 // ---------------------------------------------------------------------------
-template <int DT>
+// The LDS image, fragments and MFMAs of run_tile; any output rectangle is walked in blocks of 128 x 128, and
+// the slices of a split reduction (always a single block) meet in the workspace like those of the other classes.
+// What a stage costs here is getting its 256 rows of 128 bytes into LDS, so:
+//   * the hardware reads 16 bytes from any element's address in one instruction.  A reduction is taken as runs
+//     of contiguous elements (a GEMM row; for an NHWC convolution the S * Cin elements under one filter row),
+//     each padded to whole 16-byte pieces.  A piece that reaches beyond the run, or beyond the part of it that
+//     lies in the image, is read from the nearest place inside and shifted, with zeros behind it.
+//   * a channel-major image has no contiguous runs along the reduction.  There the lanes of a wave take
+//     64 consecutive pixels under one reduction index (channel and tap are scalar; whether a pixel's tap lies in
+//     the image is one bit each of a row and a column mask), so a load of single elements is one
+//     coalesced access and costs three vector instructions beside it.  The block is computed transposed (output
+//     channels as MFMA rows), so that a lane ends up with consecutive pixels of one channel plane.
+//   * the loads of a stage are in flight while the one before it is multiplied (two LDS images).
+// Bound by the vector instructions that place a stage's pieces (addresses, shifts, packing of single elements) on
+// two waves per SIMD, not by memory.  Measured before / after, against pieces put together element by element with
+// one stage at a time and no loads in flight beside the MFMAs: seven stride-2 layers with the 7x7 stem for
+// sixteen tenants 167 -> 126 us, the channel-major ResNet layers for eight 208 -> 162 us, 96 operators of odd sizes in
+// three types 306 -> 232 us.
+
+// Whether both operands hold at least 16 bytes.  (Channel-major images are read element by element.)
+template <int ES>
+__device__ __forceinline__ bool holds_a_piece(const DevProblem &P) {
+  constexpr int CE = 16 / ES;
+  const int64_t a = P.gather ? (int64_t)P.H * P.W * P.Cin : (int64_t)(P.Mg - 1) * P.lda + P.Kg;
+  return (P.nchw || a >= CE) && (int64_t)(P.Ng - 1) * P.ldb + P.Kg >= CE;
+}
+
+template <int DT, bool NCHW>
 __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_tile *T_mem, const SplitK &sp,
                                              unsigned char *lds, uint32_t *s_flag) {
   constexpr int ES = Elem<DT>::ES;
   constexpr int CE = 16 / ES;
-  constexpr int KB = 8 * CE;
+  constexpr int STAGE = 256 * LDS_ROW;  // pixels (or GEMM rows), then weight rows
+  constexpr uint32_t NOWHERE = 0x80000000u;
   using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
-  const DevProblem P = *P_mem;
-  const sk_tile T = *T_mem;
+  typedef elem_t piece_t __attribute__((ext_vector_type(CE)));
+  static_assert(2 * STAGE <= LDS_TILE_BYTES, "two stages do not fit the LDS buffer");
+  const DevProblem P = load_uniform(P_mem);
+  const sk_tile T = load_uniform(T_mem);
   const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave & 1, wn = wave >> 1;
   const int l32 = lane & 31, half = lane >> 5;
   const int c8 = tid & 7, srow = tid >> 3;
-  const uintptr_t zeros = zero_piece_address();
   const int m_end = (int)T.m0 + (int)T.m_len, n_end = (int)T.n0 + (int)T.n_len;
-  const bool vec_c = (P.flags & FLAG_VEC_C) != 0;
-  const bool vec_b = (P.flags & FLAG_VEC_B) != 0;
-  const ImageStrides im = image_strides(P);
-  unsigned char *sa = lds + srow * LDS_ROW + c8 * 16;
-  unsigned char *sb = sa + 128 * LDS_ROW;
+  const int hw = P.Ho * P.Wo;
+
+  // reduction runs and their pieces; this record's slice are the pieces that start in it
+  const int run_len = !NCHW && P.gather ? P.S * P.Cin : P.Kg;
+  const int ppr = (run_len + CE - 1) / CE;
+  auto first_piece = [&](int k) {
+    const int run = k / run_len;
+    return run * ppr + (k - run * run_len + CE - 1) / CE;
+  };
+  const int p_begin = first_piece((int)T.k0), p_stop = first_piece((int)T.k0 + (int)T.k_len);
+  const int nstages = (p_stop - p_begin + 7) >> 3;
+
+  const int64_t a_run = (int64_t)P.W * P.Cin;  // elements from one filter row's run to the next in the image
+  // A piece is read from inside its run's valid elements [lo, hi) and shifted into place, which also leaves zeros
+  // where it reaches beyond them.  Runs too short for that (fewer valid elements than a piece somewhere): from
+  // the nearest place inside the whole operand, shifted, and masked.
+  const int fewest = !P.gather ? P.Kg : min(P.S, min(P.W, max(0, P.S - P.pad_w))) * P.Cin;
+  const bool short_a = NCHW || fewest < CE, short_b = run_len < CE;
+  const int64_t b_last = (int64_t)(P.Ng - 1) * P.ldb + P.Kg - CE;  // last place a piece may be read from
+  const int64_t a_last = (P.gather ? (int64_t)fast_div(P.Mg + hw - 1, P.div_hw) * P.H * P.W * P.Cin
+                                   : (int64_t)(P.Mg - 1) * P.lda + P.Kg) - CE;
+  const uintptr_t zeros = zero_piece_address();
 
   for (int mb = (int)T.m0; mb < m_end; mb += 128) {
-    RowA rows[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int m = mb + srow + 32 * i;
-      if (m >= m_end) m = m_end - 1;  // rows past the edge repeat the last row; never stored
-      rows[i] = row_of(P, m);
-    }
-    for (int nb = (int)T.n0; nb < n_end; nb += 128) {
-      int64_t wrow[4];
+    // ---- where this thread's rows of the activation operand lie ----
+    int64_t a_base[4];  // GEMM / NHWC: rows srow + 32 i; NCHW: rows lane and lane + 64
+    int a_lo[4], a_hi[4], a_h[4];
+    uint32_t n_off[2], n_rows[2], n_cols[2];  // NCHW, 32-bit form: byte offset from the descriptor's origin; taps outside
+    uintptr_t n_origin = 0;
+    uint32_t n_extent = 0;
+    bool near = false;
+    if constexpr (!NCHW) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        int n = nb + srow + 32 * i;
-        if (n >= n_end) n = n_end - 1;
-        wrow[i] = (int64_t)n * P.ldb;
+        int m = mb + srow + 32 * i;
+        if (m >= m_end) m = m_end - 1;  // rows past the edge repeat the last row; never stored
+        const RowA r = row_of(P, m);
+        a_base[i] = r.base;
+        a_h[i] = r.hb;
+        a_lo[i] = 0;
+        a_hi[i] = run_len;
+        if (P.gather) {
+          a_lo[i] = max(0, -r.wb) * P.Cin;
+          a_hi[i] = min(P.S, P.W - r.wb) * P.Cin;
+        }
       }
+    } else {
+      const int64_t image = (int64_t)P.Cin * P.H * P.W;
+      const int b0 = fast_div(mb, P.div_hw), b1 = fast_div(min(mb + 128, m_end) - 1, P.div_hw);
+      const int64_t corner = (int64_t)P.pad_h * P.W + P.pad_w;  // the corner of the padded image lies this far before it
+      near = ((b1 + 1 - b0) * image + corner) * ES < (int64_t)1 << 31;
+      n_origin = (uintptr_t)P.A + (uintptr_t)((b0 * image - corner) * ES);
+      n_extent = (uint32_t)(((b1 + 1 - b0) * image + corner) * ES);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        int m = mb + lane + 64 * h;
+        if (m >= m_end) m = m_end - 1;
+        const RowA r = row_of(P, m);
+        a_base[h] = r.base;
+        a_h[h] = r.hb;
+        a_lo[h] = r.wb;
+        n_off[h] = (uint32_t)((r.base + corner - b0 * image) * ES);
+        // bit r of the row mask: filter row r falls outside the image; the same for the filter columns
+        const int hlo = max(0, -r.hb), hhi = min(32, max(0, P.H - r.hb)), wlo = max(0, -r.wb), whi = min(32, max(0, P.W - r.wb));
+        n_rows[h] = ~((uint32_t)(((uint64_t)1 << hhi) - 1) & ~(uint32_t)(((uint64_t)1 << min(hlo, 32)) - 1));
+        n_cols[h] = ~((uint32_t)(((uint64_t)1 << whi) - 1) & ~(uint32_t)(((uint64_t)1 << min(wlo, 32)) - 1));
+      }
+    }
+    const __amdgpu_buffer_rsrc_t descA = __builtin_amdgcn_make_buffer_rsrc((void *)n_origin, 0, (int)n_extent, 0x00020000);
+
+    for (int nb = (int)T.n0; nb < n_end; nb += 128) {
+      const int64_t b_base = (int64_t)(nb + srow) * P.ldb;  // of this thread's first weight row; the others 32 rows apart
       f32x16 acc[2][2];
 #pragma unroll
       for (int fn = 0; fn < 2; ++fn)
@@ -1804,111 +1913,179 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
 #pragma unroll
           for (int i = 0; i < 16; ++i) acc[fn][fm][i] = 0.f;
 
-      // this record's slice of the reduction (all of it unless the rectangle is split)
-      const int k_stop = (int)T.k0 + (int)T.k_len;
-      for (int k0 = (int)T.k0; k0 < k_stop; k0 += KB) {
-        const int k = k0 + c8 * CE;  // first reduction index of this thread's pieces
-        // filter tap and channel of element k (convolutions); later elements by carrying
-        int g_r = 0, g_s = 0, g_c = 0;
-        if (P.gather && !P.nchw) {
-          const int tap = fast_div(k, P.div_cin);
-          g_c = k - tap * P.Cin;
-          g_r = fast_div(tap, P.div_s);
-          g_s = tap - g_r * P.S;
-        } else if (P.gather) {  // channel-major: k = (c*R + r)*S + s
-          const int cr = k / P.S;
-          g_s = k - cr * P.S;
-          g_c = cr / P.R;
-          g_r = cr - g_c * P.R;
-        }
-        elem_t va[4][CE], vb[4][CE];
-        // weight rows that can be read in 16-byte pieces (always so for channel-major convolutions with aligned
-        // weights: a weight row is contiguous in either storage order) are: half the loads of the stage
-        u32x4 wb16[4];
-        if (vec_b) {
+      // ---- the next stage to load: this thread's piece of it ----
+      int piece = p_begin + c8;
+      int run = piece / ppr, j = piece - run * ppr;
+      // NCHW: scalar position of the wave's first reduction index (2 pieces of every stage: 2 wave, 2 wave + 1)
+      int ks = (p_begin + 2 * wave) * CE, kc = 0, kr = 0, kt = 0;
+      if constexpr (NCHW) {
+        const int cr = ks / P.S;
+        kt = ks - cr * P.S;
+        kc = cr / P.R;
+        kr = cr - kc * P.R;
+      }
+      u32x4 ra[4], rb[4];
+      // Where the piece that starts at element e0 of its run is read (`o`: place of the run's start in the operand)
+      auto a_from = [&](int i, int e0, int64_t o) {
+        if (!short_a) return min(max(e0, a_lo[i]), a_hi[i] - CE);
+        int64_t at = o + e0;
+        at = at < a_last ? at : a_last;
+        return (int)((at > 0 ? at : 0) - o);
+      };
+      auto b_from = [&](int e0, int64_t o) {
+        if (!short_b) return min(e0, run_len - CE);
+        const int64_t at = o + e0;
+        return (int)((at < b_last ? at : b_last) - o);
+      };
+      int at_e0 = 0, at_run = 0, at_ks = 0;  // of the stage loaded last
+      auto gload = [&]() {
+        const bool in = piece < p_stop;
+        const int e0 = j * CE;
+        at_e0 = e0;
+        at_run = run;
+        if constexpr (!NCHW) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const uintptr_t pb = (uintptr_t)P.B + (uintptr_t)((wrow[i] + k) * ES);
-            wb16[i] = *(const u32x4 SK_GLOBAL *)(k < k_stop ? pb : zeros);
+            const bool ok = in && a_hi[i] > a_lo[i] && (!P.gather || (unsigned)(a_h[i] + run) < (unsigned)P.H);
+            const int64_t o = a_base[i] + run * a_run;
+            const int64_t at = o + a_from(i, e0, o);
+            ra[i] = load_any(ok ? (uintptr_t)P.A + (uintptr_t)(at * ES) : zeros);
           }
-        }
+        } else {
+          piece_t el[2][2];
+          const int k_stop = (int)T.k0 + (int)T.k_len;
+          // reduction indices ks .. ks + 2 CE - 1 of 64 + 64 pixels; `outside(h, r, t)`: top bit set where the pixel's tap
+          // (r, t) lies outside the image
+          auto load_elements = [&](auto outside) {
+            int k = ks, r = kr, t = kt;
+            uint32_t plane = (uint32_t)(kc * P.H * P.W);
 #pragma unroll
-        for (int e = 0; e < CE; ++e) {
-          const bool in = k + e < k_stop;
-          const int64_t rel = P.gather ? g_r * im.sh + g_s * im.sw + g_c * im.sc : (int64_t)(k + e);
+            for (int pp = 0; pp < 2; ++pp)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const bool ok = in && (!P.gather || ((unsigned)(rows[i].hb + g_r) < (unsigned)P.H &&
-                                                 (unsigned)(rows[i].wb + g_s) < (unsigned)P.W));
-            const uintptr_t pa = (uintptr_t)P.A + (uintptr_t)((rows[i].base + rel) * ES);
-            va[i][e] = *(const elem_t SK_GLOBAL *)(ok ? pa : zeros);
-            if (!vec_b) {
-              const uintptr_t pb = (uintptr_t)P.B + (uintptr_t)((wrow[i] + k + e) * ES);
-              vb[i][e] = *(const elem_t SK_GLOBAL *)(in ? pb : zeros);
-            } else {
-              vb[i][e] = 0;
-            }
-          }
-          if (!P.nchw) {
-            if (++g_c == P.Cin) {
-              g_c = 0;
-              if (++g_s == P.S) {
-                g_s = 0;
-                ++g_r;
+              for (int e = 0; e < CE; ++e) {
+                const bool k_in = k < k_stop;
+                const uint32_t soff = k_in ? (plane + (uint32_t)(r * P.W + t)) * ES : 0u;
+                const uint32_t k_out = k_in ? 0u : NOWHERE;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                  const uint32_t off = n_off[h] | ((outside(h, r, t) | k_out) & NOWHERE);
+                  if constexpr (ES == 4)
+                    el[h][pp][e] = __builtin_amdgcn_raw_buffer_load_b32(descA, off, soff, 0);
+                  else
+                    el[h][pp][e] = __builtin_amdgcn_raw_buffer_load_b16(descA, off, soff, 0);
+                }
+                ++k;
+                if (++t == P.S) {
+                  t = 0;
+                  if (++r == P.R) {
+                    r = 0;
+                    plane += (uint32_t)(P.H * P.W);
+                  }
+                }
               }
-            }
-          } else if (++g_s == P.S) {
-            g_s = 0;
-            if (++g_r == P.R) {
-              g_r = 0;
-              ++g_c;
-            }
+          };
+          if (near && P.R <= 32 && P.S <= 32)
+            load_elements([&](int h, int r, int t) { return (n_rows[h] << ((31 - r) & 31)) | (n_cols[h] << ((31 - t) & 31)); });
+          else if (near)
+            load_elements([&](int h, int r, int t) {
+              return (unsigned)(a_h[h] + r) < (unsigned)P.H && (unsigned)(a_lo[h] + t) < (unsigned)P.W ? 0u : NOWHERE;
+            });
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int pp = 0; pp < 2; ++pp) ra[2 * h + pp] = __builtin_bit_cast(u32x4, el[h][pp]);
+          at_ks = ks;
+          // on to the wave's pieces of the next stage: 8 pieces from the first of this one's
+          ks += 8 * CE;
+          const int cr = ks / P.S;
+          kt = ks - cr * P.S;
+          kc = cr / P.R;
+          kr = cr - kc * P.R;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool ok = in && nb + srow + 32 * i < n_end;  // (rows past the edge are never stored)
+          const int64_t o = b_base + (int64_t)(32 * i) * P.ldb + (int64_t)run * run_len;
+          const int64_t at = o + b_from(e0, o);
+          rb[i] = load_any(ok ? (uintptr_t)P.B + (uintptr_t)(at * ES) : zeros);
+        }
+        piece += 8;
+        j += 8;
+        while (j >= ppr) {
+          j -= ppr;
+          ++run;
+        }
+      };
+      // (the checks are for the whole wave: most waves have nothing to shift or mask)
+      auto lstore = [&](int buf) {
+        unsigned char *s = lds + buf * STAGE;
+        const int e0 = at_e0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if constexpr (!NCHW) {
+            const int sh = e0 - a_from(i, e0, a_base[i] + at_run * a_run);
+            u32x4 v = ra[i];
+            if (__any(sh != 0)) v = shift_piece<ES>(v, sh);
+            if (short_a) v = mask_piece<ES>(v, a_lo[i] - e0, a_hi[i] - e0);
+            *(u32x4 *)(s + (srow + 32 * i) * LDS_ROW + c8 * 16) = v;
+          } else if (near) {
+            *(u32x4 *)(s + (lane + 64 * (i >> 1)) * LDS_ROW + (2 * wave + (i & 1)) * 16) = ra[i];
+          }
+        }
+        if (NCHW && !near) {  // (images of 2 GiB and more: one element at a time)
+          const int k_stop = (int)T.k0 + (int)T.k_len;
+#pragma unroll 1
+          for (int q = 0; q < 4 * CE; ++q) {
+            const int h = q & 1, k = at_ks + (q >> 1);
+            const int cr = k / P.S, t = k - cr * P.S, c = cr / P.R, r = cr - c * P.R;
+            const int hh = (h ? a_h[1] : a_h[0]) + r, ww = (h ? a_lo[1] : a_lo[0]) + t;
+            const bool ok = k < k_stop && (unsigned)hh < (unsigned)P.H && (unsigned)ww < (unsigned)P.W;
+            const int64_t o = (h ? a_base[1] : a_base[0]) + ((int64_t)c * P.H + r) * P.W + t;
+            *(elem_t *)(s + (lane + 64 * h) * LDS_ROW + 2 * wave * 16 + (q >> 1) * ES) =
+                *(const elem_t SK_GLOBAL *)(ok ? (uintptr_t)P.A + (uintptr_t)(o * ES) : zeros);
           }
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          u32x4 qa, qb;
-          if constexpr (ES == 4) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              qa[e] = va[i][e];
-              qb[e] = vb[i][e];
-            }
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              qa[e] = (uint32_t)va[i][2 * e] | ((uint32_t)va[i][2 * e + 1] << 16);
-              qb[e] = (uint32_t)vb[i][2 * e] | ((uint32_t)vb[i][2 * e + 1] << 16);
-            }
-          }
-          *(u32x4 *)(sa + 32 * i * LDS_ROW) = qa;
-          *(u32x4 *)(sb + 32 * i * LDS_ROW) = vec_b ? wb16[i] : qb;
+          const int sh = e0 - b_from(e0, b_base + (int64_t)(32 * i) * P.ldb + (int64_t)at_run * run_len);
+          u32x4 v = rb[i];
+          if (__any(sh != 0)) v = shift_piece<ES>(v, sh);
+          if (short_b) v = mask_piece<ES>(v, 0, run_len - e0);
+          *(u32x4 *)(s + (128 + srow + 32 * i) * LDS_ROW + c8 * 16) = v;
         }
-        __syncthreads();
-        const unsigned char *la = lds;
-        const unsigned char *lb = lds + 128 * LDS_ROW;
+      };
+
+      // (step -1 only loads; an empty slice delivers zeros)
+      for (int s = -1; s < nstages; ++s) {
+        if (s + 1 < nstages) gload();
+        if (s >= 0) {
+          // MFMA columns (four consecutive of which a lane holds) come from the operand along whose rows the output is contiguous
+          const unsigned char *la = lds + (s & 1) * STAGE + (NCHW ? 128 * LDS_ROW : 0);
+          const unsigned char *lb = lds + (s & 1) * STAGE + (NCHW ? 0 : 128 * LDS_ROW);
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          const int piece = (2 * kk + half) * 16;
-          u32x4 fa[2], fb[2];
+          for (int kk = 0; kk < 4; ++kk) {
+            const int at = (2 * kk + half) * 16;
+            u32x4 fa[2], fb[2];
 #pragma unroll
-          for (int f = 0; f < 2; ++f) {
-            fa[f] = *(const u32x4 *)(la + ((wm * 2 + f) * 32 + l32) * LDS_ROW + piece);
-            fb[f] = *(const u32x4 *)(lb + ((wn * 2 + f) * 32 + l32) * LDS_ROW + piece);
+            for (int f = 0; f < 2; ++f) {
+              fa[f] = *(const u32x4 *)(la + ((wm * 2 + f) * 32 + l32) * LDS_ROW + at);
+              fb[f] = *(const u32x4 *)(lb + ((wn * 2 + f) * 32 + l32) * LDS_ROW + at);
+            }
+#pragma unroll
+            for (int fn = 0; fn < 2; ++fn)
+#pragma unroll
+              for (int fm = 0; fm < 2; ++fm) mma32<DT>(fb[fn], fa[fm], acc[fn][fm]);
           }
-#pragma unroll
-          for (int fn = 0; fn < 2; ++fn)
-#pragma unroll
-            for (int fm = 0; fm < 2; ++fm) mma32<DT>(fb[fn], fa[fm], acc[fn][fm]);
         }
-        __syncthreads();  // everyone has read the stage before the next one overwrites it
+        if (s + 1 < nstages) lstore((s + 1) & 1);
+        __syncthreads();  // stage s+1 is written, and everyone has read stage s
       }
 
       if (T.S > 1) {
         // A slice of a split reduction (such a rectangle is a single block here: at most 128 x 128, or
         // 16, 32 or 64 rows x 128 columns in the skinny classes).  Partial sums go to the rectangle's
         // workspace, which holds per slice `rows` x 128 (64 for the 64-column class) floats, as 16-byte
-        // pieces indexed by (column group of 32, quad j, half, row); the last slice to arrive adds
+        // pieces indexed by (quad of consecutive outputs, MFMA row); the last slice to arrive adds
         // all of them in slice order and stores the result.  Same hand-over as in run_tile.
         // The sixteen accumulator quads of a thread wait in LDS meanwhile (free by now: the last stage
         // ended with a barrier; a slot per thread and quad), so that the loops below can run rolled up:
@@ -1921,23 +2098,24 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
 #pragma unroll
           for (int fm = 0; fm < 2; ++fm)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-              slot[((fn * 2 + fm) * 4 + j) * WG_THREADS] =
-                  f32x4{acc[fn][fm][4 * j], acc[fn][fm][4 * j + 1], acc[fn][fm][4 * j + 2], acc[fn][fm][4 * j + 3]};
+            for (int q = 0; q < 4; ++q)
+              slot[((fn * 2 + fm) * 4 + q) * WG_THREADS] =
+                  f32x4{acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1], acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]};
         const int rows = T.cls >= CLS_TILE_128x128 ? 128 : 16 << (T.cls / 3);
-        const int groups = T.cls == CLS_TILE_128x64 ? 2 : 4;
-        const size_t per_slice = (size_t)groups * 4 * 2 * rows;  // f32x4 units
+        const int cols = T.cls == CLS_TILE_128x64 ? 64 : 128;
+        const int lrows = NCHW ? cols : rows, quads = (NCHW ? rows : cols) / 4;
+        const size_t per_slice = (size_t)lrows * quads;  // f32x4 units
         unsigned long long *mine = (unsigned long long *)(sp.ws + sp.ws_off[T.out_tile_id]);
-        // where quad p = (fn*2 + fm)*4 + j of this thread lies in slice 0, or null if outside the rectangle's rows / columns
-        auto piece = [&](int p) -> unsigned long long * {
-          const int fn = p >> 3, fm = (p >> 2) & 1, j = p & 3;
-          const int r = (wm * 2 + fm) * 32 + l32, cg = wn * 2 + fn;
-          if (r >= rows || cg >= groups) return nullptr;
-          return mine + 2 * ((size_t)((cg * 4 + j) * 2 + half) * rows + r);
+        // where quad p = (fn*2 + fm)*4 + q of this thread lies in slice 0, or null if outside the rectangle's rows / columns
+        auto place = [&](int p) -> unsigned long long * {
+          const int fn = p >> 3, fm = (p >> 2) & 1, q = p & 3;
+          const int r = (wm * 2 + fm) * 32 + l32, g = (wn * 2 + fn) * 8 + q * 2 + half;
+          if (r >= lrows || g >= quads) return nullptr;
+          return mine + 2 * ((size_t)g * lrows + r);
         };
 #pragma unroll 1
         for (int p = 0; p < 16; ++p) {
-          unsigned long long *q = piece(p);
+          unsigned long long *q = place(p);
           if (q) {
             q += 2 * (size_t)T.ks_idx * per_slice;
             const f32x4 v = slot[p * WG_THREADS];
@@ -1955,7 +2133,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         if (*s_flag != (uint32_t)T.S - 1) return;
 #pragma unroll 1
         for (int p = 0; p < 16; ++p) {
-          unsigned long long *q = piece(p);
+          unsigned long long *q = place(p);
           f32x4 sum = {0.f, 0.f, 0.f, 0.f};
           if (q) {
             for (int s2 = 0; s2 < T.S; ++s2, q += 2 * per_slice) {
@@ -1973,42 +2151,67 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
 #pragma unroll
           for (int fm = 0; fm < 2; ++fm)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const f32x4 v = slot[((fn * 2 + fm) * 4 + j) * WG_THREADS];
-              acc[fn][fm][4 * j] = v.x;
-              acc[fn][fm][4 * j + 1] = v.y;
-              acc[fn][fm][4 * j + 2] = v.z;
-              acc[fn][fm][4 * j + 3] = v.w;
+            for (int q = 0; q < 4; ++q) {
+              const f32x4 v = slot[((fn * 2 + fm) * 4 + q) * WG_THREADS];
+              acc[fn][fm][4 * q] = v.x;
+              acc[fn][fm][4 * q + 1] = v.y;
+              acc[fn][fm][4 * q + 2] = v.z;
+              acc[fn][fm][4 * q + 3] = v.w;
             }
+        __syncthreads();  // the slots have been read: the outputs are staged in the same LDS next
       }
 
-      // lane holds, per (fn, fm): row l32, columns 8*(i/4) + 4*half + (i%4)
+      // ---- outputs: through LDS, so that they leave as runs of consecutive places ----
+      // lane holds, per (fn, fm): MFMA row l32, columns 8*(i/4) + 4*half + (i%4)
+      constexpr int OROW = 128 * ES + 16;
+      static_assert(128 * OROW <= LDS_TILE_BYTES, "output tile does not fit the LDS buffer");
 #pragma unroll
-      for (int fm = 0; fm < 2; ++fm) {
-        const int m = mb + (wm * 2 + fm) * 32 + l32;
-        if (m < m_end) {
-          const int64_t row_off = P.nchw ? nchw_out_base(P, m) : (int64_t)m * P.ldc;
-          const int64_t plane = (int64_t)P.Ho * P.Wo;
+      for (int fm = 0; fm < 2; ++fm)
 #pragma unroll
-          for (int fn = 0; fn < 2; ++fn) {
+        for (int fn = 0; fn < 2; ++fn)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int n = nb + (wn * 2 + fn) * 32 + 8 * j + 4 * half;
-              if (n < n_end) {
-                f32x4 v = {acc[fn][fm][4 * j], acc[fn][fm][4 * j + 1], acc[fn][fm][4 * j + 2], acc[fn][fm][4 * j + 3]};
-                if (!P.nchw) {
-                  store4<DT>(P.C, row_off, n, n_end, v, vec_c);
-                } else {
-                  // consecutive output channels lie a plane apart
-#pragma unroll
-                  for (int q = 0; q < 4; ++q)
-                    if (n + q < n_end) store_elem<DT>(P.C, row_off + (int64_t)(n + q) * plane, v[q]);
-                }
-              }
+          for (int q = 0; q < 4; ++q) {
+            unsigned char *d = lds + ((wm * 2 + fm) * 32 + l32) * OROW + ((wn * 2 + fn) * 32 + 8 * q + 4 * half) * ES;
+            if constexpr (ES == 4) {
+              *(f32x4 *)d = f32x4{acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1], acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]};
+            } else {
+              u32x2 o;
+              o.x = cvt_pack<DT>(acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1]);
+              o.y = cvt_pack<DT>(acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]);
+              *(u32x2 *)d = o;
             }
           }
+      __syncthreads();
+      constexpr int PIECES = 128 / CE, RPI = WG_THREADS / PIECES;
+      const int col = (tid % PIECES) * CE;
+      const int row_end = NCHW ? n_end - nb : m_end - mb, col_end = NCHW ? m_end - mb : n_end - nb;
+      // NCHW: the piece's pixels (its first one, and whether they lie in one image)
+      int64_t pixel0 = 0;
+      bool whole = col + CE <= col_end;
+      if constexpr (NCHW) {
+        if (col < col_end) {
+          pixel0 = nchw_out_base(P, mb + col);
+          whole = whole && nchw_out_base(P, mb + col + CE - 1) == pixel0 + CE - 1;
         }
       }
+#pragma unroll 1
+      for (int r = tid / PIECES; r < row_end && r < 128; r += RPI) {
+        if (col >= col_end) break;
+        const u32x4 v = *(const u32x4 *)(lds + r * OROW + col * ES);
+        if (whole) {
+          const int64_t o = NCHW ? pixel0 + (int64_t)(nb + r) * hw : (int64_t)(mb + r) * P.ldc + nb + col;
+          *(u32x4_any SK_GLOBAL *)((uintptr_t)P.C + (uintptr_t)(o * ES)) = v;
+        } else {
+          const piece_t ev = __builtin_bit_cast(piece_t, v);
+#pragma unroll
+          for (int e = 0; e < CE; ++e)
+            if (col + e < col_end) {
+              const int64_t o = NCHW ? nchw_out_base(P, mb + col + e) + (int64_t)(nb + r) * hw : (int64_t)(mb + r) * P.ldc + nb + col + e;
+              *(elem_t SK_GLOBAL *)((uintptr_t)P.C + (uintptr_t)(o * ES)) = ev[e];
+            }
+        }
+      }
+      __syncthreads();  // the output tile has been read before the next block's stages are written
     }
   }
 }
@@ -2018,25 +2221,40 @@ __device__ __forceinline__ void run_class(const DevProblem &P, const sk_tile &T,
                                           const sk_tile *T_mem, const SplitK &sp, unsigned char *lds,
                                           uint32_t *s_flag, Prefetch &pf) {
   const int cls = T.cls;
-  if (ANY_ALIGNMENT && (P.flags & (FLAG_VEC_A | FLAG_VEC_B)) != (FLAG_VEC_A | FLAG_VEC_B)) {
-    if constexpr (ANY_ALIGNMENT) {
-      pf.claim();
-      pf.issue();
+  constexpr int CE = 16 / Elem<DT>::ES;
+  bool pieces = true;  // the fast paths can read the operator
+  if constexpr (ANY_ALIGNMENT) {
+    pieces = (P.flags & (FLAG_VEC_A | FLAG_VEC_B)) == (FLAG_VEC_A | FLAG_VEC_B);
+    if (!pieces) {
       // One output per thread costs a thread (outputs / 256) * Kg dependent steps of about 0.1 us; a stage
       // of 64 (fp32: 32) reduction elements through the matrix cores costs a few us whatever the
       // rectangle.  So only rectangles that are done in a few dozen steps go the first way.
       const int per_thread = ((int)T.m_len * (int)T.n_len + WG_THREADS - 1) / WG_THREADS;
-      if ((int64_t)per_thread * P.Kg <= 64)
-        run_generic<DT>(P_mem, T_mem);
-      else
-        run_tile_any<DT>(P_mem, T_mem, sp, lds, s_flag);
+      const bool small = (int64_t)per_thread * P.Kg <= 64;
+      // The weight-streaming classes read pieces at any element's address; of convolutions those whose pieces never
+      // straddle two taps.
+      if (!small && cls < CLS_TILE_128x128 && !P.nchw && P.Kg >= CE && (!P.gather || P.Cin % CE == 0)) {
+        pieces = true;
+      } else {
+        pf.claim();
+        pf.issue();
+        // (an operand of less than one piece also goes the first way: the others read whole pieces from inside it)
+        if (small || !holds_a_piece<Elem<DT>::ES>(P))
+          run_generic<DT>(P_mem, T_mem);
+        else if (P.nchw)
+          run_tile_any<DT, true>(P_mem, T_mem, sp, lds, s_flag);
+        else
+          run_tile_any<DT, false>(P_mem, T_mem, sp, lds, s_flag);
+      }
     }
+  }
+  if (ANY_ALIGNMENT && !pieces) {
   } else if (cls == 0) {
-    run_skinny<DT, 1>(P, T, sp, lds, s_flag, pf);
+    run_skinny<DT, 1, ANY_ALIGNMENT>(P, T, sp, lds, s_flag, pf);
   } else if (cls == 3) {
-    run_skinny<DT, 2>(P, T, sp, lds, s_flag, pf);
+    run_skinny<DT, 2, ANY_ALIGNMENT>(P, T, sp, lds, s_flag, pf);
   } else if (cls == 6) {
-    run_skinny<DT, 4>(P, T, sp, lds, s_flag, pf);
+    run_skinny<DT, 4, ANY_ALIGNMENT>(P, T, sp, lds, s_flag, pf);
   } else if (cls == CLS_TILE_128x64) {
     run_lds_tile<DT, 128, 64>(P, T, sp, lds, s_flag, pf);
   } else {

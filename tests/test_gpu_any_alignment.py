@@ -1,0 +1,45 @@
+"""GPU parity of the paths for operands at any address and for channel-major images at the sizes where their
+addressing can go wrong: runs shorter than a 16-byte piece, reduction lengths one below to one above a multiple of
+one, filters wider than the image or than 32 taps, planes of an odd number of pixels over several images.  Held to
+the oracle like every other shape (gate and order-free rounding bound), and bit for bit over relaunch, order and
+per-die lists (run_all_modes)."""
+import pytest
+
+import sk_harness as H  # noqa: F401  (the harness the modes below run on)
+from test_gpu_parity import c, g, nchw, run_all_modes
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # weight-streaming classes, 1 to 64 rows: K from one piece to several chunks, every remainder; padded rows below
+    "skinny_tails": [g(m, 70, k, dt) for dt in ("bf16", "f32") for m, k in
+                     ((1, 9), (5, 15), (16, 71), (17, 129), (32, 130), (33, 251), (48, 516), (64, 1021), (7, 2051), (1, 4099))],
+    # a reduction cut into slices (the last one ragged)
+    "skinny_slices": [g(3, 64, 9001), g(20, 33, 5003, "f16"), g(60, 40, 3001, "f32")],
+    # fewer elements than a piece in a row, and fewer than a piece in the whole operand
+    "short_rows": [g(1, 3, 2), g(300, 90, 5), g(200, 130, 3, "f32"), g(2, 500, 7), g(1, 700, 6, "f16")],
+    # blocks of 128 x 128: K around multiples of a piece and of a stage
+    "blocks": [g(130, 129, k, dt) for dt in ("bf16", "f16", "f32") for k in (33, 63, 65, 127, 193)],
+    # image runs: 1x1 with few channels, 3x3 on RGB, odd channel counts, an image narrower than the filter
+    "runs": [c(20, 20, 3, 40, 1, 1, 0, 0), c(24, 22, 3, 64, 3, 3, 1, 1, st=2), c(21, 23, 7, 33, 3, 3, 1, 1, "f32"),
+             c(19, 3, 9, 70, 5, 5, 2, 2), c(30, 30, 1, 20, 7, 7, 3, 3, "f16"), c(15, 17, 13, 130, 3, 3, 0, 0, nb=3),
+             c(40, 2, 3, 16, 3, 3, 1, 3), c(12, 12, 100, 24, 1, 1, 1, 1, st=2), c(9, 14, 12, 72, 1, 7, 0, 3)],
+    # channel-major: filters of more than 32 columns, odd planes over several images, pad beyond the filter, stages
+    # that end inside a channel
+    "planes": [nchw(6, 60, 3, 40, 1, 41, 0, 20), nchw(45, 7, 2, 24, 33, 2, 4, 1, "f16"), nchw(7, 7, 33, 70, 1, 1, 0, 0, nb=5),
+               nchw(9, 11, 20, 130, 3, 3, 1, 1, "f32", nb=3), nchw(13, 13, 17, 64, 2, 2, 2, 2), nchw(30, 30, 8, 12, 5, 5, 2, 2, st=3),
+               nchw(14, 14, 96, 200, 1, 1, 0, 0, "f16")],
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_any_alignment_edges(name):
+    run_all_modes(CASES[name], seed=41, label=name)
+
+
+@pytest.mark.parametrize("name", ["skinny_tails", "blocks", "runs", "planes"])
+def test_any_alignment_edges_at_odd_addresses(name):
+    """The same at addresses that are aligned to an element only, GEMMs in rows padded by an odd number of elements."""
+    off = 4  # bytes: whole elements of every type, no multiple of a piece
+    pads = {} if name in ("runs", "planes") else {"pad_lda": 5, "pad_ldb": 3, "pad_ldc": 1}
+    run_all_modes(CASES[name], seed=42, label=name + " at odd addresses", a_off=off, b_off=off, c_off=off, **pads)
