@@ -1217,18 +1217,13 @@ __device__ __forceinline__ void run_tile(const DevProblem &P, const sk_tile &T, 
 }
 
 // ---------------------------------------------------------------------------
-// LDS tiles with lean operand addressing
+// LDS tiles fed by direct global-to-LDS loads
 // ---------------------------------------------------------------------------
-// The stage of run_tile above spends more instructions on forming addresses than on anything
-// else: per 16-byte piece a 64-bit add, two selects against the piece of zeros and, for a
-// convolution, the bounds of the tap in both directions.  With two waves per SIMD those
-// instructions, not the memory system, set the pace of a stage.  This variant keeps the same
-// pipeline (ring of register stages, two LDS stages, the same LDS image, fragments and MFMAs)
-// and reads its operands through buffer descriptors instead:
+// The operands are read through buffer descriptors:
 //   * one descriptor per operand and tile, based at the tile's first row, its size the extent of
 //     the tile's rows: a piece's address is a 32-bit row offset kept in a register for the whole
 //     tile plus a scalar offset that advances with the stage, and a piece that lies outside the
-//     descriptor reads as zero, so a piece that must not be read gets the offset 2^31;
+//     descriptor reads as zero, so a piece that must not be read gets an offset of 2^31 and more;
 //   * for a convolution whose channel count is a multiple of a stage (64 elements of 2 bytes),
 //     all pieces of a stage lie under one filter tap: the tap and its offset are scalar, and
 //     whether a row's pixel under that tap lies in the image is one bit of a mask that is
@@ -1246,7 +1241,7 @@ template <int ES>
 __device__ __forceinline__ bool lean_operands(const DevProblem &P, const sk_tile &T, LeanOperands &L) {
   constexpr int CE = 16 / ES;
   constexpr int KB = 8 * CE;
-  constexpr int64_t LIMIT = (int64_t)1 << 31;
+  constexpr int64_t LIMIT = ((int64_t)1 << 31) - 4096;  // (the descriptors are based up to 3 KB in front, see dma_stage)
   const int64_t extB = ((int64_t)((int)T.n_len - 1) * P.ldb + P.Kg) * ES;
   L.baseB = (uintptr_t)P.B + (uintptr_t)((int64_t)T.n0 * P.ldb * ES);
   L.extB = (uint32_t)extB;
@@ -1272,187 +1267,17 @@ __device__ __forceinline__ bool lean_operands(const DevProblem &P, const sk_tile
   return extA < LIMIT && extB < LIMIT;
 }
 
-template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, bool GATHER>
-__device__ __forceinline__ void run_tile_lean(const DevProblem &P, const sk_tile &T, const SplitK &sp, unsigned char *lds,
-                                              uint32_t *s_flag, Prefetch &pf, const LeanOperands &L) {
-  constexpr int ES = Elem<DT>::ES;
-  constexpr int CE = 16 / ES;
-  constexpr int KB = 8 * CE;                  // reduction elements per stage
-  constexpr int FM = BM / (32 * WAVES_M);     // 32x32 blocks per wave along m
-  constexpr int FN = BN / (32 * WAVES_N);     // ... along n
-  constexpr int A_ITERS = BM / 32;            // 16-byte pieces per thread per stage, activations
-  constexpr int B_ITERS = BN / 32;            // ... weights
-  constexpr int STAGE = (BM + BN) * LDS_ROW;  // bytes of one stage in LDS
-  constexpr int NS = 3;
-  constexpr uint32_t NOWHERE = 0x80000000u;   // an offset outside every descriptor: the piece reads as zero
-  static_assert(WAVES_M * WAVES_N == 4, "four waves per workgroup");
-  static_assert(2 * STAGE <= LDS_TILE_BYTES, "two stages do not fit the LDS buffer");
-
-  const int tid = pf.tid;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63;
-  const int wm = wave % WAVES_M, wn = wave / WAVES_M;
-  const int l32 = lane & 31, half = lane >> 5;
-
-  const int m0 = (int)T.m0, n0 = (int)T.n0;
-  const int m_end = m0 + (int)T.m_len, n_end = n0 + (int)T.n_len;
-  const int k_begin = (int)T.k0, k_stop = (int)T.k0 + (int)T.k_len;
-
-  const __amdgpu_buffer_rsrc_t descA = __builtin_amdgcn_make_buffer_rsrc((void *)L.baseA, 0, (int)L.extA, 0x00020000);
-  const __amdgpu_buffer_rsrc_t descB = __builtin_amdgcn_make_buffer_rsrc((void *)L.baseB, 0, (int)L.extB, 0x00020000);
-
-  // staging map: thread -> piece c8 of rows (tid/8) + 32*i
-  const int c8 = tid & 7;
-  const int srow = tid >> 3;
-  uint32_t offA[A_ITERS];   // byte offset of this thread's piece of row i at reduction index 0 (tap (0,0), channel 0)
-  uint32_t tapsA[A_ITERS];  // convolution: bit (r*S + s) set if the row's pixel under tap (r, s) lies in the image
-#pragma unroll
-  for (int i = 0; i < A_ITERS; ++i) {
-    int m = m0 + srow + 32 * i;
-    if (m >= m_end) m = m_end - 1;  // rows past the edge repeat the last row; never stored
-    if constexpr (!GATHER) {
-      offA[i] = (uint32_t)((m - m0) * (int)P.lda * ES) + (uint32_t)c8 * 16u;
-      tapsA[i] = 0;
-    } else {
-      const RowA r = row_of(P, m);
-      offA[i] = (uint32_t)((r.base - L.originA) * ES) + (uint32_t)c8 * 16u;
-      // filter rows rr with 0 <= hb + rr < H form a range [lo, hi), and so do the filter columns
-      const int hlo = max(0, -r.hb), hhi = min(P.R, P.H - r.hb);
-      const int wlo = max(0, -r.wb), whi = min(P.S, P.W - r.wb);
-      const uint32_t wmk = whi > wlo ? ((1u << whi) - 1u) & ~((1u << wlo) - 1u) : 0u;  // (at most 31 taps)
-      uint32_t taps = 0;
-      for (int rr = 0; rr < P.R; ++rr) taps |= (rr >= hlo && rr < hhi) ? wmk << (rr * P.S) : 0u;
-      tapsA[i] = taps;
-    }
-  }
-  uint32_t offB[B_ITERS];
-#pragma unroll
-  for (int i = 0; i < B_ITERS; ++i) {
-    int n = n0 + srow + 32 * i;
-    if (n >= n_end) n = n_end - 1;
-    offB[i] = (uint32_t)((n - n0) * (int)P.ldb * ES) + (uint32_t)c8 * 16u;
-  }
-
-  f32x16 acc[FN][FM];
-#pragma unroll
-  for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-    for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[fn][fm][i] = 0.f;
-
-  // scalar position of the next stage to load: reduction index k_next; for a convolution the tap
-  // (t_r, t_s) and the first channel t_c of the stage
-  int k_next = k_begin;
-  int t_r = 0, t_s = 0, t_c = 0;
-  if constexpr (GATHER) {
-    const int tap = fast_div(k_begin, P.div_cin);
-    t_c = k_begin - tap * P.Cin;
-    t_r = fast_div(tap, P.div_s);
-    t_s = tap - t_r * P.S;
-  }
-  u32x4 ra[NS][A_ITERS], rb[NS][B_ITERS];
-  // Loads are unconditional (stages past the end of the reduction read whatever lies there, or zeros
-  // past the descriptor, and are never multiplied), so the number of loads in flight is the same on
-  // every path.
-  auto gload = [&](u32x4(&xa)[A_ITERS], u32x4(&xb)[B_ITERS]) {
-    const uint32_t kbytes = (uint32_t)k_next * ES;
-    if constexpr (GATHER) {
-      // (no reduction tail: the reduction length is a multiple of the channel count, that of a stage)
-      const uint32_t tapbit = 1u << ((t_r * P.S + t_s) & 31);
-      const uint32_t tapoff = (uint32_t)(((t_r * P.W + t_s) * P.Cin + t_c) * ES);
-#pragma unroll
-      for (int i = 0; i < A_ITERS; ++i)
-        xa[i] = __builtin_amdgcn_raw_buffer_load_b128(descA, (tapsA[i] & tapbit) ? offA[i] : NOWHERE, tapoff, 0);
-#pragma unroll
-      for (int i = 0; i < B_ITERS; ++i) xb[i] = __builtin_amdgcn_raw_buffer_load_b128(descB, offB[i], kbytes, 0);
-      t_c += KB;
-      if (t_c >= P.Cin) {
-        t_c = 0;
-        if (++t_s == P.S) {
-          t_s = 0;
-          ++t_r;
-        }
-      }
-    } else {
-      // this thread's piece lies beyond the end of the reduction (last stage of a length that is not a
-      // multiple of a stage): nowhere
-      const uint32_t tail = k_next + c8 * CE < k_stop ? 0u : NOWHERE;
-#pragma unroll
-      for (int i = 0; i < A_ITERS; ++i) xa[i] = __builtin_amdgcn_raw_buffer_load_b128(descA, offA[i] | tail, kbytes, 0);
-#pragma unroll
-      for (int i = 0; i < B_ITERS; ++i) xb[i] = __builtin_amdgcn_raw_buffer_load_b128(descB, offB[i] | tail, kbytes, 0);
-    }
-    k_next += KB;
-  };
-  auto lstore = [&](int buf, const u32x4(&xa)[A_ITERS], const u32x4(&xb)[B_ITERS]) {
-    unsigned char *a = lds + buf * STAGE + srow * LDS_ROW + c8 * 16;
-    unsigned char *bb = a + BM * LDS_ROW;
-#pragma unroll
-    for (int i = 0; i < A_ITERS; ++i) *(u32x4 *)(a + 32 * i * LDS_ROW) = xa[i];
-#pragma unroll
-    for (int i = 0; i < B_ITERS; ++i) *(u32x4 *)(bb + 32 * i * LDS_ROW) = xb[i];
-  };
-
-  const int nstages = (k_stop - k_begin + KB - 1) / KB;
-#pragma unroll
-  for (int u = 0; u < NS - 1; ++u) gload(ra[u], rb[u]);
-  lstore(0, ra[0], rb[0]);
-  __syncthreads();
-  int buf = 0;
-  for (int s0 = 0; s0 < nstages; s0 += NS) {
-#pragma unroll
-    for (int u = 0; u < NS; ++u) {
-      pf.at_step(s0 + u, nstages, CLAIM_LEAD, ISSUE_GAP);
-      gload(ra[(u + NS - 1) % NS], rb[(u + NS - 1) % NS]);
-      if (s0 + u < nstages) {
-        // stage s0+u is in LDS buffer `buf`; put stage s0+u+1 into the other one while this one is used
-        const unsigned char *la = lds + buf * STAGE;
-        const unsigned char *lb = la + BM * LDS_ROW;
-        u32x4 fa[2][FM], fb[2][FN];
-        auto frag = [&](int kk, u32x4(&xa)[FM], u32x4(&xb)[FN]) {
-          const int piece = (2 * kk + half) * 16;
-#pragma unroll
-          for (int fm = 0; fm < FM; ++fm)
-            xa[fm] = *(const u32x4 *)(la + ((wm * FM + fm) * 32 + l32) * LDS_ROW + piece);
-#pragma unroll
-          for (int fn = 0; fn < FN; ++fn)
-            xb[fn] = *(const u32x4 *)(lb + ((wn * FN + fn) * 32 + l32) * LDS_ROW + piece);
-        };
-        frag(0, fa[0], fb[0]);
-        lstore(buf ^ 1, ra[(u + 1) % NS], rb[(u + 1) % NS]);
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          if (kk + 1 < 4) frag(kk + 1, fa[(kk + 1) & 1], fb[(kk + 1) & 1]);
-#pragma unroll
-          for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-            for (int fm = 0; fm < FM; ++fm) mma32<DT>(fb[kk & 1][fn], fa[kk & 1][fm], acc[fn][fm]);
-        }
-        __syncthreads();
-        buf ^= 1;
-      }
-    }
-  }
-  finish_tile<DT, BM, BN, WAVES_M, WAVES_N>(P, T, sp, lds, s_flag, tid, acc);
-}
-
-// ---------------------------------------------------------------------------
-// LDS tiles fed by direct global-to-LDS loads
-// ---------------------------------------------------------------------------
-// The same tile, fragments and MFMAs, but the operand pieces never pass through registers:
-// a buffer load with the LDS modifier writes the 16 bytes of lane i at (M0 + 16 i) of the LDS,
-// 1 KB per wave and instruction, and a piece whose offset lies outside the descriptor arrives
-// as zeros.  What this removes from a stage: the register ring (96 registers), the LDS stores
-// with their counted waits, and all but one or two instructions per piece.
+// The operand pieces never pass through registers: a buffer load with the LDS modifier writes the 16
+// bytes of lane i at (M0 + 16 i) of the LDS, 1 KB per wave and instruction, and a piece whose offset lies outside
+// the descriptor arrives as zeros.
 //   * LDS image of a stage: (BM + BN) rows of 128 bytes, no padding (a load instruction fills
 //     eight consecutive rows); position p of row r holds the row's piece p ^ ((r >> 1) & 7), so
 //     the 16 lanes that a fragment read serves together (rows r .. r+15, one piece) fall into
 //     16 different groups of four banks.  The swizzle is applied on the global side: lane i of
 //     a load asks for piece (i & 7) ^ swizzle(row of the lane).
-//   * a ring of NS such images (as many as fit LDS_TILE_BYTES): stages h+1 .. h+NS-2 are in
-//     flight while stage h is multiplied; one barrier per stage says both "everyone's part of
-//     stage h has landed" and "everyone is done with the image that stage h+NS-1 will overwrite".
+//   * a ring of NS such images (as many as fit LDS_TILE_BYTES); one barrier per stage, ahead of its last
+//     step's MFMAs, says both "everyone's part of stage h+1 has landed" and "everyone has stage h's last fragments
+//     in registers", so that stage h+NS may overwrite its image: NS-1 stages are in flight for most of a stage.
 //   * the compiler does not see these loads (inline assembly; told about them it would wait for
 //     all of them before every LDS read), so the waits are written out: loads complete in order,
 //     hence "at most n outstanding" with n the loads of the stages issued later.  Loads and
@@ -1463,44 +1288,52 @@ __device__ __forceinline__ void run_tile_lean(const DevProblem &P, const sk_tile
 //     compiler keeps spilled scalars in lanes of a vector register and fetches them with v_readlane
 //     wherever it needs them, also right in front of these loads) must not be read by a memory
 //     instruction in the next five cycles, and M0 not by an LDS-writing load in the cycle after it
-//     was written.  So all loads of a stage sit in ONE statement that opens with the five cycles
-//     and moves M0 from piece to piece itself (the pieces of a wave lie 4 KB apart), and hands M0 back
-//     as it got it.
+//     was written.  So all loads of a stage sit in ONE statement that opens with the five cycles and
+//     hands M0 back as it got it.
+//   * with two waves per SIMD a wave's own instruction stream sets the pace of a stage as much as the MFMAs do (one
+//     instruction every four cycles at best, the scalar ones included).  So a stage is kept to little more
+//     than its MFMAs, fragment reads and loads: the loop is unrolled over the ring's slots (every LDS address is a register of
+//     the tile plus a constant), the pieces a wave loads lie 1 KB apart in LDS and are told apart by the
+//     instruction's own offset (which counts on both sides, so the lane's global offset is lowered by as
+//     much and the descriptor based 3 KB in front), and positions advance by additions only.
+//     @DMA_FIGURES@
+// The wave's pieces: NA of activations from M0 on, NBW of weights from M0 + to_b on, each 1 KB after the one before; va and vb are
+// offsets from the descriptors' bases (3072 bytes in front of the operand's first byte) less 1024 i.
 template <int NA, int NBW>
 __device__ __forceinline__ void dma_stage(__amdgpu_buffer_rsrc_t descA, __amdgpu_buffer_rsrc_t descB, const uint32_t (&va)[NA],
-                                          const uint32_t (&vb)[NBW], uint32_t soffA, uint32_t soffB, uint32_t lds_addr) {
+                                          const uint32_t (&vb)[NBW], uint32_t soffA, uint32_t soffB, uint32_t lds_addr, uint32_t to_b) {
   static_assert(NA == 4 && (NBW == 4 || NBW == 2), "written out for 128 rows of activations and 128 or 64 of weights");
-#define SK_DMA_NEXT "s_add_u32 m0, m0, 0x1000\n\ts_nop 0\n\t"
   if constexpr (NBW == 4) {
     asm volatile("s_nop 4\n\t"
-                 "buffer_load_dwordx4 %0, %8, %10 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %1, %8, %10 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %2, %8, %10 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %3, %8, %10 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %4, %9, %11 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %5, %9, %11 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %6, %9, %11 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %7, %9, %11 offen lds\n\t"
-                 "s_sub_u32 m0, m0, 0x7000"
+                 "buffer_load_dwordx4 %0, %8, %10 offen lds\n\t"
+                 "buffer_load_dwordx4 %1, %8, %10 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %2, %8, %10 offen offset:2048 lds\n\t"
+                 "buffer_load_dwordx4 %3, %8, %10 offen offset:3072 lds\n\t"
+                 "s_add_u32 m0, m0, %12\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %4, %9, %11 offen lds\n\t"
+                 "buffer_load_dwordx4 %5, %9, %11 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %6, %9, %11 offen offset:2048 lds\n\t"
+                 "buffer_load_dwordx4 %7, %9, %11 offen offset:3072 lds\n\t"
+                 "s_sub_u32 m0, m0, %12"
                  :
                  : "v"(va[0]), "v"(va[1]), "v"(va[2]), "v"(va[3]), "v"(vb[0]), "v"(vb[1]), "v"(vb[2]), "v"(vb[3]), "s"(descA),
-                   "s"(descB), "s"(soffA), "s"(soffB), "{m0}"(lds_addr)
+                   "s"(descB), "s"(soffA), "s"(soffB), "s"(to_b), "{m0}"(lds_addr)
                  : "memory", "scc");
   } else {
     asm volatile("s_nop 4\n\t"
-                 "buffer_load_dwordx4 %0, %6, %8 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %1, %6, %8 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %2, %6, %8 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %3, %6, %8 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %4, %7, %9 offen lds\n\t" SK_DMA_NEXT
-                 "buffer_load_dwordx4 %5, %7, %9 offen lds\n\t"
-                 "s_sub_u32 m0, m0, 0x5000"
+                 "buffer_load_dwordx4 %0, %6, %8 offen lds\n\t"
+                 "buffer_load_dwordx4 %1, %6, %8 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %2, %6, %8 offen offset:2048 lds\n\t"
+                 "buffer_load_dwordx4 %3, %6, %8 offen offset:3072 lds\n\t"
+                 "s_add_u32 m0, m0, %10\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %4, %7, %9 offen lds\n\t"
+                 "buffer_load_dwordx4 %5, %7, %9 offen offset:1024 lds\n\t"
+                 "s_sub_u32 m0, m0, %10"
                  :
                  : "v"(va[0]), "v"(va[1]), "v"(va[2]), "v"(va[3]), "v"(vb[0]), "v"(vb[1]), "s"(descA), "s"(descB), "s"(soffA),
-                   "s"(soffB), "{m0}"(lds_addr)
+                   "s"(soffB), "s"(to_b), "{m0}"(lds_addr)
                  : "memory", "scc");
   }
-#undef SK_DMA_NEXT
 }
 template <int N>
 __device__ __forceinline__ void wait_loads_but() {
@@ -1520,7 +1353,6 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
   constexpr int NS = LDS_TILE_BYTES / SLOT;   // ring slots
   constexpr uint32_t NOWHERE = 0x80000000u;   // an offset outside every descriptor: the piece arrives as zeros
   static_assert(NS == 2 || NS == 3, "waits below are written for two or three slots");
-  static_assert(BM == 128, "a wave's pieces of a stage lie 4 KB apart, activations first (dma_stage)");
   static_assert(NPW < 32, "load counter");
 
   const int tid = pf.tid;
@@ -1533,16 +1365,18 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
   const int m_end = m0 + (int)T.m_len, n_end = n0 + (int)T.n_len;
   const int k_begin = (int)T.k0, k_stop = (int)T.k0 + (int)T.k_len;
 
-  const __amdgpu_buffer_rsrc_t descA = __builtin_amdgcn_make_buffer_rsrc((void *)L.baseA, 0, (int)L.extA, 0x00020000);
-  const __amdgpu_buffer_rsrc_t descB = __builtin_amdgcn_make_buffer_rsrc((void *)L.baseB, 0, (int)L.extB, 0x00020000);
+  constexpr uint32_t FRONT = 3072;  // see dma_stage
+  const __amdgpu_buffer_rsrc_t descA = __builtin_amdgcn_make_buffer_rsrc((void *)(L.baseA - FRONT), 0, (int)(L.extA + FRONT), 0x00020000);
+  const __amdgpu_buffer_rsrc_t descB = __builtin_amdgcn_make_buffer_rsrc((void *)(L.baseB - FRONT), 0, (int)(L.extB + FRONT), 0x00020000);
 
-  // load map: instruction i of this wave fills rows 8 (wave + 4 i) .. + 7 of the operand's block; this lane
-  // supplies position lane & 7 of row 8 (wave + 4 i) + lane / 8, which holds the logical piece c_log
-  // (the swizzle of the lane's row is the same for every i)
+  // load map: instruction i of this wave fills rows 8 (NA wave + i) .. + 7 of the operand's block (NBW for the weights);
+  // this lane supplies position lane & 7 of row lane / 8 of these, which holds the logical piece c_log[i & 1]
   const int lrow = lane >> 3;
-  const int c_log = (lane & 7) ^ (((wave & 1) << 2) | (lane >> 4));
-  uint32_t offA[NA];   // byte offset of this lane's piece of row i at reduction index 0 (tap (0,0), channel 0)
-  uint32_t tapsA[NA];  // convolution: bit (r*S + s) set if the row's pixel under tap (r, s) lies in the image
+  const int c_log[2] = {(lane & 7) ^ (lane >> 4), (lane & 7) ^ (lane >> 4) ^ 4};
+  // what is added to a row's byte offset for piece i
+  auto piece_off = [&](int i) { return (uint32_t)c_log[i & 1] * 16u + FRONT - 1024u * (uint32_t)i; };
+  uint32_t offA[NA];   // offset of this lane's piece of row i at reduction index 0 (tap (0,0), channel 0), as dma_stage wants it
+  uint32_t tapsA[NA];  // convolution: top bit set if the row's pixel under the next stage's tap lies outside the image, then the later taps' bits
   // convolution, scalar: pixels per image, first image of the tile, bit rr*S for every filter row rr
   int g_hw = 0, g_b0 = 0;
   uint32_t g_rows = 0;
@@ -1553,10 +1387,10 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
   }
 #pragma unroll
   for (int i = 0; i < NA; ++i) {
-    const int m = m0 + 8 * (wave + 4 * i) + lrow;
+    const int m = m0 + 8 * (NA * wave + i) + lrow;
     const bool in = m < m_end;  // rows past the edge arrive as zeros; never stored
     if constexpr (!GATHER) {
-      offA[i] = in ? (uint32_t)((m - m0) * (int)P.lda * ES) + (uint32_t)c_log * 16u : NOWHERE;
+      offA[i] = in ? (uint32_t)((m - m0) * (int)P.lda * ES) + piece_off(i) : NOWHERE;
       tapsA[i] = 0;
     } else {
       // Pixel (b, ho, wo) of the row; its offset from the descriptor's origin (the corner of the padded first
@@ -1566,7 +1400,7 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
       const int rem = mm - b * g_hw;
       const int ho = fast_div(rem, P.div_wo);
       const int hs = ho * P.stride, ws = (rem - ho * P.Wo) * P.stride;  // row and column of tap (0,0) in the padded image
-      offA[i] = (uint32_t)((((b - g_b0) * P.H + hs) * P.W + ws) * P.Cin * ES) + (uint32_t)c_log * 16u;
+      offA[i] = (uint32_t)((((b - g_b0) * P.H + hs) * P.W + ws) * P.Cin * ES) + piece_off(i);
       // filter rows rr with 0 <= hb + rr < H form a range [lo, hi), and so do the filter columns; the
       // columns' bits times the bits rr*S of the rows in range is the mask of all taps in the image (no two
       // products overlap: the columns' bits lie below S; at most 31 taps)
@@ -1575,14 +1409,14 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
       const int wlo = max(0, -wb), whi = min(P.S, P.W - wb);
       const uint32_t wmk = whi > wlo ? ((1u << whi) - 1u) & ~((1u << wlo) - 1u) : 0u;
       const uint32_t rmk = hhi > hlo ? g_rows & ((1u << (hhi * P.S)) - 1u) & ~((1u << (hlo * P.S)) - 1u) : 0u;
-      tapsA[i] = in ? wmk * rmk : 0u;
+      tapsA[i] = __builtin_bitreverse32(~(in ? wmk * rmk : 0u));  // tap 0 in the top bit
     }
   }
   uint32_t offB[NBW];
 #pragma unroll
   for (int i = 0; i < NBW; ++i) {
-    const int n = n0 + 8 * (wave + 4 * i) + lrow;
-    offB[i] = n < n_end ? (uint32_t)((n - n0) * (int)P.ldb * ES) + (uint32_t)c_log * 16u : NOWHERE;
+    const int n = n0 + 8 * (NBW * wave + i) + lrow;
+    offB[i] = n < n_end ? (uint32_t)((n - n0) * (int)P.ldb * ES) + piece_off(i) : NOWHERE;
   }
 
   f32x16 acc[FN][FM];
@@ -1593,107 +1427,144 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[fn][fm][i] = 0.f;
 
-  // scalar position of the next stage to load: reduction index k_next; for a convolution the tap
-  // (t_r, t_s) and the first channel t_c of the stage
+  // scalar position of the next stage to load: reduction index k_next, byte offset from the rows' starts (weights) and
+  // from the pixels under tap (0,0) (a convolution's image: consecutive channels and consecutive taps of a filter row follow
+  // one another, the next filter row lies row_jump further); stages left under the tap, taps left in the filter row
   int k_next = k_begin;
-  int t_r = 0, t_s = 0, t_c = 0;
+  uint32_t soffB = (uint32_t)k_begin * ES, soffA = soffB;
+  int left_c = 0, left_s = 0;
+  const int stages_per_tap = GATHER ? P.Cin / KB : 1;
+  const uint32_t row_jump = GATHER ? (uint32_t)((P.W - P.S) * P.Cin * ES) : 0u;
   if constexpr (GATHER) {
     const int tap = fast_div(k_begin, P.div_cin);
-    t_c = k_begin - tap * P.Cin;
-    t_r = fast_div(tap, P.div_s);
-    t_s = tap - t_r * P.S;
+    const int t_c = k_begin - tap * P.Cin;
+    const int t_r = fast_div(tap, P.div_s);
+    const int t_s = tap - t_r * P.S;
+    soffA = (uint32_t)(((t_r * P.W + t_s) * P.Cin + t_c) * ES);
+    left_c = stages_per_tap - t_c / KB;
+    left_s = P.S - t_s;
+#pragma unroll
+    for (int i = 0; i < NA; ++i) tapsA[i] <<= tap;
   }
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
-  const uint32_t my_blocks = lds_base + (uint32_t)wave * 1024u;  // + slot*SLOT + 4096 i (activations), + BM*128 + 4096 i (weights)
+  const uint32_t my_blocks = lds_base + (uint32_t)wave * (NA * 1024u);  // + slot*SLOT
+  const uint32_t to_b = BM * 128 - (uint32_t)wave * ((NA - NBW) * 1024u);
   auto issue = [&](int slot) {
-    const uint32_t kbytes = (uint32_t)k_next * ES;
     const uint32_t dst = my_blocks + (uint32_t)slot * SLOT;
-    uint32_t va[NA], vb[NBW];
+    uint32_t va[NA];
     if constexpr (GATHER) {
       // (no reduction tail: the reduction length is a multiple of the channel count, that of a stage)
-      const uint32_t tapbit = 1u << ((t_r * P.S + t_s) & 31);
-      const uint32_t tapoff = (uint32_t)(((t_r * P.W + t_s) * P.Cin + t_c) * ES);
 #pragma unroll
-      for (int i = 0; i < NA; ++i) va[i] = (tapsA[i] & tapbit) ? offA[i] : NOWHERE;
+      for (int i = 0; i < NA; ++i) va[i] = offA[i] | (tapsA[i] & NOWHERE);
+      dma_stage<NA, NBW>(descA, descB, va, offB, soffA, soffB, dst, to_b);
+      soffA += KB * ES;
+      if (--left_c == 0) {
+        left_c = stages_per_tap;
 #pragma unroll
-      for (int i = 0; i < NBW; ++i) vb[i] = offB[i];
-      dma_stage<NA, NBW>(descA, descB, va, vb, tapoff, kbytes, dst);
-      t_c += KB;
-      if (t_c >= P.Cin) {
-        t_c = 0;
-        if (++t_s == P.S) {
-          t_s = 0;
-          ++t_r;
+        for (int i = 0; i < NA; ++i) tapsA[i] <<= 1;
+        if (--left_s == 0) {
+          left_s = P.S;
+          soffA += row_jump;
         }
       }
     } else {
-      // this lane's piece lies beyond the end of the reduction (last stage of a length that is not a
-      // multiple of a stage): nowhere
-      const uint32_t tail = k_next + c_log * CE < k_stop ? 0u : NOWHERE;
+      if (k_next + KB <= k_stop) {
+        dma_stage<NA, NBW>(descA, descB, offA, offB, soffB, soffB, dst, to_b);
+      } else {
+        // last stage of a length that is not a multiple of a stage: pieces beyond the end of the reduction come from nowhere
+        uint32_t vb[NBW];
 #pragma unroll
-      for (int i = 0; i < NA; ++i) va[i] = offA[i] | tail;
+        for (int i = 0; i < NA; ++i) va[i] = k_next + c_log[i & 1] * CE < k_stop ? offA[i] : NOWHERE;
 #pragma unroll
-      for (int i = 0; i < NBW; ++i) vb[i] = offB[i] | tail;
-      dma_stage<NA, NBW>(descA, descB, va, vb, kbytes, kbytes, dst);
+        for (int i = 0; i < NBW; ++i) vb[i] = k_next + c_log[i & 1] * CE < k_stop ? offB[i] : NOWHERE;
+        dma_stage<NA, NBW>(descA, descB, va, vb, soffB, soffB, dst, to_b);
+      }
+      k_next += KB;
     }
-    k_next += KB;
+    soffB += KB * ES;
   };
 
   // fragment addresses inside a slot: row (w*F + f)*32 + l32, logical piece 2 kk + half at position
   // (2 kk + half) ^ swizzle(row), and swizzle(row) = (l32 >> 1) & 7 for every block of 32 rows
-  const int frag_off = l32 * 128;
-  const int frag_pos = half ^ ((l32 >> 1) & 7);  // position of piece `half`; piece 2 kk + half is at frag_pos ^ 2 kk
-  const int a_base = wm * FM * 4096;
-  const int b_base = BM * 128 + wn * FN * 4096;
+  int fragA[4], fragB[4];  // piece 2 kk + half of block 0's row, in slot 0
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    const int at = l32 * 128 + (((2 * kk + half) ^ ((l32 >> 1) & 7)) << 4);
+    fragA[kk] = wm * FM * 4096 + at;
+    fragB[kk] = BM * 128 + wn * FN * 4096 + at;
+  }
 
 #ifdef SK_DIAG_CLOCKS
   const int diag_tile = pf.diag_tile;
 #endif
   SK_DIAG(1);
   const int nstages = (k_stop - k_begin + KB - 1) / KB;
+  // the fragments of step kk of the stage in slot sl
+  u32x4 fa[2][FM], fb[2][FN];
+  auto frag = [&](int sl, int kk, u32x4(&xa)[FM], u32x4(&xb)[FN]) {
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm) xa[fm] = *(const u32x4 *)(lds + fragA[kk] + (sl * SLOT + fm * 4096));
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn) xb[fn] = *(const u32x4 *)(lds + fragB[kk] + (sl * SLOT + fn * 4096));
+  };
+  auto multiply = [&](const u32x4(&xa)[FM], const u32x4(&xb)[FN]) {
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+      for (int fm = 0; fm < FM; ++fm) mma32<DT>(xb[fn], xa[fm], acc[fn][fm]);
+  };
   // (the previous tile's readers of this LDS buffer have passed the barrier at the end of their tile)
 #pragma unroll
-  for (int u = 0; u < NS - 1; ++u)
+  for (int u = 0; u < NS; ++u)
     if (u < nstages) issue(u);
-  int slot = 0;
-  for (int h = 0; h < nstages; ++h) {
-    pf.at_step(h, nstages, CLAIM_LEAD, ISSUE_GAP);
-    // this wave's loads of stage h have landed: the only loads issued after them are those of stage h+1
-    if (NS == 3 && h + 1 < nstages)
-      wait_loads_but<NPW>();
-    else
-      wait_loads_but<0>();
-    __builtin_amdgcn_s_barrier();  // ... and everyone's; everyone is done with stage h-1
-    asm volatile("" ::: "memory");
-    if (h + NS - 1 < nstages) issue(slot == 0 ? NS - 1 : slot - 1);  // stage h+NS-1 into the slot stage h-1 used
-    __builtin_amdgcn_sched_barrier(0);
-    const unsigned char *la = lds + slot * SLOT + a_base + frag_off;
-    const unsigned char *lb = lds + slot * SLOT + b_base + frag_off;
-    // the fragments of step kk+1 are requested before the MFMAs of step kk (the scheduler is held to
-    // that order: left alone it sinks every read to just above its first use).  Requesting all four
-    // steps' fragments at the start of the stage was measured slower: the waves of a workgroup leave
-    // the barrier together, and their reads then queue at the LDS.
-    u32x4 fa[2][FM], fb[2][FN];
-    auto frag = [&](int kk, u32x4(&xa)[FM], u32x4(&xb)[FN]) {
-      const int pos = (frag_pos ^ (2 * kk)) << 4;
+  if (nstages >= NS)
+    wait_loads_but<(NS - 1) * NPW>();
+  else
+    wait_loads_but<0>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  frag(0, 0, fa[0], fb[0]);
+  const int claim_at = nstages > CLAIM_LEAD ? nstages - CLAIM_LEAD : 0;
+  const int issue_at = min(claim_at + ISSUE_GAP, nstages - 1);
+  for (int h0 = 0; h0 < nstages; h0 += NS) {
+    if ((unsigned)(claim_at - h0) < (unsigned)NS) pf.claim();
+    if ((unsigned)(issue_at - h0) < (unsigned)NS) pf.issue();
 #pragma unroll
-      for (int fm = 0; fm < FM; ++fm) xa[fm] = *(const u32x4 *)(la + fm * 4096 + pos);
+    for (int slot = 0; slot < NS; ++slot) {
+      const int h = h0 + slot;
+      if (h < nstages) {
+        // The fragments of step kk+1 are requested before the MFMAs of step kk (the scheduler is held to
+        // that order: left alone it sinks every read to just above its first use).  Requesting all four
+        // steps' fragments at the start of the stage was measured slower: the waves of a workgroup leave
+        // the barrier together, and their reads then queue at the LDS.
 #pragma unroll
-      for (int fn = 0; fn < FN; ++fn) xb[fn] = *(const u32x4 *)(lb + fn * 4096 + pos);
-    };
-    frag(0, fa[0], fb[0]);
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      if (kk + 1 < 4) frag(kk + 1, fa[(kk + 1) & 1], fb[(kk + 1) & 1]);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-        for (int fm = 0; fm < FM; ++fm) mma32<DT>(fb[kk & 1][fn], fa[kk & 1][fm], acc[fn][fm]);
-      __builtin_amdgcn_sched_barrier(0);
+        for (int kk = 0; kk < 3; ++kk) {
+          frag(slot, kk + 1, fa[(kk + 1) & 1], fb[(kk + 1) & 1]);
+          __builtin_amdgcn_sched_barrier(0);
+          multiply(fa[kk & 1], fb[kk & 1]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        // The stages change hands ahead of the last step's MFMAs, not behind them: its fragments are in registers
+        // (so this stage's slot is free once everyone has got here) and stage h+1 has landed, so the barrier, the
+        // loads of stage h+NS and the first fragments of stage h+1 all run beside the MFMAs.
+        if (h + 1 < nstages) {
+          // this wave's loads of stage h+1 have landed: the only ones issued after them are those of the NS - 2 stages behind it
+          if (NS > 2 && h + NS - 1 < nstages)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * NPW) : "memory");
+          else
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+          if (h + NS < nstages) issue(slot);
+          __builtin_amdgcn_sched_barrier(0);
+          frag(slot + 1 == NS ? 0 : slot + 1, 0, fa[0], fb[0]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(fa[1], fb[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (h == 0) SK_DIAG(2);
+      }
     }
-    if (h == 0) SK_DIAG(2);
-    slot = slot + 1 == NS ? 0 : slot + 1;
   }
   SK_DIAG(3);
   __syncthreads();  // everyone is done with the last stage before the output tile is staged in the same LDS
@@ -1705,23 +1576,14 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
 template <int DT, int BM, int BN>
 __device__ __forceinline__ void run_lds_tile(const DevProblem &P, const sk_tile &T, const SplitK &sp, unsigned char *lds,
                                              uint32_t *s_flag, Prefetch &pf) {
-#ifndef SK_NO_LEAN_TILES
   LeanOperands L;
   if (lean_operands<Elem<DT>::ES>(P, T, L)) {
-#ifdef SK_REGISTER_RING_TILES
-    if (P.gather)
-      run_tile_lean<DT, BM, BN, 2, 2, true>(P, T, sp, lds, s_flag, pf, L);
-    else
-      run_tile_lean<DT, BM, BN, 2, 2, false>(P, T, sp, lds, s_flag, pf, L);
-#else
     if (P.gather)
       run_tile_dma<DT, BM, BN, true>(P, T, sp, lds, s_flag, pf, L);
     else
       run_tile_dma<DT, BM, BN, false>(P, T, sp, lds, s_flag, pf, L);
-#endif
     return;
   }
-#endif
   run_tile<DT, BM, BN, 2, 2>(P, T, sp, lds, s_flag, pf);
 }
 
