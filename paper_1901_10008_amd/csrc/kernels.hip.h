@@ -69,14 +69,21 @@ __device__ __forceinline__ S load_uniform(const S *src) {
   return __builtin_bit_cast(S, v);
 }
 
-// The same from a copy in LDS.
+// The same through the scalar cache, for records that nothing writes while the kernel runs: a few loads straight into
+// scalar registers.  (Handed over through LDS instead, every wave spent two vector instructions per dword on it.)
+#define SK_CONSTANT __attribute__((address_space(4)))
 template <class S>
-__device__ __forceinline__ S unpack_uniform(const uint32_t *src) {
+__device__ __forceinline__ S load_record(const S *src) {
+  static_assert(sizeof(S) % 4 == 0, "whole dwords");
   struct Words {
     uint32_t w[sizeof(S) / 4];
   } v;
+  uintptr_t at = (uintptr_t)src;
+  // (opaque, so that a record read again later is not kept in registers meanwhile)
+  asm volatile("" : "+s"(at));
+  const uint32_t SK_CONSTANT *p = (const uint32_t SK_CONSTANT *)at;
 #pragma unroll
-  for (unsigned i = 0; i < sizeof(S) / 4; ++i) v.w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)src[i]);
+  for (unsigned i = 0; i < sizeof(S) / 4; ++i) v.w[i] = p[i];
   return __builtin_bit_cast(S, v);
 }
 
@@ -499,6 +506,7 @@ struct Prefetch {
                       // every load in flight.
   uint32_t last;      // last valid index of the launch
   int tid;            // this tile's copy of the thread index (see the tile loop)
+  const TileWork *rec;  // the record of the tile that is running
   uint32_t word = 0;
   // An LDS tile is run by the die whose list holds it (see the tile loop).  While such a tile runs, the
   // workgroup also draws the next entry of its die's list (xhead not null), on the guess that its next
@@ -999,7 +1007,20 @@ __device__ __forceinline__ void finish_tile(const DevProblem &P, const sk_tile &
     constexpr int RPI = WG_THREADS / PIECES;         // rows per store instruction
     const int pc = tid % PIECES, pr = tid / PIECES;
     const int n = n0 + pc * CE;
+    // 32-bit offsets from the tile's corner; rows past the edge lie outside the descriptor and are not stored
+    const int64_t extent = ((int64_t)((int)T.m_len - 1) * P.ldc + (int)T.n_len) * ES;
+    if (n + CE <= n_end && 256 * P.ldc * ES < (int64_t)1 << 31) {
+      const __amdgpu_buffer_rsrc_t desc = __builtin_amdgcn_make_buffer_rsrc(
+          (void *)((uintptr_t)P.C + (uintptr_t)(((int64_t)m0 * P.ldc + n0) * ES)), 0, (int)extent, 0x00020000);
+      const uint32_t ld = (uint32_t)(P.ldc * ES), voff = (uint32_t)pr * ld + (uint32_t)pc * 16u;
+      u32x4 v[BM / RPI];
 #pragma unroll
+      for (int i = 0; i < BM / RPI; ++i) v[i] = *(const u32x4 *)(lds + pr * OROW + pc * 16 + i * (RPI * OROW));
+#pragma unroll
+      for (int i = 0; i < BM / RPI; ++i) __builtin_amdgcn_raw_buffer_store_b128(v[i], desc, voff + (uint32_t)(i * RPI) * ld, 0, 0);
+      return;
+    }
+#pragma unroll 1
     for (int i = 0; i < BM / RPI; ++i) {
       const int r = pr + i * RPI;
       const int m = m0 + r;
@@ -1362,8 +1383,7 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
   const int wm = wave & 1, wn = wave >> 1;
   const int l32 = lane & 31, half = lane >> 5;
 
-  const int m0 = (int)T.m0, n0 = (int)T.n0;
-  const int m_end = m0 + (int)T.m_len, n_end = n0 + (int)T.n_len;
+  const int m0 = (int)T.m0, m_end = m0 + (int)T.m_len;
   const int k_begin = (int)T.k0, k_stop = (int)T.k0 + (int)T.k_len;
 
   constexpr uint32_t FRONT = 3072;  // see dma_stage
@@ -1378,46 +1398,56 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
   auto piece_off = [&](int i) { return (uint32_t)c_log[i & 1] * 16u + FRONT - 1024u * (uint32_t)i; };
   uint32_t offA[NA];   // offset of this lane's piece of row i at reduction index 0 (tap (0,0), channel 0), as dma_stage wants it
   uint32_t tapsA[NA];  // convolution: top bit set if the row's pixel under the next stage's tap lies outside the image, then the later taps' bits
-  // convolution, scalar: pixels per image, first image of the tile, bit rr*S for every filter row rr
-  int g_hw = 0, g_b0 = 0;
-  uint32_t g_rows = 0;
-  if constexpr (GATHER) {
-    g_hw = P.Ho * P.Wo;
-    g_b0 = fast_div(m0, P.div_hw);
-    for (int rr = 0; rr < P.R; ++rr) g_rows |= 1u << (rr * P.S);
-  }
+  if constexpr (!GATHER) {
+    const uint32_t step = 8u * (uint32_t)((int)P.lda * ES) - 1024u;  // from one piece's row to the next, see dma_stage
+    const int row = 8 * NA * wave + lrow;
+    uint32_t off = (uint32_t)(row * ((int)P.lda * ES)) + FRONT;
 #pragma unroll
-  for (int i = 0; i < NA; ++i) {
-    const int m = m0 + 8 * (NA * wave + i) + lrow;
-    const bool in = m < m_end;  // rows past the edge arrive as zeros; never stored
-    if constexpr (!GATHER) {
-      offA[i] = in ? (uint32_t)((m - m0) * (int)P.lda * ES) + piece_off(i) : NOWHERE;
+    for (int i = 0; i < NA; ++i, off += step) {
+      offA[i] = row + 8 * i < (int)T.m_len ? off + (uint32_t)c_log[i & 1] * 16u : NOWHERE;  // rows past the edge arrive as zeros; never stored
       tapsA[i] = 0;
-    } else {
-      // Pixel (b, ho, wo) of the row; its offset from the descriptor's origin (the corner of the padded first
-      // image of the tile) in 32 bits: lean_operands has checked that the tile's images lie within 2^31 bytes.
-      const int mm = in ? m : m_end - 1;
-      const int b = fast_div(mm, P.div_hw);
-      const int rem = mm - b * g_hw;
-      const int ho = fast_div(rem, P.div_wo);
-      const int hs = ho * P.stride, ws = (rem - ho * P.Wo) * P.stride;  // row and column of tap (0,0) in the padded image
-      offA[i] = (uint32_t)((((b - g_b0) * P.H + hs) * P.W + ws) * P.Cin * ES) + piece_off(i);
-      // filter rows rr with 0 <= hb + rr < H form a range [lo, hi), and so do the filter columns; the
-      // columns' bits times the bits rr*S of the rows in range is the mask of all taps in the image (no two
-      // products overlap: the columns' bits lie below S; at most 31 taps)
-      const int hb = hs - P.pad_h, wb = ws - P.pad_w;
-      const int hlo = max(0, -hb), hhi = min(P.R, P.H - hb);
-      const int wlo = max(0, -wb), whi = min(P.S, P.W - wb);
-      const uint32_t wmk = whi > wlo ? ((1u << whi) - 1u) & ~((1u << wlo) - 1u) : 0u;
-      const uint32_t rmk = hhi > hlo ? g_rows & ((1u << (hhi * P.S)) - 1u) & ~((1u << (hlo * P.S)) - 1u) : 0u;
-      tapsA[i] = __builtin_bitreverse32(~(in ? wmk * rmk : 0u));  // tap 0 in the top bit
+    }
+  } else {
+    // Lane l works out row l of the wave's 8 NA rows (the lanes of a piece's row would all do the same divisions), then
+    // every lane fetches those of its NA rows.
+    static_assert(8 * NA <= 64, "one row per lane");
+    const int g_hw = P.Ho * P.Wo, g_b0 = fast_div(m0, P.div_hw);
+    uint32_t g_rows = 0;  // bit rr*S for every filter row rr
+    for (int rr = 0; rr < P.R; ++rr) g_rows |= 1u << (rr * P.S);
+    // Pixel (b, ho, wo) of the row; its offset from the descriptor's origin (the corner of the padded first
+    // image of the tile) in 32 bits: lean_operands has checked that the tile's images lie within 2^31 bytes.
+    const int m = m0 + 8 * NA * wave + (lane & (8 * NA - 1));
+    const bool in = m < m_end;  // rows past the edge arrive as zeros; never stored
+    const int mm = in ? m : m_end - 1;
+    const int b = fast_div(mm, P.div_hw);
+    const int rem = mm - b * g_hw;
+    const int ho = fast_div(rem, P.div_wo);
+    const int hs = ho * P.stride, ws = (rem - ho * P.Wo) * P.stride;  // row and column of tap (0,0) in the padded image
+    const uint32_t off = (uint32_t)((((b - g_b0) * P.H + hs) * P.W + ws) * P.Cin * ES);
+    // filter rows rr with 0 <= hb + rr < H form a range [lo, hi), and so do the filter columns; the
+    // columns' bits times the bits rr*S of the rows in range is the mask of all taps in the image (no two
+    // products overlap: the columns' bits lie below S; at most 31 taps)
+    const int hb = hs - P.pad_h, wb = ws - P.pad_w;
+    const int hlo = max(0, -hb), hhi = min(P.R, P.H - hb);
+    const int wlo = max(0, -wb), whi = min(P.S, P.W - wb);
+    const uint32_t wmk = whi > wlo ? ((1u << whi) - 1u) & ~((1u << wlo) - 1u) : 0u;
+    const uint32_t rmk = hhi > hlo ? g_rows & ((1u << (hhi * P.S)) - 1u) & ~((1u << (hlo * P.S)) - 1u) : 0u;
+    const uint32_t taps = __builtin_bitreverse32(~(in ? wmk * rmk : 0u));  // tap 0 in the top bit
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int from = (8 * i + lrow) * 4;
+      offA[i] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)off) + piece_off(i);
+      tapsA[i] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)taps);
     }
   }
   uint32_t offB[NBW];
+  {
+    const uint32_t step = 8u * (uint32_t)((int)P.ldb * ES) - 1024u;
+    const int row = 8 * NBW * wave + lrow;
+    uint32_t off = (uint32_t)(row * ((int)P.ldb * ES)) + FRONT;
 #pragma unroll
-  for (int i = 0; i < NBW; ++i) {
-    const int n = n0 + 8 * (NBW * wave + i) + lrow;
-    offB[i] = n < n_end ? (uint32_t)((n - n0) * (int)P.ldb * ES) + piece_off(i) : NOWHERE;
+    for (int i = 0; i < NBW; ++i, off += step)
+      offB[i] = row + 8 * i < (int)T.n_len ? off + (uint32_t)c_log[i & 1] * 16u : NOWHERE;
   }
 
   f32x16 acc[FN][FM];
@@ -1569,7 +1599,9 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
   }
   SK_DIAG(3);
   __syncthreads();  // everyone is done with the last stage before the output tile is staged in the same LDS
-  finish_tile<DT, BM, BN, 2, 2>(P, T, sp, lds, s_flag, tid, acc);
+  // (read again: kept through the stages, what the outputs need of the record cost the loop its scalar registers)
+  const TileWork again = load_record(pf.rec);
+  finish_tile<DT, BM, BN, 2, 2>(again.prob, again.tile, sp, lds, s_flag, tid, acc);
   SK_DIAG(4);
 }
 
@@ -2137,8 +2169,8 @@ __global__ void sk_arm_start_stamp(uint64_t *slot) { *slot = ~0ull; }
 template <int ONLY_DT, bool ANY_ALIGNMENT>
 __global__ void __launch_bounds__(WG_THREADS, 2) sk_superkernel(const TileWork *__restrict__ work, KernelArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_TILE_BYTES];
-  // next record by parity; behind it [0] its ticket, [1] flags (MAIL_*), [2] its index in xwork, [3] the ticket
-  // that waits while it runs
+  // By parity: the next record as wave 0 fetched it (which brings it into the L2 for everyone, see load_record); behind it
+  // [0] its ticket, [1] flags (MAIL_*), [2] its index in xwork, [3] the ticket that waits while it runs
   __shared__ __attribute__((aligned(16))) uint32_t s_mail[2][WORK_DWORDS + 4];
   __shared__ uint32_t s_flag;
   const SplitK sp{a.ws, a.ws_off, a.arrive};
@@ -2302,9 +2334,10 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sk_superkernel(const TileWork *
 #endif
     if (!(flags & MAIL_RUN)) break;
     const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mail[par][WORK_DWORDS]);
-    const TileWork W = unpack_uniform<TileWork>(s_mail[par]);
     const TileWork *cur =
         (flags & MAIL_FROM_LIST) ? a.xwork + (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mail[par][WORK_DWORDS + 2]) : work + t;
+    // (wave 0 has fetched the record ahead of time: it is in this die's L2)
+    const TileWork W = load_record(cur);
     const bool pending = (flags & MAIL_PENDING) != 0;  // a ticket waits: this tile takes no new one
     owes = (flags & MAIL_OWES) != 0;
     const uint32_t waits = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mail[par][WORK_DWORDS + 3]);
@@ -2318,7 +2351,7 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sk_superkernel(const TileWork *
     asm volatile("" : "+v"(tid));
     const bool queue = a.dynamic && !pending;
     Prefetch pf{work, queue ? &a.counters[0] : nullptr, queue ? a.tile_begin + gridDim.x : 0u,
-                pending ? waits : t + gridDim.x, last, tid};
+                pending ? waits : t + gridDim.x, last, tid, cur};
     const sk_tile &T = W.tile;
     drew = lists && T.cls >= CLS_TILE_128x128 && !pending && !owes && !((used_up >> die) & 1u);
     if (drew) {
@@ -2352,8 +2385,11 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sk_superkernel(const TileWork *
     got_base = pf.base;
     got_word = pf.word;
     have_done = true;
-    done_problem = T.problem;
-    done_count = (uint32_t)P.tile_count;
+    if (a.remaining) {
+      const TileWork again = load_record(cur);
+      done_problem = again.tile.problem;
+      done_count = (uint32_t)again.prob.tile_count;
+    }
   }
 
   // the last workgroup to leave re-arms the queue for the next launch
