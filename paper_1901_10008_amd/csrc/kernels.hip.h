@@ -553,8 +553,8 @@ constexpr int CLAIM_LEAD = 8, ISSUE_GAP = 4;
 // piece that would reach beyond the end of a row is read so that it ends with the row, and shifted into
 // place (shift_piece) when it is used; only the last block of a row has such pieces.  Everything else is
 // the same, so aligned operators of a plan that has others too run through this form as well.
-template <int DT, int RM, bool ANY>
-__device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T, const SplitK &sp,
+template <int DT, int RM, bool ANY, bool GATHER>
+__device__ __forceinline__ void run_skinny_form(const DevProblem &P, const sk_tile &T, const SplitK &sp,
                                            unsigned char *lds, uint32_t *s_flag, Prefetch &pf) {
   constexpr int ES = Elem<DT>::ES;
   constexpr int CE = 16 / ES;
@@ -567,9 +567,16 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
   constexpr int BPC = 1 << BPC_LOG2;                // blocks per chunk: 4, 2, 1
   constexpr int PPR = ROWB / 16;                    // pieces per row and chunk
   constexpr int BUF = ROWS * LROW;                  // bytes per LDS buffer
-  constexpr int NB = 2;                             // ring slots: one block in flight while one is multiplied.
-  // (With every workgroup streaming, the memory system is saturated by far fewer bytes in flight
-  // than the launch holds even at this depth; deeper rings only lengthen every load's wait.)
+  // Ring slots (weight blocks in flight plus one) and activation chunks in flight.  Loads come back in order, so a chunk
+  // needed one step after it was asked for also makes every weight load issued before it late.  A convolution's
+  // chunks are gathered, and its tiles mostly run beside LDS tiles that leave the memory system idle: with one of each in flight a
+  // 64-row tile of a 3x3 layer took a memory round trip, 1.8 us, per step; with three and two the ResNet mix x16 takes 85.6
+  // instead of 90.4 us.  GEMMs stream: every workgroup of the launch does, the memory system is saturated by far
+  // fewer bytes in flight than the launch holds even at one block, and a deeper ring only lengthens every load's
+  // wait (BERT mix x8 176 us with one and one, 181 with three and two; main workload 1035, 1041).
+  constexpr int NB = GATHER ? 4 : 2;
+  constexpr int AD = GATHER && BPC < 4 ? 2 : 1;
+  static_assert(AD == 1 || BPC * AD <= NB, "a chunk's registers are told apart by the step within the unrolled loop");
   static_assert(ROWB == BPC * 128, "chunk geometry");
   static_assert(2 * BUF <= LDS_TILE_BYTES, "activation chunks do not fit");
 
@@ -596,8 +603,8 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
   const bool s_ok = s_row < P.Mg;
   const RowA srow = row_of(P, s_ok ? s_row : 0);
   const int s_lds = s_row * LROW + s_piece * 16;
-  u32x4 ar[SPT];
-  int ar_k = 0;  // (ANY) reduction index of ar[0]
+  u32x4 ar[AD][SPT];
+  int ar_k[AD] = {};  // (ANY) reduction index of the first piece
   const bool ragged = ANY && P.Kg % CE != 0;  // some pieces end beyond their row
   // For a convolution: filter tap (g_r, g_s) and channel g_c of this thread's first piece in the
   // chunk that stage_load will fetch next, and g_off = ((g_r*W + g_s)*Cin + g_c), its distance in
@@ -606,7 +613,7 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
   int g_r = 0, g_s = 0, g_c = 0;
   int64_t g_off = 0;
   const int64_t next_filter_row = (int64_t)(P.W - P.S) * P.Cin;
-  if (P.gather) {
+  if constexpr (GATHER) {
     const int kk = k0 + s_piece * CE;
     const int tap = fast_div(kk, P.div_cin);
     g_c = kk - tap * P.Cin;
@@ -616,9 +623,9 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
   }
   const int g_r0 = g_r, g_s0 = g_s, g_c0 = g_c;
   const int64_t g_off0 = g_off;
-  auto stage_load = [&](int c) {
+  auto stage_load = [&](int c, u32x4(&ar)[SPT], int &ar_k) {
     const int k = k0 + ((c << BPC_LOG2) * 8 + s_piece) * CE;
-    if (!P.gather) {
+    if constexpr (!GATHER) {
       ar_k = k;
 #pragma unroll
       for (int i = 0; i < SPT; ++i) {
@@ -665,7 +672,7 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
       }
     }
   };
-  auto stage_store = [&](int c) {
+  auto stage_store = [&](int c, u32x4(&ar)[SPT], int ar_k) {
     unsigned char *base = lds + (c & 1) * BUF + s_lds;
     if (ragged) {
 #pragma unroll
@@ -751,13 +758,25 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
 #endif
   SK_DIAG(1);
   set_load_rows(0);
-  stage_load(0);
+  // the next chunk to fetch: chunk l_c of pass l_it
+  int l_c = 0, l_it = 0;
+  auto next_chunk = [&](u32x4(&x)[SPT], int &k) {
+    if (l_it >= iters) return;
+    stage_load(l_c, x, k);
+    if (++l_c == nchunks) {
+      l_c = 0;
+      ++l_it;
+    }
+  };
+  next_chunk(ar[0], ar_k[0]);
   u32x4 w[NB][4];
+  next_load(w[0]);
+  if (AD == 2 && restage_each) next_chunk(ar[AD - 1], ar_k[AD - 1]);
 #pragma unroll
-  for (int u = 0; u < NB - 1; ++u) next_load(w[u]);
+  for (int u = 1; u < NB - 1; ++u) next_load(w[u]);
   if (!restage_each) {
     // the only activation chunk serves every pass
-    stage_store(0);
+    stage_store(0, ar[0], ar_k[0]);
     buf = 0;
     __syncthreads();
   }
@@ -769,16 +788,13 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
       const bool live = i0 + u < total;
       pf.at_step(i0 + u, total, CLAIM_LEAD, ISSUE_GAP);
       if (live && restage_each && (blk & (BPC - 1)) == 0) {
-        // first block of a chunk: publish it, then start fetching the one after it
-        // (chunk c+1 of this pass, or chunk 0 again for the next pass)
+        // first block of a chunk: publish it, then start fetching the AD-th after it (of this pass, or of the next).
+        // (Chunks and unrolled steps keep step: a pass has whole chunks, so steps u of one parity of u / BPC meet chunks of one.)
+        constexpr int set = AD == 2 ? 1 : 0;
         buf ^= 1;
-        stage_store(buf);
+        stage_store(buf, ar[(u / BPC) & set], ar_k[(u / BPC) & set]);
         __syncthreads();
-        const int c_next = (blk >> BPC_LOG2) + 1;
-        if (c_next < nchunks)
-          stage_load(c_next);
-        else if (it + 1 < iters)
-          stage_load(0);
+        next_chunk(ar[(u / BPC) & set], ar_k[(u / BPC) & set]);
       }
       next_load(w[(u + NB - 1) % NB]);
       if (live) {
@@ -892,6 +908,15 @@ __device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T
   }
   if (finish) store_pass();
   SK_DIAG(4);
+}
+
+template <int DT, int RM, bool ANY>
+__device__ __forceinline__ void run_skinny(const DevProblem &P, const sk_tile &T, const SplitK &sp, unsigned char *lds,
+                                           uint32_t *s_flag, Prefetch &pf) {
+  if (P.gather)
+    run_skinny_form<DT, RM, ANY, true>(P, T, sp, lds, s_flag, pf);
+  else
+    run_skinny_form<DT, RM, ANY, false>(P, T, sp, lds, s_flag, pf);
 }
 
 // A slice of a split reduction hands its partial sums over; true in the workgroup that arrived last, with the
