@@ -94,6 +94,13 @@ constexpr int WG_THREADS = 256;
 constexpr int LDS_ROW = 144;                  // 128 bytes of K + 16 bytes of padding (bank spread)
 constexpr int LDS_TILE_BYTES = 512 * LDS_ROW;  // 72 KB per workgroup: two workgroups share a CU's 160 KB
 
+// Plans of which every tile is a lean 128 x 64 tile ("narrow": the 3x3 layers with at most 64 output channels of many
+// tenants) run in a kernel of their own: without the other classes' registers and with two stage images instead of
+// three, three workgroups share a CU.  Such a tile spends half its time around its few stages (set-up, first loads,
+// outputs, hand-over), which only the CU's other workgroups
+// can fill: the 3x3 64-channel convolutions on 56x56 of 512 tenants take 214 us instead of 239.
+constexpr int NARROW_LDS_BYTES = 2 * (128 + 64) * 128;
+
 // Queue counters of a table: [0] tiles handed out beyond the first grid-full, [1] finished workgroups,
 // [16 * (1 + x)] entries handed out from die x's list of LDS tiles (a 64-byte line each).
 constexpr int QUEUE_COUNTERS = 16 * 9 + 1;
@@ -1004,7 +1011,7 @@ __device__ __forceinline__ void finish_tile(const DevProblem &P, const sk_tile &
   // Where C allows 16-byte stores the tile goes through LDS instead (free by now: every wave has
   // passed the last stage's barrier) and leaves as whole rows: 16 lanes x 16 bytes side by side.
   constexpr int OROW = BN * ES + 16;  // padded row of the output tile in LDS
-  static_assert(BM * OROW <= LDS_TILE_BYTES, "output tile does not fit the LDS buffer");
+  static_assert(BM * OROW <= (BN == 64 ? NARROW_LDS_BYTES : LDS_TILE_BYTES), "output tile does not fit the LDS buffer");
   const bool wide = ((uintptr_t)P.C % 16 == 0) && ((P.ldc * ES) % 16 == 0);
   if (wide) {
 #pragma unroll
@@ -1321,7 +1328,7 @@ __device__ __forceinline__ bool lean_operands(const DevProblem &P, const sk_tile
 //     the 16 lanes that a fragment read serves together (rows r .. r+15, one piece) fall into
 //     16 different groups of four banks.  The swizzle is applied on the global side: lane i of
 //     a load asks for piece (i & 7) ^ swizzle(row of the lane).
-//   * a ring of NS such images (as many as fit LDS_TILE_BYTES); one barrier per stage, ahead of its last
+//   * a ring of NS such images (as many as fit the kernel's LDS buffer); one barrier per stage, ahead of its last
 //     step's MFMAs, says both "everyone's part of stage h+1 has landed" and "everyone has stage h's last fragments
 //     in registers", so that stage h+NS may overwrite its image: NS-1 stages are in flight for most of a stage.
 //   * the compiler does not see these loads (inline assembly; told about them it would wait for
@@ -1387,7 +1394,7 @@ __device__ __forceinline__ void wait_loads_but() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <int DT, int BM, int BN, bool GATHER>
+template <int DT, int BM, int BN, bool GATHER, int LDS_BYTES>
 __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile &T, const SplitK &sp, unsigned char *lds,
                                              uint32_t *s_flag, Prefetch &pf, const LeanOperands &L) {
   constexpr int ES = Elem<DT>::ES;
@@ -1397,7 +1404,7 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
   constexpr int NA = BM / 32, NBW = BN / 32;  // load instructions per wave and stage: activations, weights
   constexpr int NPW = NA + NBW;
   constexpr int SLOT = (BM + BN) * 128;       // bytes of a stage in LDS
-  constexpr int NS = LDS_TILE_BYTES / SLOT;   // ring slots
+  constexpr int NS = LDS_BYTES / SLOT;        // ring slots
   constexpr uint32_t NOWHERE = 0x80000000u;   // an offset outside every descriptor: the piece arrives as zeros
   static_assert(NS == 2 || NS == 3, "waits below are written for two or three slots");
   static_assert(NPW < 32, "load counter");
@@ -1631,18 +1638,20 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
 }
 
 // One LDS tile: the lean path where the operator allows it.
-template <int DT, int BM, int BN>
+template <int DT, int BM, int BN, bool NARROW>
 __device__ __forceinline__ void run_lds_tile(const DevProblem &P, const sk_tile &T, const SplitK &sp, unsigned char *lds,
                                              uint32_t *s_flag, Prefetch &pf) {
+  constexpr int BYTES = NARROW ? NARROW_LDS_BYTES : LDS_TILE_BYTES;
   LeanOperands L;
   if (lean_operands<Elem<DT>::ES>(P, T, L)) {
     if (P.gather)
-      run_tile_dma<DT, BM, BN, true>(P, T, sp, lds, s_flag, pf, L);
+      run_tile_dma<DT, BM, BN, true, BYTES>(P, T, sp, lds, s_flag, pf, L);
     else
-      run_tile_dma<DT, BM, BN, false>(P, T, sp, lds, s_flag, pf, L);
+      run_tile_dma<DT, BM, BN, false, BYTES>(P, T, sp, lds, s_flag, pf, L);
     return;
   }
-  run_tile<DT, BM, BN, 2, 2>(P, T, sp, lds, s_flag, pf);
+  // (the host lets only operators into a narrow plan for which every tile is lean)
+  if constexpr (!NARROW) run_tile<DT, BM, BN, 2, 2>(P, T, sp, lds, s_flag, pf);
 }
 
 // ---------------------------------------------------------------------------
@@ -2136,49 +2145,53 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
   }
 }
 
-template <int DT, bool ANY_ALIGNMENT>
+template <int DT, bool ANY_ALIGNMENT, bool NARROW>
 __device__ __forceinline__ void run_class(const DevProblem &P, const sk_tile &T, const DevProblem *P_mem,
                                           const sk_tile *T_mem, const SplitK &sp, unsigned char *lds,
                                           uint32_t *s_flag, Prefetch &pf) {
-  const int cls = T.cls;
-  constexpr int CE = 16 / Elem<DT>::ES;
-  bool pieces = true;  // the fast paths can read the operator
-  if constexpr (ANY_ALIGNMENT) {
-    pieces = (P.flags & (FLAG_VEC_A | FLAG_VEC_B)) == (FLAG_VEC_A | FLAG_VEC_B);
-    if (!pieces) {
-      // One output per thread costs a thread (outputs / 256) * Kg dependent steps of about 0.1 us; a stage
-      // of 64 (fp32: 32) reduction elements through the matrix cores costs a few us whatever the
-      // rectangle.  So only rectangles that are done in a few dozen steps go the first way.
-      const int per_thread = ((int)T.m_len * (int)T.n_len + WG_THREADS - 1) / WG_THREADS;
-      const bool small = (int64_t)per_thread * P.Kg <= 64;
-      // The weight-streaming classes read pieces at any element's address; of convolutions those whose pieces never
-      // straddle two taps.
-      if (!small && cls < CLS_TILE_128x128 && !P.nchw && P.Kg >= CE && (!P.gather || P.Cin % CE == 0)) {
-        pieces = true;
-      } else {
-        pf.claim();
-        pf.issue();
-        // (an operand of less than one piece also goes the first way: the others read whole pieces from inside it)
-        if (small || !holds_a_piece<Elem<DT>::ES>(P))
-          run_generic<DT>(P_mem, T_mem);
-        else if (P.nchw)
-          run_tile_any<DT, true>(P_mem, T_mem, sp, lds, s_flag);
-        else
-          run_tile_any<DT, false>(P_mem, T_mem, sp, lds, s_flag);
+  if constexpr (NARROW) {
+    run_lds_tile<DT, 128, 64, true>(P, T, sp, lds, s_flag, pf);
+  } else {
+    const int cls = T.cls;
+    constexpr int CE = 16 / Elem<DT>::ES;
+    bool pieces = true;  // the fast paths can read the operator
+    if constexpr (ANY_ALIGNMENT) {
+      pieces = (P.flags & (FLAG_VEC_A | FLAG_VEC_B)) == (FLAG_VEC_A | FLAG_VEC_B);
+      if (!pieces) {
+        // One output per thread costs a thread (outputs / 256) * Kg dependent steps of about 0.1 us; a stage
+        // of 64 (fp32: 32) reduction elements through the matrix cores costs a few us whatever the
+        // rectangle.  So only rectangles that are done in a few dozen steps go the first way.
+        const int per_thread = ((int)T.m_len * (int)T.n_len + WG_THREADS - 1) / WG_THREADS;
+        const bool small = (int64_t)per_thread * P.Kg <= 64;
+        // The weight-streaming classes read pieces at any element's address; of convolutions those whose pieces never
+        // straddle two taps.
+        if (!small && cls < CLS_TILE_128x128 && !P.nchw && P.Kg >= CE && (!P.gather || P.Cin % CE == 0)) {
+          pieces = true;
+        } else {
+          pf.claim();
+          pf.issue();
+          // (an operand of less than one piece also goes the first way: the others read whole pieces from inside it)
+          if (small || !holds_a_piece<Elem<DT>::ES>(P))
+            run_generic<DT>(P_mem, T_mem);
+          else if (P.nchw)
+            run_tile_any<DT, true>(P_mem, T_mem, sp, lds, s_flag);
+          else
+            run_tile_any<DT, false>(P_mem, T_mem, sp, lds, s_flag);
+        }
       }
     }
-  }
-  if (ANY_ALIGNMENT && !pieces) {
-  } else if (cls == 0) {
-    run_skinny<DT, 1, ANY_ALIGNMENT>(P, T, sp, lds, s_flag, pf);
-  } else if (cls == 3) {
-    run_skinny<DT, 2, ANY_ALIGNMENT>(P, T, sp, lds, s_flag, pf);
-  } else if (cls == 6) {
-    run_skinny<DT, 4, ANY_ALIGNMENT>(P, T, sp, lds, s_flag, pf);
-  } else if (cls == CLS_TILE_128x64) {
-    run_lds_tile<DT, 128, 64>(P, T, sp, lds, s_flag, pf);
-  } else {
-    run_lds_tile<DT, 128, 128>(P, T, sp, lds, s_flag, pf);
+    if (ANY_ALIGNMENT && !pieces) {
+    } else if (cls == 0) {
+      run_skinny<DT, 1, ANY_ALIGNMENT>(P, T, sp, lds, s_flag, pf);
+    } else if (cls == 3) {
+      run_skinny<DT, 2, ANY_ALIGNMENT>(P, T, sp, lds, s_flag, pf);
+    } else if (cls == 6) {
+      run_skinny<DT, 4, ANY_ALIGNMENT>(P, T, sp, lds, s_flag, pf);
+    } else if (cls == CLS_TILE_128x64) {
+      run_lds_tile<DT, 128, 64, false>(P, T, sp, lds, s_flag, pf);
+    } else {
+      run_lds_tile<DT, 128, 128, false>(P, T, sp, lds, s_flag, pf);
+    }
   }
 }
 
@@ -2191,9 +2204,10 @@ __global__ void sk_arm_start_stamp(uint64_t *slot) { *slot = ~0ull; }
 // ANY_ALIGNMENT false: every operator can be read in aligned 16-byte pieces, and the kernel
 // does not carry the paths for the others (their calls cost the fast paths registers and a
 // stack); true: operators of either kind.
-template <int ONLY_DT, bool ANY_ALIGNMENT>
-__global__ void __launch_bounds__(WG_THREADS, 2) sk_superkernel(const TileWork *__restrict__ work, KernelArgs a) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_TILE_BYTES];
+// NARROW: every tile of the plan is a lean 128 x 64 tile (see NARROW_LDS_BYTES).
+template <int ONLY_DT, bool ANY_ALIGNMENT, bool NARROW>
+__global__ void __launch_bounds__(WG_THREADS, NARROW ? 3 : 2) sk_superkernel(const TileWork *__restrict__ work, KernelArgs a) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[NARROW ? NARROW_LDS_BYTES : LDS_TILE_BYTES];
   // By parity: the next record as wave 0 fetched it (which brings it into the L2 for everyone, see load_record); behind it
   // [0] its ticket, [1] flags (MAIL_*), [2] its index in xwork, [3] the ticket that waits while it runs
   __shared__ __attribute__((aligned(16))) uint32_t s_mail[2][WORK_DWORDS + 4];
@@ -2396,12 +2410,12 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sk_superkernel(const TileWork *
 #endif
     const DevProblem &P = W.prob;
     if constexpr (ONLY_DT >= 0) {
-      run_class<ONLY_DT, ANY_ALIGNMENT>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf);
+      run_class<ONLY_DT, ANY_ALIGNMENT, NARROW>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf);
     } else {
       switch (P.dtype) {
-        case SK_BF16: run_class<SK_BF16, ANY_ALIGNMENT>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
-        case SK_F16: run_class<SK_F16, ANY_ALIGNMENT>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
-        default: run_class<SK_F32, ANY_ALIGNMENT>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
+        case SK_BF16: run_class<SK_BF16, ANY_ALIGNMENT, NARROW>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
+        case SK_F16: run_class<SK_F16, ANY_ALIGNMENT, NARROW>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
+        default: run_class<SK_F32, ANY_ALIGNMENT, NARROW>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
       }
     }
 

@@ -431,6 +431,25 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
   return SK_OK;
 }
 
+bool narrow_plan(const HostPlan &hp) {
+  if (hp.tiles.empty()) return false;
+  for (const sk_tile &t : hp.tiles)
+    if (t.cls != CLS_TILE_128x64) return false;
+  for (const DevProblem &d : hp.dev) {
+    const int64_t es = elem_size(d.dtype), limit = (int64_t)1 << 30;  // (bytes; a tile's descriptor covers at most the operand and a padding)
+    if ((d.flags & (FLAG_VEC_A | FLAG_VEC_B)) != (FLAG_VEC_A | FLAG_VEC_B) || d.nchw) return false;
+    if ((int64_t)d.Ng * d.ldb * es >= limit) return false;
+    if (!d.gather) {
+      if (128 * d.lda * es >= limit) return false;
+    } else {
+      if (d.Cin % (128 / es) != 0 || d.R * d.S > 31) return false;
+      const int64_t images = d.Mg / ((int64_t)d.Ho * d.Wo);
+      if ((images * d.H * d.W + (int64_t)d.pad_h * d.W + d.pad_w) * d.Cin * es >= limit) return false;
+    }
+  }
+  return true;
+}
+
 sk_status plan_host_each_alone(const HostPlan &whole, HostPlan &out, std::string &err) {
   const int32_t n = (int32_t)whole.problems.size();
   out = HostPlan{};

@@ -92,6 +92,9 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
 
 // The tile tables of the one-launch-per-operator baseline: every operator of `whole` planned
 // by plan_host as if it were submitted alone, concatenated in submission order.
+// Whether every tile of the plan, and of each of its operators planned alone, is a 128 x 64 LDS tile whose operands can
+// be read through 32-bit descriptors (the device's lean_operands, for the whole operator instead of tile by tile).
+bool narrow_plan(const HostPlan &hp);
 sk_status plan_host_each_alone(const HostPlan &whole, HostPlan &out, std::string &err);
 
 inline int elem_size(int32_t dtype) { return dtype == SK_F32 ? 4 : 2; }

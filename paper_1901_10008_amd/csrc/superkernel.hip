@@ -231,6 +231,7 @@ struct sk_plan {
   int64_t grid_cap = 0;  // most workgroups any launch of this plan may use
   int only_dtype = -1;   // the element type all operators share, or -1 if they differ
   bool any_alignment = false;  // some operator cannot be read in aligned 16-byte pieces
+  bool narrow = false;         // every tile is a lean 128 x 64 tile, of one element type: the kernel of which three workgroups share a CU
   // Every tile is short (at most 64 KB of operands): sk_launch gives workgroup b the tiles b, b + grid, ...
   // instead of running the queue.  A queue claim is an atomic round trip before the next record can be
   // fetched, and such tiles are over before it returns: three thousand tiny operators take 29 instead of
@@ -362,6 +363,7 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
     for (const sk::DevProblem &d : plan->host.dev)
       if ((d.flags & vec) != vec) plan->any_alignment = true;
   }
+  plan->narrow = sk::narrow_plan(plan->host) && plan->only_dtype >= 0;
   plan->fixed_assignment = !plan->host.tiles.empty();
   for (const sk_tile &t : plan->host.tiles) {
     const int es = sk::elem_size(plan->host.problems[t.problem].dtype);
@@ -396,7 +398,7 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
       return hip_error("hipDeviceGetAttribute", e);
     }
     plan->ticks_per_ms = (double)clock_khz;
-    const int64_t limit = prm.grid_limit > 0 ? prm.grid_limit : 2 * (int64_t)cus;
+    const int64_t limit = prm.grid_limit > 0 ? prm.grid_limit : (plan->narrow ? 3 : 2) * (int64_t)cus;
     const int64_t ntiles = (int64_t)plan->host.tiles.size();
     plan->grid_cap = limit;
     plan->grid = (int)(ntiles < limit ? ntiles : limit);
@@ -489,19 +491,25 @@ static sk_status launch_range(sk_plan *plan, const DeviceTables &dt, hipStream_t
   a.arrive = dt.arrive;
   const dim3 g((unsigned)grid), b(sk::WG_THREADS);
   void (*kernel)(const sk::TileWork *, sk::KernelArgs) = nullptr;
-  if (plan->any_alignment) {
+  if (plan->narrow) {
     switch (plan->only_dtype) {
-      case SK_F32: kernel = sk::sk_superkernel<SK_F32, true>; break;
-      case SK_BF16: kernel = sk::sk_superkernel<SK_BF16, true>; break;
-      case SK_F16: kernel = sk::sk_superkernel<SK_F16, true>; break;
-      default: kernel = sk::sk_superkernel<-1, true>; break;
+      case SK_F32: kernel = sk::sk_superkernel<SK_F32, false, true>; break;
+      case SK_BF16: kernel = sk::sk_superkernel<SK_BF16, false, true>; break;
+      default: kernel = sk::sk_superkernel<SK_F16, false, true>; break;
+    }
+  } else if (plan->any_alignment) {
+    switch (plan->only_dtype) {
+      case SK_F32: kernel = sk::sk_superkernel<SK_F32, true, false>; break;
+      case SK_BF16: kernel = sk::sk_superkernel<SK_BF16, true, false>; break;
+      case SK_F16: kernel = sk::sk_superkernel<SK_F16, true, false>; break;
+      default: kernel = sk::sk_superkernel<-1, true, false>; break;
     }
   } else {
     switch (plan->only_dtype) {
-      case SK_F32: kernel = sk::sk_superkernel<SK_F32, false>; break;
-      case SK_BF16: kernel = sk::sk_superkernel<SK_BF16, false>; break;
-      case SK_F16: kernel = sk::sk_superkernel<SK_F16, false>; break;
-      default: kernel = sk::sk_superkernel<-1, false>; break;
+      case SK_F32: kernel = sk::sk_superkernel<SK_F32, false, false>; break;
+      case SK_BF16: kernel = sk::sk_superkernel<SK_BF16, false, false>; break;
+      case SK_F16: kernel = sk::sk_superkernel<SK_F16, false, false>; break;
+      default: kernel = sk::sk_superkernel<-1, false, false>; break;
     }
   }
   hipLaunchKernelGGL(kernel, g, b, 0, stream, dt.work, a);
@@ -629,7 +637,7 @@ sk_status sk_launch_static(sk_plan *plan, void *hip_stream) {
   if (e != hipSuccess) return hip_error("hipMemcpyAsync", e);
   DeviceTables dt;
   bind_tables(dt, base, l);
-  const int64_t limit = plan->host.params.grid_limit > 0 ? plan->host.params.grid_limit : 2 * (int64_t)cus;
+  const int64_t limit = plan->host.params.grid_limit > 0 ? plan->host.params.grid_limit : (plan->narrow ? 3 : 2) * (int64_t)cus;
   const int64_t ntiles = (int64_t)plan->host.tiles.size();
   plan->grid_cap = limit;
   plan->grid = (int)(ntiles < limit ? ntiles : limit);
