@@ -1730,6 +1730,8 @@ __device__ __forceinline__ void run_generic(const DevProblem *P_mem, const sk_ti
 //     coalesced access and costs three vector instructions beside it.  The block is computed transposed (output
 //     channels as MFMA rows), so that a lane ends up with consecutive pixels of one channel plane.
 //   * the loads of a stage are in flight while the one before it is multiplied (two LDS images).
+//   * blocks of 64 rows or columns where the record has no more, and where the device's work list cuts long records
+//     (refine_tiles): a tile of 51 fp32 stages takes 225 us by itself at 128 x 128.
 // Bound by the vector instructions that place a stage's pieces (addresses, shifts, packing of single elements) on
 // two waves per SIMD, not by memory.  Measured before / after, against pieces put together element by element with
 // one stage at a time and no loads in flight beside the MFMAs: seven stride-2 layers with the 7x7 stem for
@@ -1744,12 +1746,16 @@ __device__ __forceinline__ bool holds_a_piece(const DevProblem &P) {
   return (P.nchw || a >= CE) && (int64_t)(P.Ng - 1) * P.ldb + P.Kg >= CE;
 }
 
-template <int DT, bool NCHW>
+template <int DT, bool NCHW, int BM, int BN>
 __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_tile *T_mem, const SplitK &sp,
                                              unsigned char *lds, uint32_t *s_flag) {
   constexpr int ES = Elem<DT>::ES;
   constexpr int CE = 16 / ES;
-  constexpr int STAGE = 256 * LDS_ROW;  // pixels (or GEMM rows), then weight rows
+  constexpr int STAGE = (BM + BN) * LDS_ROW;  // pixels (or GEMM rows), then weight rows
+  constexpr int NA = BM / 32, NBW = BN / 32;  // pieces per thread and stage
+  constexpr int NH = BM / 64;                 // NCHW: pixels per lane
+  constexpr int ROWS = NCHW ? BN : BM, COLS = NCHW ? BM : BN;  // of the block as the MFMAs see it
+  constexpr int FM = ROWS / 64, FN = COLS / 64;                // 32x32 blocks per wave (2 x 2 waves)
   constexpr uint32_t NOWHERE = 0x80000000u;
   using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
   typedef elem_t piece_t __attribute__((ext_vector_type(CE)));
@@ -1785,17 +1791,17 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
                                    : (int64_t)(P.Mg - 1) * P.lda + P.Kg) - CE;
   const uintptr_t zeros = zero_piece_address();
 
-  for (int mb = (int)T.m0; mb < m_end; mb += 128) {
+  for (int mb = (int)T.m0; mb < m_end; mb += BM) {
     // ---- where this thread's rows of the activation operand lie ----
-    int64_t a_base[4];  // GEMM / NHWC: rows srow + 32 i; NCHW: rows lane and lane + 64
-    int a_lo[4], a_hi[4], a_h[4];
-    uint32_t n_off[2], n_rows[2], n_cols[2];  // NCHW, 32-bit form: byte offset from the descriptor's origin; taps outside
+    int64_t a_base[NA];  // GEMM / NHWC: rows srow + 32 i; NCHW: rows lane and lane + 64
+    int a_lo[NA], a_hi[NA], a_h[NA];
+    uint32_t n_off[NH], n_rows[NH], n_cols[NH];  // NCHW, 32-bit form: byte offset from the descriptor's origin; taps outside
     uintptr_t n_origin = 0;
     uint32_t n_extent = 0;
     bool near = false;
     if constexpr (!NCHW) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < NA; ++i) {
         int m = mb + srow + 32 * i;
         if (m >= m_end) m = m_end - 1;  // rows past the edge repeat the last row; never stored
         const RowA r = row_of(P, m);
@@ -1810,13 +1816,13 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
       }
     } else {
       const int64_t image = (int64_t)P.Cin * P.H * P.W;
-      const int b0 = fast_div(mb, P.div_hw), b1 = fast_div(min(mb + 128, m_end) - 1, P.div_hw);
+      const int b0 = fast_div(mb, P.div_hw), b1 = fast_div(min(mb + BM, m_end) - 1, P.div_hw);
       const int64_t corner = (int64_t)P.pad_h * P.W + P.pad_w;  // the corner of the padded image lies this far before it
       near = ((b1 + 1 - b0) * image + corner) * ES < (int64_t)1 << 31;
       n_origin = (uintptr_t)P.A + (uintptr_t)((b0 * image - corner) * ES);
       n_extent = (uint32_t)(((b1 + 1 - b0) * image + corner) * ES);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < NH; ++h) {
         int m = mb + lane + 64 * h;
         if (m >= m_end) m = m_end - 1;
         const RowA r = row_of(P, m);
@@ -1832,13 +1838,13 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
     }
     const __amdgpu_buffer_rsrc_t descA = __builtin_amdgcn_make_buffer_rsrc((void *)n_origin, 0, (int)n_extent, 0x00020000);
 
-    for (int nb = (int)T.n0; nb < n_end; nb += 128) {
+    for (int nb = (int)T.n0; nb < n_end; nb += BN) {
       const int64_t b_base = (int64_t)(nb + srow) * P.ldb;  // of this thread's first weight row; the others 32 rows apart
-      f32x16 acc[2][2];
+      f32x16 acc[FN][FM];
 #pragma unroll
-      for (int fn = 0; fn < 2; ++fn)
+      for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
-        for (int fm = 0; fm < 2; ++fm)
+        for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
           for (int i = 0; i < 16; ++i) acc[fn][fm][i] = 0.f;
 
@@ -1853,7 +1859,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         kc = cr / P.R;
         kr = cr - kc * P.R;
       }
-      u32x4 ra[4], rb[4];
+      u32x4 ra[NA], rb[NBW];
       // Where the piece that starts at element e0 of its run is read (`o`: place of the run's start in the operand)
       auto a_from = [&](int i, int e0, int64_t o) {
         if (!short_a) return min(max(e0, a_lo[i]), a_hi[i] - CE);
@@ -1874,14 +1880,14 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         at_run = run;
         if constexpr (!NCHW) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
+          for (int i = 0; i < NA; ++i) {
             const bool ok = in && a_hi[i] > a_lo[i] && (!P.gather || (unsigned)(a_h[i] + run) < (unsigned)P.H);
             const int64_t o = a_base[i] + run * a_run;
             const int64_t at = o + a_from(i, e0, o);
             ra[i] = load_any(ok ? (uintptr_t)P.A + (uintptr_t)(at * ES) : zeros);
           }
         } else {
-          piece_t el[2][2];
+          piece_t el[NH][2];
           const int k_stop = (int)T.k0 + (int)T.k_len;
           // reduction indices ks .. ks + 2 CE - 1 of 64 + 64 pixels; `outside(h, r, t)`: top bit set where the pixel's tap
           // (r, t) lies outside the image
@@ -1896,7 +1902,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
                 const uint32_t soff = k_in ? (plane + (uint32_t)(r * P.W + t)) * ES : 0u;
                 const uint32_t k_out = k_in ? 0u : NOWHERE;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
+                for (int h = 0; h < NH; ++h) {
                   const uint32_t off = n_off[h] | ((outside(h, r, t) | k_out) & NOWHERE);
                   if constexpr (ES == 4)
                     el[h][pp][e] = __builtin_amdgcn_raw_buffer_load_b32(descA, off, soff, 0);
@@ -1920,7 +1926,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
               return (unsigned)(a_h[h] + r) < (unsigned)P.H && (unsigned)(a_lo[h] + t) < (unsigned)P.W ? 0u : NOWHERE;
             });
 #pragma unroll
-          for (int h = 0; h < 2; ++h)
+          for (int h = 0; h < NH; ++h)
 #pragma unroll
             for (int pp = 0; pp < 2; ++pp) ra[2 * h + pp] = __builtin_bit_cast(u32x4, el[h][pp]);
           at_ks = ks;
@@ -1932,7 +1938,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
           kr = cr - kc * P.R;
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < NBW; ++i) {
           const bool ok = in && nb + srow + 32 * i < n_end;  // (rows past the edge are never stored)
           const int64_t o = b_base + (int64_t)(32 * i) * P.ldb + (int64_t)run * run_len;
           const int64_t at = o + b_from(e0, o);
@@ -1950,7 +1956,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         unsigned char *s = lds + buf * STAGE;
         const int e0 = at_e0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < NA; ++i) {
           if constexpr (!NCHW) {
             const int sh = e0 - a_from(i, e0, a_base[i] + at_run * a_run);
             u32x4 v = ra[i];
@@ -1964,23 +1970,23 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         if (NCHW && !near) {  // (images of 2 GiB and more: one element at a time)
           const int k_stop = (int)T.k0 + (int)T.k_len;
 #pragma unroll 1
-          for (int q = 0; q < 4 * CE; ++q) {
-            const int h = q & 1, k = at_ks + (q >> 1);
+          for (int q = 0; q < 2 * CE * NH; ++q) {
+            const int h = q & (NH - 1), k = at_ks + q / NH;
             const int cr = k / P.S, t = k - cr * P.S, c = cr / P.R, r = cr - c * P.R;
-            const int hh = (h ? a_h[1] : a_h[0]) + r, ww = (h ? a_lo[1] : a_lo[0]) + t;
+            const int hh = (h ? a_h[NH - 1] : a_h[0]) + r, ww = (h ? a_lo[NH - 1] : a_lo[0]) + t;
             const bool ok = k < k_stop && (unsigned)hh < (unsigned)P.H && (unsigned)ww < (unsigned)P.W;
-            const int64_t o = (h ? a_base[1] : a_base[0]) + ((int64_t)c * P.H + r) * P.W + t;
-            *(elem_t *)(s + (lane + 64 * h) * LDS_ROW + 2 * wave * 16 + (q >> 1) * ES) =
+            const int64_t o = (h ? a_base[NH - 1] : a_base[0]) + ((int64_t)c * P.H + r) * P.W + t;
+            *(elem_t *)(s + (lane + 64 * h) * LDS_ROW + 2 * wave * 16 + q / NH * ES) =
                 *(const elem_t SK_GLOBAL *)(ok ? (uintptr_t)P.A + (uintptr_t)(o * ES) : zeros);
           }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < NBW; ++i) {
           const int sh = e0 - b_from(e0, b_base + (int64_t)(32 * i) * P.ldb + (int64_t)at_run * run_len);
           u32x4 v = rb[i];
           if (__any(sh != 0)) v = shift_piece<ES>(v, sh);
           if (short_b) v = mask_piece<ES>(v, 0, run_len - e0);
-          *(u32x4 *)(s + (128 + srow + 32 * i) * LDS_ROW + c8 * 16) = v;
+          *(u32x4 *)(s + (BM + srow + 32 * i) * LDS_ROW + c8 * 16) = v;
         }
       };
 
@@ -1989,21 +1995,20 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         if (s + 1 < nstages) gload();
         if (s >= 0) {
           // MFMA columns (four consecutive of which a lane holds) come from the operand along whose rows the output is contiguous
-          const unsigned char *la = lds + (s & 1) * STAGE + (NCHW ? 128 * LDS_ROW : 0);
-          const unsigned char *lb = lds + (s & 1) * STAGE + (NCHW ? 0 : 128 * LDS_ROW);
+          const unsigned char *la = lds + (s & 1) * STAGE + (NCHW ? BM * LDS_ROW : 0);
+          const unsigned char *lb = lds + (s & 1) * STAGE + (NCHW ? 0 : BM * LDS_ROW);
 #pragma unroll
           for (int kk = 0; kk < 4; ++kk) {
             const int at = (2 * kk + half) * 16;
-            u32x4 fa[2], fb[2];
+            u32x4 fa[FM], fb[FN];
 #pragma unroll
-            for (int f = 0; f < 2; ++f) {
-              fa[f] = *(const u32x4 *)(la + ((wm * 2 + f) * 32 + l32) * LDS_ROW + at);
-              fb[f] = *(const u32x4 *)(lb + ((wn * 2 + f) * 32 + l32) * LDS_ROW + at);
-            }
+            for (int f = 0; f < FM; ++f) fa[f] = *(const u32x4 *)(la + ((wm * FM + f) * 32 + l32) * LDS_ROW + at);
 #pragma unroll
-            for (int fn = 0; fn < 2; ++fn)
+            for (int f = 0; f < FN; ++f) fb[f] = *(const u32x4 *)(lb + ((wn * FN + f) * 32 + l32) * LDS_ROW + at);
 #pragma unroll
-              for (int fm = 0; fm < 2; ++fm) mma32<DT>(fb[fn], fa[fm], acc[fn][fm]);
+            for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+              for (int fm = 0; fm < FM; ++fm) mma32<DT>(fb[fn], fa[fm], acc[fn][fm]);
           }
         }
         if (s + 1 < nstages) lstore((s + 1) & 1);
@@ -2016,34 +2021,34 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         // workspace, which holds per slice `rows` x 128 (64 for the 64-column class) floats, as 16-byte
         // pieces indexed by (quad of consecutive outputs, MFMA row); the last slice to arrive adds
         // all of them in slice order and stores the result.  Same hand-over as in run_tile.
-        // The sixteen accumulator quads of a thread wait in LDS meanwhile (free by now: the last stage
+        // The accumulator quads of a thread wait in LDS meanwhile (free by now: the last stage
         // ended with a barrier; a slot per thread and quad), so that the loops below can run rolled up:
         // unrolled over the accumulators they cost this kernel forty registers it does not have.
         typedef float f32x2 __attribute__((ext_vector_type(2)));
-        static_assert(16 * WG_THREADS * 16 <= LDS_TILE_BYTES, "the accumulators do not fit the LDS buffer");
+        static_assert(FN * FM * 4 * WG_THREADS * 16 <= LDS_TILE_BYTES, "the accumulators do not fit the LDS buffer");
         f32x4 *slot = (f32x4 *)lds + tid;  // quad p of this thread: slot[p * WG_THREADS]
 #pragma unroll
-        for (int fn = 0; fn < 2; ++fn)
+        for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
-          for (int fm = 0; fm < 2; ++fm)
+          for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-              slot[((fn * 2 + fm) * 4 + q) * WG_THREADS] =
+              slot[((fn * FM + fm) * 4 + q) * WG_THREADS] =
                   f32x4{acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1], acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]};
         const int rows = T.cls >= CLS_TILE_128x128 ? 128 : 16 << (T.cls / 3);
         const int cols = T.cls == CLS_TILE_128x64 ? 64 : 128;
         const int lrows = NCHW ? cols : rows, quads = (NCHW ? rows : cols) / 4;
         const size_t per_slice = (size_t)lrows * quads;  // f32x4 units
         unsigned long long *mine = (unsigned long long *)(sp.ws + sp.ws_off[T.out_tile_id]);
-        // where quad p = (fn*2 + fm)*4 + q of this thread lies in slice 0, or null if outside the rectangle's rows / columns
+        // where quad p = (fn*FM + fm)*4 + q of this thread lies in slice 0, or null if outside the rectangle's rows / columns
         auto place = [&](int p) -> unsigned long long * {
-          const int fn = p >> 3, fm = (p >> 2) & 1, q = p & 3;
-          const int r = (wm * 2 + fm) * 32 + l32, g = (wn * 2 + fn) * 8 + q * 2 + half;
+          const int fn = p / (4 * FM), fm = (p >> 2) % FM, q = p & 3;
+          const int r = (wm * FM + fm) * 32 + l32, g = (wn * FN + fn) * 8 + q * 2 + half;
           if (r >= lrows || g >= quads) return nullptr;
           return mine + 2 * ((size_t)g * lrows + r);
         };
 #pragma unroll 1
-        for (int p = 0; p < 16; ++p) {
+        for (int p = 0; p < FN * FM * 4; ++p) {
           unsigned long long *q = place(p);
           if (q) {
             q += 2 * (size_t)T.ks_idx * per_slice;
@@ -2061,7 +2066,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         __syncthreads();
         if (*s_flag != (uint32_t)T.S - 1) return;
 #pragma unroll 1
-        for (int p = 0; p < 16; ++p) {
+        for (int p = 0; p < FN * FM * 4; ++p) {
           unsigned long long *q = place(p);
           f32x4 sum = {0.f, 0.f, 0.f, 0.f};
           if (q) {
@@ -2076,12 +2081,12 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         if (tid == 0)  // re-arm for the next launch
           __hip_atomic_store(&sp.arrive[T.out_tile_id], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int fn = 0; fn < 2; ++fn)
+        for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
-          for (int fm = 0; fm < 2; ++fm)
+          for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              const f32x4 v = slot[((fn * 2 + fm) * 4 + q) * WG_THREADS];
+              const f32x4 v = slot[((fn * FM + fm) * 4 + q) * WG_THREADS];
               acc[fn][fm][4 * q] = v.x;
               acc[fn][fm][4 * q + 1] = v.y;
               acc[fn][fm][4 * q + 2] = v.z;
@@ -2092,15 +2097,15 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
 
       // ---- outputs: through LDS, so that they leave as runs of consecutive places ----
       // lane holds, per (fn, fm): MFMA row l32, columns 8*(i/4) + 4*half + (i%4)
-      constexpr int OROW = 128 * ES + 16;
-      static_assert(128 * OROW <= LDS_TILE_BYTES, "output tile does not fit the LDS buffer");
+      constexpr int OROW = COLS * ES + 16;
+      static_assert(ROWS * OROW <= LDS_TILE_BYTES, "output tile does not fit the LDS buffer");
 #pragma unroll
-      for (int fm = 0; fm < 2; ++fm)
+      for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
-        for (int fn = 0; fn < 2; ++fn)
+        for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            unsigned char *d = lds + ((wm * 2 + fm) * 32 + l32) * OROW + ((wn * 2 + fn) * 32 + 8 * q + 4 * half) * ES;
+            unsigned char *d = lds + ((wm * FM + fm) * 32 + l32) * OROW + ((wn * FN + fn) * 32 + 8 * q + 4 * half) * ES;
             if constexpr (ES == 4) {
               *(f32x4 *)d = f32x4{acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1], acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]};
             } else {
@@ -2111,7 +2116,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
             }
           }
       __syncthreads();
-      constexpr int PIECES = 128 / CE, RPI = WG_THREADS / PIECES;
+      constexpr int PIECES = COLS / CE, RPI = WG_THREADS / PIECES;
       const int col = (tid % PIECES) * CE;
       const int row_end = NCHW ? n_end - nb : m_end - mb, col_end = NCHW ? m_end - mb : n_end - nb;
       // NCHW: the piece's pixels (its first one, and whether they lie in one image)
@@ -2124,7 +2129,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         }
       }
 #pragma unroll 1
-      for (int r = tid / PIECES; r < row_end && r < 128; r += RPI) {
+      for (int r = tid / PIECES; r < row_end && r < ROWS; r += RPI) {
         if (col >= col_end) break;
         const u32x4 v = *(const u32x4 *)(lds + r * OROW + col * ES);
         if (whole) {
@@ -2143,6 +2148,19 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
       __syncthreads();  // the output tile has been read before the next block's stages are written
     }
   }
+}
+
+template <int DT, bool NCHW>
+__device__ __forceinline__ void run_block_any(const DevProblem *P_mem, const sk_tile *T_mem, int m_len, int n_len, const SplitK &sp,
+                                              unsigned char *lds, uint32_t *s_flag) {
+  if (m_len <= 64 && n_len <= 64)
+    run_tile_any<DT, NCHW, 64, 64>(P_mem, T_mem, sp, lds, s_flag);
+  else if (m_len <= 64)
+    run_tile_any<DT, NCHW, 64, 128>(P_mem, T_mem, sp, lds, s_flag);
+  else if (n_len <= 64)
+    run_tile_any<DT, NCHW, 128, 64>(P_mem, T_mem, sp, lds, s_flag);
+  else
+    run_tile_any<DT, NCHW, 128, 128>(P_mem, T_mem, sp, lds, s_flag);
 }
 
 template <int DT, bool ANY_ALIGNMENT, bool NARROW>
@@ -2174,9 +2192,9 @@ __device__ __forceinline__ void run_class(const DevProblem &P, const sk_tile &T,
           if (small || !holds_a_piece<Elem<DT>::ES>(P))
             run_generic<DT>(P_mem, T_mem);
           else if (P.nchw)
-            run_tile_any<DT, true>(P_mem, T_mem, sp, lds, s_flag);
+            run_block_any<DT, true>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag);
           else
-            run_tile_any<DT, false>(P_mem, T_mem, sp, lds, s_flag);
+            run_block_any<DT, false>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag);
         }
       }
     }

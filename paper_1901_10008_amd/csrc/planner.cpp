@@ -431,6 +431,52 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
   return SK_OK;
 }
 
+// A record that the element-wise or any-address blocks run takes (stages of 128 bytes of the reduction) x (128 x 128
+// blocks) x (2 for fp32, whose MFMAs take longer than everything else) units of about 2 us, all in one workgroup.  In a plan of
+// few records the launch then waits for one of them.  So where a record takes longer than an even share of
+// all such records over 512 workgroups it is cut into parts of at most 64 x 64 outputs: a quarter of the time each, and half
+// as much again in all.  Slices of split reductions stay whole (their workspace is laid out by rectangle), and
+// so do plans with per-die lists, which name the table's records.  The sums of an output do not change.
+bool refine_tiles(const HostPlan &hp, std::vector<sk_tile> &work, std::vector<int64_t> &count) {
+  if (!hp.xorder.empty()) return false;
+  auto cost = [&](const sk_tile &t) -> int64_t {
+    const DevProblem &d = hp.dev[t.problem];
+    const int32_t vec = FLAG_VEC_A | FLAG_VEC_B;
+    if ((d.flags & vec) == vec) return 0;
+    const int64_t es = elem_size(d.dtype), kb = 128 / es, ce = 16 / es;
+    // (the weight-streaming classes run any GEMM, and convolutions with whole pieces under a tap)
+    if (t.cls < CLS_TILE_128x128 && !d.nchw && d.Kg >= ce && (!d.gather || d.Cin % ce == 0)) return 0;
+    return ((t.k_len + kb - 1) / kb) * ((t.m_len + 127) / 128) * ((t.n_len + 127) / 128) * (es == 4 ? 2 : 1);
+  };
+  int64_t total = 0;
+  for (const sk_tile &t : hp.tiles) total += cost(t);
+  // (up to 64 reduction elements a small rectangle may go the one-output-per-thread way, whose sums round differently: a
+  // part must not where its record does not)
+  auto cut = [&](const sk_tile &t) {
+    return t.S == 1 && (t.m_len > 64 || t.n_len > 64) && hp.dev[t.problem].Kg > 64 && cost(t) * 512 > total;
+  };
+  bool any = false;
+  for (const sk_tile &t : hp.tiles) any = any || cut(t);
+  if (!any) return false;
+  work.clear();
+  count.assign(hp.dev.size(), 0);
+  for (const sk_tile &t : hp.tiles) {
+    const bool c = cut(t);
+    const uint32_t bm = c ? 64u : t.m_len, bn = c ? 64u : t.n_len;
+    for (uint32_t m = 0; m < t.m_len; m += bm)
+      for (uint32_t n = 0; n < t.n_len; n += bn) {
+        sk_tile u = t;
+        u.m0 = t.m0 + m;
+        u.n0 = t.n0 + n;
+        u.m_len = (uint16_t)std::min<uint32_t>(bm, t.m_len - m);
+        u.n_len = (uint16_t)std::min<uint32_t>(bn, t.n_len - n);
+        work.push_back(u);
+        ++count[t.problem];
+      }
+  }
+  return true;
+}
+
 bool narrow_plan(const HostPlan &hp) {
   if (hp.tiles.empty()) return false;
   for (const sk_tile &t : hp.tiles)

@@ -84,17 +84,26 @@ struct HostPlan {
   uint32_t xoff[9] = {};
   sk_plan_params params;
   int64_t target_tile_bytes = 0;
+  // what the device runs in place of the table (see refine_tiles); empty: the table itself
+  std::vector<sk_tile> work;
+  std::vector<int64_t> work_count;  // records per operator
+  const std::vector<sk_tile> &records() const { return work.empty() ? tiles : work; }
+  int64_t record_count(size_t i) const { return work.empty() ? count[i] : work_count[i]; }
 };
 
 // Pure host planning (no HIP call).  Returns SK_OK or an error with `err` set.
 sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params *params,
                     HostPlan &out, std::string &err);
 
-// The tile tables of the one-launch-per-operator baseline: every operator of `whole` planned
-// by plan_host as if it were submitted alone, concatenated in submission order.
+// The device's work list: the table's records, of which the long ones of operators without 16-byte pieces are cut into
+// parts of 64 x 64 outputs (`work`; `count` of them per operator; false and untouched if nothing is to be cut).
+bool refine_tiles(const HostPlan &hp, std::vector<sk_tile> &work, std::vector<int64_t> &count);
+
 // Whether every tile of the plan, and of each of its operators planned alone, is a 128 x 64 LDS tile whose operands can
 // be read through 32-bit descriptors (the device's lean_operands, for the whole operator instead of tile by tile).
 bool narrow_plan(const HostPlan &hp);
+// The tile tables of the one-launch-per-operator baseline: every operator of `whole` planned
+// by plan_host as if it were submitted alone, concatenated in submission order.
 sk_status plan_host_each_alone(const HostPlan &whole, HostPlan &out, std::string &err);
 
 inline int elem_size(int32_t dtype) { return dtype == SK_F32 ? 4 : 2; }

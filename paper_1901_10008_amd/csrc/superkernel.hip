@@ -262,7 +262,7 @@ struct TableLayout {
 };
 
 TableLayout layout_of(const sk::HostPlan &hp) {
-  const size_t nt = hp.tiles.size(), np = hp.dev.size(), nrect = hp.ws_off.size();
+  const size_t nt = hp.records().size(), np = hp.dev.size(), nrect = hp.ws_off.size();
   TableLayout l;
   l.off_work = 0;
   l.off_xwork = align_up(l.off_work + nt * sizeof(sk::TileWork), 256);
@@ -279,15 +279,16 @@ TableLayout layout_of(const sk::HostPlan &hp) {
 
 // The host image of the uploaded part: work records, zeroed counters and stamps, countdowns, offsets.
 void fill_image(const sk::HostPlan &hp, const TableLayout &l, char *stage) {
-  const size_t nt = hp.tiles.size(), np = hp.dev.size(), nrect = hp.ws_off.size();
+  const size_t nt = hp.records().size(), np = hp.dev.size(), nrect = hp.ws_off.size();
   // the work records are written in full below; everything behind them starts at zero
   std::memset(stage + nt * sizeof(sk::TileWork), 0, l.upload - nt * sizeof(sk::TileWork));
   if (nrect) std::memcpy(&stage[l.off_wsoff], hp.ws_off.data(), nrect * sizeof(uint32_t));
   for (size_t i = 0; i < nt; ++i) {
     sk::TileWork w;
     std::memset(&w, 0, sizeof(w));
-    w.tile = hp.tiles[i];
+    w.tile = hp.records()[i];
     w.prob = hp.dev[w.tile.problem];
+    w.prob.tile_count = (int32_t)hp.record_count(w.tile.problem);
     std::memcpy(&stage[l.off_work + i * sizeof(w)], &w, sizeof(w));
   }
   for (size_t i = 0; i < hp.xorder.size(); ++i)
@@ -295,7 +296,7 @@ void fill_image(const sk::HostPlan &hp, const TableLayout &l, char *stage) {
                 sizeof(sk::TileWork));
   std::memcpy(&stage[l.off_xoff], hp.xoff, sizeof(hp.xoff));
   for (size_t i = 0; i < np; ++i) {
-    const uint32_t c = (uint32_t)hp.count[i];
+    const uint32_t c = (uint32_t)hp.record_count(i);
     std::memcpy(&stage[l.off_rem + i * sizeof(uint32_t)], &c, sizeof(c));
   }
 }
@@ -346,6 +347,11 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
   sk_status st;
   try {
     st = sk::plan_host(problems, n, params, plan->host, err);
+    sk::HostPlan &hp = plan->host;
+    if (st == SK_OK && sk::refine_tiles(hp, hp.work, hp.work_count) && hp.params.host_only && layout_of(hp).total > STATIC_SCRATCH_BYTES) {
+      hp.work.clear();  // (the static scratch holds the table at most)
+      hp.work_count.clear();
+    }
   } catch (const std::bad_alloc &) {
     delete plan;
     return set_error(SK_ERR_ALLOC, "host allocation failed while planning");
@@ -399,7 +405,7 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
     }
     plan->ticks_per_ms = (double)clock_khz;
     const int64_t limit = prm.grid_limit > 0 ? prm.grid_limit : (plan->narrow ? 3 : 2) * (int64_t)cus;
-    const int64_t ntiles = (int64_t)plan->host.tiles.size();
+    const int64_t ntiles = (int64_t)plan->host.records().size();
     plan->grid_cap = limit;
     plan->grid = (int)(ntiles < limit ? ntiles : limit);
     st = upload_tables(plan->host, plan->device, plan->dev);
@@ -574,7 +580,7 @@ sk_status sk_launch(sk_plan *plan, void *hip_stream) {
   if (st != SK_OK) return st;
   st = arm_start_stamp(plan, stream);
   if (st != SK_OK) return st;
-  st = launch_range(plan, plan->dev, stream, 0u, (uint32_t)plan->host.tiles.size(), plan->grid,
+  st = launch_range(plan, plan->dev, stream, 0u, (uint32_t)plan->host.records().size(), plan->grid,
                     !plan->fixed_assignment, true, true);
   note_launch(plan, stream, capturing);
   return st;
@@ -638,7 +644,7 @@ sk_status sk_launch_static(sk_plan *plan, void *hip_stream) {
   DeviceTables dt;
   bind_tables(dt, base, l);
   const int64_t limit = plan->host.params.grid_limit > 0 ? plan->host.params.grid_limit : (plan->narrow ? 3 : 2) * (int64_t)cus;
-  const int64_t ntiles = (int64_t)plan->host.tiles.size();
+  const int64_t ntiles = (int64_t)plan->host.records().size();
   plan->grid_cap = limit;
   plan->grid = (int)(ntiles < limit ? ntiles : limit);
   return launch_range(plan, dt, stream, 0u, (uint32_t)ntiles, plan->grid, !plan->fixed_assignment, false, true);
