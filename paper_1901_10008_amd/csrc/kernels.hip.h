@@ -2213,10 +2213,6 @@ __device__ __forceinline__ void run_class(const DevProblem &P, const sk_tile &T,
   }
 }
 
-// Sets the start stamp to all ones ahead of a stamped launch (a kernel, not a memset: launches may be
-// captured into graphs).
-__global__ void sk_arm_start_stamp(uint64_t *slot) { *slot = ~0ull; }
-
 // ONLY_DT >= 0: every operator of the plan has that element type (one third of the
 // code, fewer registers); ONLY_DT < 0: operators of mixed types.
 // ANY_ALIGNMENT false: every operator can be read in aligned 16-byte pieces, and the kernel

@@ -14,6 +14,32 @@
 
 static_assert(sizeof(sk_tile) == 32, "tile records are 32 bytes");
 
+namespace sk {
+
+#ifndef SK_DIAG_CLOCKS
+// (compiled in units of their own: instances.hip; the diagnostic build, whose kernels share one stamp array, compiles
+// them here)
+#define SK_KERNEL(dt, any, narrow) extern template __global__ void sk_superkernel<dt, any, narrow>(const TileWork *__restrict__, KernelArgs);
+SK_KERNEL(SK_F32, false, true)
+SK_KERNEL(SK_BF16, false, true)
+SK_KERNEL(SK_F16, false, true)
+SK_KERNEL(SK_F32, false, false)
+SK_KERNEL(SK_BF16, false, false)
+SK_KERNEL(SK_F16, false, false)
+SK_KERNEL(-1, false, false)
+SK_KERNEL(SK_F32, true, false)
+SK_KERNEL(SK_BF16, true, false)
+SK_KERNEL(SK_F16, true, false)
+SK_KERNEL(-1, true, false)
+#undef SK_KERNEL
+#endif
+
+// Sets the start stamp to all ones ahead of a stamped launch (a kernel, not a memset: launches may be
+// captured into graphs).
+__global__ void sk_arm_start_stamp(uint64_t *slot) { *slot = ~0ull; }
+
+}  // namespace sk
+
 namespace {
 
 thread_local std::string g_last_error;
