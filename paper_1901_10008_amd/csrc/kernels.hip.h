@@ -22,9 +22,10 @@
 //     on the fly from an NHWC image (implicit GEMM for convolutions, any stride).
 //   * operands that cannot be read in aligned 16-byte pieces, and convolutions
 //     on channel-major (NCHW) arrays, whose patch rows and output rows are not
-//     contiguous: one output per thread for small rectangles, MFMA tiles
-//     assembled element by element for larger ones; only in the kernel
-//     instantiation for plans that need them.
+//     contiguous: one output per thread for small rectangles; MFMA blocks whose
+//     pieces are read at any address and shifted into place (images in channel
+//     planes: element by element, lanes along pixels) for larger ones; only in
+//     the kernel instantiations for plans that need them.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -224,8 +225,8 @@ __device__ __forceinline__ void store4(void *C, int64_t row_off, int n, int n_en
 
 // The MFMA paths below require both operands to be readable in aligned 16-byte
 // pieces (FLAG_VEC_A and FLAG_VEC_B: 16-byte aligned bases and row strides, Kg
-// and, for a convolution, Cin multiples of a piece).  Everything else goes
-// through run_generic.
+// and, for a convolution, Cin multiples of a piece), except where they say so:
+// the weight-streaming classes with ANY, and run_tile_any.
 
 // Loads in the MFMA paths are never placed under a branch (a conditional load makes the
 // compiler wait for it at the end of the branch, which serialises the loads of a stage)

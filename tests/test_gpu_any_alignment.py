@@ -29,6 +29,11 @@ CASES = {
     "planes": [nchw(6, 60, 3, 40, 1, 41, 0, 20), nchw(45, 7, 2, 24, 33, 2, 4, 1, "f16"), nchw(7, 7, 33, 70, 1, 1, 0, 0, nb=5),
                nchw(9, 11, 20, 130, 3, 3, 1, 1, "f32", nb=3), nchw(13, 13, 17, 64, 2, 2, 2, 2), nchw(30, 30, 8, 12, 5, 5, 2, 2, st=3),
                nchw(14, 14, 96, 200, 1, 1, 0, 0, "f16")],
+    # channel-major, image size kept (pixels in a row under every tap): planes smaller than a piece and a block, planes and channel
+    # counts around multiples of a piece, several images that whole pieces fit into and that they do not
+    "kept_sizes": [nchw(3, 3, 40, 70, 3, 3, 1, 1), nchw(8, 8, 24, 130, 3, 3, 1, 1, nb=3), nchw(7, 9, 33, 40, 3, 3, 1, 1, nb=2),
+                   nchw(1, 17, 19, 20, 1, 3, 0, 1, "f16"), nchw(23, 1, 9, 65, 3, 1, 1, 0), nchw(12, 10, 65, 64, 1, 1, 0, 0, nb=2),
+                   nchw(11, 13, 7, 129, 3, 3, 1, 1, "f32"), nchw(6, 6, 50, 30, 3, 3, 1, 1, "f32", nb=4), nchw(29, 31, 16, 16, 1, 1, 0, 0, "f32")],
 }
 
 
@@ -37,9 +42,9 @@ def test_any_alignment_edges(name):
     run_all_modes(CASES[name], seed=41, label=name)
 
 
-@pytest.mark.parametrize("name", ["skinny_tails", "blocks", "runs", "planes"])
+@pytest.mark.parametrize("name", ["skinny_tails", "blocks", "runs", "planes", "kept_sizes"])
 def test_any_alignment_edges_at_odd_addresses(name):
     """The same at addresses that are aligned to an element only, GEMMs in rows padded by an odd number of elements."""
     off = 4  # bytes: whole elements of every type, no multiple of a piece
-    pads = {} if name in ("runs", "planes") else {"pad_lda": 5, "pad_ldb": 3, "pad_ldc": 1}
+    pads = {} if name in ("runs", "planes", "kept_sizes") else {"pad_lda": 5, "pad_ldb": 3, "pad_ldc": 1}
     run_all_modes(CASES[name], seed=42, label=name + " at odd addresses", a_off=off, b_off=off, c_off=off, **pads)
