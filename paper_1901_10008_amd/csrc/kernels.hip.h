@@ -1419,6 +1419,12 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
   const int m0 = (int)T.m0, m_end = m0 + (int)T.m_len;
   const int k_begin = (int)T.k0, k_stop = (int)T.k0 + (int)T.k_len;
 
+  const int nstages = (k_stop - k_begin + KB - 1) / KB;
+  // A tile of few stages takes its next ticket at once: taken in its first stage, the answer (a memory round trip) and the record
+  // behind it (another) would both be waited for at the tile's end (ResNet mix x16 85.7 -> 84.3 us).
+  const int claim_at = nstages > CLAIM_LEAD ? nstages - CLAIM_LEAD : -1;
+  if (claim_at < 0) pf.claim();
+
   constexpr uint32_t FRONT = 3072;  // see dma_stage
   const __amdgpu_buffer_rsrc_t descA = __builtin_amdgcn_make_buffer_rsrc((void *)(L.baseA - FRONT), 0, (int)(L.extA + FRONT), 0x00020000);
   const __amdgpu_buffer_rsrc_t descB = __builtin_amdgcn_make_buffer_rsrc((void *)(L.baseB - FRONT), 0, (int)(L.extB + FRONT), 0x00020000);
@@ -1562,7 +1568,6 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
   const int diag_tile = pf.diag_tile;
 #endif
   SK_DIAG(1);
-  const int nstages = (k_stop - k_begin + KB - 1) / KB;
   // the fragments of step kk of the stage in slot sl
   u32x4 fa[2][FM], fb[2][FN];
   auto frag = [&](int sl, int kk, u32x4(&xa)[FM], u32x4(&xb)[FN]) {
@@ -1588,10 +1593,9 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   frag(0, 0, fa[0], fb[0]);
-  const int claim_at = nstages > CLAIM_LEAD ? nstages - CLAIM_LEAD : 0;
-  const int issue_at = min(claim_at + ISSUE_GAP, nstages - 1);
+  const int issue_at = claim_at < 0 ? 0 : claim_at + ISSUE_GAP;
   for (int h0 = 0; h0 < nstages; h0 += NS) {
-    if ((unsigned)(claim_at - h0) < (unsigned)NS) pf.claim();
+    if (claim_at >= h0 && claim_at < h0 + NS) pf.claim();
     if ((unsigned)(issue_at - h0) < (unsigned)NS) pf.issue();
 #pragma unroll
     for (int slot = 0; slot < NS; ++slot) {
