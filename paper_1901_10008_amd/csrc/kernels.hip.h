@@ -1277,16 +1277,19 @@ __device__ __forceinline__ void run_tile(const DevProblem &P, const sk_tile &T, 
 //   * one descriptor per operand and tile, based at the tile's first row, its size the extent of
 //     the tile's rows: a piece's address is a 32-bit row offset kept in a register for the whole
 //     tile plus a scalar offset that advances with the stage, and a piece that lies outside the
-//     descriptor reads as zero, so a piece that must not be read gets an offset of 2^31 and more;
+//     descriptor reads as zero, so a piece that must not be read gets an offset of 2^31 and more (no sum of a
+//     row's offset and a scalar offset reaches 2^31, so the two never wrap, and the scalar offset never exceeds the
+//     descriptor's size);
 //   * for a convolution whose channel count is a multiple of a stage (64 elements of 2 bytes),
 //     all pieces of a stage lie under one filter tap: the tap and its offset are scalar, and
 //     whether a row's pixel under that tap lies in the image is one bit of a mask that is
 //     worked out once per tile and row.
 // It serves operators whose tile extents fit 31 bits of byte offset and, for convolutions,
 // those with such channel counts and at most 31 filter taps; the others keep run_tile.
+constexpr int DMA_FRONT = 3072;  // the descriptors are based this far in front of the operand's first byte, see dma_stage
 struct LeanOperands {
-  uintptr_t baseA, baseB;  // first byte the descriptors cover
-  uint32_t extA, extB;     // bytes they cover
+  uintptr_t baseA, baseB;  // first byte the offsets count from
+  uint32_t extA, extB;     // bytes from there to the descriptors' ends
   int64_t originA;         // element offset of baseA from P.A
 };
 
@@ -1295,30 +1298,29 @@ template <int ES>
 __device__ __forceinline__ bool lean_operands(const DevProblem &P, const sk_tile &T, LeanOperands &L) {
   constexpr int CE = 16 / ES;
   constexpr int KB = 8 * CE;
-  constexpr int64_t LIMIT = ((int64_t)1 << 31) - 4096;  // (the descriptors are based up to 3 KB in front, see dma_stage)
+  constexpr int64_t LIMIT = ((int64_t)1 << 31) - 4096;  // (with DMA_FRONT added still below 2^31)
   const int64_t extB = ((int64_t)((int)T.n_len - 1) * P.ldb + P.Kg) * ES;
   L.baseB = (uintptr_t)P.B + (uintptr_t)((int64_t)T.n0 * P.ldb * ES);
   L.extB = (uint32_t)extB;
-  int64_t extA;
   if (!P.gather) {
-    extA = ((int64_t)((int)T.m_len - 1) * P.lda + P.Kg) * ES;
+    const int64_t extA = ((int64_t)((int)T.m_len - 1) * P.lda + P.Kg) * ES;
     L.originA = (int64_t)T.m0 * P.lda;
+    L.extA = (uint32_t)extA;
+    if (extA >= LIMIT) return false;
   } else {
     if (P.nchw || P.Cin % KB != 0 || P.R * P.S > 31) return false;
-    // from the corner of the padded first image of the tile to the end of the array
-    const int hw = P.Ho * P.Wo;
+    // From the corner of the padded first image of the tile.  The scalar offset of a late tap can lie beyond the array's end
+    // (a 3x3 filter on images of one pixel), so the descriptor is as large as an offset can be without the top
+    // bit: what is read is inside because its tap is, and NOWHERE is outside whether the hardware compares the offset
+    // alone, its sum with the scalar offset, or the offset with the size less the scalar offset.
     const int b0 = fast_div((int)T.m0, P.div_hw);
-    const int nb = fast_div(P.Mg + hw - 1, P.div_hw);
-    L.originA = (((int64_t)b0 * P.H - P.pad_h) * P.W - P.pad_w) * P.Cin;
     const int b1 = fast_div((int)T.m0 + (int)T.m_len - 1, P.div_hw);
-    // (the last image the tile touches must lie inside 2^31 bytes; the descriptor itself ends with the array)
-    if ((((int64_t)(b1 + 1) * P.H * P.W) * P.Cin - L.originA) * ES >= LIMIT) return false;
-    extA = (((int64_t)nb * P.H * P.W) * P.Cin - L.originA) * ES;
-    if (extA >= LIMIT) extA = LIMIT - 1;
+    L.originA = (((int64_t)b0 * P.H - P.pad_h) * P.W - P.pad_w) * P.Cin;
+    L.extA = (uint32_t)(((int64_t)1 << 31) - DMA_FRONT);
+    if (!offsets_below(P, b1 - b0, ES, LIMIT)) return false;
   }
   L.baseA = (uintptr_t)P.A + (uintptr_t)(L.originA * ES);
-  L.extA = (uint32_t)extA;
-  return extA < LIMIT && extB < LIMIT;
+  return extB < LIMIT;
 }
 
 // The operand pieces never pass through registers: a buffer load with the LDS modifier writes the 16
@@ -1425,7 +1427,7 @@ __device__ __forceinline__ void run_tile_dma(const DevProblem &P, const sk_tile 
   const int claim_at = nstages > CLAIM_LEAD ? nstages - CLAIM_LEAD : -1;
   if (claim_at < 0) pf.claim();
 
-  constexpr uint32_t FRONT = 3072;  // see dma_stage
+  constexpr uint32_t FRONT = DMA_FRONT;
   const __amdgpu_buffer_rsrc_t descA = __builtin_amdgcn_make_buffer_rsrc((void *)(L.baseA - FRONT), 0, (int)(L.extA + FRONT), 0x00020000);
   const __amdgpu_buffer_rsrc_t descB = __builtin_amdgcn_make_buffer_rsrc((void *)(L.baseB - FRONT), 0, (int)(L.extB + FRONT), 0x00020000);
 
@@ -1802,7 +1804,6 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
     int a_lo[NA], a_hi[NA], a_h[NA];
     uint32_t n_off[NH], n_rows[NH], n_cols[NH];  // NCHW, 32-bit form: byte offset from the descriptor's origin; taps outside
     uintptr_t n_origin = 0;
-    uint32_t n_extent = 0;
     bool near = false;
     if constexpr (!NCHW) {
 #pragma unroll
@@ -1823,9 +1824,9 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
       const int64_t image = (int64_t)P.Cin * P.H * P.W;
       const int b0 = fast_div(mb, P.div_hw), b1 = fast_div(min(mb + BM, m_end) - 1, P.div_hw);
       const int64_t corner = (int64_t)P.pad_h * P.W + P.pad_w;  // the corner of the padded image lies this far before it
-      near = ((b1 + 1 - b0) * image + corner) * ES < (int64_t)1 << 31;
+      // (no pixel's offset and tap's offset add up to 2^31, inside the image or not; for the descriptor's size see lean_operands)
+      near = offsets_below(P, b1 - b0, ES, (int64_t)1 << 31);
       n_origin = (uintptr_t)P.A + (uintptr_t)((b0 * image - corner) * ES);
-      n_extent = (uint32_t)(((b1 + 1 - b0) * image + corner) * ES);
 #pragma unroll
       for (int h = 0; h < NH; ++h) {
         int m = mb + lane + 64 * h;
@@ -1841,7 +1842,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         n_cols[h] = ~((uint32_t)(((uint64_t)1 << whi) - 1) & ~(uint32_t)(((uint64_t)1 << min(wlo, 32)) - 1));
       }
     }
-    const __amdgpu_buffer_rsrc_t descA = __builtin_amdgcn_make_buffer_rsrc((void *)n_origin, 0, (int)n_extent, 0x00020000);
+    const __amdgpu_buffer_rsrc_t descA = __builtin_amdgcn_make_buffer_rsrc((void *)n_origin, 0, (int)NOWHERE, 0x00020000);
 
     for (int nb = (int)T.n0; nb < n_end; nb += BN) {
       const int64_t b_base = (int64_t)(nb + srow) * P.ldb;  // of this thread's first weight row; the others 32 rows apart

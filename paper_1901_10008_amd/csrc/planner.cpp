@@ -272,6 +272,9 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
         d.nchw = 1;
         d.gather = 1;  // neither a patch row nor an output row is contiguous in this storage order
       }
+      const __int128 row = (__int128)(c.Ho - 1) * d.stride + p.R - 1, col = (__int128)(c.Wo - 1) * d.stride + p.S - 1;
+      const __int128 reach = (d.nchw ? ((__int128)(p.Cin - 1) * p.H + row) * p.Wd + col + 1 : (row * p.Wd + col + 1) * p.Cin) * es;
+      d.reach = (uint32_t)std::min<__int128>(reach, (__int128)1 << 31);
     }
     int32_t flags = 0;
     if (d.nchw) {
@@ -482,7 +485,7 @@ bool narrow_plan(const HostPlan &hp) {
   for (const sk_tile &t : hp.tiles)
     if (t.cls != CLS_TILE_128x64) return false;
   for (const DevProblem &d : hp.dev) {
-    const int64_t es = elem_size(d.dtype), limit = (int64_t)1 << 30;  // (bytes; a tile's descriptor covers at most the operand and a padding)
+    const int64_t es = elem_size(d.dtype), limit = (int64_t)1 << 30;  // (bytes; a tile spans at most the operand)
     if ((d.flags & (FLAG_VEC_A | FLAG_VEC_B)) != (FLAG_VEC_A | FLAG_VEC_B) || d.nchw) return false;
     if ((int64_t)d.Ng * d.ldb * es >= limit) return false;
     if (!d.gather) {
@@ -490,7 +493,7 @@ bool narrow_plan(const HostPlan &hp) {
     } else {
       if (d.Cin % (128 / es) != 0 || d.R * d.S > 31) return false;
       const int64_t images = d.Mg / ((int64_t)d.Ho * d.Wo);
-      if ((images * d.H * d.W + (int64_t)d.pad_h * d.W + d.pad_w) * d.Cin * es >= limit) return false;
+      if (!offsets_below(d, images - 1, es, limit)) return false;
     }
   }
   return true;

@@ -40,12 +40,25 @@ struct DevProblem {
   int32_t tile_first, tile_count;
   int32_t stride;  // of a convolution, both directions (>= 1)
   int32_t nchw;    // convolution on channel-major arrays: X[Nb,Cin,H,W], W[Cout,Cin,R,S], Y[Nb,Cout,Ho,Wo]
-  int32_t pad0;
+  // convolution: bytes from the corner of the padded image (row -pad_h, column -pad_w; channel-major: of channel 0) to the end of the
+  // last element that any output pixel meets under any tap, in the image or not; 2^31 stands for more
+  uint32_t reach;
   // Division by a convolution's Ho*Wo, Wo, Cin and S as multiply and shift (see FastDiv): the tile set-up
   // divides row and reduction indices by them for every row a thread stages.
   uint32_t div_hw[2], div_wo[2], div_cin[2], div_s[2];
 };
 static_assert(sizeof(DevProblem) % 8 == 0, "DevProblem must stay 8-byte sized");
+
+#ifdef __HIPCC__
+#define SK_HOST_DEVICE __host__ __device__ __forceinline__
+#else
+#define SK_HOST_DEVICE inline
+#endif
+// Whether every offset that an element of a convolution's images b .. b + later can get, counted from the corner of image b's
+// padding (a pixel's offset plus its tap's, and the element itself), lies below `limit` bytes.
+SK_HOST_DEVICE bool offsets_below(const DevProblem &d, int64_t later, int64_t es, int64_t limit) {
+  return later * ((int64_t)d.H * d.W * d.Cin * es) + (int64_t)d.reach < limit;
+}
 
 // n / d for 0 <= n < 2^31 as (n * mul) >> shift with mul = floor(2^(31+l) / d) + 1, l = ceil(log2 d), shift = 31 + l:
 // mul * d = 2^(31+l) + e with 0 < e <= d <= 2^l, so the quotient is off by less than n / (d * 2^31) < 1 / d.

@@ -108,6 +108,58 @@ int main() {
     if (sk::plan_host_each_alone(hp, alone, err) != SK_OK) return fail("plan_host_each_alone", seed);
     if (alone.dev.size() != hp.dev.size()) return fail("baseline tables", seed);
   }
+  // Convolution operands read through descriptors: the offset of a pixel, the scalar offset of a tap and the element itself must
+  // stay below what offsets_below() promises for every pixel and tap, those outside the image too (their offset
+  // carries the top bit, and no sum may wrap or lose it); inside the image they must name the element.
+  for (int seed = 0; seed < 400; ++seed) {
+    std::mt19937 g(seed);
+    auto upto = [&](int n) { return (int)(g() % (unsigned)n); };
+    sk_problem p{};
+    p.op = seed % 2 ? SK_CONV2D_NCHW : SK_CONV2D_NHWC;
+    p.dtype = upto(2) ? SK_BF16 : SK_F32;
+    const int64_t es = p.dtype == SK_F32 ? 4 : 2;
+    do {
+      p.Nb = 1 + upto(4), p.H = 1 + upto(6), p.Wd = 1 + upto(6), p.Cin = 1 + upto(9), p.Cout = 3;
+      p.R = 1 + upto(7), p.S = 1 + upto(7), p.pad_h = upto(9), p.pad_w = upto(9), p.stride = 1 + upto(3);
+    } while (p.H + 2 * p.pad_h < p.R || p.Wd + 2 * p.pad_w < p.S);
+    p.A = (const void *)0x10000, p.B = (const void *)0x20000, p.C = (void *)0x30000;
+    sk_plan_params prm;
+    sk_plan_params_default(&prm);
+    prm.host_only = 1;
+    sk::HostPlan hp;
+    std::string err;
+    if (sk::plan_host(&p, 1, &prm, hp, err) != SK_OK) return fail("plan_host failed on a small convolution", seed);
+    const sk::DevProblem &d = hp.dev[0];
+    int64_t most = 0;  // bytes an offset, a scalar offset and the element reach, over one tile of all images
+    const int64_t image = (int64_t)p.H * p.Wd * p.Cin, corner = (int64_t)p.pad_h * p.Wd + p.pad_w;
+    for (int64_t b = 0; b < p.Nb; ++b)
+      for (int64_t ho = 0; ho < d.Ho; ++ho)
+        for (int64_t wo = 0; wo < d.Wo; ++wo)
+          for (int64_t r = 0; r < p.R; ++r)
+            for (int64_t t = 0; t < p.S; ++t)
+              for (int64_t c = 0; c < p.Cin; ++c) {
+                const int64_t hs = ho * p.stride, ws = wo * p.stride, h = hs - p.pad_h + r, w = ws - p.pad_w + t;
+                const int64_t off = p.op == SK_CONV2D_NCHW ? b * image + hs * p.Wd + ws : ((b * p.H + hs) * p.Wd + ws) * p.Cin;
+                const int64_t soff = p.op == SK_CONV2D_NCHW ? (c * p.H + r) * p.Wd + t : (r * p.Wd + t) * p.Cin + c;
+                most = std::max(most, (off + soff + 1) * es);
+                if (h < 0 || h >= p.H || w < 0 || w >= p.Wd) continue;
+                const int64_t place = p.op == SK_CONV2D_NCHW ? ((b * p.Cin + c) * p.H + h) * p.Wd + w : ((b * p.H + h) * p.Wd + w) * p.Cin + c;
+                if (off + soff - corner * (p.op == SK_CONV2D_NCHW ? 1 : p.Cin) != place) return fail("an offset misses its element", seed);
+              }
+    if (!sk::offsets_below(d, p.Nb - 1, es, most + 1) || sk::offsets_below(d, p.Nb - 1, es, most))
+      return fail("offsets_below is not the largest offset", seed);
+  }
+  {
+    // sizes at which 32 bits do not hold the products: never below any limit
+    sk_problem p{};
+    p.op = SK_CONV2D_NHWC, p.dtype = SK_F32, p.Nb = 1, p.H = 1 << 19, p.Wd = 1 << 19, p.Cin = 1 << 10, p.Cout = 1, p.R = 1, p.S = 1;
+    p.stride = 1 << 10;
+    p.A = (const void *)0x10000, p.B = (const void *)0x20000, p.C = (void *)0x30000;
+    sk::HostPlan hp;
+    std::string err;
+    if (sk::plan_host(&p, 1, nullptr, hp, err) != SK_OK) return fail("plan_host failed on a large convolution", -4);
+    if (hp.dev[0].reach != 1u << 31 || sk::offsets_below(hp.dev[0], 0, 4, (int64_t)1 << 31)) return fail("reach of a large image", -4);
+  }
   // lists the planner must reject
   {
     sk::HostPlan hp;

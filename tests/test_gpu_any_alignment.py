@@ -29,6 +29,9 @@ CASES = {
     "planes": [nchw(6, 60, 3, 40, 1, 41, 0, 20), nchw(45, 7, 2, 24, 33, 2, 4, 1, "f16"), nchw(7, 7, 33, 70, 1, 1, 0, 0, nb=5),
                nchw(9, 11, 20, 130, 3, 3, 1, 1, "f32", nb=3), nchw(13, 13, 17, 64, 2, 2, 2, 2), nchw(30, 30, 8, 12, 5, 5, 2, 2, st=3),
                nchw(14, 14, 96, 200, 1, 1, 0, 0, "f16")],
+    # channel-major, filters that overhang a small image: the scalar offset of the last taps lies beyond the image
+    "overhang": [nchw(1, 1, 64, 70, 3, 3, 1, 1), nchw(2, 2, 32, 40, 5, 5, 2, 2, nb=30), nchw(3, 3, 32, 70, 7, 7, 3, 3, "f16"),
+                 nchw(1, 64, 8, 40, 5, 1, 2, 0), nchw(70, 1, 8, 33, 1, 5, 0, 2, "f32"), nchw(1, 1, 24, 30, 3, 3, 1, 1, "f32", nb=129)],
     # channel-major, image size kept (pixels in a row under every tap): planes smaller than a piece and a block, planes and channel
     # counts around multiples of a piece, several images that whole pieces fit into and that they do not
     "kept_sizes": [nchw(3, 3, 40, 70, 3, 3, 1, 1), nchw(8, 8, 24, 130, 3, 3, 1, 1, nb=3), nchw(7, 9, 33, 40, 3, 3, 1, 1, nb=2),
@@ -42,9 +45,9 @@ def test_any_alignment_edges(name):
     run_all_modes(CASES[name], seed=41, label=name)
 
 
-@pytest.mark.parametrize("name", ["skinny_tails", "blocks", "runs", "planes", "kept_sizes"])
+@pytest.mark.parametrize("name", ["skinny_tails", "blocks", "runs", "planes", "overhang", "kept_sizes"])
 def test_any_alignment_edges_at_odd_addresses(name):
     """The same at addresses that are aligned to an element only, GEMMs in rows padded by an odd number of elements."""
     off = 4  # bytes: whole elements of every type, no multiple of a piece
-    pads = {} if name in ("runs", "planes", "kept_sizes") else {"pad_lda": 5, "pad_ldb": 3, "pad_ldc": 1}
+    pads = {} if name in ("runs", "planes", "overhang", "kept_sizes") else {"pad_lda": 5, "pad_ldb": 3, "pad_ldc": 1}
     run_all_modes(CASES[name], seed=42, label=name + " at odd addresses", a_off=off, b_off=off, c_off=off, **pads)

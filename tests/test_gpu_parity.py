@@ -159,6 +159,14 @@ def test_direct_load_tiles():
             H.check_against_oracle(b, f"direct-load tiles among operands of any alignment {prm}")
 
 
+@pytest.mark.parametrize("cout", [64, 130])
+def test_direct_load_tiles_under_filters_that_overhang_the_image(cout):
+    """Images smaller than their filter: the scalar offset of the last taps lies beyond the operand (plans of 64 columns run
+    in the kernel of their own, wider ones in the general one)."""
+    run_all_modes([c(1, 1, 64, cout, 3, 3, 1, 1, nb=129), c(1, 80, 64, cout, 5, 1, 2, 0), c(80, 1, 64, cout, 1, 5, 0, 2),
+                   c(2, 2, 128, cout, 5, 5, 2, 2, nb=40)], seed=34, label="overhang")
+
+
 def nchw(h, w, cin, cout, r, s, ph, pw, dtype="bf16", nb=1, d=math.inf, st=1):
     return Problem(op="conv_nchw", dtype=dtype, Nb=nb, H=h, W=w, Cin=cin, Cout=cout, R=r, S=s, pad_h=ph, pad_w=pw,
                    stride=st, deadline_ms=d, a_dist=("uniform", 0.0, 1.0), b_dist=("normal", 0.1))
