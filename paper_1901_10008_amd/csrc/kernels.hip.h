@@ -1816,8 +1816,9 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         a_lo[i] = 0;
         a_hi[i] = run_len;
         if (P.gather) {
-          a_lo[i] = max(0, -r.wb) * P.Cin;
-          a_hi[i] = min(P.S, P.W - r.wb) * P.Cin;
+          // (columns held to 0 .. S before they are multiplied: a padding of many filters' width times the channels does not fit 32 bits)
+          a_lo[i] = min(max(0, -r.wb), P.S) * P.Cin;
+          a_hi[i] = max(0, min(P.S, P.W - r.wb)) * P.Cin;
         }
       }
     } else {

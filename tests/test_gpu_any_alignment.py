@@ -51,3 +51,9 @@ def test_any_alignment_edges_at_odd_addresses(name):
     off = 4  # bytes: whole elements of every type, no multiple of a piece
     pads = {} if name in ("runs", "planes", "overhang", "kept_sizes") else {"pad_lda": 5, "pad_ldb": 3, "pad_ldc": 1}
     run_all_modes(CASES[name], seed=42, label=name + " at odd addresses", a_off=off, b_off=off, c_off=off, **pads)
+
+
+def test_padding_whose_width_in_elements_does_not_fit_32_bits():
+    """One pixel of 8193 channels in the middle of 262144 columns of padding on either side, sampled every 1024 columns."""
+    run_all_modes([c(1, 1, 8193, 3, 1, 1, 0, 1 << 18, st=1024), c(1, 1, 8193, 70, 1, 1, 0, 1 << 18, "f16", st=1024),
+                   nchw(1, 1, 8193, 3, 1, 1, 0, 1 << 18, st=1024), c(1, 1, 8200, 66, 1, 1, 0, 1 << 18, st=1024)], seed=43, label="wide padding")
