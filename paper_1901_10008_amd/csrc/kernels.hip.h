@@ -57,21 +57,8 @@ __device__ __forceinline__ T SK_GLOBAL *as_global_mut(void *p) {
   return (T SK_GLOBAL *)(uintptr_t)p;
 }
 
-// A record that every lane reads from the same address, returned in scalar registers.
-template <class S>
-__device__ __forceinline__ S load_uniform(const S *src) {
-  static_assert(sizeof(S) % 4 == 0, "whole dwords");
-  struct Words {
-    uint32_t w[sizeof(S) / 4];
-  } v;
-  const uint32_t SK_GLOBAL *p = as_global<uint32_t>(src);
-#pragma unroll
-  for (unsigned i = 0; i < sizeof(S) / 4; ++i) v.w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)p[i]);
-  return __builtin_bit_cast(S, v);
-}
-
-// The same through the scalar cache, for records that nothing writes while the kernel runs: a few loads straight into
-// scalar registers.  (Handed over through LDS instead, every wave spent two vector instructions per dword on it.)
+// A record that every lane reads from the same address, in scalar registers, through the scalar cache: for records that
+// nothing writes while the kernel runs.  (Handed over through LDS instead, every wave spent two vector instructions per dword on it.)
 #define SK_CONSTANT __attribute__((address_space(4)))
 template <class S>
 __device__ __forceinline__ S load_record(const S *src) {
@@ -1672,16 +1659,18 @@ __device__ __forceinline__ void run_lds_tile(const DevProblem &P, const sk_tile 
 // ---------------------------------------------------------------------------
 // (Inlined, like every path of the kernel: as real calls the two slow paths gave the kernel a stack,
 // and how well its fast paths then ran changed from build to build.  They exist only in the kernel
-// instantiation for plans with such operands, which takes a few registers more.  They are given the
-// records' addresses in memory rather than references to the caller's copies.)
+// instantiations for plans with such operands: 239 to 248 registers instead of 233 to 242, about twice the code.  They
+// are given the records' addresses in memory rather than references to the caller's copies, and the
+// tile's own copy of the thread index (see the tile loop): taken from threadIdx, what run_tile_any derives from it was
+// hoisted out of the tile loop and cost these kernels 1 to 18 spilled vector registers and a stack.)
 template <int DT>
-__device__ __forceinline__ void run_generic(const DevProblem *P_mem, const sk_tile *T_mem) {
+__device__ __forceinline__ void run_generic(const DevProblem *P_mem, const sk_tile *T_mem, int tid) {
   const DevProblem P = *P_mem;
   const sk_tile T = *T_mem;
   const int m_len = T.m_len, n_len = T.n_len;
   // a split reduction is done whole by the record of its first slice; the others have nothing to do
   if (T.ks_idx != 0) return;
-  for (int idx = threadIdx.x; idx < m_len * n_len; idx += WG_THREADS) {
+  for (int idx = tid; idx < m_len * n_len; idx += WG_THREADS) {
     const int m = (int)T.m0 + idx / n_len;
     const int n = (int)T.n0 + idx % n_len;
     const RowA row = row_of(P, m);
@@ -1755,7 +1744,7 @@ __device__ __forceinline__ bool holds_a_piece(const DevProblem &P) {
 
 template <int DT, bool NCHW, int BM, int BN>
 __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_tile *T_mem, const SplitK &sp,
-                                             unsigned char *lds, uint32_t *s_flag) {
+                                             unsigned char *lds, uint32_t *s_flag, int tid) {
   constexpr int ES = Elem<DT>::ES;
   constexpr int CE = 16 / ES;
   constexpr int STAGE = (BM + BN) * LDS_ROW;  // pixels (or GEMM rows), then weight rows
@@ -1767,9 +1756,8 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
   using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
   typedef elem_t piece_t __attribute__((ext_vector_type(CE)));
   static_assert(2 * STAGE <= LDS_TILE_BYTES, "two stages do not fit the LDS buffer");
-  const DevProblem P = load_uniform(P_mem);
-  const sk_tile T = load_uniform(T_mem);
-  const int tid = threadIdx.x;
+  const DevProblem P = load_record(P_mem);
+  const sk_tile T = load_record(T_mem);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave & 1, wn = wave >> 1;
   const int l32 = lane & 31, half = lane >> 5;
@@ -2103,6 +2091,12 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
       }
 
       // ---- outputs: through LDS, so that they leave as runs of consecutive places ----
+      {
+      // (the record is read again: kept through the stages, what the outputs need of it costs the mixed-type kernel a quarter
+      // more spilled scalars)
+      const DevProblem P = load_record(P_mem);
+      const sk_tile T = load_record(T_mem);
+      const int m_end = (int)T.m0 + (int)T.m_len, n_end = (int)T.n0 + (int)T.n_len, hw = P.Ho * P.Wo;
       // lane holds, per (fn, fm): MFMA row l32, columns 8*(i/4) + 4*half + (i%4)
       constexpr int OROW = COLS * ES + 16;
       static_assert(ROWS * OROW <= LDS_TILE_BYTES, "output tile does not fit the LDS buffer");
@@ -2152,22 +2146,26 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
             }
         }
       }
+      }
       __syncthreads();  // the output tile has been read before the next block's stages are written
     }
   }
 }
 
+// (A slice of a split reduction must be a single block, so a shape may only be wider than its rectangle.  64 x 128 and 128 x 64
+// beside the square ones: without them the channel-major ResNet layers for eight take 173 instead of 152 us, the stride-2
+// layers for sixteen 123 instead of 113.)
 template <int DT, bool NCHW>
 __device__ __forceinline__ void run_block_any(const DevProblem *P_mem, const sk_tile *T_mem, int m_len, int n_len, const SplitK &sp,
-                                              unsigned char *lds, uint32_t *s_flag) {
+                                              unsigned char *lds, uint32_t *s_flag, int tid) {
   if (m_len <= 64 && n_len <= 64)
-    run_tile_any<DT, NCHW, 64, 64>(P_mem, T_mem, sp, lds, s_flag);
+    run_tile_any<DT, NCHW, 64, 64>(P_mem, T_mem, sp, lds, s_flag, tid);
   else if (m_len <= 64)
-    run_tile_any<DT, NCHW, 64, 128>(P_mem, T_mem, sp, lds, s_flag);
+    run_tile_any<DT, NCHW, 64, 128>(P_mem, T_mem, sp, lds, s_flag, tid);
   else if (n_len <= 64)
-    run_tile_any<DT, NCHW, 128, 64>(P_mem, T_mem, sp, lds, s_flag);
+    run_tile_any<DT, NCHW, 128, 64>(P_mem, T_mem, sp, lds, s_flag, tid);
   else
-    run_tile_any<DT, NCHW, 128, 128>(P_mem, T_mem, sp, lds, s_flag);
+    run_tile_any<DT, NCHW, 128, 128>(P_mem, T_mem, sp, lds, s_flag, tid);
 }
 
 template <int DT, bool ANY_ALIGNMENT, bool NARROW>
@@ -2197,11 +2195,11 @@ __device__ __forceinline__ void run_class(const DevProblem &P, const sk_tile &T,
           pf.issue();
           // (an operand of less than one piece also goes the first way: the others read whole pieces from inside it)
           if (small || !holds_a_piece<Elem<DT>::ES>(P))
-            run_generic<DT>(P_mem, T_mem);
+            run_generic<DT>(P_mem, T_mem, pf.tid);
           else if (P.nchw)
-            run_block_any<DT, true>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag);
+            run_block_any<DT, true>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag, pf.tid);
           else
-            run_block_any<DT, false>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag);
+            run_block_any<DT, false>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag, pf.tid);
         }
       }
     }
