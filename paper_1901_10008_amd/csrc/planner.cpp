@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <limits>
 #include <numeric>
 #include <unordered_set>
@@ -434,37 +435,134 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
   return SK_OK;
 }
 
-// A record that the element-wise or any-address blocks run takes (stages of 128 bytes of the reduction) x (128 x 128
-// blocks) x (2 for fp32, whose MFMAs take longer than everything else) units of about 2 us, all in one workgroup.  In a plan of
-// few records the launch then waits for one of them.  So where a record takes longer than an even share of
-// all such records over 512 workgroups it is cut into parts of at most 64 x 64 outputs: a quarter of the time each, and half
-// as much again in all.  Slices of split reductions stay whole (their workspace is laid out by rectangle), and
-// so do plans with per-die lists, which name the table's records.  The sums of an output do not change.
-bool refine_tiles(const HostPlan &hp, std::vector<sk_tile> &work, std::vector<int64_t> &count) {
-  if (!hp.xorder.empty()) return false;
-  auto cost = [&](const sk_tile &t) -> int64_t {
-    const DevProblem &d = hp.dev[t.problem];
-    const int32_t vec = FLAG_VEC_A | FLAG_VEC_B;
-    if ((d.flags & vec) == vec) return 0;
-    const int64_t es = elem_size(d.dtype), kb = 128 / es, ce = 16 / es;
-    // (the weight-streaming classes run any GEMM, and convolutions with whole pieces under a tap)
-    if (t.cls < CLS_TILE_128x128 && !d.nchw && d.Kg >= ce && (!d.gather || d.Cin % ce == 0)) return 0;
+// What a record costs, in nanoseconds: `time` by itself on a compute unit, and `work`, its share of a compute unit that two
+// workgroups keep busy.  Measured on plans of one kind of record each, 1 to 1024 of them, over 3 to 27 stages (fp32 blocks that
+// read rows: 1.2 times that time, which is what they take among other records).  They decide which records are cut
+// (refine_tiles) and nothing else.
+struct RecordCost {
+  int64_t time, work;
+};
+
+// Whether the blocks for operands of any alignment run the record (the weight-streaming classes read GEMMs at any address too,
+// and convolutions with whole pieces under a tap).
+static bool runs_in_any_blocks(const DevProblem &d, const sk_tile &t) {
+  const int32_t vec = FLAG_VEC_A | FLAG_VEC_B;
+  if ((d.flags & vec) == vec) return false;
+  const int64_t ce = 16 / elem_size(d.dtype);
+  return !(t.cls < CLS_TILE_128x128 && !d.nchw && d.Kg >= ce && (!d.gather || d.Cin % ce == 0));
+}
+
+// A record of m_len x n_len outputs in blocks of any alignment, `stages` of 128 bytes of the reduction.
+static RecordCost any_block_cost(const DevProblem &d, int64_t m_len, int64_t n_len, int64_t stages) {
+  const bool m64 = m_len <= 64, n64 = n_len <= 64;
+  const int64_t blocks = (m64 ? 1 : (m_len + 127) / 128) * (n64 ? 1 : (n_len + 127) / 128);
+  // per stage, [channel-major][fp32][128 x 128, 128 x 64, 64 x 128, 64 x 64]
+  static const RecordCost per_stage[2][2][4] = {{{{1850, 1120}, {1560, 900}, {1300, 790}, {1200, 730}},
+                                                 {{3700, 2630}, {2500, 1600}, {2300, 1540}, {1550, 930}}},
+                                                {{{2500, 1900}, {2450, 1500}, {2250, 1400}, {1800, 1150}},
+                                                 {{3500, 3050}, {2560, 1800}, {2250, 1700}, {1600, 1240}}}};
+  const int shape = (m64 ? 2 : 0) + (n64 ? 1 : 0);
+  const RecordCost &s = per_stage[d.nchw ? 1 : 0][d.dtype == SK_F32 ? 1 : 0][shape];
+  const int64_t start = shape == 0 ? 8000 : shape == 3 ? 5000 : 7000;  // set-up, first loads and outputs
+  return RecordCost{blocks * (start + stages * s.time), blocks * (start / 2 + stages * s.work)};
+}
+
+static RecordCost record_cost(const DevProblem &d, const sk_tile &t) {
+  const int64_t es = elem_size(d.dtype), kb = 128 / es, stages = ((int64_t)t.k_len + kb - 1) / kb;
+  const bool f32 = d.dtype == SK_F32;
+  if (runs_in_any_blocks(d, t)) return any_block_cost(d, t.m_len, t.n_len, stages);
+  if (t.cls < CLS_TILE_128x128) {
+    const int64_t steps = stages * ((t.n_len + 127) / 128);
+    const bool rows64 = t.cls >= 6;
+    return RecordCost{4000 + steps * (rows64 ? (f32 ? 1450 : 800) : 600), 2500 + steps * (rows64 ? (f32 ? 1200 : 720) : 620)};
+  }
+  if (t.cls == CLS_TILE_128x64) return RecordCost{4000 + stages * (f32 ? 1100 : 600), 2500 + stages * (f32 ? 820 : 650)};
+  return RecordCost{5000 + stages * (f32 ? 2000 : 700), 2500 + stages * (f32 ? 1800 : 1000)};
+}
+
+// A launch lasts at least as long as its longest record, and as long as the work of all records spread over the compute
+// units.  Where a record without 16-byte pieces is what it would wait for, such records are cut into parts of at most 64 x 64
+// outputs.  A part takes 0.4 (fp32) to 0.7 (16-bit types) of the time of a 128 x 128 block, but the parts together 1.4 to 2.6
+// times its work, so nothing is cut where the launch waits for a record that cannot be cut, or fills the chip anyway.
+// Measured, all records beyond an even share cut against none: stride-2 layers with the stem for two tenants 38.0 and 32.9 us, for
+// four 55.9 and 49.4, channel-major ResNet layers for eight 151 and 145, in fp32 for two 218 and 164.
+// Which records are cut where it pays:
+//   * 16-bit types: those that take 0.6 of what the launch lasts with the longest cut.  In a plan whose records all start at
+//     once the parts do too if those of the records that outlast the rest can: then as many others are cut,
+//     the longest first, as there are workgroups left.  (60 odd bf16 operators 49 us with none cut, 44 with all beyond
+//     an even share, 33 so.)
+//   * fp32 among them: all beyond an even share of the stages over the workgroups.  Blocks that keep the matrix cores busy
+//     slow down whoever shares their compute unit, so the shorter ones are worth cutting as well (96 operators in
+//     three types 208 us with none cut, 134 so; the rule for 16-bit types takes 80 to 135 % of the time of this
+//     one on plans of 20 to 96 odd fp32 operators).
+// Slices of split reductions stay whole (their workspace is laid out by rectangle), and so do plans with per-die
+// lists, which name the table's records.  The sums of an output do not change.
+bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &work, std::vector<int64_t> &count) {
+  if (!hp.xorder.empty() || workgroups < 1) return false;
+  const int32_t vec = FLAG_VEC_A | FLAG_VEC_B;
+  if (std::all_of(hp.dev.begin(), hp.dev.end(), [&](const DevProblem &d) { return (d.flags & vec) == vec; })) return false;
+  auto parts_of = [](const sk_tile &t) { return ((t.m_len + 63) / 64) * ((t.n_len + 63) / 64); };
+  auto stages_of = [&](const sk_tile &t) -> int64_t {  // 128 bytes of the reduction each; twice for fp32, over all 128 x 128 blocks
+    const int64_t es = elem_size(hp.dev[t.problem].dtype), kb = 128 / es;
     return ((t.k_len + kb - 1) / kb) * ((t.m_len + 127) / 128) * ((t.n_len + 127) / 128) * (es == 4 ? 2 : 1);
   };
-  int64_t total = 0;
-  for (const sk_tile &t : hp.tiles) total += cost(t);
-  // (up to 64 reduction elements a small rectangle may go the one-output-per-thread way, whose sums round differently: a
-  // part must not where its record does not)
-  auto cut = [&](const sk_tile &t) {
-    return t.S == 1 && (t.m_len > 64 || t.n_len > 64) && hp.dev[t.problem].Kg > 64 && cost(t) * 512 > total;
-  };
-  bool any = false;
-  for (const sk_tile &t : hp.tiles) any = any || cut(t);
-  if (!any) return false;
+  // time of every record that can be cut, 0 for the others
+  std::vector<int64_t> time(hp.tiles.size(), 0);
+  int64_t longest = 0, whole = 0, part = 0, total = 0;  // cuttable; not cuttable; a part of the longest; work of all
+  int64_t stages = 0;                                   // of all records in such blocks
+  bool fp32 = false;                                    // one of those that can be cut is
+  for (size_t i = 0; i < hp.tiles.size(); ++i) {
+    const sk_tile &t = hp.tiles[i];
+    const DevProblem &d = hp.dev[t.problem];
+    const RecordCost c = record_cost(d, t);
+    const bool any = runs_in_any_blocks(d, t);
+    total += c.work;
+    if (any) stages += stages_of(t);
+    // (up to 64 reduction elements a small rectangle may go the one-output-per-thread way, whose sums round differently: a
+    // part must not where its record does not)
+    if (t.S != 1 || (t.m_len <= 64 && t.n_len <= 64) || d.Kg <= 64 || !any) {
+      whole = std::max(whole, c.time);
+      continue;
+    }
+    time[i] = c.time;
+    fp32 = fp32 || d.dtype == SK_F32;
+    if (c.time > longest) {
+      longest = c.time;
+      const int64_t kb = 128 / elem_size(d.dtype);
+      part = any_block_cost(d, 64, 64, ((int64_t)t.k_len + kb - 1) / kb).time;
+    }
+  }
+  const int64_t length = std::max(std::max(whole, part), 2 * total / workgroups);  // (two workgroups per compute unit)
+  if (longest * 32 <= length * 33) return false;
+  int64_t from = length * 6 / 10;  // 16-bit types: the time from which records are cut
+  if (!fp32 && (int64_t)hp.tiles.size() <= workgroups) {
+    std::vector<std::pair<int64_t, int64_t>> more;  // records that need not be cut, by how many records their parts are more
+    int64_t all = (int64_t)hp.tiles.size(), least = all;
+    for (size_t i = 0; i < hp.tiles.size(); ++i) {
+      if (time[i] < from || time[i] == 0) continue;
+      const int64_t n = parts_of(hp.tiles[i]) - 1;
+      all += n;
+      if (time[i] > length)
+        least += n;
+      else
+        more.emplace_back(time[i], n);
+    }
+    if (all > workgroups && least <= workgroups) {
+      std::sort(more.begin(), more.end(), std::greater<std::pair<int64_t, int64_t>>());
+      for (const auto &m : more) {
+        least += m.second;
+        if (least > workgroups) {
+          from = m.first + 1;
+          break;
+        }
+      }
+    }
+  }
   work.clear();
   count.assign(hp.dev.size(), 0);
-  for (const sk_tile &t : hp.tiles) {
-    const bool c = cut(t);
+  for (size_t i = 0; i < hp.tiles.size(); ++i) {
+    const sk_tile &t = hp.tiles[i];
+    const bool c = time[i] > 0 && (fp32 ? stages_of(t) * workgroups > stages : time[i] >= from);
     const uint32_t bm = c ? 64u : t.m_len, bn = c ? 64u : t.n_len;
     for (uint32_t m = 0; m < t.m_len; m += bm)
       for (uint32_t n = 0; n < t.n_len; n += bn) {

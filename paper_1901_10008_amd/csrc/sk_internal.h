@@ -108,9 +108,10 @@ struct HostPlan {
 sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params *params,
                     HostPlan &out, std::string &err);
 
-// The device's work list: the table's records, of which the long ones of operators without 16-byte pieces are cut into
-// parts of 64 x 64 outputs (`work`; `count` of them per operator; false and untouched if nothing is to be cut).
-bool refine_tiles(const HostPlan &hp, std::vector<sk_tile> &work, std::vector<int64_t> &count);
+// The device's work list for a launch of that many workgroups: the table's records, of which those of operators without 16-byte
+// pieces that the launch would wait for are cut into parts of 64 x 64 outputs (`work`; `count` of them per operator; false
+// and untouched if nothing is to be cut).
+bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &work, std::vector<int64_t> &count);
 
 // Whether every tile of the plan, and of each of its operators planned alone, is a 128 x 64 LDS tile whose operands can
 // be read through 32-bit descriptors (the device's lean_operands, for the whole operator instead of tile by tile).

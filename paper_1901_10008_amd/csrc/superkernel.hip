@@ -361,6 +361,19 @@ sk_status upload_tables(const sk::HostPlan &hp, int device, DeviceTables &dt) {
   return SK_OK;
 }
 
+// Compute units of an MI355X, for plans that are made before their device is known (host-only ones).
+constexpr int COMPUTE_UNITS = 256;
+
+// What the device runs in place of the table, in a launch of that many workgroups.
+sk_status refine(sk::HostPlan &hp, int64_t workgroups) {
+  try {
+    (void)sk::refine_tiles(hp, workgroups, hp.work, hp.work_count);
+  } catch (const std::bad_alloc &) {
+    return set_error(SK_ERR_ALLOC, "host allocation failed while planning");
+  }
+  return SK_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -373,11 +386,6 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
   sk_status st;
   try {
     st = sk::plan_host(problems, n, params, plan->host, err);
-    sk::HostPlan &hp = plan->host;
-    if (st == SK_OK && sk::refine_tiles(hp, hp.work, hp.work_count) && hp.params.host_only && layout_of(hp).total > STATIC_SCRATCH_BYTES) {
-      hp.work.clear();  // (the static scratch holds the table at most)
-      hp.work_count.clear();
-    }
   } catch (const std::bad_alloc &) {
     delete plan;
     return set_error(SK_ERR_ALLOC, "host allocation failed while planning");
@@ -405,6 +413,12 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
     }
   }
   if (prm.host_only && !plan->host.tiles.empty()) {
+    st = refine(plan->host, prm.grid_limit > 0 ? prm.grid_limit : 2 * (int64_t)COMPUTE_UNITS);
+    if (st != SK_OK) {
+      delete plan;
+      return st;
+    }
+    if (layout_of(plan->host).total > STATIC_SCRATCH_BYTES) plan->host.work.clear();  // (the table itself may still fit)
     const TableLayout l = layout_of(plan->host);
     if (l.total <= STATIC_SCRATCH_BYTES) {  // (larger plans cannot use sk_launch_static anyway)
       try {
@@ -431,6 +445,11 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
     }
     plan->ticks_per_ms = (double)clock_khz;
     const int64_t limit = prm.grid_limit > 0 ? prm.grid_limit : (plan->narrow ? 3 : 2) * (int64_t)cus;
+    st = refine(plan->host, limit);
+    if (st != SK_OK) {
+      delete plan;
+      return st;
+    }
     const int64_t ntiles = (int64_t)plan->host.records().size();
     plan->grid_cap = limit;
     plan->grid = (int)(ntiles < limit ? ntiles : limit);

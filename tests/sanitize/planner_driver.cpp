@@ -6,6 +6,7 @@
 // Python tests' job.
 #include <cstdint>
 #include <algorithm>
+#include <array>
 #include <cstdio>
 #include <limits>
 #include <random>
@@ -104,6 +105,38 @@ int main() {
           t.out_tile_id >= hp.ws_off.size())
         return fail("record leaves its operator", seed);
     }
+    // the device's work list: every record once, whole or in parts that tile it; only what may be cut is
+    for (int64_t wgs : {(int64_t)1, (int64_t)7, (int64_t)512}) {
+      std::vector<sk_tile> work;
+      std::vector<int64_t> counts;
+      if (!sk::refine_tiles(hp, wgs, work, counts)) {
+        if (!work.empty() || !counts.empty()) return fail("a work list that nothing is cut in", seed);
+        continue;
+      }
+      size_t at = 0;
+      std::vector<int64_t> seen((size_t)n, 0);
+      for (const sk_tile &t : hp.tiles) {
+        const sk::DevProblem &d = hp.dev[t.problem];
+        const bool vec = (d.flags & (sk::FLAG_VEC_A | sk::FLAG_VEC_B)) == (sk::FLAG_VEC_A | sk::FLAG_VEC_B);
+        uint32_t m = t.m0, nn = t.n0;
+        int64_t area = 0;
+        while (area < (int64_t)t.m_len * t.n_len) {
+          if (at == work.size()) return fail("work list ends early", seed);
+          const sk_tile &u = work[at++];
+          ++seen[t.problem];
+          if (u.problem != t.problem || u.cls != t.cls || u.S != t.S || u.ks_idx != t.ks_idx || u.k0 != t.k0 || u.k_len != t.k_len ||
+              u.out_tile_id != t.out_tile_id || u.m0 != m || u.n0 != nn || u.m_len < 1 || u.n_len < 1)
+            return fail("a part that is not of its record", seed);
+          const bool whole = u.m_len == t.m_len && u.n_len == t.n_len;
+          if (!whole && (t.S != 1 || d.Kg <= 64 || vec || u.m_len > 64 || u.n_len > 64)) return fail("cut what must stay whole", seed);
+          area += (int64_t)u.m_len * u.n_len;
+          nn += u.n_len;
+          if (nn == t.n0 + t.n_len) nn = t.n0, m += u.m_len;
+        }
+        if (area != (int64_t)t.m_len * t.n_len) return fail("parts overlap", seed);
+      }
+      if (at != work.size() || seen != counts) return fail("work list counts", seed);
+    }
     sk::HostPlan alone;
     if (sk::plan_host_each_alone(hp, alone, err) != SK_OK) return fail("plan_host_each_alone", seed);
     if (alone.dev.size() != hp.dev.size()) return fail("baseline tables", seed);
@@ -159,6 +192,71 @@ int main() {
     std::string err;
     if (sk::plan_host(&p, 1, nullptr, hp, err) != SK_OK) return fail("plan_host failed on a large convolution", -4);
     if (hp.dev[0].reach != 1u << 31 || sk::offsets_below(hp.dev[0], 0, 4, (int64_t)1 << 31)) return fail("reach of a large image", -4);
+  }
+  // What is cut, on hand-worked plans.
+  {
+    sk_plan_params prm;
+    sk_plan_params_default(&prm);
+    prm.host_only = 1;
+    uintptr_t addr = 0x10000000;
+    auto place = [&](sk_problem &p) {
+      p.A = (const void *)addr, p.B = (const void *)(addr + (1u << 30)), p.C = (void *)(addr + (2u << 30));
+      addr += (uintptr_t)3 << 30;
+    };
+    auto gemm = [&](int dt, int m, int nn, int k) {
+      sk_problem p{};
+      p.op = SK_GEMM, p.dtype = dt, p.M = m, p.N = nn, p.K = k;
+      place(p);
+      return p;
+    };
+    auto conv = [&](int op, int dt, int hw, int ci, int co, int r, int stride, int pad) {
+      sk_problem p{};
+      p.op = op, p.dtype = dt, p.Nb = 1, p.H = p.Wd = hw, p.Cin = ci, p.Cout = co, p.R = p.S = r, p.stride = stride, p.pad_h = p.pad_w = pad;
+      place(p);
+      return p;
+    };
+    auto records = [&](const std::vector<sk_problem> &ps, int64_t wgs) -> int64_t {
+      sk::HostPlan hp;
+      std::string err;
+      if (sk::plan_host(ps.data(), (int)ps.size(), &prm, hp, err) != SK_OK) return -1;
+      std::vector<sk_tile> work;
+      std::vector<int64_t> counts;
+      return sk::refine_tiles(hp, wgs, work, counts) ? (int64_t)work.size() : 0;  // 0: nothing cut
+    };
+    // 300 x 130 outputs over 1001: 3 x 2 records of 16 stages, (128, 128) 37.6 us, (128, 2) 32, (44, 128) 27.8, (44, 2) 24.2, a part 24.2.
+    // All but the last are cut: 2 * 4 + 2 * 2 + 2 + 1.
+    const sk_problem odd = gemm(SK_BF16, 300, 130, 1001);
+    if (records({odd}, 512) != 15) return fail("an odd operator by itself", -5);
+    // ten workgroups start the six records at once, but not the parts of the five that outlast a part: all are cut
+    if (records({odd}, 10) != 15) return fail("parts that cannot start at once", -5);
+    // two records of 8 stages besides, 22.8 us each: cut where all 23 parts and records start at once, else not
+    const sk_problem shorter = gemm(SK_BF16, 256, 128, 449);
+    if (records({odd, shorter}, 23) != 23) return fail("a workgroup for every part", -5);
+    if (records({odd, shorter}, 20) != 17) return fail("a workgroup for every part that must be", -5);
+    // four workgroups: 2 * 110 us of work / 4 is more than the longest record
+    if (records({odd}, 4) != 0) return fail("a full chip", -5);
+    // beside an fp32 operator of 64 stages (133 us) in aligned pieces
+    if (records({odd, gemm(SK_F32, 128, 128, 2040)}, 512) != 0) return fail("a longer record that cannot be cut", -5);
+    // at most 64 reduction elements: never
+    if (records({gemm(SK_BF16, 300, 130, 63)}, 512) != 0) return fail("a short reduction", -5);
+    // the stride-2 layers with the 7x7 stem: records of three stages, for one tenant to six
+    std::vector<sk_problem> mix;
+    for (int t = 0; t < 6; ++t) {
+      for (const auto &l : {std::array<int, 5>{224, 3, 64, 7, 3}, {56, 128, 128, 3, 1}, {56, 256, 512, 1, 0}, {28, 256, 256, 3, 1},
+                            {28, 512, 1024, 1, 0}, {14, 512, 512, 3, 1}, {14, 1024, 2048, 1, 0}})
+        mix.push_back(conv(SK_CONV2D_NHWC, SK_BF16, l[0], l[1], l[2], l[3], 2, l[4]));
+      if (records(mix, 512) != 0) return fail("stems of a few tenants", t);
+    }
+    // channel-major ResNet layers: the sliced 14 x 14 layer is what one tenant to five wait for
+    for (int dt : {SK_F16, SK_F32}) {
+      mix.clear();
+      for (int t = 0; t < 5; ++t) {
+        for (const auto &l : {std::array<int, 4>{56, 64, 256, 1}, {56, 64, 64, 3}, {28, 128, 512, 1}, {28, 128, 128, 3}, {14, 256, 1024, 1},
+                              {14, 256, 256, 3}, {7, 512, 2048, 1}, {7, 512, 512, 3}})
+          mix.push_back(conv(SK_CONV2D_NCHW, dt, l[0], l[1], l[2], l[3], 1, l[3] / 2));
+        if (records(mix, 512) != 0) return fail("channel-major layers of a few tenants", t);
+      }
+    }
   }
   // lists the planner must reject
   {
