@@ -597,7 +597,7 @@ bool narrow_plan(const HostPlan &hp) {
   return true;
 }
 
-sk_status plan_host_each_alone(const HostPlan &whole, HostPlan &out, std::string &err) {
+sk_status plan_host_each_alone(const HostPlan &whole, int64_t workgroups, HostPlan &out, std::string &err) {
   const int32_t n = (int32_t)whole.problems.size();
   out = HostPlan{};
   out.params = whole.params;
@@ -615,9 +615,11 @@ sk_status plan_host_each_alone(const HostPlan &whole, HostPlan &out, std::string
     HostPlan one;
     const sk_status st = plan_host(&whole.problems[i], 1, &prm, one, err);
     if (st != SK_OK) return st;
+    std::vector<int64_t> counts;
+    (void)refine_tiles(one, workgroups, one.work, counts);
     out.first[i] = (int64_t)out.tiles.size();
-    out.count[i] = (int64_t)one.tiles.size();
-    for (sk_tile t : one.tiles) {
+    out.count[i] = (int64_t)one.records().size();
+    for (sk_tile t : one.records()) {
       t.problem = (uint32_t)i;
       t.out_tile_id += rect_base;
       out.tiles.push_back(t);

@@ -117,8 +117,9 @@ bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &
 // be read through 32-bit descriptors (the device's lean_operands, for the whole operator instead of tile by tile).
 bool narrow_plan(const HostPlan &hp);
 // The tile tables of the one-launch-per-operator baseline: every operator of `whole` planned
-// by plan_host as if it were submitted alone, concatenated in submission order.
-sk_status plan_host_each_alone(const HostPlan &whole, HostPlan &out, std::string &err);
+// by plan_host as if it were submitted alone, with its long records cut as for a launch of its own on that many workgroups,
+// concatenated in submission order.
+sk_status plan_host_each_alone(const HostPlan &whole, int64_t workgroups, HostPlan &out, std::string &err);
 
 inline int elem_size(int32_t dtype) { return dtype == SK_F32 ? 4 : 2; }
 

@@ -637,7 +637,7 @@ sk_status sk_launch_sequential(sk_plan *plan, void *hip_stream) {
   if (!plan->seq_ready) {
     std::string err;
     try {
-      st = sk::plan_host_each_alone(plan->host, plan->seq_host, err);
+      st = sk::plan_host_each_alone(plan->host, plan->grid_cap, plan->seq_host, err);
     } catch (const std::bad_alloc &) {
       return set_error(SK_ERR_ALLOC, "host allocation failed while planning");
     }

@@ -138,7 +138,7 @@ int main() {
       if (at != work.size() || seen != counts) return fail("work list counts", seed);
     }
     sk::HostPlan alone;
-    if (sk::plan_host_each_alone(hp, alone, err) != SK_OK) return fail("plan_host_each_alone", seed);
+    if (sk::plan_host_each_alone(hp, 512, alone, err) != SK_OK) return fail("plan_host_each_alone", seed);
     if (alone.dev.size() != hp.dev.size()) return fail("baseline tables", seed);
   }
   // Convolution operands read through descriptors: the offset of a pixel, the scalar offset of a tap and the element itself must
@@ -225,8 +225,19 @@ int main() {
     };
     // 300 x 130 outputs over 1001: 3 x 2 records of 16 stages, (128, 128) 37.6 us, (128, 2) 32, (44, 128) 27.8, (44, 2) 24.2, a part 24.2.
     // All but the last are cut: 2 * 4 + 2 * 2 + 2 + 1.
-    const sk_problem odd = gemm(SK_BF16, 300, 130, 1001);
+    const sk_problem odd = gemm(SK_BF16, 300, 130, 1001), odd2 = gemm(SK_F16, 300, 130, 1001);
     if (records({odd}, 512) != 15) return fail("an odd operator by itself", -5);
+    // the one-launch-per-operator baseline cuts every operator as if it were alone, whatever the plan waits for
+    {
+      const std::vector<sk_problem> ps = {odd, gemm(SK_F32, 128, 128, 2040), odd2};
+      sk::HostPlan hp, alone;
+      std::string err;
+      if (sk::plan_host(ps.data(), 3, &prm, hp, err) != SK_OK || sk::plan_host_each_alone(hp, 512, alone, err) != SK_OK)
+        return fail("baseline of odd operators", -5);
+      if (alone.count != std::vector<int64_t>{15, 1, 15} || alone.first != std::vector<int64_t>{0, 15, 16} || alone.tiles.size() != 31 ||
+          alone.dev[2].tile_count != 15 || alone.tiles[30].problem != 2 || alone.tiles[30].out_tile_id != 12)
+        return fail("tables of the baseline", -5);
+    }
     // ten workgroups start the six records at once, but not the parts of the five that outlast a part: all are cut
     if (records({odd}, 10) != 15) return fail("parts that cannot start at once", -5);
     // two records of 8 stages besides, 22.8 us each: cut where all 23 parts and records start at once, else not
