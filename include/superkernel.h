@@ -129,9 +129,8 @@ typedef struct {
   int32_t balance_div;    /* default 512                                                     */
   int32_t max_groups;     /* cap on 32-row weight groups per skinny tile, default 256        */
   int32_t grid_limit;     /* upper bound on persistent workgroups per launch;                */
-                          /* 0 = 2 per compute unit of the current device, 3 for a plan of   */
-                          /* which every tile is a 128x64 LDS tile that the direct loads can */
-                          /* serve                                                           */
+                          /* 0 = 2 per compute unit of the current device, or 3 for plans of */
+                          /* short 128x64 LDS tiles alone whose number makes 3 the faster    */
   int32_t tail_div;       /* tiles shrink towards the end of the table: an operator's target */
                           /* is also capped by (such bytes of it and of all operators        */
                           /* after it in execution order) / tail_div, so that the launch     */

@@ -85,8 +85,8 @@ constexpr int LDS_TILE_BYTES = 512 * LDS_ROW;  // 72 KB per workgroup: two workg
 // Plans of which every tile is a lean 128 x 64 tile ("narrow": the 3x3 layers with at most 64 output channels of many
 // tenants) run in a kernel of their own: without the other classes' registers and with two stage images instead of
 // three, three workgroups share a CU.  Such a tile spends half its time around its few stages (set-up, first loads,
-// outputs, hand-over), which only the CU's other workgroups
-// can fill: the 3x3 64-channel convolutions on 56x56 of 512 tenants take 214 us instead of 239.
+// outputs, hand-over), which only the CU's other workgroups can fill: the 3x3 64-channel convolutions on 56x56 of 512
+// tenants take 214 to 223 us instead of 239.  Not every number of tiles gains (narrow_pays).
 constexpr int NARROW_LDS_BYTES = 2 * (128 + 64) * 128;
 
 // Queue counters of a table: [0] tiles handed out beyond the first grid-full, [1] finished workgroups,

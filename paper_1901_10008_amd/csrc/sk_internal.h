@@ -116,6 +116,9 @@ bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &
 // Whether every tile of the plan, and of each of its operators planned alone, is a 128 x 64 LDS tile whose operands can
 // be read through 32-bit descriptors (the device's lean_operands, for the whole operator instead of tile by tile).
 bool narrow_plan(const HostPlan &hp);
+// Whether a launch of that many such tiles, the longest of so many stages of the reduction, is faster in the kernel of which three
+// workgroups share a compute unit than in the general one.
+bool narrow_pays(bool fp32, int64_t stages, int64_t tiles, int64_t compute_units);
 // The tile tables of the one-launch-per-operator baseline: every operator of `whole` planned
 // by plan_host as if it were submitted alone, with its long records cut as for a launch of its own on that many workgroups,
 // concatenated in submission order.

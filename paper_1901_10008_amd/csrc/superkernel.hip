@@ -2,6 +2,7 @@
 // the one-launch-per-operator baseline (Sections 4.1, 5.1 and 5.3 of the paper).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -254,10 +255,17 @@ struct sk_plan {
   bool resident = false;
   int device = -1;
   int grid = 0;      // persistent workgroups of sk_launch
-  int64_t grid_cap = 0;  // most workgroups any launch of this plan may use
   int only_dtype = -1;   // the element type all operators share, or -1 if they differ
   bool any_alignment = false;  // some operator cannot be read in aligned 16-byte pieces
-  bool narrow = false;         // every tile is a lean 128 x 64 tile, of one element type: the kernel of which three workgroups share a CU
+  // Every tile is a lean 128 x 64 tile, of one element type: launches go to the kernel of which three workgroups share a CU
+  // where that pays (sk::narrow_pays).
+  bool narrow = false;
+  int64_t longest_stages = 0;  // stages of the reduction of the longest such tile
+  int cus = 0;                 // compute units of the plan's device
+  bool narrow_launch(int64_t tiles) const { return narrow && sk::narrow_pays(only_dtype == SK_F32, longest_stages, tiles, cus); }
+  int64_t most_workgroups(int64_t tiles) const {
+    return host.params.grid_limit > 0 ? host.params.grid_limit : (narrow_launch(tiles) ? 3 : 2) * (int64_t)cus;
+  }
   // Every tile is short (at most 64 KB of operands): sk_launch gives workgroup b the tiles b, b + grid, ...
   // instead of running the queue.  A queue claim is an atomic round trip before the next record can be
   // fetched, and such tiles are over before it returns: three thousand tiny operators take 29 instead of
@@ -404,6 +412,11 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
       if ((d.flags & vec) != vec) plan->any_alignment = true;
   }
   plan->narrow = sk::narrow_plan(plan->host) && plan->only_dtype >= 0;
+  if (plan->narrow)
+    for (const sk_tile &t : plan->host.tiles) {
+      const int64_t kb = 128 / sk::elem_size(plan->only_dtype);
+      plan->longest_stages = std::max<int64_t>(plan->longest_stages, (t.k_len + kb - 1) / kb);
+    }
   plan->fixed_assignment = !plan->host.tiles.empty();
   for (const sk_tile &t : plan->host.tiles) {
     const int es = sk::elem_size(plan->host.problems[t.problem].dtype);
@@ -413,7 +426,8 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
     }
   }
   if (prm.host_only && !plan->host.tiles.empty()) {
-    st = refine(plan->host, prm.grid_limit > 0 ? prm.grid_limit : 2 * (int64_t)COMPUTE_UNITS);
+    plan->cus = COMPUTE_UNITS;
+    st = refine(plan->host, plan->most_workgroups((int64_t)plan->host.tiles.size()));
     if (st != SK_OK) {
       delete plan;
       return st;
@@ -436,22 +450,21 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
       delete plan;
       return hip_error("hipGetDevice", e);
     }
-    int cus = 0, clock_khz = 0;
-    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, plan->device);
+    int clock_khz = 0;
+    e = hipDeviceGetAttribute(&plan->cus, hipDeviceAttributeMultiprocessorCount, plan->device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&clock_khz, hipDeviceAttributeWallClockRate, plan->device);
     if (e != hipSuccess) {
       delete plan;
       return hip_error("hipDeviceGetAttribute", e);
     }
     plan->ticks_per_ms = (double)clock_khz;
-    const int64_t limit = prm.grid_limit > 0 ? prm.grid_limit : (plan->narrow ? 3 : 2) * (int64_t)cus;
+    const int64_t limit = plan->most_workgroups((int64_t)plan->host.tiles.size());
     st = refine(plan->host, limit);
     if (st != SK_OK) {
       delete plan;
       return st;
     }
     const int64_t ntiles = (int64_t)plan->host.records().size();
-    plan->grid_cap = limit;
     plan->grid = (int)(ntiles < limit ? ntiles : limit);
     st = upload_tables(plan->host, plan->device, plan->dev);
     if (st != SK_OK) {
@@ -542,7 +555,7 @@ static sk_status launch_range(sk_plan *plan, const DeviceTables &dt, hipStream_t
   a.arrive = dt.arrive;
   const dim3 g((unsigned)grid), b(sk::WG_THREADS);
   void (*kernel)(const sk::TileWork *, sk::KernelArgs) = nullptr;
-  if (plan->narrow) {
+  if (plan->narrow_launch((int64_t)end - begin)) {
     switch (plan->only_dtype) {
       case SK_F32: kernel = sk::sk_superkernel<SK_F32, false, true>; break;
       case SK_BF16: kernel = sk::sk_superkernel<SK_BF16, false, true>; break;
@@ -637,7 +650,7 @@ sk_status sk_launch_sequential(sk_plan *plan, void *hip_stream) {
   if (!plan->seq_ready) {
     std::string err;
     try {
-      st = sk::plan_host_each_alone(plan->host, plan->grid_cap, plan->seq_host, err);
+      st = sk::plan_host_each_alone(plan->host, plan->most_workgroups(1), plan->seq_host, err);
     } catch (const std::bad_alloc &) {
       return set_error(SK_ERR_ALLOC, "host allocation failed while planning");
     }
@@ -656,7 +669,8 @@ sk_status sk_launch_sequential(sk_plan *plan, void *hip_stream) {
   if (st != SK_OK) return st;
   for (size_t i = 0; i < n && st == SK_OK; ++i) {
     const int64_t first = plan->seq_host.first[i], count = plan->seq_host.count[i];
-    const int grid = (int)(count < plan->grid_cap ? count : plan->grid_cap);
+    const int64_t limit = plan->most_workgroups(count);
+    const int grid = (int)(count < limit ? count : limit);
     st = launch_range(plan, plan->seq_dev, stream, (uint32_t)first, (uint32_t)(first + count), grid, false, i == 0);
   }
   note_launch(plan, stream, capturing);  // also after a failure: some launches may be out
@@ -688,9 +702,9 @@ sk_status sk_launch_static(sk_plan *plan, void *hip_stream) {
   if (e != hipSuccess) return hip_error("hipMemcpyAsync", e);
   DeviceTables dt;
   bind_tables(dt, base, l);
-  const int64_t limit = plan->host.params.grid_limit > 0 ? plan->host.params.grid_limit : (plan->narrow ? 3 : 2) * (int64_t)cus;
+  plan->cus = cus;
   const int64_t ntiles = (int64_t)plan->host.records().size();
-  plan->grid_cap = limit;
+  const int64_t limit = plan->most_workgroups(ntiles);
   plan->grid = (int)(ntiles < limit ? ntiles : limit);
   return launch_range(plan, dt, stream, 0u, (uint32_t)ntiles, plan->grid, !plan->fixed_assignment, false, true);
 }

@@ -269,6 +269,70 @@ int main() {
       }
     }
   }
+  // Narrow plans: every tile, of the plan and of its operators alone, must satisfy what the device's direct loads ask for (a tile
+  // that does not would never be run there); at the limits of that, and where the kernel for them is taken.
+  {
+    auto lean = [](const sk::DevProblem &d, const sk_tile &t) {
+      const int64_t es = sk::elem_size(d.dtype), limit = ((int64_t)1 << 31) - 4096, kb = 128 / es;
+      if ((d.flags & (sk::FLAG_VEC_A | sk::FLAG_VEC_B)) != (sk::FLAG_VEC_A | sk::FLAG_VEC_B) || t.cls != sk::CLS_TILE_128x64) return false;
+      if (((int64_t)(t.n_len - 1) * d.ldb + d.Kg) * es >= limit) return false;
+      if (!d.gather) return ((int64_t)(t.m_len - 1) * d.lda + d.Kg) * es < limit;
+      const int64_t hw = (int64_t)d.Ho * d.Wo;
+      return !d.nchw && d.Cin % kb == 0 && d.R * d.S <= 31 && sk::offsets_below(d, (t.m0 + t.m_len - 1) / hw - t.m0 / hw, es, limit);
+    };
+    int narrow = 0;
+    for (int seed = 0; seed < 2000; ++seed) {
+      std::mt19937 g(seed);
+      auto pick = [&](std::initializer_list<int> v) { return *(v.begin() + g() % v.size()); };
+      std::vector<sk_problem> ps(1 + g() % 3);
+      uintptr_t addr = 0x10000000;
+      const int dt = pick({SK_F32, SK_BF16});
+      for (sk_problem &p : ps) {
+        p = sk_problem{};
+        p.dtype = dt;
+        if (g() % 2) {
+          p.op = SK_GEMM, p.M = pick({65, 128, 200, 5000}), p.N = pick({1, 40, 64, 64, 65}), p.K = pick({8, 64, 1000, 4096, 4100});
+          p.lda = pick({0, 0, 1 << 20, 1 << 21, 1 << 22, 1 << 23}), p.ldb = pick({0, 0, 1 << 21, 1 << 22, 1 << 23});
+        } else {
+          p.op = g() % 8 ? SK_CONV2D_NHWC : SK_CONV2D_NCHW, p.Nb = pick({1, 2, 40}), p.H = pick({1, 9, 56, 2000}), p.Wd = pick({9, 56, 700});
+          p.Cin = pick({32, 64, 64, 96, 128}), p.Cout = pick({8, 64}), p.R = pick({1, 3, 5}), p.S = pick({1, 3, 5, 7}), p.pad_h = p.R / 2, p.pad_w = pick({0, 3, 3000});
+          p.stride = pick({1, 2, 3});
+        }
+        p.A = (const void *)addr, p.B = (const void *)(addr + ((uintptr_t)1 << 40)), p.C = (void *)(addr + ((uintptr_t)2 << 40));
+        addr += (uintptr_t)3 << 40;
+      }
+      sk_plan_params prm;
+      sk_plan_params_default(&prm);
+      prm.host_only = 1;
+      prm.tile_bytes_max = prm.tile_bytes_min * pick({1, 64});
+      sk::HostPlan hp, alone;
+      std::string err;
+      if (sk::plan_host(ps.data(), (int)ps.size(), &prm, hp, err) != SK_OK || !sk::narrow_plan(hp)) continue;
+      ++narrow;
+      if (sk::plan_host_each_alone(hp, 512, alone, err) != SK_OK) return fail("plan_host_each_alone", seed);
+      for (const sk::HostPlan *h : {&hp, &alone})
+        for (const sk_tile &t : h->tiles)
+          if (!lean(h->dev[t.problem], t)) return fail("a tile of a narrow plan that the direct loads cannot serve", seed);
+    }
+    if (narrow < 100) return fail("hardly any narrow plan", narrow);
+    auto one = [](int64_t lda, int64_t ldb) {
+      sk_problem p{};
+      p.op = SK_GEMM, p.dtype = SK_BF16, p.M = 300, p.N = 64, p.K = 64, p.lda = lda, p.ldb = ldb;
+      p.A = (const void *)0x10000, p.B = (const void *)((uintptr_t)1 << 44), p.C = (void *)((uintptr_t)1 << 45);
+      sk::HostPlan hp;
+      std::string err;
+      return sk::plan_host(&p, 1, nullptr, hp, err) == SK_OK && sk::narrow_plan(hp);
+    };
+    if (!one(0, 0) || one(1 << 22, 0) || !one((1 << 22) - 8, 0) || one(0, 1 << 23) || !one(0, (1 << 23) - 8))
+      return fail("narrow_plan at its limits", -6);
+    for (bool f : {false, true}) {
+      const int64_t c = 256;
+      if (!sk::narrow_pays(f, 9, c, c) || sk::narrow_pays(f, 9, c + 1, c) || sk::narrow_pays(f, 9, 2 * c, c) || !sk::narrow_pays(f, 9, 2 * c + 1, c) ||
+          !sk::narrow_pays(f, 9, 691, c) || sk::narrow_pays(f, 9, 692, c) || sk::narrow_pays(f, 9, (f ? 8 : 15) * c - 1, c) ||
+          !sk::narrow_pays(f, 9, (f ? 8 : 15) * c, c) || sk::narrow_pays(f, 13, 15 * c, c) != f || sk::narrow_pays(f, 13, c, c))
+        return fail("narrow_pays", f);
+    }
+  }
   // lists the planner must reject
   {
     sk::HostPlan hp;
