@@ -2227,9 +2227,9 @@ __device__ __forceinline__ void run_class(const DevProblem &P, const sk_tile &T,
 template <int ONLY_DT, bool ANY_ALIGNMENT, bool NARROW>
 __global__ void __launch_bounds__(WG_THREADS, NARROW ? 3 : 2) sk_superkernel(const TileWork *__restrict__ work, KernelArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[NARROW ? NARROW_LDS_BYTES : LDS_TILE_BYTES];
-  // By parity: the next record as wave 0 fetched it (which brings it into the L2 for everyone, see load_record); behind it
-  // [0] its ticket, [1] flags (MAIL_*), [2] its index in xwork, [3] the ticket that waits while it runs
-  __shared__ __attribute__((aligned(16))) uint32_t s_mail[2][WORK_DWORDS + 4];
+  // By parity: [0] the next record's ticket, [1] flags (MAIL_*), [2] its index in xwork, [3] the ticket that waits while it runs.
+  // (Wave 0 has fetched the record itself ahead of time, which brings it into the L2 for everyone's load_record.)
+  __shared__ __attribute__((aligned(16))) uint32_t s_mail[2][4];
   __shared__ uint32_t s_flag;
   const SplitK sp{a.ws, a.ws_off, a.arrive};
   enum : uint32_t { MAIL_RUN = 1, MAIL_FROM_LIST = 2, MAIL_PENDING = 4, MAIL_OWES = 8 };
@@ -2366,12 +2366,11 @@ __global__ void __launch_bounds__(WG_THREADS, NARROW ? 3 : 2) sk_superkernel(con
         }
         if (owes) flags |= MAIL_OWES;
       }
-      if (lane0 < WORK_DWORDS) s_mail[par][lane0] = word;
       if (lane0 == 0) {
-        s_mail[par][WORK_DWORDS] = idx;
-        s_mail[par][WORK_DWORDS + 1] = flags;
-        s_mail[par][WORK_DWORDS + 2] = xi;
-        s_mail[par][WORK_DWORDS + 3] = waits;
+        s_mail[par][0] = idx;
+        s_mail[par][1] = flags;
+        s_mail[par][2] = xi;
+        s_mail[par][3] = waits;
       }
     }
     __syncthreads();
@@ -2383,7 +2382,7 @@ __global__ void __launch_bounds__(WG_THREADS, NARROW ? 3 : 2) sk_superkernel(con
         a.remaining[done_problem] = done_count;
       }
     }
-    const uint32_t flags = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mail[par][WORK_DWORDS + 1]);
+    const uint32_t flags = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mail[par][1]);
 #ifdef SK_DIAG_CLOCKS
     if (have_done) {
       SK_DIAG(5);
@@ -2391,14 +2390,14 @@ __global__ void __launch_bounds__(WG_THREADS, NARROW ? 3 : 2) sk_superkernel(con
     }
 #endif
     if (!(flags & MAIL_RUN)) break;
-    const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mail[par][WORK_DWORDS]);
+    const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mail[par][0]);
     const TileWork *cur =
-        (flags & MAIL_FROM_LIST) ? a.xwork + (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mail[par][WORK_DWORDS + 2]) : work + t;
+        (flags & MAIL_FROM_LIST) ? a.xwork + (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mail[par][2]) : work + t;
     // (wave 0 has fetched the record ahead of time: it is in this die's L2)
     const TileWork W = load_record(cur);
     const bool pending = (flags & MAIL_PENDING) != 0;  // a ticket waits: this tile takes no new one
     owes = (flags & MAIL_OWES) != 0;
-    const uint32_t waits = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mail[par][WORK_DWORDS + 3]);
+    const uint32_t waits = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mail[par][3]);
     par ^= 1;
 
     // Everything a tile derives from the thread index is derived again for each tile, from a
