@@ -90,9 +90,9 @@ typedef enum { SK_GEMM = 0, SK_CONV2D_NHWC = 1, SK_CONV2D_NCHW = 2 } sk_op;
  *   Y[b,co,ho,wo] = sum_{c,r,s} X[b, c, ho*stride-pad_h+r, wo*stride-pad_w+s] * W[co,c,r,s].
  *   Same fields and output size.  The reduction index is (c*R+r)*S+s, so the
  *   weights are still one contiguous row per output channel; activations and
- *   outputs are not contiguous along it, and the operator runs through the
- *   element-wise tile paths (correct for every shape, several times slower
- *   than the NHWC form).
+ *   outputs are not contiguous along it: the matrix-core blocks read the image
+ *   element by element, lanes along pixels (about three times the NHWC form's
+ *   time).
  *
  * deadline_ms: latency budget measured from the start of the launch.  <= 0, NaN
  *   or +inf mean "none".  It only orders the operators (earliest first, ties by

@@ -102,6 +102,8 @@ __global__ void __launch_bounds__(256, 2) lds_read_loop(int iters, f32x4 *sink) 
 // 2048 x 2048 x 2048 bf16 products (C = A . B^T, both K-contiguous) in 128 x 128 tiles that are handed out
 // statically (workgroup b takes tiles b, b + grid, ...), operands by direct global-to-LDS loads into two
 // swizzled stage images, fragments one step ahead of the 32x32x16 MFMAs, one barrier per stage.
+// (The superkernel's loop has since moved its barrier ahead of a stage's last step and unrolled over the ring, and
+// hands such products out die by die: it passes MODE 0, which is a reference for the loop alone and no upper bound.)
 // MODE 0: the whole loop.  1: no operand loads (fragment reads, MFMAs and the barrier: what LDS and the
 // matrix cores allow).  2: operand loads and barrier only (what the path from the L2s to LDS allows).
 __device__ __forceinline__ void tile_dma16(const void *gptr, uint32_t lds_addr) {
