@@ -1659,7 +1659,7 @@ __device__ __forceinline__ void run_lds_tile(const DevProblem &P, const sk_tile 
 // ---------------------------------------------------------------------------
 // (Inlined, like every path of the kernel: as real calls the two slow paths gave the kernel a stack,
 // and how well its fast paths then ran changed from build to build.  They exist only in the kernel
-// instantiations for plans with such operands: 239 to 248 registers instead of 233 to 242, about twice the code.  They
+// instantiations for plans with such operands: 235 to 242 registers instead of 232 to 240, about twice the code.  They
 // are given the records' addresses in memory rather than references to the caller's copies, and the
 // tile's own copy of the thread index (see the tile loop): taken from threadIdx, what run_tile_any derives from it was
 // hoisted out of the tile loop and cost these kernels 1 to 18 spilled vector registers and a stack.)

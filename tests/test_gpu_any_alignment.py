@@ -3,9 +3,13 @@ addressing can go wrong: runs shorter than a 16-byte piece, reduction lengths on
 one, filters wider than the image or than 32 taps, planes of an odd number of pixels over several images.  Held to
 the oracle like every other shape (gate and order-free rounding bound), and bit for bit over relaunch, order and
 per-die lists (run_all_modes)."""
+import numpy as np
 import pytest
+import torch
 
-import sk_harness as H  # noqa: F401  (the harness the modes below run on)
+import paper_1901_10008_amd as sk
+
+import sk_harness as H
 from test_gpu_parity import c, g, nchw, run_all_modes
 
 pytestmark = pytest.mark.gpu
@@ -57,3 +61,21 @@ def test_padding_whose_width_in_elements_does_not_fit_32_bits():
     """One pixel of 8193 channels in the middle of 262144 columns of padding on either side, sampled every 1024 columns."""
     run_all_modes([c(1, 1, 8193, 3, 1, 1, 0, 1 << 18, st=1024), c(1, 1, 8193, 70, 1, 1, 0, 1 << 18, "f16", st=1024),
                    nchw(1, 1, 8193, 3, 1, 1, 0, 1 << 18, st=1024), c(1, 1, 8200, 66, 1, 1, 0, 1 << 18, st=1024)], seed=43, label="wide padding")
+
+
+def test_cut_records_without_device_memory():
+    """Records that are cut (one long odd operator per type) run the same through sk_launch_static, which plans for a device it
+    does not know yet."""
+    b = H.Batch([g(300, 130, 1001), g(200, 200, 501, "f16"), g(300, 130, 501, "f32"), c(20, 20, 33, 130, 3, 3, 1, 1)], seed=44)
+    with b.plan() as plan:
+        assert sk.sk_plan_grid(plan) > sk.sk_plan_num_tiles(plan)  # more workgroups than records in the table: some are cut
+        sk.sk_launch(plan, H.stream_handle())
+        torch.cuda.synchronize()
+        H.check_against_oracle(b, "cut records")
+        bits = b.all_output_bits()
+    with b.plan(host_only=1) as plan:
+        b.reset_outputs()
+        sk.sk_launch_static(plan, H.stream_handle())
+        torch.cuda.synchronize()
+        for i, (x, y) in enumerate(zip(bits, b.all_output_bits())):
+            assert np.array_equal(x, y), f"operator {i} differs through the static scratch"
