@@ -207,6 +207,10 @@ sk_status sk_release_cached_memory(void);
  * workgroup b starts on tile b and takes further tiles through a single atomic
  * counter; a plan whose tiles are all short (at most 64 KB of operands each)
  * skips the counter and gives workgroup b the tiles b, b + grid, ...  With
+ * (Operators of one deadline, so all that have none, may start in another
+ * order than the table's, those with the longest tiles first, and long tiles
+ * may run in parts: the table is the contract of what is computed and of the
+ * deadlines' order.)  With
  * per-die lists (params.xcd_part) a position of the table that holds an LDS tile only says
  * that one LDS tile is due: the workgroup runs the next tile of its die's list
  * (sk_plan_get_xcd_lists), so operators still start in table order, and every

@@ -93,6 +93,12 @@ double deadline_key(double d) {
   return d;
 }
 
+// Partial sums of one slice of an output rectangle, in 16-byte units: 4 waves x (2 * rm) accumulators x 64 lanes (LDS tiles: 256
+// threads x 16 accumulator quads, 8 for the 64-column tile).
+int64_t slice_f32x4(uint16_t cls) {
+  return cls == CLS_TILE_128x128 ? 4096 : cls == CLS_TILE_128x64 ? 2048 : 4 * 2 * ((int64_t)1 << (cls / 3)) * 64;
+}
+
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace
@@ -411,12 +417,8 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
           out.tiles.push_back(t);
         }
         if (S > 1) {
-          // partial sums of this rectangle: S slices x 4 waves x (2 * rm) accumulators x 64 lanes, 16 bytes each
-          // (LDS tiles: S slices x 256 threads x 16 accumulator quads, 8 for the 64-column tile)
           out.ws_off.push_back((uint32_t)out.ws_f32x4);
-          out.ws_f32x4 += cls == CLS_TILE_128x128  ? S * 4096
-                          : cls == CLS_TILE_128x64 ? S * 2048
-                                                   : S * 4 * 2 * ((int64_t)1 << (cls / 3)) * 64;
+          out.ws_f32x4 += S * slice_f32x4(cls);
         } else {
           out.ws_off.push_back(0u);
         }
@@ -497,8 +499,8 @@ static RecordCost record_cost(const DevProblem &d, const sk_tile &t) {
 //     one on plans of 20 to 96 odd fp32 operators).
 // Slices of split reductions stay whole (their workspace is laid out by rectangle), and so do plans with per-die
 // lists, which name the table's records.  The sums of an output do not change.
-bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &work, std::vector<int64_t> &count) {
-  if (!hp.xorder.empty() || workgroups < 1) return false;
+static bool refine_blocks(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &work, std::vector<int64_t> &count) {
+  if (workgroups < 1) return false;
   const int32_t vec = FLAG_VEC_A | FLAG_VEC_B;
   if (std::all_of(hp.dev.begin(), hp.dev.end(), [&](const DevProblem &d) { return (d.flags & vec) == vec; })) return false;
   auto parts_of = [](const sk_tile &t) { return ((t.m_len + 63) / 64) * ((t.n_len + 63) / 64); };
@@ -578,6 +580,255 @@ bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &
   return true;
 }
 
+bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &work, std::vector<int64_t> &count) {
+  return hp.xorder.empty() && refine_blocks(hp, workgroups, work, count);
+}
+
+// What a record takes on a chip whose compute units hold two workgroups each, in nanoseconds: `start` around its steps (set-up, first
+// loads, outputs, the next record), `step` per 128 bytes of the reduction, `hand` more if it hands partial sums over.  Means of clock
+// stamps at the phase boundaries of the ResNet, BERT, stride-2 and odd-sized mixes.
+struct RecordTime {
+  int64_t start, step, hand;
+};
+static RecordTime record_time(const DevProblem &d, const sk_tile &t, bool any) {
+  const bool f32 = d.dtype == SK_F32;
+  if (any) {
+    const int64_t one = any_block_cost(d, t.m_len, t.n_len, 1).time, step = any_block_cost(d, t.m_len, t.n_len, 2).time - one;
+    return RecordTime{one - step, f32 ? step * 13 / 10 : step, 8000};
+  }
+  if (t.cls < CLS_TILE_128x128) return RecordTime{4500, f32 && t.cls >= 6 ? 2000 : 1100, 3000};
+  if (t.cls == CLS_TILE_128x64) return RecordTime{5000, f32 ? 1700 : 650, 4000};
+  return RecordTime{6000, f32 ? 3400 : 950, 5000};
+}
+
+// The table is cut by bytes and ordered by deadline; how long its records take, and that the last of them end together, is
+// settled here, for the device's list alone.  Stamped ends of the workgroups before: ResNet layers x16 41 to 78 us after the start,
+// channel-major ones x8 23 to 135, 96 odd-sized operators 11 to 128, BERT layers x8 127 to 170.
+//   * Operators of one deadline (all that have none) have no order among them that anyone asked for: those with the longest
+//     records go first, so that the launch ends on short ones.  Whole operators move, so their tiles still meet in the L2s.
+//   * A record longer than its share is cut: weight-streaming ones by columns (nothing but one more start per part; half a
+//     workgroup's share of the whole launch: LSTM cells 64 230 -> 215 us, a quarter no better; not those of
+//     operators with deadlines, which run where the table puts them and shrink towards its end: 52 mixed operators 215 -> 217), the others, if they outlast an
+//     even share by a quarter (LDS tiles of 16-bit types: twice that share, a compute unit's that runs one of them at a time: six 45x45 convolutions of
+//     256 channels 35.7 us whole, 43.7 in two slices), into slices of the reduction, of at least 16 stages (blocks of any alignment six), because a slice writes its
+//     sums to memory and the last one reads all of them (with 6 stages nine 15x15 convolutions of 256 channels 24.7 -> 32.6 us,
+//     with 16 24.5).  Weight-streaming records are not sliced any further: 16 low-batch layers 32 -> 39 us.
+//   * Nothing is cut below 14 us: 10 and 18 measure the same.
+// Before / after, us: channel-major ResNet layers x8 140 -> 96, odd-sized operators 134 -> 73, ResNet layers x16 80 -> 70, x3 34 -> 28,
+// BERT layers x8 173 -> 156, stride-2 layers x3 43 -> 33; mixes whose operators all have deadlines of their own as before.
+// Slices change the order of summation with the load of the launch, so plans without the tail rule, whose tiles may not depend on what
+// else is in the plan, get none.  Plans with per-die lists get the same slices as without (the bits of a result do not depend on who
+// runs a tile) and stay otherwise as they are.
+bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, int64_t workgroups, WorkList &out) {
+  constexpr int64_t SHORTEST = 14000;
+  if (workgroups < 1 || records.empty()) return false;
+  const bool lists = !hp.xorder.empty();
+  const int32_t vec = FLAG_VEC_A | FLAG_VEC_B;
+  // an output rectangle of the table: its records (reduction slices, or parts that refine_tiles has made), and how they are cut
+  struct Rect {
+    size_t first, count;
+    int64_t time;             // of the longest of them
+    int64_t width, S, slice;  // columns and reduction slices of a part, reduction elements per slice
+  };
+  struct Op {
+    int32_t problem;
+    size_t first, count;  // records
+    int64_t longest;
+    size_t rect, rects;  // of an operator with a record that may be cut
+  };
+  std::vector<Rect> rects;
+  std::vector<Op> ops;
+  ops.reserve(hp.dev.size());
+  auto any_of = [&](const sk_tile &t) { return runs_in_any_blocks(hp.dev[t.problem], t); };
+  auto stages_of = [&](const sk_tile &t) {
+    const int64_t kb = 128 / elem_size(hp.dev[t.problem].dtype);
+    return ((int64_t)t.k_len + kb - 1) / kb;
+  };
+  auto columns_of = [](const sk_tile &t, bool any) -> int64_t {  // blocks of 128 that a weight-streaming record walks one after the other
+    return t.cls < CLS_TILE_128x128 && !any ? (t.n_len + 127) / 128 : 1;
+  };
+  auto time_of = [&](const sk_tile &t) {
+    const bool any = any_of(t);
+    const RecordTime rt = record_time(hp.dev[t.problem], t, any);
+    return rt.start + stages_of(t) * columns_of(t, any) * rt.step + (t.S > 1 ? rt.hand : 0);
+  };
+  auto alike = [](const sk_tile &a, const sk_tile &b) { return a.m_len == b.m_len && a.n_len == b.n_len && a.k_len == b.k_len; };
+  int64_t total = 0;
+  for (size_t i = 0; i < records.size();) {
+    Op op{(int32_t)records[i].problem, i, 0, 0, 0, 0};
+    int64_t time = 0;
+    const sk_tile *timed = nullptr;  // (an operator's records are mostly alike)
+    for (; i < records.size() && records[i].problem == (uint32_t)op.problem; ++i) {
+      if (!timed || !alike(*timed, records[i])) {
+        timed = &records[i];
+        time = time_of(*timed);
+        op.longest = std::max(op.longest, time);
+      }
+      total += time;
+    }
+    op.count = i - op.first;
+    ops.push_back(op);
+  }
+  const int64_t share = total / workgroups;
+
+  bool changed = false;
+  for (Op &op : ops) {
+    if (op.longest * 10 <= std::max(SHORTEST, share / 2) * 11) continue;
+    const bool dated = hp.params.edf && std::isfinite(deadline_key(hp.problems[op.problem].deadline_ms));
+    op.rect = rects.size();
+    for (size_t i = op.first; i < op.first + op.count; ++i) {
+      const sk_tile &t = records[i];
+      if (i == op.first || t.out_tile_id != records[i - 1].out_tile_id) rects.push_back(Rect{i, 0, 0, t.n_len, t.S, t.k_len});
+      Rect &x = rects.back();
+      ++x.count;
+      x.time = std::max(x.time, time_of(t));
+      x.width = std::max<int64_t>(x.width, t.n_len);
+    }
+    op.rects = rects.size() - op.rect;
+    op.longest = 0;
+    for (size_t r = op.rect; r < op.rect + op.rects; ++r) {
+      Rect &x = rects[r];
+      const sk_tile &t = records[x.first];
+      const DevProblem &d = hp.dev[t.problem];
+      const bool any = any_of(t), stream = !any && t.cls < CLS_TILE_128x128;
+      const int64_t most = std::max<int64_t>(SHORTEST, stream ? share / 2 : any || d.dtype == SK_F32 ? share * 5 / 4 : share * 2);
+      // (up to 64 reduction elements an operator without 16-byte pieces may go the one-output-per-thread way, by the size of its record)
+      if (x.time * 10 > most * 11 && ((d.flags & vec) == vec || d.Kg > 64)) {
+        const RecordTime rt = record_time(d, t, any);
+        if (stream) {
+          const int64_t cols = columns_of(t, any);
+          if (t.S == 1 && cols > 1 && !lists && !dated) {
+            const int64_t parts = std::min(cols, (cols * stages_of(t) * rt.step + most - rt.start - 1) / (most - rt.start));
+            const int64_t wide = (cols + parts - 1) / parts;
+            x.width = wide * 128;
+            x.time = rt.start + stages_of(t) * wide * rt.step;
+            changed = changed || x.width < t.n_len;
+          }
+        } else if (hp.params.tail_div > 0 && t.m_len <= 128 && t.n_len <= 128) {
+          constexpr int64_t GRAIN = 4;  // stages
+          const int64_t kb = 128 / elem_size(d.dtype), k = t.S > 1 ? d.Kg : (int64_t)t.k_len, all = (k + kb - 1) / kb;
+          const int64_t fits = (std::max<int64_t>((most - rt.start - rt.hand) / rt.step, any ? 6 : 16) + GRAIN - 1) / GRAIN * GRAIN;
+          const int64_t want = std::min<int64_t>((all + fits - 1) / fits, 255);
+          const int64_t per = ((all + want - 1) / want + GRAIN - 1) / GRAIN * GRAIN, n = (all + per - 1) / per;
+          const int64_t time = rt.start + per * rt.step + rt.hand;
+          if (n > t.S && time * 10 < x.time * 8) {
+            x.S = n;
+            x.slice = per * kb;
+            x.time = time;
+            changed = true;
+          }
+        }
+      }
+      op.longest = std::max(op.longest, x.time);
+    }
+  }
+  if (hp.params.edf && !lists) {
+    auto before = [&](const Op &a, const Op &b) {
+      const double da = deadline_key(hp.problems[a.problem].deadline_ms), db = deadline_key(hp.problems[b.problem].deadline_ms);
+      return da != db ? da < db : a.longest > b.longest;
+    };
+    if (!std::is_sorted(ops.begin(), ops.end(), before)) {
+      std::stable_sort(ops.begin(), ops.end(), before);
+      changed = true;
+    }
+  }
+  if (!changed) return false;
+
+  out = WorkList{};
+  out.work.reserve(records.size() + records.size() / 4);
+  out.ws_off.reserve(records.size());
+  out.count.assign(hp.dev.size(), 0);
+  auto new_rect = [&](const sk_tile &t, int64_t S) {
+    out.ws_off.push_back(S > 1 ? (uint32_t)out.ws_f32x4 : 0u);
+    if (S > 1) out.ws_f32x4 += S * slice_f32x4(t.cls);
+  };
+  // records as they are
+  auto copy = [&](const std::vector<sk_tile> &from, size_t first, size_t n) {
+    const size_t at = out.work.size();
+    out.work.insert(out.work.end(), from.begin() + (int64_t)first, from.begin() + (int64_t)(first + n));
+    for (size_t i = 0; i < n; ++i) {
+      const sk_tile &t = from[first + i];
+      if (i == 0 || t.out_tile_id != from[first + i - 1].out_tile_id) new_rect(t, t.S);
+      out.work[at + i].out_tile_id = (uint32_t)out.ws_off.size() - 1u;
+    }
+    if (n) out.count[from[first].problem] += (int64_t)n;
+  };
+  // columns of t, `width` at a time, in the slices of x
+  auto emit = [&](const sk_tile &t, const Rect &x, int64_t width) {
+    const int64_t k = t.S > 1 ? hp.dev[t.problem].Kg : (int64_t)t.k_len;
+    for (int64_t n = 0; n < t.n_len; n += width) {
+      new_rect(t, x.S);
+      for (int64_t ks = 0; ks < x.S; ++ks) {
+        sk_tile u = t;
+        u.S = (uint8_t)x.S;
+        u.ks_idx = (uint8_t)ks;
+        u.k0 = (uint32_t)(ks * x.slice);
+        u.k_len = (uint32_t)std::min<int64_t>(x.slice, k - ks * x.slice);
+        u.n0 = t.n0 + (uint32_t)n;
+        u.n_len = (uint16_t)std::min<int64_t>(width, t.n_len - n);
+        u.out_tile_id = (uint32_t)out.ws_off.size() - 1u;
+        out.work.push_back(u);
+        ++out.count[t.problem];
+      }
+    }
+  };
+  if (!lists) {
+    for (const Op &op : ops) {
+      if (op.rects == 0) copy(records, op.first, op.count);
+      for (size_t r = op.rect; r < op.rect + op.rects; ++r) {
+        const Rect &x = rects[r];
+        const sk_tile &t = records[x.first];
+        if (x.S == t.S && x.width >= t.n_len)
+          copy(records, x.first, x.count);
+        else
+          for (size_t i = x.first; i < x.first + x.count; i += records[i].S) emit(records[i], x, x.width);
+      }
+    }
+  } else {
+    std::vector<uint32_t> at(hp.tiles.size() + 1);  // where a table record's slices start in the list
+    size_t i = 0;  // table record; the operators and their rectangles are in the table's order
+    for (const Op &op : ops) {
+      const size_t end = i + (size_t)hp.count[(size_t)op.problem];
+      for (size_t r = op.rect; i < end; ++r) {
+        const sk_tile &t = hp.tiles[i];
+        const Rect *x = op.rects ? &rects[r] : nullptr;
+        for (int64_t ks = 0; ks < t.S; ++ks) at[i + (size_t)ks] = (uint32_t)(out.work.size() + (x && x->S != t.S ? 0 : (size_t)ks));
+        if (x && x->S != t.S)
+          emit(t, *x, 128);  // (a slice of a record without 16-byte pieces must be a single block)
+        else
+          copy(hp.tiles, i, t.S);
+        i += t.S;
+      }
+    }
+    at[hp.tiles.size()] = (uint32_t)out.work.size();
+    for (int die = 0; die < 8; ++die) {
+      out.xoff[die] = (uint32_t)out.xorder.size();
+      for (uint32_t e = hp.xoff[die]; e < hp.xoff[die + 1]; ++e) {
+        const sk_tile &t = hp.tiles[hp.xorder[e]];
+        if (t.ks_idx != 0) continue;
+        const uint32_t from = at[hp.xorder[e]], to = at[hp.xorder[e] + t.S];
+        for (uint32_t w = from; w < to; ++w) out.xorder.push_back(w);
+      }
+    }
+    out.xoff[8] = (uint32_t)out.xorder.size();
+  }
+  return out.work.size() <= (size_t)1 << 30 && out.ws_f32x4 <= ((int64_t)1 << 31);
+}
+
+bool device_list(const HostPlan &hp, int64_t workgroups, WorkList &out) {
+  std::vector<sk_tile> cut;
+  std::vector<int64_t> count;
+  const bool refined = refine_blocks(hp, workgroups, cut, count);
+  if (balance_records(hp, refined ? cut : hp.tiles, workgroups, out)) return true;
+  if (!refined || !hp.xorder.empty()) return false;
+  out = WorkList{};
+  out.work = std::move(cut);
+  out.count = std::move(count);
+  out.ws_off = hp.ws_off;
+  out.ws_f32x4 = hp.ws_f32x4;
+  return true;
+}
+
 // Measured against the general kernel as it is now (3x3 64-channel convolutions in bf16, us, general / narrow): 25 tiles 11.4 / 10.6,
 // 100 tiles 12.4 / 11.6, 300 to 500 tiles 1 to 4 % slower; 550 to 680 tiles, which start at once in threes but not in
 // twos, 26 / 24; 750 tiles 27.3 / 28.4, 2800 tiles 59.4 / 63.3 (whole rounds of longer tiles); 4000 tiles 87.2 / 85.0, 12800 tiles 240
@@ -628,10 +879,11 @@ sk_status plan_host_each_alone(const HostPlan &whole, int64_t workgroups, HostPl
     const sk_status st = plan_host(&whole.problems[i], 1, &prm, one, err);
     if (st != SK_OK) return st;
     std::vector<int64_t> counts;
-    (void)refine_tiles(one, workgroups, one.work, counts);
+    std::vector<sk_tile> cut;
+    const std::vector<sk_tile> &records = refine_blocks(one, workgroups, cut, counts) ? cut : one.tiles;
     out.first[i] = (int64_t)out.tiles.size();
-    out.count[i] = (int64_t)one.records().size();
-    for (sk_tile t : one.records()) {
+    out.count[i] = (int64_t)records.size();
+    for (sk_tile t : records) {
       t.problem = (uint32_t)i;
       t.out_tile_id += rect_base;
       out.tiles.push_back(t);
@@ -647,6 +899,45 @@ sk_status plan_host_each_alone(const HostPlan &whole, int64_t workgroups, HostPl
     }
   }
   return SK_OK;
+}
+
+bool balance_each_alone(HostPlan &alone, int64_t workgroups) {
+  HostPlan out = alone;
+  out.tiles.clear();
+  out.ws_off.clear();
+  out.ws_f32x4 = 0;
+  bool changed = false;
+  for (size_t i = 0; i < alone.dev.size(); ++i) {
+    std::vector<sk_tile> own(alone.tiles.begin() + alone.first[i], alone.tiles.begin() + alone.first[i] + alone.count[i]);
+    WorkList w;
+    const bool cut = balance_records(alone, own, workgroups, w);
+    changed = changed || cut;
+    out.first[i] = (int64_t)out.tiles.size();
+    const uint32_t base = (uint32_t)out.ws_off.size();
+    for (sk_tile t : cut ? w.work : own) {
+      if (cut) {
+        t.out_tile_id += base;
+      } else {  // its rectangles' workspace moves as a whole
+        const uint32_t id = t.out_tile_id;
+        if (out.tiles.size() == (size_t)out.first[i] || id != own[out.tiles.size() - (size_t)out.first[i] - 1].out_tile_id) {
+          out.ws_off.push_back(t.S > 1 ? (uint32_t)out.ws_f32x4 : 0u);
+          if (t.S > 1) out.ws_f32x4 += t.S * slice_f32x4(t.cls);
+        }
+        t.out_tile_id = (uint32_t)out.ws_off.size() - 1u;
+      }
+      out.tiles.push_back(t);
+    }
+    if (cut) {
+      for (const uint32_t w_off : w.ws_off) out.ws_off.push_back(w_off + (uint32_t)out.ws_f32x4);
+      out.ws_f32x4 += w.ws_f32x4;
+    }
+    out.count[i] = (int64_t)out.tiles.size() - out.first[i];
+    out.dev[i].tile_first = (int32_t)out.first[i];
+    out.dev[i].tile_count = (int32_t)out.count[i];
+    if (out.ws_f32x4 > ((int64_t)1 << 31)) return false;
+  }
+  if (changed) alone = std::move(out);
+  return changed;
 }
 
 // A launch on the stream of the previous launch is ordered behind it by the stream.  On another stream it

@@ -83,6 +83,16 @@ struct TileWork {
 };
 static_assert(sizeof(TileWork) == 192, "TileWork layout");
 
+// The records the device runs, with output rectangles and a split-K workspace numbered for them, and the per-die lists over them.
+struct WorkList {
+  std::vector<sk_tile> work;
+  std::vector<int64_t> count;    // per operator
+  std::vector<uint32_t> ws_off;  // per output rectangle
+  int64_t ws_f32x4 = 0;
+  std::vector<uint32_t> xorder;
+  uint32_t xoff[9] = {};
+};
+
 struct HostPlan {
   std::vector<sk_problem> problems;
   std::vector<DevProblem> dev;
@@ -97,11 +107,14 @@ struct HostPlan {
   uint32_t xoff[9] = {};
   sk_plan_params params;
   int64_t target_tile_bytes = 0;
-  // what the device runs in place of the table (see refine_tiles); empty: the table itself
-  std::vector<sk_tile> work;
-  std::vector<int64_t> work_count;  // records per operator
-  const std::vector<sk_tile> &records() const { return work.empty() ? tiles : work; }
-  int64_t record_count(size_t i) const { return work.empty() ? count[i] : work_count[i]; }
+  // what the device runs in place of the table (see device_list); without records: the table itself
+  WorkList run;
+  const std::vector<sk_tile> &records() const { return run.work.empty() ? tiles : run.work; }
+  int64_t record_count(size_t i) const { return run.work.empty() ? count[i] : run.count[i]; }
+  const std::vector<uint32_t> &rect_off() const { return run.work.empty() ? ws_off : run.ws_off; }
+  int64_t ws_units() const { return run.work.empty() ? ws_f32x4 : run.ws_f32x4; }
+  const std::vector<uint32_t> &die_order() const { return run.work.empty() ? xorder : run.xorder; }
+  const uint32_t *die_offsets() const { return run.work.empty() ? xoff : run.xoff; }
 };
 
 // Pure host planning (no HIP call).  Returns SK_OK or an error with `err` set.
@@ -112,6 +125,14 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
 // pieces that the launch would wait for are cut into parts of 64 x 64 outputs (`work`; `count` of them per operator; false
 // and untouched if nothing is to be cut).
 bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &work, std::vector<int64_t> &count);
+
+// `records` (the table's, or what refine_tiles makes of them) once more, for a launch of that many workgroups: long records cut, operators
+// of one deadline the longest first (false: nothing to change).
+bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, int64_t workgroups, WorkList &out);
+// What the device runs in place of the plan's table: both of these (false: the table itself).
+bool device_list(const HostPlan &hp, int64_t workgroups, WorkList &out);
+// balance_records for every operator of the baseline's tables (plan_host_each_alone), each a launch of its own; false: nothing changed.
+bool balance_each_alone(HostPlan &alone, int64_t workgroups);
 
 // Whether every tile of the plan, and of each of its operators planned alone, is a 128 x 64 LDS tile whose operands can
 // be read through 32-bit descriptors (the device's lean_operands, for the whole operator instead of tile by tile).

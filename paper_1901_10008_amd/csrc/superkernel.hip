@@ -296,27 +296,27 @@ struct TableLayout {
 };
 
 TableLayout layout_of(const sk::HostPlan &hp) {
-  const size_t nt = hp.records().size(), np = hp.dev.size(), nrect = hp.ws_off.size();
+  const size_t nt = hp.records().size(), np = hp.dev.size(), nrect = hp.rect_off().size();
   TableLayout l;
   l.off_work = 0;
   l.off_xwork = align_up(l.off_work + nt * sizeof(sk::TileWork), 256);
-  l.off_xoff = align_up(l.off_xwork + hp.xorder.size() * sizeof(sk::TileWork), 256);
+  l.off_xoff = align_up(l.off_xwork + hp.die_order().size() * sizeof(sk::TileWork), 256);
   l.off_cnt = align_up(l.off_xoff + 9 * sizeof(uint32_t), 256);
   l.off_rem = align_up(l.off_cnt + sk::QUEUE_COUNTERS * sizeof(uint32_t), 256);
   l.off_stamps = align_up(l.off_rem + np * sizeof(uint32_t), 256);
   l.off_wsoff = align_up(l.off_stamps + (np + 1) * sizeof(uint64_t), 256);
   l.off_arrive = align_up(l.off_wsoff + nrect * sizeof(uint32_t), 256);
   l.upload = align_up(l.off_arrive + nrect * sizeof(uint32_t), 256);
-  l.total = l.upload + (size_t)hp.ws_f32x4 * 16;
+  l.total = l.upload + (size_t)hp.ws_units() * 16;
   return l;
 }
 
 // The host image of the uploaded part: work records, zeroed counters and stamps, countdowns, offsets.
 void fill_image(const sk::HostPlan &hp, const TableLayout &l, char *stage) {
-  const size_t nt = hp.records().size(), np = hp.dev.size(), nrect = hp.ws_off.size();
+  const size_t nt = hp.records().size(), np = hp.dev.size(), nrect = hp.rect_off().size();
   // the work records are written in full below; everything behind them starts at zero
   std::memset(stage + nt * sizeof(sk::TileWork), 0, l.upload - nt * sizeof(sk::TileWork));
-  if (nrect) std::memcpy(&stage[l.off_wsoff], hp.ws_off.data(), nrect * sizeof(uint32_t));
+  if (nrect) std::memcpy(&stage[l.off_wsoff], hp.rect_off().data(), nrect * sizeof(uint32_t));
   for (size_t i = 0; i < nt; ++i) {
     sk::TileWork w;
     std::memset(&w, 0, sizeof(w));
@@ -325,10 +325,10 @@ void fill_image(const sk::HostPlan &hp, const TableLayout &l, char *stage) {
     w.prob.tile_count = (int32_t)hp.record_count(w.tile.problem);
     std::memcpy(&stage[l.off_work + i * sizeof(w)], &w, sizeof(w));
   }
-  for (size_t i = 0; i < hp.xorder.size(); ++i)
-    std::memcpy(&stage[l.off_xwork + i * sizeof(sk::TileWork)], &stage[l.off_work + hp.xorder[i] * sizeof(sk::TileWork)],
+  for (size_t i = 0; i < hp.die_order().size(); ++i)
+    std::memcpy(&stage[l.off_xwork + i * sizeof(sk::TileWork)], &stage[l.off_work + hp.die_order()[i] * sizeof(sk::TileWork)],
                 sizeof(sk::TileWork));
-  std::memcpy(&stage[l.off_xoff], hp.xoff, sizeof(hp.xoff));
+  std::memcpy(&stage[l.off_xoff], hp.die_offsets(), 9 * sizeof(uint32_t));
   for (size_t i = 0; i < np; ++i) {
     const uint32_t c = (uint32_t)hp.record_count(i);
     std::memcpy(&stage[l.off_rem + i * sizeof(uint32_t)], &c, sizeof(c));
@@ -372,10 +372,11 @@ sk_status upload_tables(const sk::HostPlan &hp, int device, DeviceTables &dt) {
 // Compute units of an MI355X, for plans that are made before their device is known (host-only ones).
 constexpr int COMPUTE_UNITS = 256;
 
-// What the device runs in place of the table, in a launch of that many workgroups.
-sk_status refine(sk::HostPlan &hp, int64_t workgroups) {
+// What the device runs in place of the table, in a launch of that many workgroups.  (The tiles of a narrow plan are short and alike.)
+sk_status refine(sk::HostPlan &hp, int64_t workgroups, bool narrow) {
   try {
-    (void)sk::refine_tiles(hp, workgroups, hp.work, hp.work_count);
+    sk::WorkList w;
+    if (!narrow && sk::device_list(hp, workgroups, w)) hp.run = std::move(w);
   } catch (const std::bad_alloc &) {
     return set_error(SK_ERR_ALLOC, "host allocation failed while planning");
   }
@@ -427,12 +428,12 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
   }
   if (prm.host_only && !plan->host.tiles.empty()) {
     plan->cus = COMPUTE_UNITS;
-    st = refine(plan->host, plan->most_workgroups((int64_t)plan->host.tiles.size()));
+    st = refine(plan->host, plan->most_workgroups((int64_t)plan->host.tiles.size()), plan->narrow);
     if (st != SK_OK) {
       delete plan;
       return st;
     }
-    if (layout_of(plan->host).total > STATIC_SCRATCH_BYTES) plan->host.work.clear();  // (the table itself may still fit)
+    if (layout_of(plan->host).total > STATIC_SCRATCH_BYTES) plan->host.run = sk::WorkList{};  // (the table itself may still fit)
     const TableLayout l = layout_of(plan->host);
     if (l.total <= STATIC_SCRATCH_BYTES) {  // (larger plans cannot use sk_launch_static anyway)
       try {
@@ -459,7 +460,7 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
     }
     plan->ticks_per_ms = (double)clock_khz;
     const int64_t limit = plan->most_workgroups((int64_t)plan->host.tiles.size());
-    st = refine(plan->host, limit);
+    st = refine(plan->host, limit, plan->narrow);
     if (st != SK_OK) {
       delete plan;
       return st;
@@ -651,6 +652,7 @@ sk_status sk_launch_sequential(sk_plan *plan, void *hip_stream) {
     std::string err;
     try {
       st = sk::plan_host_each_alone(plan->host, plan->most_workgroups(1), plan->seq_host, err);
+      if (st == SK_OK && !plan->narrow) (void)sk::balance_each_alone(plan->seq_host, plan->most_workgroups(1));
     } catch (const std::bad_alloc &) {
       return set_error(SK_ERR_ALLOC, "host allocation failed while planning");
     }

@@ -1,0 +1,161 @@
+// Host-only driver for the device's work list under AddressSanitizer / UndefinedBehaviorSanitizer: on seeded random operator lists,
+// the list made for a launch must cover every output rectangle of the table once (parts that tile it, slices that tile the
+// reduction, the same whatever the per-die lists), keep deadlines in order, give every rectangle with slices a workspace of its
+// own, and name every LDS tile in the per-die lists once.
+#include <algorithm>
+#include <cmath>
+#include <cstdio>
+#include <map>
+#include <random>
+#include <string>
+#include <tuple>
+#include <vector>
+
+#include "sk_internal.h"
+
+static int fail(const char *what, int seed) {
+  std::fprintf(stderr, "work_list_driver: %s (seed %d)\n", what, seed);
+  return 1;
+}
+
+using Slices = std::vector<std::pair<uint32_t, uint32_t>>;  // k0, k_len
+
+// The list against the table: 0, or a message.  `slices`: of every output column block of every operator.
+static const char *check(const sk::HostPlan &hp, const sk::WorkList &w, std::map<std::tuple<uint32_t, uint32_t, uint32_t>, Slices> &slices) {
+  std::vector<int64_t> count(hp.dev.size(), 0), area(hp.dev.size(), 0);
+  std::vector<std::pair<int64_t, int64_t>> used;
+  for (size_t i = 0; i < w.work.size(); ++i) {
+    const sk_tile &t = w.work[i];
+    const sk::DevProblem &d = hp.dev[t.problem];
+    if (t.m_len < 1 || t.n_len < 1 || t.k_len < 1 || (int64_t)t.m0 + t.m_len > d.Mg || (int64_t)t.n0 + t.n_len > d.Ng ||
+        (int64_t)t.k0 + t.k_len > d.Kg || t.ks_idx >= t.S || t.out_tile_id >= w.ws_off.size())
+      return "record leaves its operator";
+    ++count[t.problem];
+    if (t.ks_idx != 0) {
+      const sk_tile &b = w.work[i - 1];
+      if (b.problem != t.problem || b.out_tile_id != t.out_tile_id || b.ks_idx + 1 != t.ks_idx || b.k0 + b.k_len != t.k0 || b.m0 != t.m0 ||
+          b.n0 != t.n0 || b.m_len != t.m_len || b.n_len != t.n_len || b.S != t.S)
+        return "slices that do not follow one another";
+    } else {
+      if (t.k0 != 0) return "the first slice starts late";
+      area[t.problem] += (int64_t)t.m_len * t.n_len;
+      if (t.S > 1) {
+        const int64_t size = t.cls == sk::CLS_TILE_128x128 ? 4096 : t.cls == sk::CLS_TILE_128x64 ? 2048 : 512 << (t.cls / 3);
+        used.emplace_back(w.ws_off[t.out_tile_id], w.ws_off[t.out_tile_id] + size * t.S);
+        if (t.n_len > 128 || t.m_len > 128) return "slices of more than one block";
+      }
+    }
+    if (t.ks_idx + 1 == t.S && (int64_t)t.k0 + t.k_len != d.Kg) return "the last slice ends early";
+    for (uint32_t m = t.m0 / 64; m <= (t.m0 + t.m_len - 1) / 64; ++m)
+      for (uint32_t n = t.n0 / 32; n <= (t.n0 + t.n_len - 1) / 32; ++n) slices[{t.problem, m, n}].emplace_back(t.k0, t.k_len);
+  }
+  if (count != w.count) return "records per operator";
+  for (size_t i = 0; i < hp.dev.size(); ++i)
+    if (area[i] != (int64_t)hp.dev[i].Mg * hp.dev[i].Ng) return "outputs missing or made twice";
+  std::sort(used.begin(), used.end());
+  for (size_t i = 0; i < used.size(); ++i)
+    if (used[i].second > w.ws_f32x4 || (i && used[i].first < used[i - 1].second)) return "workspaces overlap";
+  if (hp.xorder.empty()) return w.xorder.empty() ? nullptr : "lists of a plan without";
+  std::vector<int> named(w.work.size(), 0);
+  for (uint32_t e : w.xorder) {
+    if (e >= w.work.size()) return "an entry of a list names no record";
+    ++named[e];
+  }
+  for (size_t i = 0; i < w.work.size(); ++i)
+    if (named[i] != (w.work[i].cls >= sk::CLS_TILE_128x128 ? 1 : 0)) return "an LDS tile that no list, or more than one, names";
+  return w.xoff[8] == w.xorder.size() ? nullptr : "offsets of the lists";
+}
+
+int main() {
+  int cut = 0, sliced = 0, moved = 0;
+  for (int seed = 0; seed < 400; ++seed) {
+    std::mt19937 g(seed);
+    auto pick = [&](std::initializer_list<int> v) { return *(v.begin() + g() % v.size()); };
+    const int n = 1 + (int)(g() % 30);
+    std::vector<sk_problem> ps((size_t)n);
+    uintptr_t addr = 0x10000000;
+    for (sk_problem &p : ps) {
+      p = sk_problem{};
+      p.dtype = pick({SK_F32, SK_BF16, SK_F16});
+      if (g() % 2) {
+        p.op = SK_GEMM, p.M = pick({1, 16, 33, 64, 65, 129, 300}), p.N = pick({5, 64, 129, 500, 4100}), p.K = pick({40, 64, 129, 1001, 4096, 9001});
+      } else {
+        p.op = g() % 2 ? SK_CONV2D_NHWC : SK_CONV2D_NCHW, p.Nb = pick({1, 3}), p.H = p.Wd = pick({7, 14, 30}), p.Cin = pick({3, 9, 64, 256});
+        p.Cout = pick({20, 64, 200}), p.R = p.S = pick({1, 3}), p.pad_h = p.pad_w = p.R / 2, p.stride = pick({1, 2});
+      }
+      p.deadline_ms = pick({0, 0, 0, 1, 2});
+      p.A = (const void *)addr, p.B = (const void *)(addr + (1u << 28)), p.C = (void *)(addr + (2u << 28));
+      addr += (uintptr_t)3 << 28;
+    }
+    sk_plan_params prm;
+    sk_plan_params_default(&prm);
+    prm.host_only = 1;
+    prm.edf = g() % 4 != 0;
+    prm.tail_div = g() % 4 ? 384 : 0;
+    prm.tile_bytes_min = pick({4096, 32768});
+    const int64_t wgs = pick({1, 60, 512, 512});
+    std::map<std::tuple<uint32_t, uint32_t, uint32_t>, Slices> plain;
+    for (int part : {0, 4}) {
+      prm.xcd_part = part;
+      sk::HostPlan hp;
+      std::string err;
+      if (sk::plan_host(ps.data(), n, &prm, hp, err) != SK_OK) return fail(err.c_str(), seed);
+      sk::WorkList w;
+      if (!sk::device_list(hp, wgs, w)) {  // the table itself
+        w.work = hp.tiles, w.count = hp.count, w.ws_off = hp.ws_off, w.ws_f32x4 = hp.ws_f32x4, w.xorder = hp.xorder;
+        std::copy(std::begin(hp.xoff), std::end(hp.xoff), std::begin(w.xoff));
+      } else if (part == 0) {
+        ++cut;
+      }
+      std::map<std::tuple<uint32_t, uint32_t, uint32_t>, Slices> slices;
+      if (const char *what = check(hp, w, slices)) return fail(what, seed);
+      size_t before = 0;
+      for (size_t i = 1; i < w.work.size(); ++i) {
+        const uint32_t a = w.work[i - 1].problem, b = w.work[i].problem;
+        if (a == b) continue;
+        if (++before >= hp.dev.size()) return fail("an operator's records are not together", seed);
+        auto key = [&](uint32_t p) { return ps[p].deadline_ms > 0 ? ps[p].deadline_ms : INFINITY; };
+        if (prm.edf ? key(a) > key(b) : a > b) return fail("deadlines out of order", seed);
+        if (a > b && key(a) == key(b)) ++moved;
+      }
+      if (prm.tail_div == 0)
+        for (const sk_tile &t : w.work)
+          if (t.S != hp.tiles[(size_t)hp.first[t.problem]].S) return fail("slices without the tail rule", seed);
+      if (part == 0) {
+        plain = slices;
+        for (const sk_tile &t : w.work) sliced += t.S != hp.tiles[(size_t)hp.first[t.problem]].S;
+        // the baseline: an operator by itself gets the slices of a plan of that operator
+        sk::HostPlan alone;
+        if (sk::plan_host_each_alone(hp, wgs, alone, err) != SK_OK) return fail("plan_host_each_alone", seed);
+        (void)sk::balance_each_alone(alone, wgs);
+        for (int i = 0; i < n; ++i) {
+          sk::HostPlan one;
+          sk::WorkList o;
+          if (sk::plan_host(&ps[(size_t)i], 1, &prm, one, err) != SK_OK) return fail("plan_host", seed);
+          const std::vector<sk_tile> &want = sk::device_list(one, wgs, o) ? o.work : one.tiles;
+          if ((int64_t)want.size() != alone.count[(size_t)i]) return fail("records of an operator alone", seed);
+          for (size_t k = 0; k < want.size(); ++k) {
+            const sk_tile &a = want[k], &b = alone.tiles[(size_t)alone.first[(size_t)i] + k];
+            if (b.problem != (uint32_t)i || a.m0 != b.m0 || a.n0 != b.n0 || a.m_len != b.m_len || a.n_len != b.n_len || a.k0 != b.k0 ||
+                a.k_len != b.k_len || a.S != b.S || a.ks_idx != b.ks_idx)
+              return fail("a record of an operator alone", seed);
+          }
+        }
+        sk::WorkList all;
+        all.work = alone.tiles, all.count = alone.count, all.ws_off = alone.ws_off, all.ws_f32x4 = alone.ws_f32x4;
+        std::map<std::tuple<uint32_t, uint32_t, uint32_t>, Slices> ignored;
+        if (const char *what = check(hp, all, ignored)) return fail(what, seed);
+      } else {
+        for (const auto &s : slices) {
+          Slices a = s.second, b = plain[s.first];
+          std::sort(a.begin(), a.end()), std::sort(b.begin(), b.end());
+          a.erase(std::unique(a.begin(), a.end()), a.end()), b.erase(std::unique(b.begin(), b.end()), b.end());
+          if (a != b) return fail("the per-die lists change the slices", seed);
+        }
+      }
+    }
+  }
+  if (cut < 100 || sliced < 100 || moved < 100) return fail("too few plans with a list of their own", cut);
+  std::puts("work_list_driver: ok");
+  return 0;
+}
