@@ -1,5 +1,6 @@
 // C ABI of the superkernel library: plan upload, the one-launch superkernel and
 // the one-launch-per-operator baseline (Sections 4.1, 5.1 and 5.3 of the paper).
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -535,8 +536,9 @@ sk_status sk_release_cached_memory(void) {
   return SK_OK;
 }
 
+// `behind`: an event to complete with the launch (null: none).
 static sk_status launch_range(sk_plan *plan, const DeviceTables &dt, hipStream_t stream, uint32_t begin, uint32_t end,
-                              int grid, bool dynamic, bool write_start, bool whole_table = false) {
+                              int grid, bool dynamic, bool write_start, bool whole_table = false, hipEvent_t behind = nullptr) {
   if (end <= begin || grid <= 0) return SK_OK;
   sk::KernelArgs a;
   // the per-die lists cover the LDS tiles of the whole table, and only the queue hands them out
@@ -577,7 +579,14 @@ static sk_status launch_range(sk_plan *plan, const DeviceTables &dt, hipStream_t
       default: kernel = sk::sk_superkernel<-1, false, false>; break;
     }
   }
-  hipLaunchKernelGGL(kernel, g, b, 0, stream, dt.work, a);
+  // The event is the launch's own completion signal.  Recorded behind the launch, as a packet of its own with a flush of its own, it
+  // held up whatever came next in the stream: four small fp32 layers, launch after launch, 13.0 us a launch, 11.0 so, and an event
+  // that the caller records behind a single launch completes 2.4 us earlier.  (A device-wide wait right behind a single
+  // launch returns 2 us later: it then needs that packet itself.)
+  if (behind)
+    hipExtLaunchKernelGGL(kernel, g, b, 0, stream, nullptr, behind, 0, dt.work, a);
+  else
+    hipLaunchKernelGGL(kernel, g, b, 0, stream, dt.work, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error("kernel launch", e);
   return SK_OK;
@@ -599,15 +608,15 @@ static sk_status admit_launch(sk_plan *plan, hipStream_t stream, bool *capturing
   return SK_OK;
 }
 
-// Records the event that the next launch on another stream and sk_plan_destroy look at.
-static void note_launch(sk_plan *plan, hipStream_t stream, bool capturing) {
-  bool recorded = false;
-  if (!capturing) {
-    if (!plan->last_use && hipEventCreateWithFlags(&plan->last_use, hipEventDisableTiming) != hipSuccess)
-      plan->last_use = nullptr;
-    recorded = plan->last_use && hipEventRecord(plan->last_use, stream) == hipSuccess;
+// The event that the next launch on another stream and sk_plan_destroy look at, for the launch about to be made (null inside a stream
+// capture, or if there is none to be had: then the ledger covers the launch device-wide).
+static hipEvent_t launch_event(sk_plan *plan, bool capturing) {
+  if (capturing) return nullptr;
+  if (!plan->last_use && hipEventCreateWithFlags(&plan->last_use, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
+    plan->last_use = nullptr;
   }
-  plan->ledger.after_launch((uintptr_t)stream, capturing, recorded);
+  return plan->last_use;
 }
 
 // Ahead of a stamped launch: the start stamp is a running minimum over the workgroups' first clocks.
@@ -639,9 +648,10 @@ sk_status sk_launch(sk_plan *plan, void *hip_stream) {
   if (st != SK_OK) return st;
   st = arm_start_stamp(plan, stream);
   if (st != SK_OK) return st;
+  const hipEvent_t behind = launch_event(plan, capturing);
   st = launch_range(plan, plan->dev, stream, 0u, (uint32_t)plan->host.records().size(), plan->grid,
-                    !plan->fixed_assignment, true, true);
-  note_launch(plan, stream, capturing);
+                    !plan->fixed_assignment, true, true, behind);
+  plan->ledger.after_launch((uintptr_t)stream, capturing, behind && st == SK_OK);
   return st;
 }
 
@@ -669,13 +679,15 @@ sk_status sk_launch_sequential(sk_plan *plan, void *hip_stream) {
   if (st != SK_OK) return st;
   st = arm_start_stamp(plan, stream);
   if (st != SK_OK) return st;
+  const hipEvent_t behind = launch_event(plan, capturing);
   for (size_t i = 0; i < n && st == SK_OK; ++i) {
     const int64_t first = plan->seq_host.first[i], count = plan->seq_host.count[i];
     const int64_t limit = plan->most_workgroups(count);
     const int grid = (int)(count < limit ? count : limit);
-    st = launch_range(plan, plan->seq_dev, stream, (uint32_t)first, (uint32_t)(first + count), grid, false, i == 0);
+    st = launch_range(plan, plan->seq_dev, stream, (uint32_t)first, (uint32_t)(first + count), grid, false, i == 0, false,
+                      i + 1 == n ? behind : nullptr);
   }
-  note_launch(plan, stream, capturing);  // also after a failure: some launches may be out
+  plan->ledger.after_launch((uintptr_t)stream, capturing, behind && st == SK_OK);  // also after a failure: some launches may be out
   return st;
 }
 
