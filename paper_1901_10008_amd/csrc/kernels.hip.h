@@ -26,6 +26,8 @@
 //     pieces are read at any address and shifted into place (images in channel
 //     planes: element by element, lanes along pixels) for larger ones; only in
 //     the kernel instantiations for plans that need them.
+//   * 3x3 convolutions of 64 channels in plans that fill the chip (run_window): weights in registers, pixels through a
+//     ring in LDS, every pixel read once for its nine taps.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -1029,7 +1031,7 @@ __device__ __forceinline__ void finish_tile(const DevProblem &P, const sk_tile &
     const int n = n0 + pc * CE;
     // 32-bit offsets from the tile's corner; rows past the edge lie outside the descriptor and are not stored
     const int64_t extent = ((int64_t)((int)T.m_len - 1) * P.ldc + (int)T.n_len) * ES;
-    if (n + CE <= n_end && 256 * P.ldc * ES < (int64_t)1 << 31) {
+    if (n + CE <= n_end && (uint64_t)(256 * P.ldc * ES) >> 31 == 0) {
       const __amdgpu_buffer_rsrc_t desc = __builtin_amdgcn_make_buffer_rsrc(
           (void *)((uintptr_t)P.C + (uintptr_t)(((int64_t)m0 * P.ldc + n0) * ES)), 0, (int)extent, 0x00020000);
       const uint32_t ld = (uint32_t)(P.ldc * ES), voff = (uint32_t)pr * ld + (uint32_t)pc * 16u;
@@ -1285,7 +1287,9 @@ template <int ES>
 __device__ __forceinline__ bool lean_operands(const DevProblem &P, const sk_tile &T, LeanOperands &L) {
   constexpr int CE = 16 / ES;
   constexpr int KB = 8 * CE;
-  constexpr int64_t LIMIT = ((int64_t)1 << 31) - 4096;  // (with DMA_FRONT added still below 2^31)
+  // (with DMA_FRONT added still below 2^31; the extents are compared with it by shifts, which are scalar: the 64-bit comparisons' constants
+  // were kept in vector registers over the whole tile loop)
+  constexpr int64_t LIMIT = ((int64_t)1 << 31) - 4096;
   const int64_t extB = ((int64_t)((int)T.n_len - 1) * P.ldb + P.Kg) * ES;
   L.baseB = (uintptr_t)P.B + (uintptr_t)((int64_t)T.n0 * P.ldb * ES);
   L.extB = (uint32_t)extB;
@@ -1293,7 +1297,7 @@ __device__ __forceinline__ bool lean_operands(const DevProblem &P, const sk_tile
     const int64_t extA = ((int64_t)((int)T.m_len - 1) * P.lda + P.Kg) * ES;
     L.originA = (int64_t)T.m0 * P.lda;
     L.extA = (uint32_t)extA;
-    if (extA >= LIMIT) return false;
+    if ((uint64_t)(extA + 4096) >> 31) return false;
   } else {
     if (P.nchw || P.Cin % KB != 0 || P.R * P.S > 31) return false;
     // From the corner of the padded first image of the tile.  The scalar offset of a late tap can lie beyond the array's end
@@ -1307,7 +1311,7 @@ __device__ __forceinline__ bool lean_operands(const DevProblem &P, const sk_tile
     if (!offsets_below(P, b1 - b0, ES, LIMIT)) return false;
   }
   L.baseA = (uintptr_t)P.A + (uintptr_t)(L.originA * ES);
-  return extB < LIMIT;
+  return (uint64_t)(extB + 4096) >> 31 == 0;
 }
 
 // The operand pieces never pass through registers: a buffer load with the LDS modifier writes the 16
@@ -1646,6 +1650,201 @@ __device__ __forceinline__ void run_lds_tile(const DevProblem &P, const sk_tile 
   }
   // (the host lets only operators into a narrow plan for which every tile is lean)
   if constexpr (!NARROW) run_tile<DT, BM, BN, 2, 2>(P, T, sp, lds, s_flag, pf);
+}
+
+// ---------------------------------------------------------------------------
+// 3x3 convolutions of 64 channels with their weights in registers
+// ---------------------------------------------------------------------------
+// Size-keeping 3x3 NHWC convolutions of 64 channels (16-bit: a pixel is one 128-byte row) into at most 64.  As tiles they spend
+// most on bringing every pixel nine times, and the same weights for every tile, from the L2 into LDS and from LDS into registers, with a
+// barrier per 24 KB, and on the tiles' ends.  Here a record is a run of an operator's output pixels (window_records), and:
+//   * a wave makes 64 pixels x 32 channels at a time and holds its 32 x 576 weights in 144 registers for the whole record;
+//   * pixels pass through a ring of three blocks of 128 in LDS, each read once; the nine taps are nine places in
+//     the ring (a tap outside the image reads a row of zeros instead: one bit per pixel and tap);
+//   * one barrier per 128 pixels (72 MFMAs a wave): the block read next has landed, the one before last is free;
+//   * a step's outputs are staged by the wave itself and stored at the next step's top, so that the wait there is for loads and stores a
+//     whole step old; past the caches, which leaves room there for the pixels (2 to 5 %).
+// The sums are taken in the tiles' order: the same bits.
+// 512 tenants of 56x56, 64 to 64 (0.45 GB, 118 GFLOP), every launch on other operands: 214 to 230 us in the kernel for tiles
+// alone, 132 here: 3.4 TB/s of operands and outputs against the 4.8 of a large copy.  Without its MFMAs it takes 107, without its
+// fragment reads 120, without storing the outputs 112 (of 130, operands the same every time): bound by memory, with the
+// MFMAs (46 % of the cycles) not quite beside it.  Fragments two or three steps ahead measure the same.
+constexpr int NONTEMPORAL = 2;                         // of a buffer store
+constexpr int WIN_BLOCK = 128;                          // pixels per step and ring block
+constexpr int WIN_RING = 3 * WIN_BLOCK;                 // pixels in the ring
+constexpr int WIN_OROW = 80;                            // bytes of 32 outputs in LDS, padded
+constexpr int WIN_OUT = WIN_RING * 128;                 // where the waves' outputs are staged
+constexpr int WIN_ZERO = WIN_OUT + 4 * 64 * WIN_OROW;   // the row of zeros
+static_assert(WIN_ZERO + 128 <= LDS_TILE_BYTES, "the ring, the outputs and the row of zeros do not fit the LDS buffer");
+static_assert(WIN_ZERO % 128 == 0, "places in the row of zeros are told apart by the low seven bits");
+
+// Four times 8 pixels side by side, of a wave, to LDS: lane i brings 16 bytes of pixel i / 8.
+__device__ __forceinline__ void dma_pixels(__amdgpu_buffer_rsrc_t desc, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3, uint32_t lds_addr) {
+  // (the instruction's own offset counts in memory and in LDS; for the wait states see dma_stage)
+  asm volatile("s_nop 4\n\t"
+               "buffer_load_dwordx4 %0, %4, 0 offen lds\n\t"
+               "buffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\t"
+               "buffer_load_dwordx4 %2, %4, 0 offen offset:2048 lds\n\t"
+               "buffer_load_dwordx4 %3, %4, 0 offen offset:3072 lds"
+               :
+               : "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(desc), "{m0}"(lds_addr)
+               : "memory");
+}
+
+template <int DT>
+__device__ __forceinline__ void run_window(const DevProblem &P, const sk_tile &T, unsigned char *lds, Prefetch &pf) {
+  constexpr uint32_t NOWHERE = 0x80000000u;
+  const int tid = pf.tid;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wm = wave & 1, wn = wave >> 1, l32 = lane & 31, half = lane >> 5;
+  const int m0 = (int)T.m0, m_len = (int)T.m_len;
+  const int steps = (m_len + WIN_BLOCK - 1) / WIN_BLOCK;
+  const int halo = P.W + 1;  // ring pixel 0 is output pixel m0's tap (0, 0)
+  const int pixels = m_len + 2 * halo;  // that any tap of the record names
+
+  // ---- the ring's blocks: pixels m0 - halo + 128 b + (0 .. 127); outside the operand: zeros ----
+  const int64_t first = (int64_t)m0 - halo;
+  const int64_t have = (int64_t)P.Mg - first;  // (a size-keeping convolution has as many pixels as outputs)
+  const __amdgpu_buffer_rsrc_t desc = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)((uintptr_t)P.A + (uintptr_t)(first * 128)), 0, (int)((have < pixels ? have : (int64_t)pixels) * 128), 0x00020000);
+  const int before = first < 0 ? (int)-first : 0;  // pixels of block 0 in front of the operand (at most halo)
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
+  // (what only a step's ends need is worked out there, from a copy of the lane index the compiler cannot see through: kept over the
+  // MFMAs beside the weights it would not fit the registers)
+  auto lane_again = [&]() {
+    int l = lane;
+    asm volatile("" : "+v"(l));
+    return l;
+  };
+  // instruction i of this wave: pixels 32 wave + 8 i + lane / 8 of the block; position p of ring row r holds piece p ^ ((r >> 1) & 7)
+  auto load_block = [&](int b, int slot) {
+    const int l = lane_again(), row = 32 * wave + (l >> 3);
+    const uint32_t at = (uint32_t)(b * WIN_BLOCK + row) * 128u, piece = (uint32_t)((l & 7) ^ (l >> 4)) * 16u;
+    uint32_t v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = b == 0 && row + 8 * i < before ? NOWHERE : at + (piece ^ (uint32_t)(i & 1) * 64u);
+    dma_pixels(desc, v[0], v[1], v[2], v[3], lds_base + (uint32_t)slot * (WIN_BLOCK * 128u) + (uint32_t)wave * 4096u);
+  };
+  const int blocks = (pixels + WIN_BLOCK - 1) / WIN_BLOCK;
+  if (tid < 8) ((u32x4 *)(lds + WIN_ZERO))[tid] = u32x4{0u, 0u, 0u, 0u};
+  load_block(0, 0);
+  if (blocks > 1) load_block(1, 1);
+
+  // ---- the weights: piece 2 kk + half of tap t of this lane's output channel ----
+  u32x4 w[9][4];
+  {
+    int n = 32 * wn + l32;
+    if (n >= P.Ng) n = P.Ng - 1;  // (never stored)
+    const u32x4 SK_GLOBAL *src = as_global<u32x4>((const void *)((uintptr_t)P.B + (uintptr_t)n * (576 * 2))) + half;
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) w[t][kk] = src[t * 8 + 2 * kk];
+  }
+
+  __builtin_amdgcn_s_waitcnt(0);  // (the builtin: the compiler, too, takes the weights as arrived and waits for nothing in the loop)
+
+  unsigned char *out = lds + WIN_OUT + wave * (64 * WIN_OROW);
+  const __amdgpu_buffer_rsrc_t descC = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)((uintptr_t)P.C + (uintptr_t)((int64_t)m0 * P.Ng * 2)), 0, m_len * P.Ng * 2, 0x00020000);
+  // a step's outputs, staged by the wave itself: 64 rows of 64 bytes (rows past the record's end lie outside the descriptor)
+  auto store_step = [&](int i) {
+    const int l = lane_again(), r = l >> 2, n = 32 * wn + (l & 3) * 8;
+    u32x4 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = *(const u32x4 *)(out + (r + 16 * q) * WIN_OROW + (l & 3) * 16);
+    const uint32_t at = n < P.Ng ? (uint32_t)(((i * WIN_BLOCK + 64 * wm + r) * P.Ng + n) * 2) : NOWHERE;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) __builtin_amdgcn_raw_buffer_store_b128(v[q], descC, at + (uint32_t)(q * 16 * P.Ng * 2), 0, NONTEMPORAL);
+  };
+
+  // this lane's two pixels of a step, counted within their image, and how far these move from one step to the next
+  const int hw = P.Ho * P.Wo;
+  int rem[2];
+#pragma unroll
+  for (int f = 0; f < 2; ++f) {
+    const int m = m0 + 64 * wm + 32 * f + l32;
+    rem[f] = m - fast_div(m, P.div_hw) * hw;
+  }
+  const int by = WIN_BLOCK - fast_div(WIN_BLOCK, P.div_hw) * hw;
+
+  int slot = 0;  // of block i, and with it the ring row of step i's first pixel under tap (0, 0), over 128
+  for (int i = 0; i < steps; ++i) {
+    // blocks i and i + 1 have landed (all that this wave has in flight was asked for a step ago), block i - 1's readers are done
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (i + 2 < blocks) load_block(i + 2, slot == 0 ? 2 : slot - 1);
+    if (i > 0) store_step(i - 1);
+    if (i == steps - 2 || steps == 1) pf.claim();
+    if (i == steps - 1) pf.issue();
+    // ring row under tap (0, 0), times 128; bit t of `taps`: tap t lies in the image
+    uint32_t row128[2], taps[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      const uint32_t r = (uint32_t)(slot * WIN_BLOCK + 64 * wm + 32 * f + l32);
+      row128[f] = r << 7;
+      const int ho = fast_div(rem[f], P.div_wo), wo = rem[f] - ho * P.Wo;
+      const uint32_t rows = 0x038u | (ho > 0 ? 0x007u : 0u) | (ho + 1 < P.Ho ? 0x1c0u : 0u);
+      const uint32_t cols = 0x092u | (wo > 0 ? 0x049u : 0u) | (wo + 1 < P.Wo ? 0x124u : 0u);
+      taps[f] = rows & cols;
+      rem[f] += by;
+      if (rem[f] >= hw) rem[f] -= hw;
+    }
+    f32x16 acc[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[f][e] = 0.f;
+    // Where piece `half` of the lane's pixel f lies under tap t; piece 2 kk + half: with bits 5 and 6 turned over by kk.  (The ring's
+    // length is a multiple of 16 rows: going round does not change the swizzle.)
+    auto place = [&](int t, int f) {
+      const uint32_t straight = row128[f] + ((uint32_t)((t / 3) * P.W + t % 3) << 7);
+      const uint32_t at = min(straight, straight - WIN_RING * 128u) | ((straight >> 4) & 0x70u);
+      const uint32_t in = (uint32_t)((int)(taps[f] << (31 - t)) >> 31);
+      return ((at & in) | (WIN_ZERO & ~in)) ^ (uint32_t)(half * 16);
+    };
+    constexpr int AHEAD = 2;  // fragments asked for ahead of their MFMAs, in steps of 16 channels
+    u32x4 x[AHEAD + 1][2];
+    uint32_t at[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) at[t][f] = place(t, f);
+#pragma unroll
+    for (int z = 0; z < AHEAD; ++z)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) x[z][f] = *(const u32x4 *)(lds + (at[z >> 2][f] ^ (uint32_t)((z & 3) << 5)));
+#pragma unroll
+    for (int z = 0; z < 36; ++z) {
+      const int y = z + AHEAD, t = y >> 2, kk = y & 3;
+      __builtin_amdgcn_sched_barrier(0);
+      if (y < 36) {
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+          x[y % (AHEAD + 1)][f] = *(const u32x4 *)(lds + (at[t & 1][f] ^ (uint32_t)(kk << 5)));
+          // (places of the tap after the next, as soon as this one's are done with)
+          if (kk == 3 && t + 2 < 9) at[t & 1][f] = place(t + 2, f);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int f = 0; f < 2; ++f) mma32<DT>(w[z >> 2][z & 3], x[z % (AHEAD + 1)][f], acc[f]);
+    }
+    // lane holds, per f: pixel l32, channels 8 j + 4 half + (0 .. 3)
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        u32x2 o;
+        o.x = cvt_pack<DT>(acc[f][4 * j], acc[f][4 * j + 1]);
+        o.y = cvt_pack<DT>(acc[f][4 * j + 2], acc[f][4 * j + 3]);
+        const int l = lane_again();
+        *(u32x2 *)(out + (32 * f + (l & 31)) * WIN_OROW + (8 * j + 4 * (l >> 5)) * 2) = o;
+      }
+    slot = slot == 2 ? 0 : slot + 1;
+  }
+  store_step(steps - 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -2168,7 +2367,7 @@ __device__ __forceinline__ void run_block_any(const DevProblem *P_mem, const sk_
     run_tile_any<DT, NCHW, 128, 128>(P_mem, T_mem, sp, lds, s_flag, tid);
 }
 
-template <int DT, bool ANY_ALIGNMENT, bool NARROW>
+template <int DT, bool ANY_ALIGNMENT, bool NARROW, bool WINDOW>
 __device__ __forceinline__ void run_class(const DevProblem &P, const sk_tile &T, const DevProblem *P_mem,
                                           const sk_tile *T_mem, const SplitK &sp, unsigned char *lds,
                                           uint32_t *s_flag, Prefetch &pf) {
@@ -2204,6 +2403,8 @@ __device__ __forceinline__ void run_class(const DevProblem &P, const sk_tile &T,
       }
     }
     if (ANY_ALIGNMENT && !pieces) {
+    } else if (WINDOW && cls == CLS_WINDOW) {
+      if constexpr (WINDOW) run_window<DT>(P, T, lds, pf);
     } else if (cls == 0) {
       run_skinny<DT, 1, ANY_ALIGNMENT>(P, T, sp, lds, s_flag, pf);
     } else if (cls == 3) {
@@ -2428,12 +2629,12 @@ __global__ void __launch_bounds__(WG_THREADS, NARROW ? 3 : 2) sk_superkernel(con
 #endif
     const DevProblem &P = W.prob;
     if constexpr (ONLY_DT >= 0) {
-      run_class<ONLY_DT, ANY_ALIGNMENT, NARROW>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf);
+      run_class<ONLY_DT, ANY_ALIGNMENT, NARROW, !ANY_ALIGNMENT && !NARROW && ONLY_DT != SK_F32>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf);
     } else {
       switch (P.dtype) {
-        case SK_BF16: run_class<SK_BF16, ANY_ALIGNMENT, NARROW>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
-        case SK_F16: run_class<SK_F16, ANY_ALIGNMENT, NARROW>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
-        default: run_class<SK_F32, ANY_ALIGNMENT, NARROW>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
+        case SK_BF16: run_class<SK_BF16, ANY_ALIGNMENT, NARROW, false>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
+        case SK_F16: run_class<SK_F16, ANY_ALIGNMENT, NARROW, false>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
+        default: run_class<SK_F32, ANY_ALIGNMENT, NARROW, false>(P, T, &cur->prob, &cur->tile, sp, lds, &s_flag, pf); break;
       }
     }
 

@@ -590,6 +590,8 @@ bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &
 struct RecordTime {
   int64_t start, step, hand;
 };
+// Runs of pixels (CLS_WINDOW): around their steps, and a step of 128 pixels.
+constexpr int64_t WINDOW_START = 6000, WINDOW_STEP = 3000;
 static RecordTime record_time(const DevProblem &d, const sk_tile &t, bool any) {
   const bool f32 = d.dtype == SK_F32;
   if (any) {
@@ -597,6 +599,7 @@ static RecordTime record_time(const DevProblem &d, const sk_tile &t, bool any) {
     return RecordTime{one - step, f32 ? step * 13 / 10 : step, 8000};
   }
   if (t.cls < CLS_TILE_128x128) return RecordTime{4500, f32 && t.cls >= 6 ? 2000 : 1100, 3000};
+  if (t.cls == CLS_WINDOW) return RecordTime{WINDOW_START + (t.m_len + 127) / 128 * WINDOW_STEP, 0, 0};
   if (t.cls == CLS_TILE_128x64) return RecordTime{5000, f32 ? 1700 : 650, 4000};
   return RecordTime{6000, f32 ? 3400 : 950, 5000};
 }
@@ -619,10 +622,10 @@ static RecordTime record_time(const DevProblem &d, const sk_tile &t, bool any) {
 // Slices change the order of summation with the load of the launch, so plans without the tail rule, whose tiles may not depend on what
 // else is in the plan, get none.  Plans with per-die lists get the same slices as without (the bits of a result do not depend on who
 // runs a tile) and stay otherwise as they are.
-bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, int64_t workgroups, WorkList &out) {
+bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, int64_t workgroups, bool drop_lists, WorkList &out) {
   constexpr int64_t SHORTEST = 14000;
   if (workgroups < 1 || records.empty()) return false;
-  const bool lists = !hp.xorder.empty();
+  const bool lists = !hp.xorder.empty() && !drop_lists;
   const int32_t vec = FLAG_VEC_A | FLAG_VEC_B;
   // an output rectangle of the table: its records (reduction slices, or parts that refine_tiles has made), and how they are cut
   struct Rect {
@@ -704,7 +707,7 @@ bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, in
             x.time = rt.start + stages_of(t) * wide * rt.step;
             changed = changed || x.width < t.n_len;
           }
-        } else if (hp.params.tail_div > 0 && t.m_len <= 128 && t.n_len <= 128) {
+        } else if (t.cls != CLS_WINDOW && hp.params.tail_div > 0 && t.m_len <= 128 && t.n_len <= 128) {
           constexpr int64_t GRAIN = 4;  // stages
           const int64_t kb = 128 / elem_size(d.dtype), k = t.S > 1 ? d.Kg : (int64_t)t.k_len, all = (k + kb - 1) / kb;
           const int64_t fits = (std::max<int64_t>((most - rt.start - rt.hand) / rt.step, any ? 6 : 16) + GRAIN - 1) / GRAIN * GRAIN;
@@ -815,11 +818,110 @@ bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, in
   return out.work.size() <= (size_t)1 << 30 && out.ws_f32x4 <= ((int64_t)1 << 31);
 }
 
-bool device_list(const HostPlan &hp, int64_t workgroups, WorkList &out) {
+// Whether run_window serves the operator: a size-keeping 3x3 NHWC convolution of 64 channels of 16 bits into at most 64, of images
+// whose rows its ring takes, and whose tiles are 128 x 64 LDS tiles.
+bool window_operator(const HostPlan &hp, size_t i) {
+  const DevProblem &d = hp.dev[i];
+  const int32_t vec = FLAG_VEC_A | FLAG_VEC_B;
+  if (d.dtype == SK_F32 || !d.gather || d.nchw || d.stride != 1 || d.R != 3 || d.S != 3 || d.pad_h != 1 || d.pad_w != 1 || d.Cin != 64 ||
+      d.Ng > 64 || d.Ng % 8 != 0 || d.W > 63 || (d.flags & vec) != vec || !aligned16(d.C))
+    return false;
+  const sk_tile &t = hp.tiles[(size_t)hp.first[i]];
+  return t.cls == CLS_TILE_128x64 && t.S == 1;
+}
+
+// The table with such operators' tiles replaced by runs of pixels; false: none.
+// Only where the tiles are more than the workgroups: with a tile for each at most, a run is a single block of 128 pixels, and its
+// start (weights to registers, 36 loads a wave) is what it takes.  500 tiles of 56x56 images 18.8 us as tiles, 20.0 as runs; 525 tiles, a second
+// round for some workgroups, 20.3 and 18.6, 1600 tiles 37.5 and 28.6, 12800 tiles 214 and 132.
+// How long a run is: in a plan of nothing else, what takes the fewest steps over the rounds of runs; beside other operators, half
+// a workgroup's share of the launch, as for weight streaming.
+bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &records, std::vector<int64_t> &count) {
+  constexpr int64_t STEP = 128, START = 3, MOST = 500;  // pixels; steps that a start costs; steps of a run (its pixels fit 16 bits)
+  if (workgroups < 1 || (int64_t)hp.tiles.size() <= workgroups) return false;
+  std::vector<char> window(hp.dev.size(), 0);
+  bool some = false, all = true;
+  for (size_t i = 0; i < hp.dev.size(); ++i) {
+    if (hp.dev[i].dtype != hp.dev[0].dtype || (hp.dev[i].flags & (FLAG_VEC_A | FLAG_VEC_B)) != (FLAG_VEC_A | FLAG_VEC_B)) return false;
+    window[i] = window_operator(hp, i);
+    some = some || window[i];
+    all = all && window[i];
+  }
+  // (the per-die lists of other operators name tiles of the table)
+  if (!some || (!all && !hp.xorder.empty())) return false;
+  auto steps_of = [&](size_t i) { return (hp.dev[i].Mg + STEP - 1) / STEP; };
+  int64_t per = MOST;
+  if (all) {
+    int64_t best = 0, longest = 1;
+    for (size_t i = 0; i < hp.dev.size(); ++i) longest = std::max<int64_t>(longest, steps_of(i));
+    for (int64_t len = std::min(longest, MOST); len >= 1; len = len > 8 ? len * 7 / 8 : len - 1) {
+      int64_t n = 0, most = 0;
+      for (size_t i = 0; i < hp.dev.size(); ++i) {
+        const int64_t parts = (steps_of(i) + len - 1) / len;
+        n += parts;
+        most = std::max(most, (steps_of(i) + parts - 1) / parts);
+      }
+      const int64_t time = (n + workgroups - 1) / workgroups * (most + START);
+      if (best == 0 || time < best) best = time, per = len;
+    }
+  } else {
+    int64_t total = 0;
+    for (size_t i = 0; i < hp.dev.size(); ++i) {
+      if (window[i]) {
+        total += steps_of(i) * WINDOW_STEP;
+        continue;
+      }
+      const sk_tile &t = hp.tiles[(size_t)hp.first[i]];  // (its first record is its largest)
+      const RecordTime rt = record_time(hp.dev[i], t, false);
+      const int64_t kb = 128 / elem_size(hp.dev[i].dtype), cols = t.cls < CLS_TILE_128x128 ? (t.n_len + 127) / 128 : 1;
+      total += hp.count[i] * (rt.start + (t.k_len + kb - 1) / kb * cols * rt.step);
+    }
+    per = std::max<int64_t>(2, std::min(MOST, (total / workgroups / 2 - WINDOW_START) / WINDOW_STEP));
+  }
+  records.clear();
+  count.assign(hp.dev.size(), 0);
+  uint32_t id = 0x80000000u;  // (rectangles are numbered anew later; here they only have to differ)
+  for (const int32_t o : hp.order) {
+    const size_t i = (size_t)o;
+    if (!window[i]) {
+      records.insert(records.end(), hp.tiles.begin() + hp.first[i], hp.tiles.begin() + hp.first[i] + hp.count[i]);
+      count[i] = hp.count[i];
+      continue;
+    }
+    const int64_t parts = (steps_of(i) + per - 1) / per, rows = (steps_of(i) + parts - 1) / parts * STEP;
+    for (int64_t m = 0; m < hp.dev[i].Mg; m += rows) {
+      sk_tile t = hp.tiles[(size_t)hp.first[i]];
+      t.cls = CLS_WINDOW;
+      t.m0 = (uint32_t)m;
+      t.m_len = (uint16_t)std::min<int64_t>(rows, hp.dev[i].Mg - m);
+      t.out_tile_id = id++;
+      records.push_back(t);
+      ++count[i];
+    }
+  }
+  return true;
+}
+
+bool device_list(const HostPlan &hp, int64_t workgroups, bool tiles_only, WorkList &out) {
   std::vector<sk_tile> cut;
   std::vector<int64_t> count;
+  if (window_records(hp, workgroups, cut, count)) {
+    // (balanced as if there were no lists: none are left)
+    if (!balance_records(hp, cut, workgroups, true, out)) {
+      out = WorkList{};
+      out.work = std::move(cut);
+      out.count = std::move(count);
+      out.ws_off = hp.ws_off;
+      out.ws_f32x4 = hp.ws_f32x4;
+      for (sk_tile &t : out.work)
+        if (t.cls == CLS_WINDOW) t.out_tile_id = 0;  // (never used: no slices)
+    }
+    out.window = true;
+    return true;
+  }
+  if (tiles_only) return false;
   const bool refined = refine_blocks(hp, workgroups, cut, count);
-  if (balance_records(hp, refined ? cut : hp.tiles, workgroups, out)) return true;
+  if (balance_records(hp, refined ? cut : hp.tiles, workgroups, false, out)) return true;
   if (!refined || !hp.xorder.empty()) return false;
   out = WorkList{};
   out.work = std::move(cut);
@@ -910,7 +1012,7 @@ bool balance_each_alone(HostPlan &alone, int64_t workgroups) {
   for (size_t i = 0; i < alone.dev.size(); ++i) {
     std::vector<sk_tile> own(alone.tiles.begin() + alone.first[i], alone.tiles.begin() + alone.first[i] + alone.count[i]);
     WorkList w;
-    const bool cut = balance_records(alone, own, workgroups, w);
+    const bool cut = balance_records(alone, own, workgroups, false, w);
     changed = changed || cut;
     out.first[i] = (int64_t)out.tiles.size();
     const uint32_t base = (uint32_t)out.ws_off.size();

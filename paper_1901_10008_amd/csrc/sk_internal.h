@@ -20,6 +20,7 @@ enum : uint16_t {
   CLS_SKINNY_FIRST = 0,  // 0..8: 3*log2(rm) + log2(wk), rm = 1, 2, 4 blocks of 16 activation rows
   CLS_TILE_128x128 = 9,
   CLS_TILE_128x64 = 10,  // operators with at most 64 output columns
+  CLS_WINDOW = 11,       // device's list only: a run of output pixels of a 3x3 convolution of 64 channels (run_window)
 };
 
 // Device-side description of one operator in its canonical GEMM view
@@ -55,9 +56,10 @@ static_assert(sizeof(DevProblem) % 8 == 0, "DevProblem must stay 8-byte sized");
 #define SK_HOST_DEVICE inline
 #endif
 // Whether every offset that an element of a convolution's images b .. b + later can get, counted from the corner of image b's
-// padding (a pixel's offset plus its tap's, and the element itself), lies below `limit` bytes.
+// padding (a pixel's offset plus its tap's, and the element itself), lies below `limit` bytes, 2^31 at most.
 SK_HOST_DEVICE bool offsets_below(const DevProblem &d, int64_t later, int64_t es, int64_t limit) {
-  return later * ((int64_t)d.H * d.W * d.Cin * es) + (int64_t)d.reach < limit;
+  // (limit <= 2^31; a shift, not a 64-bit comparison: see lean_operands)
+  return (uint64_t)(later * ((int64_t)d.H * d.W * d.Cin * es) + (int64_t)d.reach + (((int64_t)1 << 31) - limit)) >> 31 == 0;
 }
 
 // n / d for 0 <= n < 2^31 as (n * mul) >> shift with mul = floor(2^(31+l) / d) + 1, l = ceil(log2 d), shift = 31 + l:
@@ -91,6 +93,7 @@ struct WorkList {
   int64_t ws_f32x4 = 0;
   std::vector<uint32_t> xorder;
   uint32_t xoff[9] = {};
+  bool window = false;  // has runs of pixels: only the general kernels of one element type take it
 };
 
 struct HostPlan {
@@ -128,9 +131,13 @@ bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &
 
 // `records` (the table's, or what refine_tiles makes of them) once more, for a launch of that many workgroups: long records cut, operators
 // of one deadline the longest first (false: nothing to change).
-bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, int64_t workgroups, WorkList &out);
-// What the device runs in place of the plan's table: both of these (false: the table itself).
-bool device_list(const HostPlan &hp, int64_t workgroups, WorkList &out);
+// (drop_lists: as if the plan had no per-die lists)
+bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, int64_t workgroups, bool drop_lists, WorkList &out);
+// Operators that run_window serves as runs of output pixels, where that pays (false: none).
+bool window_operator(const HostPlan &hp, size_t i);
+bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &records, std::vector<int64_t> &count);
+// What the device runs in place of the plan's table: all of these (false: the table itself); tiles_only: runs of pixels or nothing.
+bool device_list(const HostPlan &hp, int64_t workgroups, bool tiles_only, WorkList &out);
 // balance_records for every operator of the baseline's tables (plan_host_each_alone), each a launch of its own; false: nothing changed.
 bool balance_each_alone(HostPlan &alone, int64_t workgroups);
 

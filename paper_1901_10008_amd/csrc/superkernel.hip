@@ -263,8 +263,11 @@ struct sk_plan {
   bool narrow = false;
   int64_t longest_stages = 0;  // stages of the reduction of the longest such tile
   int cus = 0;                 // compute units of the plan's device
+  // (for a launch of the table: one of runs of pixels goes to the general kernel)
   bool narrow_launch(int64_t tiles) const { return narrow && sk::narrow_pays(only_dtype == SK_F32, longest_stages, tiles, cus); }
+  int64_t general_workgroups() const { return host.params.grid_limit > 0 ? host.params.grid_limit : 2 * (int64_t)cus; }
   int64_t most_workgroups(int64_t tiles) const {
+    if (host.run.window) return general_workgroups();
     return host.params.grid_limit > 0 ? host.params.grid_limit : (narrow_launch(tiles) ? 3 : 2) * (int64_t)cus;
   }
   // Every tile is short (at most 64 KB of operands): sk_launch gives workgroup b the tiles b, b + grid, ...
@@ -377,7 +380,7 @@ constexpr int COMPUTE_UNITS = 256;
 sk_status refine(sk::HostPlan &hp, int64_t workgroups, bool narrow) {
   try {
     sk::WorkList w;
-    if (!narrow && sk::device_list(hp, workgroups, w)) hp.run = std::move(w);
+    if (sk::device_list(hp, workgroups, narrow, w)) hp.run = std::move(w);
   } catch (const std::bad_alloc &) {
     return set_error(SK_ERR_ALLOC, "host allocation failed while planning");
   }
@@ -429,7 +432,7 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
   }
   if (prm.host_only && !plan->host.tiles.empty()) {
     plan->cus = COMPUTE_UNITS;
-    st = refine(plan->host, plan->most_workgroups((int64_t)plan->host.tiles.size()), plan->narrow);
+    st = refine(plan->host, plan->general_workgroups(), plan->narrow);
     if (st != SK_OK) {
       delete plan;
       return st;
@@ -460,13 +463,12 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
       return hip_error("hipDeviceGetAttribute", e);
     }
     plan->ticks_per_ms = (double)clock_khz;
-    const int64_t limit = plan->most_workgroups((int64_t)plan->host.tiles.size());
-    st = refine(plan->host, limit, plan->narrow);
+    st = refine(plan->host, plan->general_workgroups(), plan->narrow);
     if (st != SK_OK) {
       delete plan;
       return st;
     }
-    const int64_t ntiles = (int64_t)plan->host.records().size();
+    const int64_t ntiles = (int64_t)plan->host.records().size(), limit = plan->most_workgroups(ntiles);
     plan->grid = (int)(ntiles < limit ? ntiles : limit);
     st = upload_tables(plan->host, plan->device, plan->dev);
     if (st != SK_OK) {
@@ -558,7 +560,7 @@ static sk_status launch_range(sk_plan *plan, const DeviceTables &dt, hipStream_t
   a.arrive = dt.arrive;
   const dim3 g((unsigned)grid), b(sk::WG_THREADS);
   void (*kernel)(const sk::TileWork *, sk::KernelArgs) = nullptr;
-  if (plan->narrow_launch((int64_t)end - begin)) {
+  if (!(whole_table && plan->host.run.window) && plan->narrow_launch((int64_t)end - begin)) {
     switch (plan->only_dtype) {
       case SK_F32: kernel = sk::sk_superkernel<SK_F32, false, true>; break;
       case SK_BF16: kernel = sk::sk_superkernel<SK_BF16, false, true>; break;

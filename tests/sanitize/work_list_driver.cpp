@@ -101,7 +101,7 @@ int main() {
       std::string err;
       if (sk::plan_host(ps.data(), n, &prm, hp, err) != SK_OK) return fail(err.c_str(), seed);
       sk::WorkList w;
-      if (!sk::device_list(hp, wgs, w)) {  // the table itself
+      if (!sk::device_list(hp, wgs, false, w)) {  // the table itself
         w.work = hp.tiles, w.count = hp.count, w.ws_off = hp.ws_off, w.ws_f32x4 = hp.ws_f32x4, w.xorder = hp.xorder;
         std::copy(std::begin(hp.xoff), std::end(hp.xoff), std::begin(w.xoff));
       } else if (part == 0) {
@@ -132,7 +132,8 @@ int main() {
           sk::HostPlan one;
           sk::WorkList o;
           if (sk::plan_host(&ps[(size_t)i], 1, &prm, one, err) != SK_OK) return fail("plan_host", seed);
-          const std::vector<sk_tile> &want = sk::device_list(one, wgs, o) ? o.work : one.tiles;
+          const std::vector<sk_tile> &want = sk::device_list(one, wgs, false, o) ? o.work : one.tiles;
+          if (o.window) continue;  // (runs of pixels sum in the same order; the baseline keeps the tiles)
           if ((int64_t)want.size() != alone.count[(size_t)i]) return fail("records of an operator alone", seed);
           for (size_t k = 0; k < want.size(); ++k) {
             const sk_tile &a = want[k], &b = alone.tiles[(size_t)alone.first[(size_t)i] + k];
@@ -154,6 +155,83 @@ int main() {
         }
       }
     }
+  }
+  // Runs of pixels: every output of every operator in one record, in order, cut at blocks of 128; and what does not go there.
+  for (int seed = 0; seed < 200; ++seed) {
+    std::mt19937 g(seed);
+    auto pick = [&](std::initializer_list<int> v) { return *(v.begin() + g() % v.size()); };
+    std::vector<sk_problem> ps((size_t)(1 + g() % 40));
+    uintptr_t addr = 0x10000000;
+    const int dt = pick({SK_BF16, SK_F16});
+    for (sk_problem &p : ps) {
+      p = sk_problem{};
+      p.op = SK_CONV2D_NHWC, p.dtype = dt, p.Nb = pick({1, 1, 2, 400}), p.H = pick({9, 20, 56, 300}), p.Wd = pick({9, 56, 63}), p.Cin = 64;
+      p.Cout = pick({8, 40, 64}), p.R = p.S = 3, p.pad_h = p.pad_w = 1;
+      p.A = (const void *)addr, p.B = (const void *)(addr + (1u << 30)), p.C = (void *)(addr + (2u << 30));
+      addr += (uintptr_t)3 << 30;
+    }
+    sk_plan_params prm;
+    sk_plan_params_default(&prm);
+    prm.host_only = 1;
+    auto window = [&](const std::vector<sk_problem> &list) {
+      sk::HostPlan hp;
+      std::string err;
+      if (sk::plan_host(list.data(), (int)list.size(), &prm, hp, err) != SK_OK) return false;
+      for (size_t i = 0; i < list.size(); ++i)
+        if (!sk::window_operator(hp, i)) return false;
+      return true;
+    };
+    if (!window(ps)) return fail("not taken for size-keeping convolutions of 64 channels", seed);
+    sk::HostPlan hp;
+    std::string err;
+    if (sk::plan_host(ps.data(), (int)ps.size(), &prm, hp, err) != SK_OK) return fail(err.c_str(), seed);
+    const int64_t tiles = (int64_t)hp.tiles.size();
+    sk::WorkList w;
+    if (sk::device_list(hp, tiles, true, w)) return fail("runs of pixels for no more tiles than workgroups", seed);
+    if (tiles < 2) continue;
+    if (!sk::device_list(hp, std::min<int64_t>(tiles - 1, pick({1, 16, 512})), g() % 2, w) || !w.window)
+      return fail("no runs of pixels for more tiles than workgroups", seed);
+    std::vector<int64_t> next(ps.size(), 0), count(ps.size(), 0);
+    for (const sk_tile &t : w.work) {
+      const sk::DevProblem &d = hp.dev[t.problem];
+      if (t.cls != sk::CLS_WINDOW || t.m0 != next[t.problem] || t.m_len < 1 || t.m0 % 128 != 0 || t.n0 != 0 || t.n_len != d.Ng || t.S != 1 || t.k_len != (uint32_t)d.Kg ||
+          ((int64_t)t.m0 + t.m_len < d.Mg && t.m_len % 128 != 0))
+        return fail("a record of pixels", seed);
+      next[t.problem] += t.m_len;
+      ++count[t.problem];
+    }
+    for (size_t i = 0; i < ps.size(); ++i)
+      if (next[i] != hp.dev[i].Mg) return fail("pixels missing", seed);
+    if (count != w.count || w.ws_f32x4 != 0 || w.ws_off.size() < 1) return fail("counts of the records of pixels", seed);
+    std::vector<sk_problem> bad = ps;
+    sk_problem &b = bad[g() % bad.size()];
+    switch (g() % 9) {
+      case 0: b.Cin = 128; break;
+      case 1: b.Cout = 72; break;
+      case 2: b.Cout = 4; break;
+      case 3: b.Wd = 64; break;
+      case 4: b.stride = 2; break;
+      case 5: b.pad_w = 0; break;
+      case 6: b.op = SK_CONV2D_NCHW; break;
+      case 7: b.A = (const char *)b.A + 2; break;
+      default: b.C = (char *)b.C + 8; break;
+    }
+    if (window(bad)) return fail("taken for another operator", seed);
+    // beside operators that keep their tiles
+    sk::WorkList m;
+    if (sk::plan_host(bad.data(), (int)bad.size(), &prm, hp, err) != SK_OK) continue;
+    bool fit = hp.xorder.empty();
+    for (const sk::DevProblem &d : hp.dev) fit = fit && (d.flags & 3) == 3;
+    const bool made = sk::device_list(hp, 1, false, m) && m.window;
+    if (bad.size() > 1 && made != fit) return fail("runs of pixels beside other operators", seed);
+    if (!made) continue;
+    std::vector<int64_t> area(bad.size(), 0);
+    for (const sk_tile &t : m.work) {
+      if ((t.cls == sk::CLS_WINDOW) != sk::window_operator(hp, t.problem)) return fail("a run of pixels of another operator", seed);
+      area[t.problem] += t.ks_idx == 0 ? (int64_t)t.m_len * t.n_len : 0;
+    }
+    for (size_t i = 0; i < bad.size(); ++i)
+      if (area[i] != (int64_t)hp.dev[i].Mg * hp.dev[i].Ng) return fail("outputs beside runs of pixels", seed);
   }
   if (cut < 100 || sliced < 100 || moved < 100) return fail("too few plans with a list of their own", cut);
   std::puts("work_list_driver: ok");
