@@ -185,6 +185,11 @@ __device__ __forceinline__ uint32_t cvt_bits(float f) {
   return __builtin_bit_cast(uint32_t, f);
 }
 
+// Outputs of whole tiles are stored past the caches (this bit of a buffer store, nontemporal stores elsewhere): the launch does not read them
+// again, and what it does read stays (main workload 1028 -> 1000 us, ResNet layers x16 69.0 -> 67.5, channel-major x8 101 -> 97).  Not
+// the eight-byte stores of the weight-streaming classes: main workload 1002 -> 1019 us.
+constexpr int NONTEMPORAL = 2;
+
 // Store four consecutive outputs of one row (columns n .. n+3, clipped to n_end).
 template <int DT>
 __device__ __forceinline__ void store4(void *C, int64_t row_off, int n, int n_end, f32x4 v, bool vec_ok) {
@@ -1039,7 +1044,7 @@ __device__ __forceinline__ void finish_tile(const DevProblem &P, const sk_tile &
 #pragma unroll
       for (int i = 0; i < BM / RPI; ++i) v[i] = *(const u32x4 *)(lds + pr * OROW + pc * 16 + i * (RPI * OROW));
 #pragma unroll
-      for (int i = 0; i < BM / RPI; ++i) __builtin_amdgcn_raw_buffer_store_b128(v[i], desc, voff + (uint32_t)(i * RPI) * ld, 0, 0);
+      for (int i = 0; i < BM / RPI; ++i) __builtin_amdgcn_raw_buffer_store_b128(v[i], desc, voff + (uint32_t)(i * RPI) * ld, 0, NONTEMPORAL);
       return;
     }
 #pragma unroll 1
@@ -1669,7 +1674,6 @@ __device__ __forceinline__ void run_lds_tile(const DevProblem &P, const sk_tile 
 // alone, 132 here: 3.4 TB/s of operands and outputs against the 4.8 of a large copy.  Without its MFMAs it takes 107, without its
 // fragment reads 120, without storing the outputs 112 (of 130, operands the same every time): bound by memory, with the
 // MFMAs (46 % of the cycles) not quite beside it.  Fragments two or three steps ahead measure the same.
-constexpr int NONTEMPORAL = 2;                         // of a buffer store
 constexpr int WIN_BLOCK = 128;                          // pixels per step and ring block
 constexpr int WIN_RING = 3 * WIN_BLOCK;                 // pixels in the ring
 constexpr int WIN_OROW = 80;                            // bytes of 32 outputs in LDS, padded
@@ -2334,7 +2338,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         const u32x4 v = *(const u32x4 *)(lds + r * OROW + col * ES);
         if (whole) {
           const int64_t o = NCHW ? pixel0 + (int64_t)(nb + r) * hw : (int64_t)(mb + r) * P.ldc + nb + col;
-          *(u32x4_any SK_GLOBAL *)((uintptr_t)P.C + (uintptr_t)(o * ES)) = v;
+          __builtin_nontemporal_store(v, (u32x4_any SK_GLOBAL *)((uintptr_t)P.C + (uintptr_t)(o * ES)));
         } else {
           const piece_t ev = __builtin_bit_cast(piece_t, v);
 #pragma unroll
