@@ -31,10 +31,17 @@ struct Pending {
   int64_t bytes;
 };
 
+// Pinned host memory for the stamps of one launch.
+struct StampBuffer {
+  uint64_t *ptr = nullptr;
+  size_t cap = 0;  // stamps
+};
+
 struct Launch {
   sk_plan *plan = nullptr;  // owned unless `cached`
   bool cached = false;      // a single-operator plan of the time-multiplexing policy, kept for reuse
   hipEvent_t done = nullptr;
+  StampBuffer stamps;        // where its stamps arrive (unless `cached`)
   std::vector<Pending> ops;  // in the order they were given to the planner
   double estimate_ms = 0.0;
   int32_t number = 0;
@@ -50,6 +57,7 @@ struct sk_queue {
   std::deque<Launch> inflight;
   std::vector<sk_completion> ready;  // completions not yet handed out
   std::vector<hipEvent_t> spare_events;
+  std::vector<StampBuffer> spare_stamps;
   std::unordered_map<std::string, sk_plan *> solo;  // SK_QUEUE_SEQUENTIAL: one plan per distinct operator
   uint64_t next_ticket = 1;
   int32_t launches = 0;
@@ -77,6 +85,26 @@ sk_status get_event(sk_queue *q, hipEvent_t *ev) {
   }
   const hipError_t e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
   if (e != hipSuccess) return hip_fail("hipEventCreate", e);
+  return SK_OK;
+}
+
+// Room for n stamps: a spare buffer, the largest, or a new one.  (As many as there are launches in flight, kept until the queue goes.)
+sk_status get_stamps(sk_queue *q, size_t n, StampBuffer *out) {
+  if (!q->spare_stamps.empty()) {
+    auto most = std::max_element(q->spare_stamps.begin(), q->spare_stamps.end(),
+                                 [](const StampBuffer &a, const StampBuffer &b) { return a.cap < b.cap; });
+    *out = *most;
+    q->spare_stamps.erase(most);
+    if (out->cap >= n) return SK_OK;
+    (void)hipHostFree(out->ptr);
+    *out = StampBuffer{};
+  }
+  size_t cap = 1024;
+  while (cap < n) cap *= 2;
+  void *p = nullptr;
+  const hipError_t e = hipHostMalloc(&p, cap * sizeof(uint64_t), hipHostMallocDefault);
+  if (e != hipSuccess) return hip_fail("hipHostMalloc", e);
+  *out = StampBuffer{(uint64_t *)p, cap};
   return SK_OK;
 }
 
@@ -108,13 +136,12 @@ sk_status retire_front(sk_queue *q) {
     for (const Pending &p : l.ops) complete(q, p, t_done, l.number, false);
   } else {
     const size_t n = l.ops.size();
-    std::vector<uint64_t> done(n);
-    uint64_t start = 0;
+    const uint64_t *done = l.stamps.ptr, start = done[n];
     double rate = 0.0;
-    st = sk_plan_get_stamps(l.plan, done.data(), &start, &rate);
+    st = sk_plan_get_stamps(l.plan, nullptr, nullptr, &rate);
     if (st == SK_OK && rate > 0.0) {
       uint64_t last = 0;
-      for (uint64_t d : done) last = std::max(last, d);
+      for (size_t i = 0; i < n; ++i) last = std::max(last, done[i]);
       // anchored at the end: the host saw the launch complete at t_done
       for (size_t i = 0; i < n; ++i) complete(q, l.ops[i], t_done - (double)(last - done[i]) / rate, l.number, false);
       const double took = (double)(last - start) / rate;
@@ -126,6 +153,7 @@ sk_status retire_front(sk_queue *q) {
     const sk_status sd = sk_plan_destroy(l.plan);
     if (st == SK_OK) st = sd;
   }
+  if (l.stamps.ptr) q->spare_stamps.push_back(l.stamps);
   q->spare_events.push_back(l.done);
   q->t_free_ms = q->inflight.empty() ? t_done : std::max(t_done, q->t_free_ms);
   return st;
@@ -201,11 +229,12 @@ sk_status launch_next(sk_queue *q, bool *launched) {
       sk_plan_params prm;
       sk_plan_params_default(&prm);
       prm.stamps = 1;
-      st = sk_plan_create(probs.data(), (int32_t)probs.size(), &prm, &l.plan);
+      st = get_stamps(q, probs.size() + 1, &l.stamps);
+      if (st == SK_OK) st = sk_plan_create(probs.data(), (int32_t)probs.size(), &prm, &l.plan);
     }
   }
-  if (st == SK_OK) st = sk_launch(l.plan, q->stream);
-  if (st == SK_OK) {
+  if (st == SK_OK) st = l.cached ? sk_launch(l.plan, q->stream) : sk::launch_with_stamps(l.plan, q->stream, l.stamps.ptr, l.done);
+  if (st == SK_OK && l.cached) {
     const hipError_t e = hipEventRecord(l.done, q->stream);
     if (e != hipSuccess) st = hip_fail("hipEventRecord", e);
   }
@@ -215,6 +244,7 @@ sk_status launch_next(sk_queue *q, bool *launched) {
     for (const Pending &p : l.ops) complete(q, p, 0.0, l.number, true);
     if (l.plan && !l.cached) (void)sk_plan_destroy(l.plan);
     if (l.done) q->spare_events.push_back(l.done);
+    if (l.stamps.ptr) q->spare_stamps.push_back(l.stamps);
     return sk::set_last_error(st, why);
   }
   l.estimate_ms = sk::estimate_launch_ms(total, q->prm.bytes_per_ms, q->prm.launch_floor_ms);
@@ -283,6 +313,14 @@ sk_status sk_queue_create(const sk_queue_params *params, void *hip_stream, sk_qu
   q->prm = prm;
   q->stream = (hipStream_t)hip_stream;
   q->t0 = Clock::now();
+  if (prm.policy != SK_QUEUE_SEQUENTIAL) {
+    // (not in the first launch: pinning memory takes some 20 us; where there is none to be had that launch says so)
+    StampBuffer b;
+    if (get_stamps(q, 1, &b) == SK_OK)
+      q->spare_stamps.push_back(b);
+    else
+      (void)hipGetLastError();
+  }
   *out = q;
   return SK_OK;
 }
@@ -364,12 +402,14 @@ sk_status sk_queue_destroy(sk_queue *q) {
       const sk_status sd = sk_plan_destroy(l.plan);
       if (st == SK_OK) st = sd;
     }
+    if (l.stamps.ptr) (void)hipHostFree(l.stamps.ptr);
   }
   for (auto &kv : q->solo) {
     const sk_status sd = sk_plan_destroy(kv.second);
     if (st == SK_OK) st = sd;
   }
   for (hipEvent_t e : q->spare_events) (void)hipEventDestroy(e);
+  for (const StampBuffer &b : q->spare_stamps) (void)hipHostFree(b.ptr);
   delete q;
   return st;
 }

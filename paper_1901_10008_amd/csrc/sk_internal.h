@@ -157,6 +157,10 @@ inline int elem_size(int32_t dtype) { return dtype == SK_F32 ? 4 : 2; }
 // Sets the calling thread's sk_last_error() text and passes the status through (superkernel.hip).
 sk_status set_last_error(sk_status st, const std::string &msg);
 
+// sk_launch of a plan with stamps, which leave for `host_stamps` (the n completion stamps and the start; memory that the device can
+// write) behind it; `done` (a hipEvent_t) completes when they are there.  Not under stream capture (superkernel.hip).
+sk_status launch_with_stamps(sk_plan *plan, void *hip_stream, uint64_t *host_stamps, void *done);
+
 // ---- the arrival queue's decisions, free of HIP calls so that they can be exercised on the host ----
 
 // One submitted operator as the batch selection sees it.

@@ -36,9 +36,12 @@ SK_KERNEL(-1, true, false)
 #undef SK_KERNEL
 #endif
 
-// Sets the start stamp to all ones ahead of a stamped launch (a kernel, not a memset: launches may be
-// captured into graphs).
-__global__ void sk_arm_start_stamp(uint64_t *slot) { *slot = ~0ull; }
+// Stamps: sets them to all ones (no source), the start stamp ahead of a launch, or copies them, to the host's memory behind one.  (A kernel,
+// not a memset or a copy: launches may be captured into graphs, and a copy of a few hundred bytes that the host waits for takes
+// longer.)
+__global__ void sk_stamps(uint64_t *dst, const uint64_t *src, uint32_t n) {
+  for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src ? src[i] : ~0ull;
+}
 
 }  // namespace sk
 
@@ -276,6 +279,7 @@ struct sk_plan {
   // 47 us this way, and with tiles this short the fixed assignment cannot leave anyone idle for long.
   bool fixed_assignment = false;
   double ticks_per_ms = 0.0;
+  bool start_armed = false;  // the start stamp is as the upload left it: all ones
   DeviceTables dev;
   // the one-launch-per-operator baseline: every operator tiled as if it were alone;
   // planned and uploaded by the first sk_launch_sequential
@@ -321,14 +325,17 @@ void fill_image(const sk::HostPlan &hp, const TableLayout &l, char *stage) {
   // the work records are written in full below; everything behind them starts at zero
   std::memset(stage + nt * sizeof(sk::TileWork), 0, l.upload - nt * sizeof(sk::TileWork));
   if (nrect) std::memcpy(&stage[l.off_wsoff], hp.rect_off().data(), nrect * sizeof(uint32_t));
+  sk::TileWork w;
+  const std::vector<sk_tile> &records = hp.records();
   for (size_t i = 0; i < nt; ++i) {
-    sk::TileWork w;
-    std::memset(&w, 0, sizeof(w));
-    w.tile = hp.records()[i];
-    w.prob = hp.dev[w.tile.problem];
-    w.prob.tile_count = (int32_t)hp.record_count(w.tile.problem);
+    if (i == 0 || records[i].problem != w.tile.problem) {
+      w.prob = hp.dev[records[i].problem];
+      w.prob.tile_count = (int32_t)hp.record_count(records[i].problem);
+    }
+    w.tile = records[i];
     std::memcpy(&stage[l.off_work + i * sizeof(w)], &w, sizeof(w));
   }
+  std::memset(&stage[l.off_stamps + np * sizeof(uint64_t)], 0xff, sizeof(uint64_t));  // the start stamp, see arm_start_stamp
   for (size_t i = 0; i < hp.die_order().size(); ++i)
     std::memcpy(&stage[l.off_xwork + i * sizeof(sk::TileWork)], &stage[l.off_work + hp.die_order()[i] * sizeof(sk::TileWork)],
                 sizeof(sk::TileWork));
@@ -476,6 +483,7 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
       return st;
     }
     plan->resident = true;
+    plan->start_armed = true;
   }
   *out = plan;
   return SK_OK;
@@ -622,9 +630,14 @@ static hipEvent_t launch_event(sk_plan *plan, bool capturing) {
 }
 
 // Ahead of a stamped launch: the start stamp is a running minimum over the workgroups' first clocks.
-static sk_status arm_start_stamp(sk_plan *plan, hipStream_t stream) {
+// (The upload has armed it for the plan's first launch; one that is captured may be replayed.)
+static sk_status arm_start_stamp(sk_plan *plan, hipStream_t stream, bool capturing) {
   if (!plan->host.params.stamps) return SK_OK;
-  hipLaunchKernelGGL(sk::sk_arm_start_stamp, dim3(1), dim3(1), 0, stream, plan->dev.stamps + plan->host.dev.size());
+  if (plan->start_armed && !capturing) {
+    plan->start_armed = false;
+    return SK_OK;
+  }
+  hipLaunchKernelGGL(sk::sk_stamps, dim3(1), dim3(64), 0, stream, plan->dev.stamps + plan->host.dev.size(), (const uint64_t *)nullptr, 1u);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error("kernel launch", e);
   return SK_OK;
@@ -640,6 +653,19 @@ static sk_status check_launchable(sk_plan *plan) {
   return SK_OK;
 }
 
+}  // extern "C"
+
+sk_status sk::launch_with_stamps(sk_plan *plan, void *hip_stream, uint64_t *host_stamps, void *done) {
+  const sk_status st = sk_launch(plan, hip_stream);
+  if (st != SK_OK) return st;
+  hipExtLaunchKernelGGL(sk::sk_stamps, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, nullptr, (hipEvent_t)done, 0, host_stamps,
+                        (const uint64_t *)plan->dev.stamps, (uint32_t)plan->host.dev.size() + 1u);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? SK_OK : hip_error("kernel launch", e);
+}
+
+extern "C" {
+
 sk_status sk_launch(sk_plan *plan, void *hip_stream) {
   sk_status st = check_launchable(plan);
   if (st != SK_OK) return st;
@@ -648,7 +674,7 @@ sk_status sk_launch(sk_plan *plan, void *hip_stream) {
   bool capturing = false;
   st = admit_launch(plan, stream, &capturing);
   if (st != SK_OK) return st;
-  st = arm_start_stamp(plan, stream);
+  st = arm_start_stamp(plan, stream, capturing);
   if (st != SK_OK) return st;
   const hipEvent_t behind = launch_event(plan, capturing);
   st = launch_range(plan, plan->dev, stream, 0u, (uint32_t)plan->host.records().size(), plan->grid,
@@ -679,7 +705,7 @@ sk_status sk_launch_sequential(sk_plan *plan, void *hip_stream) {
   bool capturing = false;
   st = admit_launch(plan, stream, &capturing);
   if (st != SK_OK) return st;
-  st = arm_start_stamp(plan, stream);
+  st = arm_start_stamp(plan, stream, capturing);
   if (st != SK_OK) return st;
   const hipEvent_t behind = launch_event(plan, capturing);
   for (size_t i = 0; i < n && st == SK_OK; ++i) {
