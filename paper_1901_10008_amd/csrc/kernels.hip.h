@@ -88,7 +88,8 @@ constexpr int LDS_TILE_BYTES = 512 * LDS_ROW;  // 72 KB per workgroup: two workg
 // tenants) run in a kernel of their own: without the other classes' registers and with two stage images instead of
 // three, three workgroups share a CU.  Such a tile spends half its time around its few stages (set-up, first loads,
 // outputs, hand-over), which only the CU's other workgroups can fill: the 3x3 64-channel convolutions on 56x56 of 512
-// tenants take 214 to 223 us instead of 239.  Not every number of tiles gains (narrow_pays).
+// tenants take 214 to 223 us instead of 239 (those of 16 bits run as runs of pixels by now: run_window).  Not every number of tiles gains
+// (narrow_pays).
 constexpr int NARROW_LDS_BYTES = 2 * (128 + 64) * 128;
 
 // Queue counters of a table: [0] tiles handed out beyond the first grid-full, [1] finished workgroups,
@@ -1862,7 +1863,7 @@ __device__ __forceinline__ void run_window(const DevProblem &P, const sk_tile &T
 // ---------------------------------------------------------------------------
 // (Inlined, like every path of the kernel: as real calls the two slow paths gave the kernel a stack,
 // and how well its fast paths then ran changed from build to build.  They exist only in the kernel
-// instantiations for plans with such operands: 235 to 242 registers instead of 232 to 240, about twice the code.  They
+// instantiations for plans with such operands: about twice the code.  They
 // are given the records' addresses in memory rather than references to the caller's copies, and the
 // tile's own copy of the thread index (see the tile loop): taken from threadIdx, what run_tile_any derives from it was
 // hoisted out of the tile loop and cost these kernels 1 to 18 spilled vector registers and a stack.)

@@ -936,7 +936,8 @@ bool device_list(const HostPlan &hp, int64_t workgroups, bool tiles_only, WorkLi
 // twos, 26 / 24; 750 tiles 27.3 / 28.4, 2800 tiles 59.4 / 63.3 (whole rounds of longer tiles); 4000 tiles 87.2 / 85.0, 12800 tiles 240
 // / 223.  16-bit tiles of more than a dozen stages gain nothing (their ring of two stage images waits for
 // every load): 1024 rows of 2048 121 us instead of 113.  fp32 tiles, bound by the matrix cores, gain up to 30 % at 640 tiles
-// and 3 to 6 % from 3000 on, whatever their length.
+// and 3 to 6 % from 3000 on, whatever their length.  (16-bit 3x3 convolutions of 64 channels with more tiles than workgroups run as
+// runs of pixels by now: window_records.)
 bool narrow_pays(bool fp32, int64_t stages, int64_t tiles, int64_t compute_units) {
   if (!fp32 && stages > 12) return false;
   if (tiles <= compute_units) return !fp32 || stages <= 12;

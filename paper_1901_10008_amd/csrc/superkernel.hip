@@ -279,6 +279,7 @@ struct sk_plan {
   // 47 us this way, and with tiles this short the fixed assignment cannot leave anyone idle for long.
   bool fixed_assignment = false;
   double ticks_per_ms = 0.0;
+  bool launched = false;     // outside a stream capture
   bool start_armed = false;  // the start stamp is as the upload left it: all ones
   DeviceTables dev;
   // the one-launch-per-operator baseline: every operator tiled as if it were alone;
@@ -546,9 +547,9 @@ sk_status sk_release_cached_memory(void) {
   return SK_OK;
 }
 
-// `behind`: an event to complete with the launch (null: none).
+// `behind`: an event to complete with the launch (null: none); `packet`: recorded behind it.
 static sk_status launch_range(sk_plan *plan, const DeviceTables &dt, hipStream_t stream, uint32_t begin, uint32_t end,
-                              int grid, bool dynamic, bool write_start, bool whole_table = false, hipEvent_t behind = nullptr) {
+                              int grid, bool dynamic, bool write_start, bool whole_table = false, hipEvent_t behind = nullptr, bool packet = false) {
   if (end <= begin || grid <= 0) return SK_OK;
   sk::KernelArgs a;
   // the per-die lists cover the LDS tiles of the whole table, and only the queue hands them out
@@ -593,12 +594,18 @@ static sk_status launch_range(sk_plan *plan, const DeviceTables &dt, hipStream_t
   // held up whatever came next in the stream: four small fp32 layers, launch after launch, 13.0 us a launch, 11.0 so, and an event
   // that the caller records behind a single launch completes 2.4 us earlier.  (A device-wide wait right behind a single
   // launch returns 2 us later: it then needs that packet itself.)
-  if (behind)
+  // A plan's first launch keeps the packet (but see launch_with_stamps): an event's first use as a signal takes longer than that, and what
+  // comes next is often a wait.
+  if (behind && !packet)
     hipExtLaunchKernelGGL(kernel, g, b, 0, stream, nullptr, behind, 0, dt.work, a);
   else
     hipLaunchKernelGGL(kernel, g, b, 0, stream, dt.work, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error("kernel launch", e);
+  if (behind && packet) {
+    e = hipEventRecord(behind, stream);
+    if (e != hipSuccess) return hip_error("hipEventRecord", e);
+  }
   return SK_OK;
 }
 
@@ -655,18 +662,7 @@ static sk_status check_launchable(sk_plan *plan) {
 
 }  // extern "C"
 
-sk_status sk::launch_with_stamps(sk_plan *plan, void *hip_stream, uint64_t *host_stamps, void *done) {
-  const sk_status st = sk_launch(plan, hip_stream);
-  if (st != SK_OK) return st;
-  hipExtLaunchKernelGGL(sk::sk_stamps, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, nullptr, (hipEvent_t)done, 0, host_stamps,
-                        (const uint64_t *)plan->dev.stamps, (uint32_t)plan->host.dev.size() + 1u);
-  const hipError_t e = hipGetLastError();
-  return e == hipSuccess ? SK_OK : hip_error("kernel launch", e);
-}
-
-extern "C" {
-
-sk_status sk_launch(sk_plan *plan, void *hip_stream) {
+static sk_status launch_whole(sk_plan *plan, void *hip_stream, bool packet_first) {
   sk_status st = check_launchable(plan);
   if (st != SK_OK) return st;
   if (plan->host.tiles.empty()) return SK_OK;
@@ -678,10 +674,24 @@ sk_status sk_launch(sk_plan *plan, void *hip_stream) {
   if (st != SK_OK) return st;
   const hipEvent_t behind = launch_event(plan, capturing);
   st = launch_range(plan, plan->dev, stream, 0u, (uint32_t)plan->host.records().size(), plan->grid,
-                    !plan->fixed_assignment, true, true, behind);
+                    !plan->fixed_assignment, true, true, behind, packet_first && !plan->launched);
   plan->ledger.after_launch((uintptr_t)stream, capturing, behind && st == SK_OK);
+  plan->launched = plan->launched || !capturing;
   return st;
 }
+
+sk_status sk::launch_with_stamps(sk_plan *plan, void *hip_stream, uint64_t *host_stamps, void *done) {
+  const sk_status st = launch_whole(plan, hip_stream, false);  // (the kernel below follows)
+  if (st != SK_OK) return st;
+  hipExtLaunchKernelGGL(sk::sk_stamps, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, nullptr, (hipEvent_t)done, 0, host_stamps,
+                        (const uint64_t *)plan->dev.stamps, (uint32_t)plan->host.dev.size() + 1u);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? SK_OK : hip_error("kernel launch", e);
+}
+
+extern "C" {
+
+sk_status sk_launch(sk_plan *plan, void *hip_stream) { return launch_whole(plan, hip_stream, true); }
 
 sk_status sk_launch_sequential(sk_plan *plan, void *hip_stream) {
   sk_status st = check_launchable(plan);
