@@ -637,13 +637,13 @@ static hipEvent_t launch_event(sk_plan *plan, bool capturing) {
 }
 
 // Ahead of a stamped launch: the start stamp is a running minimum over the workgroups' first clocks.
-// (The upload has armed it for the plan's first launch; one that is captured may be replayed.)
+// (The upload has armed it for the plan's first launch.  One that is captured arms it itself, at every replay, and leaves nothing of the
+// upload's for a launch after it.)
 static sk_status arm_start_stamp(sk_plan *plan, hipStream_t stream, bool capturing) {
   if (!plan->host.params.stamps) return SK_OK;
-  if (plan->start_armed && !capturing) {
-    plan->start_armed = false;
-    return SK_OK;
-  }
+  const bool armed = plan->start_armed;
+  plan->start_armed = false;
+  if (armed && !capturing) return SK_OK;
   hipLaunchKernelGGL(sk::sk_stamps, dim3(1), dim3(64), 0, stream, plan->dev.stamps + plan->host.dev.size(), (const uint64_t *)nullptr, 1u);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_error("kernel launch", e);

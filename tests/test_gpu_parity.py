@@ -436,6 +436,29 @@ def test_launches_replayed_from_a_graph():
         del graphs
 
 
+def test_start_stamp_after_replays_of_a_graph():
+    """A plan with stamps whose first launch is captured: every replay, and every eager launch after it, reports a start of its own,
+    behind all that the launch before it did."""
+    b = H.Batch(workloads.config(2, seed=1)[:6], seed=1)
+    side = torch.cuda.Stream()
+    with b.plan(stamps=1) as warm:   # (loads the kernels ahead of the capture)
+        sk.sk_launch(warm, side.cuda_stream)
+        side.synchronize()
+    with b.plan(stamps=1) as plan:
+        gr = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(gr, stream=side):
+            sk.sk_launch(plan, side.cuda_stream)
+        before = 0
+        for call in ("replay", "replay", "eager", "eager", "replay", "eager"):
+            with torch.cuda.stream(side):
+                gr.replay() if call == "replay" else sk.sk_launch(plan, side.cuda_stream)
+            side.synchronize()
+            done, start, _ = sk.sk_plan_get_stamps(plan)
+            assert before < start and all(start < d for d in done), (call, before, start, done)
+            before = max(done)
+        del gr
+
+
 def test_plans_running_concurrently_on_several_streams():
     """The spatial-multiplexing baseline (Section 4.2): one plan per operator over several streams at once, and a
     coalesced plan of other operators beside them.  Plans share nothing but read-only state, so every output is
