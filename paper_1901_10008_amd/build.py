@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsuperkernel.so")
 CEILINGS_LIB = os.path.join(HERE, "libsk_ceilings.so")  # measuring aid of bench.py, not part of the ABI
-SOURCES = ["superkernel.hip", "planner.cpp", "queue.cpp", "instances.hip"]
+SOURCES = ["superkernel.hip", "planner.cpp", "queue.cpp", "instances.hip", "scratch.hip"]
 UNITS = 7  # units of compilation of instances.hip
 HEADERS = ["kernels.hip.h", "sk_internal.h", os.path.join(ROOT, "include", "superkernel.h")]
 
@@ -53,11 +53,13 @@ def build(force: bool = True, verbose: bool = False, extra=(), lib: str = LIB, c
     o_hip = os.path.join(obj_dir, f"superkernel{tag}.o")
     o_cpp = os.path.join(obj_dir, "planner.o")
     o_queue = os.path.join(obj_dir, "queue.o")
+    o_scratch = os.path.join(obj_dir, "scratch.o")
     # the kernels are compiled side by side (a diagnostic build, -DSK_DIAG_CLOCKS, compiles them with superkernel.hip)
     units = [] if "-DSK_DIAG_CLOCKS" in extra else list(range(UNITS))
     o_units = [os.path.join(obj_dir, f"instances{u}{tag}.o") for u in units]
     compiles = [[hipcc, *HIPCC_FLAGS, *extra, *inc, f"-DSK_UNIT={u}", "-c", srcs[3], "-o", o] for u, o in zip(units, o_units)] + [
         [hipcc, *HIPCC_FLAGS, *extra, *inc, "-c", srcs[0], "-o", o_hip],
+        [hipcc, *HIPCC_FLAGS, *inc, "-c", srcs[4], "-o", o_scratch],
         ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", *inc, "-c", srcs[1], "-o", o_cpp],
         # host code that calls the HIP runtime (events): the host compiler with the runtime's headers
         ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", *inc, "-c", srcs[2],
@@ -67,7 +69,7 @@ def build(force: bool = True, verbose: bool = False, extra=(), lib: str = LIB, c
         compiles.append([hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
                          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                          os.path.join(CSRC, "ceilings.hip"), "-o", CEILINGS_LIB])
-    link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", o_hip, *o_units, o_cpp, o_queue, "-o", lib]
+    link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", o_hip, *o_units, o_cpp, o_queue, o_scratch, "-o", lib]
 
     def run(cmd):
         if verbose:

@@ -621,8 +621,10 @@ static RecordTime record_time(const DevProblem &d, const sk_tile &t, bool any) {
 // BERT layers x8 173 -> 156, stride-2 layers x3 43 -> 33; mixes whose operators all have deadlines of their own as before.
 // Slices change the order of summation with the load of the launch, so plans without the tail rule, whose tiles may not depend on what
 // else is in the plan, get none.  Plans with per-die lists get the same slices as without (the bits of a result do not depend on who
-// runs a tile) and stay otherwise as they are.
-bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, int64_t workgroups, bool drop_lists, WorkList &out) {
+// runs a tile) and stay otherwise as they are.  Nor do they depend on the number of workgroups: `impose` names the slices of a launch that
+// fills a whole MI355X (null: this is that launch, they are settled here).
+static bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, int64_t workgroups, bool drop_lists,
+                            const std::vector<Slicing> *impose, WorkList &out) {
   constexpr int64_t SHORTEST = 14000;
   if (workgroups < 1 || records.empty()) return false;
   const bool lists = !hp.xorder.empty() && !drop_lists;
@@ -638,6 +640,7 @@ bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, in
     size_t first, count;  // records
     int64_t longest;
     size_t rect, rects;  // of an operator with a record that may be cut
+    bool sliced;         // slices imposed
   };
   std::vector<Rect> rects;
   std::vector<Op> ops;
@@ -655,10 +658,11 @@ bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, in
     const RecordTime rt = record_time(hp.dev[t.problem], t, any);
     return rt.start + stages_of(t) * columns_of(t, any) * rt.step + (t.S > 1 ? rt.hand : 0);
   };
+  auto imposed = [&](const sk_tile &t) { return impose && t.out_tile_id < impose->size() ? (*impose)[t.out_tile_id] : Slicing{}; };
   auto alike = [](const sk_tile &a, const sk_tile &b) { return a.m_len == b.m_len && a.n_len == b.n_len && a.k_len == b.k_len; };
   int64_t total = 0;
   for (size_t i = 0; i < records.size();) {
-    Op op{(int32_t)records[i].problem, i, 0, 0, 0, 0};
+    Op op{(int32_t)records[i].problem, i, 0, 0, 0, 0, false};
     int64_t time = 0;
     const sk_tile *timed = nullptr;  // (an operator's records are mostly alike)
     for (; i < records.size() && records[i].problem == (uint32_t)op.problem; ++i) {
@@ -668,6 +672,7 @@ bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, in
         op.longest = std::max(op.longest, time);
       }
       total += time;
+      op.sliced = op.sliced || imposed(records[i]).S > 0;
     }
     op.count = i - op.first;
     ops.push_back(op);
@@ -675,8 +680,9 @@ bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, in
   const int64_t share = total / workgroups;
 
   bool changed = false;
+  std::vector<Slicing> slicing;
   for (Op &op : ops) {
-    if (op.longest * 10 <= std::max(SHORTEST, share / 2) * 11) continue;
+    if (op.longest * 10 <= std::max(SHORTEST, share / 2) * 11 && !op.sliced) continue;
     const bool dated = hp.params.edf && std::isfinite(deadline_key(hp.problems[op.problem].deadline_ms));
     op.rect = rects.size();
     for (size_t i = op.first; i < op.first + op.count; ++i) {
@@ -695,6 +701,17 @@ bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, in
       const DevProblem &d = hp.dev[t.problem];
       const bool any = any_of(t), stream = !any && t.cls < CLS_TILE_128x128;
       const int64_t most = std::max<int64_t>(SHORTEST, stream ? share / 2 : any || d.dtype == SK_F32 ? share * 5 / 4 : share * 2);
+      if (const Slicing given = imposed(t); given.S > 0) {
+        const RecordTime rt = record_time(d, t, any);
+        const int64_t kb = 128 / elem_size(d.dtype);
+        x.S = given.S;
+        x.slice = given.slice;
+        x.width = std::min<int64_t>(x.width, 128);  // (a slice of a record without 16-byte pieces must be a single block)
+        x.time = rt.start + (given.slice + kb - 1) / kb * rt.step + rt.hand;
+        changed = true;
+        op.longest = std::max(op.longest, x.time);
+        continue;
+      }
       // (up to 64 reduction elements an operator without 16-byte pieces may go the one-output-per-thread way, by the size of its record)
       if (x.time * 10 > most * 11 && ((d.flags & vec) == vec || d.Kg > 64)) {
         const RecordTime rt = record_time(d, t, any);
@@ -707,7 +724,7 @@ bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, in
             x.time = rt.start + stages_of(t) * wide * rt.step;
             changed = changed || x.width < t.n_len;
           }
-        } else if (t.cls != CLS_WINDOW && hp.params.tail_div > 0 && t.m_len <= 128 && t.n_len <= 128) {
+        } else if (!impose && t.cls != CLS_WINDOW && hp.params.tail_div > 0 && t.m_len <= 128 && t.n_len <= 128) {
           constexpr int64_t GRAIN = 4;  // stages
           const int64_t kb = 128 / elem_size(d.dtype), k = t.S > 1 ? d.Kg : (int64_t)t.k_len, all = (k + kb - 1) / kb;
           const int64_t fits = (std::max<int64_t>((most - rt.start - rt.hand) / rt.step, any ? 6 : 16) + GRAIN - 1) / GRAIN * GRAIN;
@@ -719,6 +736,8 @@ bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, in
             x.slice = per * kb;
             x.time = time;
             changed = true;
+            if (slicing.size() <= t.out_tile_id) slicing.resize(t.out_tile_id + 1);
+            slicing[t.out_tile_id] = Slicing{x.S, x.slice};
           }
         }
       }
@@ -741,6 +760,7 @@ bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, in
   out.work.reserve(records.size() + records.size() / 4);
   out.ws_off.reserve(records.size());
   out.count.assign(hp.dev.size(), 0);
+  out.slicing = std::move(slicing);
   auto new_rect = [&](const sk_tile &t, int64_t S) {
     out.ws_off.push_back(S > 1 ? (uint32_t)out.ws_f32x4 : 0u);
     if (S > 1) out.ws_f32x4 += S * slice_f32x4(t.cls);
@@ -902,17 +922,24 @@ bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile>
   return true;
 }
 
-bool device_list(const HostPlan &hp, int64_t workgroups, bool tiles_only, WorkList &out) {
+// A launch that fills a whole MI355X: two workgroups on each of its 256 compute units.
+constexpr int64_t CHIP_WORKGROUPS = 512;
+
+// The list of tiles, and with `runs` of runs of pixels where they pay, for a launch of that many workgroups.
+static bool list_records(const HostPlan &hp, int64_t workgroups, bool runs, bool tiles_only, const std::vector<Slicing> *impose, WorkList &out) {
   std::vector<sk_tile> cut;
   std::vector<int64_t> count;
-  if (window_records(hp, workgroups, cut, count)) {
+  auto as_cut = [&]() {
+    out = WorkList{};
+    out.work = std::move(cut);
+    out.count = std::move(count);
+    out.ws_off = hp.ws_off;
+    out.ws_f32x4 = hp.ws_f32x4;
+  };
+  if (runs && window_records(hp, workgroups, cut, count)) {
     // (balanced as if there were no lists: none are left)
-    if (!balance_records(hp, cut, workgroups, true, out)) {
-      out = WorkList{};
-      out.work = std::move(cut);
-      out.count = std::move(count);
-      out.ws_off = hp.ws_off;
-      out.ws_f32x4 = hp.ws_f32x4;
+    if (!balance_records(hp, cut, workgroups, true, impose, out)) {
+      as_cut();
       for (sk_tile &t : out.work)
         if (t.cls == CLS_WINDOW) t.out_tile_id = 0;  // (never used: no slices)
     }
@@ -921,14 +948,26 @@ bool device_list(const HostPlan &hp, int64_t workgroups, bool tiles_only, WorkLi
   }
   if (tiles_only) return false;
   const bool refined = refine_blocks(hp, workgroups, cut, count);
-  if (balance_records(hp, refined ? cut : hp.tiles, workgroups, false, out)) return true;
+  if (balance_records(hp, refined ? cut : hp.tiles, workgroups, false, impose, out)) return true;
   if (!refined || !hp.xorder.empty()) return false;
-  out = WorkList{};
-  out.work = std::move(cut);
-  out.count = std::move(count);
-  out.ws_off = hp.ws_off;
-  out.ws_f32x4 = hp.ws_f32x4;
+  as_cut();
   return true;
+}
+
+// Slices, which change the sums' order, are those of a launch that fills the chip, whatever the grid of this one (its limit is the caller's,
+// its compute units are the device's, and a host-only plan has no device yet): results depend on the operators and the
+// table's parameters alone.  Order and cuts follow the grid.  Plans of short tiles alone get no slices.
+static bool list_records(const HostPlan &hp, int64_t workgroups, bool runs, bool tiles_only, bool slices, WorkList &out) {
+  const std::vector<Slicing> none;
+  if (!slices || tiles_only) return list_records(hp, workgroups, runs, tiles_only, &none, out);
+  if (workgroups == CHIP_WORKGROUPS) return list_records(hp, workgroups, runs, tiles_only, nullptr, out);
+  WorkList chip;
+  if (!list_records(hp, CHIP_WORKGROUPS, runs, tiles_only, nullptr, chip)) chip.slicing.clear();
+  return list_records(hp, workgroups, runs, tiles_only, &chip.slicing, out);
+}
+
+bool device_list(const HostPlan &hp, int64_t workgroups, bool tiles_only, WorkList &out, bool slices) {
+  return list_records(hp, workgroups, true, tiles_only, slices, out);
 }
 
 // Measured against the general kernel as it is now (3x3 64-channel convolutions in bf16, us, general / narrow): 25 tiles 11.4 / 10.6,
@@ -1009,32 +1048,32 @@ bool balance_each_alone(HostPlan &alone, int64_t workgroups) {
   out.tiles.clear();
   out.ws_off.clear();
   out.ws_f32x4 = 0;
+  sk_plan_params prm = alone.params;
+  prm.host_only = 1;
+  std::string err;
   bool changed = false;
   for (size_t i = 0; i < alone.dev.size(); ++i) {
-    std::vector<sk_tile> own(alone.tiles.begin() + alone.first[i], alone.tiles.begin() + alone.first[i] + alone.count[i]);
+    HostPlan one;
+    if (plan_host(&alone.problems[i], 1, &prm, one, err) != SK_OK) return false;
+    one.xorder.clear();  // (its launch is a range of the tables: no lists)
     WorkList w;
-    const bool cut = balance_records(alone, own, workgroups, false, w);
-    changed = changed || cut;
+    if (list_records(one, workgroups, false, false, true, w)) {
+      changed = true;
+    } else {
+      w.work = one.tiles;
+      w.ws_off = one.ws_off;
+      w.ws_f32x4 = one.ws_f32x4;
+    }
     out.first[i] = (int64_t)out.tiles.size();
+    out.count[i] = (int64_t)w.work.size();
     const uint32_t base = (uint32_t)out.ws_off.size();
-    for (sk_tile t : cut ? w.work : own) {
-      if (cut) {
-        t.out_tile_id += base;
-      } else {  // its rectangles' workspace moves as a whole
-        const uint32_t id = t.out_tile_id;
-        if (out.tiles.size() == (size_t)out.first[i] || id != own[out.tiles.size() - (size_t)out.first[i] - 1].out_tile_id) {
-          out.ws_off.push_back(t.S > 1 ? (uint32_t)out.ws_f32x4 : 0u);
-          if (t.S > 1) out.ws_f32x4 += t.S * slice_f32x4(t.cls);
-        }
-        t.out_tile_id = (uint32_t)out.ws_off.size() - 1u;
-      }
+    for (sk_tile t : w.work) {
+      t.problem = (uint32_t)i;
+      t.out_tile_id += base;
       out.tiles.push_back(t);
     }
-    if (cut) {
-      for (const uint32_t w_off : w.ws_off) out.ws_off.push_back(w_off + (uint32_t)out.ws_f32x4);
-      out.ws_f32x4 += w.ws_f32x4;
-    }
-    out.count[i] = (int64_t)out.tiles.size() - out.first[i];
+    for (const uint32_t w_off : w.ws_off) out.ws_off.push_back(w_off + (uint32_t)out.ws_f32x4);
+    out.ws_f32x4 += w.ws_f32x4;
     out.dev[i].tile_first = (int32_t)out.first[i];
     out.dev[i].tile_count = (int32_t)out.count[i];
     if (out.ws_f32x4 > ((int64_t)1 << 31)) return false;

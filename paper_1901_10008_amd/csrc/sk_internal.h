@@ -2,6 +2,7 @@
 // Not part of the public ABI (include/superkernel.h is).
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -85,6 +86,11 @@ struct TileWork {
 };
 static_assert(sizeof(TileWork) == 192, "TileWork layout");
 
+// How the device's list slices a rectangle of the table anew: into S slices of that many reduction elements (S == 0: as the table has it).
+struct Slicing {
+  int64_t S = 0, slice = 0;
+};
+
 // The records the device runs, with output rectangles and a split-K workspace numbered for them, and the per-die lists over them.
 struct WorkList {
   std::vector<sk_tile> work;
@@ -93,6 +99,7 @@ struct WorkList {
   int64_t ws_f32x4 = 0;
   std::vector<uint32_t> xorder;
   uint32_t xoff[9] = {};
+  std::vector<Slicing> slicing;  // of the table's rectangles, up to the last that is sliced anew
   bool window = false;  // has runs of pixels: only the general kernels of one element type take it
 };
 
@@ -129,16 +136,13 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
 // and untouched if nothing is to be cut).
 bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &work, std::vector<int64_t> &count);
 
-// `records` (the table's, or what refine_tiles makes of them) once more, for a launch of that many workgroups: long records cut, operators
-// of one deadline the longest first (false: nothing to change).
-// (drop_lists: as if the plan had no per-die lists)
-bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, int64_t workgroups, bool drop_lists, WorkList &out);
 // Operators that run_window serves as runs of output pixels, where that pays (false: none).
 bool window_operator(const HostPlan &hp, size_t i);
 bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &records, std::vector<int64_t> &count);
-// What the device runs in place of the plan's table: all of these (false: the table itself); tiles_only: runs of pixels or nothing.
-bool device_list(const HostPlan &hp, int64_t workgroups, bool tiles_only, WorkList &out);
-// balance_records for every operator of the baseline's tables (plan_host_each_alone), each a launch of its own; false: nothing changed.
+// What the device runs in place of the plan's table (false: the table itself): these and refine_tiles, long records cut, operators of one
+// deadline the longest first.  tiles_only: runs of pixels or nothing; without `slices`: none that the table does not have.
+bool device_list(const HostPlan &hp, int64_t workgroups, bool tiles_only, WorkList &out, bool slices = true);
+// The same for every operator of the baseline's tables (plan_host_each_alone), each a launch of its own, as tiles; false: nothing changed.
 bool balance_each_alone(HostPlan &alone, int64_t workgroups);
 
 // Whether every tile of the plan, and of each of its operators planned alone, is a 128 x 64 LDS tile whose operands can
@@ -153,6 +157,12 @@ bool narrow_pays(bool fp32, int64_t stages, int64_t tiles, int64_t compute_units
 sk_status plan_host_each_alone(const HostPlan &whole, int64_t workgroups, HostPlan &out, std::string &err);
 
 inline int elem_size(int32_t dtype) { return dtype == SK_F32 ? 4 : 2; }
+
+// SK_STATIC_SCRATCH_BYTES is what a plan's table may need for sk_launch_static.  The device's list slices further than the table, and both
+// launch calls have to slice alike, so such plans have a larger array (of 3300 random plans whose tables fit, 52 lists need more than
+// SK_STATIC_SCRATCH_BYTES, the largest 46 MiB).  Its address on the current device goes to *ptr (a hipError_t; scratch.hip).
+constexpr size_t LARGE_SCRATCH_BYTES = 3 * (size_t)SK_STATIC_SCRATCH_BYTES;
+int large_scratch_address(void **ptr);
 
 // Sets the calling thread's sk_last_error() text and passes the status through (superkernel.hip).
 sk_status set_last_error(sk_status st, const std::string &msg);

@@ -198,33 +198,35 @@ TablePool &table_pool() {
 // Scratch of sk_launch_static: the table block (work records, queue counters, split-K arrival counters and
 // workspace) that sk_plan_create otherwise allocates, as a fixed array in the library's code object.  Each
 // GPU the library runs on holds its own copy, at its own address, until the process ends.
+// (Plans whose list is larger use another one: scratch.hip.)
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)SK_STATIC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 
 namespace {
 
-// Device address of `scratch` and the compute-unit count, per device; looked up on the first
+// Device addresses of `scratch` and of the large one, each when it is first wanted, and the compute-unit count, per device; looked up on the first
 // sk_launch_static of a device, with that device current.  (In host code the array's name is not a
 // device address: everything below uses the looked-up pointer.)
 struct StaticScratch {
   static constexpr int MAX_DEVICES = 64;
   std::mutex mu;
-  void *ptr[MAX_DEVICES] = {};
+  void *ptr[2][MAX_DEVICES] = {};
   int cus[MAX_DEVICES] = {};
-  sk_status get(int device, void **out, int *cu_count) {
+  sk_status get(int device, bool large, void **out, int *cu_count) {
     if (device < 0 || device >= MAX_DEVICES) return set_error(SK_ERR_UNSUPPORTED, "device index beyond 63");
     std::lock_guard<std::mutex> g(mu);
-    if (!ptr[device]) {
+    void *&have = ptr[large ? 1 : 0][device];
+    if (!have) {
       void *p = nullptr;
-      hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+      hipError_t e = large ? (hipError_t)sk::large_scratch_address(&p) : hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
       if (e != hipSuccess || !p) return hip_error("hipGetSymbolAddress", e);
       int n = 0;
       e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device);
       if (e != hipSuccess) return hip_error("hipDeviceGetAttribute", e);
       cus[device] = n;
-      ptr[device] = p;
+      have = p;
     }
-    *out = ptr[device];
+    *out = have;
     *cu_count = cus[device];
     return SK_OK;
   }
@@ -304,19 +306,20 @@ struct TableLayout {
   size_t total;   // upload + split-K workspace
 };
 
-TableLayout layout_of(const sk::HostPlan &hp) {
-  const size_t nt = hp.records().size(), np = hp.dev.size(), nrect = hp.rect_off().size();
+// (`run`: of what the device runs; else of the plan's table)
+TableLayout layout_of(const sk::HostPlan &hp, bool run = true) {
+  const size_t nt = (run ? hp.records() : hp.tiles).size(), np = hp.dev.size(), nrect = (run ? hp.rect_off() : hp.ws_off).size();
   TableLayout l;
   l.off_work = 0;
   l.off_xwork = align_up(l.off_work + nt * sizeof(sk::TileWork), 256);
-  l.off_xoff = align_up(l.off_xwork + hp.die_order().size() * sizeof(sk::TileWork), 256);
+  l.off_xoff = align_up(l.off_xwork + (run ? hp.die_order() : hp.xorder).size() * sizeof(sk::TileWork), 256);
   l.off_cnt = align_up(l.off_xoff + 9 * sizeof(uint32_t), 256);
   l.off_rem = align_up(l.off_cnt + sk::QUEUE_COUNTERS * sizeof(uint32_t), 256);
   l.off_stamps = align_up(l.off_rem + np * sizeof(uint32_t), 256);
   l.off_wsoff = align_up(l.off_stamps + (np + 1) * sizeof(uint64_t), 256);
   l.off_arrive = align_up(l.off_wsoff + nrect * sizeof(uint32_t), 256);
   l.upload = align_up(l.off_arrive + nrect * sizeof(uint32_t), 256);
-  l.total = l.upload + (size_t)hp.ws_units() * 16;
+  l.total = l.upload + (size_t)(run ? hp.ws_units() : hp.ws_f32x4) * 16;
   return l;
 }
 
@@ -384,11 +387,22 @@ sk_status upload_tables(const sk::HostPlan &hp, int device, DeviceTables &dt) {
 // Compute units of an MI355X, for plans that are made before their device is known (host-only ones).
 constexpr int COMPUTE_UNITS = 256;
 
+// What sk_launch_static asks of a plan: the plan's table, or what the device runs in its place (fewer records, where these are runs of
+// pixels), is no larger than SK_STATIC_SCRATCH_BYTES.
+size_t static_bytes(const sk::HostPlan &hp) { return std::min(layout_of(hp, false).total, layout_of(hp).total); }
+
 // What the device runs in place of the table, in a launch of that many workgroups.  (The tiles of a narrow plan are short and alike.)
+// The same slices for resident and for host-only plans, so that sk_launch and sk_launch_static give the same bits: a list beyond the large
+// scratch of a plan whose table fits the other goes without, and a host-only plan that is too large even so keeps its table.
 sk_status refine(sk::HostPlan &hp, int64_t workgroups, bool narrow) {
   try {
-    sk::WorkList w;
-    if (sk::device_list(hp, workgroups, narrow, w)) hp.run = std::move(w);
+    const bool table_fits = !hp.tiles.empty() && layout_of(hp, false).total <= STATIC_SCRATCH_BYTES;
+    for (bool slices : {true, false}) {
+      sk::WorkList w;
+      hp.run = sk::device_list(hp, workgroups, narrow, w, slices) ? std::move(w) : sk::WorkList{};
+      if (!table_fits || layout_of(hp).total <= sk::LARGE_SCRATCH_BYTES) return SK_OK;
+    }
+    if (hp.params.host_only) hp.run = sk::WorkList{};
   } catch (const std::bad_alloc &) {
     return set_error(SK_ERR_ALLOC, "host allocation failed while planning");
   }
@@ -445,9 +459,8 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
       delete plan;
       return st;
     }
-    if (layout_of(plan->host).total > STATIC_SCRATCH_BYTES) plan->host.run = sk::WorkList{};  // (the table itself may still fit)
     const TableLayout l = layout_of(plan->host);
-    if (l.total <= STATIC_SCRATCH_BYTES) {  // (larger plans cannot use sk_launch_static anyway)
+    if (static_bytes(plan->host) <= STATIC_SCRATCH_BYTES) {  // (larger plans cannot use sk_launch_static anyway)
       try {
         plan->image.resize(l.upload);
       } catch (const std::bad_alloc &) {
@@ -736,16 +749,16 @@ sk_status sk_launch_static(sk_plan *plan, void *hip_stream) {
   if (plan->host.params.stamps)
     return set_error(SK_ERR_STATE, "completion stamps are not available through sk_launch_static");
   if (plan->host.tiles.empty()) return SK_OK;
+  if (static_bytes(plan->host) > STATIC_SCRATCH_BYTES)
+    return set_error(SK_ERR_UNSUPPORTED, "plan needs " + std::to_string(static_bytes(plan->host)) +
+                                             " bytes of tables and workspace, the static scratch holds " + std::to_string(STATIC_SCRATCH_BYTES));
   const TableLayout l = layout_of(plan->host);
-  if (l.total > STATIC_SCRATCH_BYTES)
-    return set_error(SK_ERR_UNSUPPORTED, "plan needs " + std::to_string(l.total) + " bytes of tables and workspace, the static scratch holds " +
-                                             std::to_string(STATIC_SCRATCH_BYTES));
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_error("hipGetDevice", e);
   void *base = nullptr;
   int cus = 0;
-  sk_status st = static_scratch().get(dev, &base, &cus);
+  sk_status st = static_scratch().get(dev, l.total > STATIC_SCRATCH_BYTES, &base, &cus);
   if (st != SK_OK) return st;
   const hipStream_t stream = (hipStream_t)hip_stream;
   // Records, zeroed queue and arrival counters, workspace offsets: everything the kernel expects to find.
@@ -759,6 +772,15 @@ sk_status sk_launch_static(sk_plan *plan, void *hip_stream) {
   const int64_t limit = plan->most_workgroups(ntiles);
   plan->grid = (int)(ntiles < limit ? ntiles : limit);
   return launch_range(plan, dt, stream, 0u, (uint32_t)ntiles, plan->grid, !plan->fixed_assignment, false, true);
+}
+
+// For tests, not part of the boundary (so not in include/superkernel.h): what the device runs in place of the plan's table; at most `cap`
+// records go to `dst` (host memory, may be null), the result is how many there are.  tile.cls 11: a run of pixels.
+int64_t sk_diag_plan_records(const sk_plan *plan, sk_tile *dst, int64_t cap) {
+  if (!plan) return -1;
+  const std::vector<sk_tile> &r = plan->host.records();
+  if (dst && cap > 0) std::memcpy(dst, r.data(), std::min<size_t>((size_t)cap, r.size()) * sizeof(sk_tile));
+  return (int64_t)r.size();
 }
 
 int64_t sk_plan_num_tiles(const sk_plan *plan) { return plan ? (int64_t)plan->host.tiles.size() : -1; }

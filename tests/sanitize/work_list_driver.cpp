@@ -20,6 +20,20 @@ static int fail(const char *what, int seed) {
 
 using Slices = std::vector<std::pair<uint32_t, uint32_t>>;  // k0, k_len
 
+static Slices same(Slices a) {
+  std::sort(a.begin(), a.end());
+  a.erase(std::unique(a.begin(), a.end()), a.end());
+  return a;
+}
+
+static std::map<std::tuple<uint32_t, uint32_t, uint32_t>, Slices> blocks(const std::vector<sk_tile> &work) {
+  std::map<std::tuple<uint32_t, uint32_t, uint32_t>, Slices> out;
+  for (const sk_tile &t : work)
+    for (uint32_t m = t.m0 / 64; m <= (t.m0 + t.m_len - 1) / 64; ++m)
+      for (uint32_t n = t.n0 / 32; n <= (t.n0 + t.n_len - 1) / 32; ++n) out[{t.problem, m, n}].emplace_back(t.k0, t.k_len);
+  return out;
+}
+
 // The list against the table: 0, or a message.  `slices`: of every output column block of every operator.
 static const char *check(const sk::HostPlan &hp, const sk::WorkList &w, std::map<std::tuple<uint32_t, uint32_t, uint32_t>, Slices> &slices) {
   std::vector<int64_t> count(hp.dev.size(), 0), area(hp.dev.size(), 0);
@@ -46,9 +60,8 @@ static const char *check(const sk::HostPlan &hp, const sk::WorkList &w, std::map
       }
     }
     if (t.ks_idx + 1 == t.S && (int64_t)t.k0 + t.k_len != d.Kg) return "the last slice ends early";
-    for (uint32_t m = t.m0 / 64; m <= (t.m0 + t.m_len - 1) / 64; ++m)
-      for (uint32_t n = t.n0 / 32; n <= (t.n0 + t.n_len - 1) / 32; ++n) slices[{t.problem, m, n}].emplace_back(t.k0, t.k_len);
   }
+  slices = blocks(w.work);
   if (count != w.count) return "records per operator";
   for (size_t i = 0; i < hp.dev.size(); ++i)
     if (area[i] != (int64_t)hp.dev[i].Mg * hp.dev[i].Ng) return "outputs missing or made twice";
@@ -121,6 +134,24 @@ int main() {
       if (prm.tail_div == 0)
         for (const sk_tile &t : w.work)
           if (t.S != hp.tiles[(size_t)hp.first[t.problem]].S) return fail("slices without the tail rule", seed);
+      // the slices are those of a launch that fills the chip, whatever the grid; without new ones they are the table's
+      for (int64_t other : {(int64_t)512, (int64_t)33}) {
+        sk::WorkList o;
+        if (!sk::device_list(hp, other, false, o)) o.work = hp.tiles;
+        std::map<std::tuple<uint32_t, uint32_t, uint32_t>, Slices> got;
+        if (const char *what = o.count.empty() ? nullptr : check(hp, o, got)) return fail(what, seed);
+        if (o.count.empty()) got = blocks(o.work);
+        if (got.size() != slices.size()) return fail("blocks on another grid", seed);
+        for (const auto &s : slices)
+          if (same(got[s.first]) != same(s.second)) return fail("the grid changes the slices", seed);
+      }
+      sk::WorkList whole;
+      if (sk::device_list(hp, wgs, false, whole, false)) {
+        std::map<std::tuple<uint32_t, uint32_t, uint32_t>, Slices> ignored;
+        if (const char *what = check(hp, whole, ignored)) return fail(what, seed);
+        for (const sk_tile &t : whole.work)
+          if (t.S != hp.tiles[(size_t)hp.first[t.problem]].S) return fail("slices of a list without", seed);
+      }
       if (part == 0) {
         plain = slices;
         for (const sk_tile &t : w.work) sliced += t.S != hp.tiles[(size_t)hp.first[t.problem]].S;
@@ -148,10 +179,7 @@ int main() {
         if (const char *what = check(hp, all, ignored)) return fail(what, seed);
       } else {
         for (const auto &s : slices) {
-          Slices a = s.second, b = plain[s.first];
-          std::sort(a.begin(), a.end()), std::sort(b.begin(), b.end());
-          a.erase(std::unique(a.begin(), a.end()), a.end()), b.erase(std::unique(b.begin(), b.end()), b.end());
-          if (a != b) return fail("the per-die lists change the slices", seed);
+          if (same(s.second) != same(plain[s.first])) return fail("the per-die lists change the slices", seed);
         }
       }
     }

@@ -1,9 +1,14 @@
 """The device's work list (long records cut, operators of one deadline the longest first): what it must cover, on the CPU under
 the sanitizers, and results of records that only the list cuts, on the GPU."""
+import ctypes
 import os
 import shutil
+import struct
 
 import pytest
+
+import paper_1901_10008_amd as sk
+from workloads import Problem
 
 from test_sanitizers import ENV, ROOT, SAN, _run
 
@@ -16,6 +21,35 @@ def test_work_list_under_sanitizers(tmp_path):
           os.path.join(ROOT, "tests", "sanitize", "work_list_driver.cpp"),
           os.path.join(ROOT, "paper_1901_10008_amd", "csrc", "planner.cpp"), "-o", exe])
     assert "work_list_driver: ok" in _run([exe], env=ENV)
+
+
+def _slices(plan):
+    """{operator: the reduction ranges of its outputs} of what the device runs, and the number of records."""
+    L = sk.lib()
+    L.sk_diag_plan_records.restype = ctypes.c_int64
+    L.sk_diag_plan_records.argtypes = [ctypes.c_void_p, ctypes.c_char_p, ctypes.c_int64]
+    n = L.sk_diag_plan_records(plan.handle, None, 0)
+    buf = ctypes.create_string_buffer(32 * n)
+    assert L.sk_diag_plan_records(plan.handle, buf, n) == n
+    got = {}
+    for r in range(n):
+        problem, _cls, _ks, _S, _m0, _n0, _ml, _nl, k0, k_len, _id = struct.unpack_from("<IHBBIIHHIII", buf.raw, 32 * r)
+        got.setdefault(problem, set()).add((k0, k_len))
+    return got, n
+
+
+# Sixteen fp32 products whose list needs more than the 32 MiB that a table may have: two slices each for a chip of 512 workgroups.
+BEYOND = [Problem(op="gemm", dtype="f32", M=128, N=2048, K=1024)] * 16
+
+
+def test_slices_do_not_depend_on_the_grid_or_the_scratch():
+    problems = [sk.make_problem(s, (1 << 40) + (i << 32), (1 << 40) + (i << 32) + (1 << 30), (1 << 40) + (i << 32) + (2 << 30))
+                for i, s in enumerate(BEYOND)]
+    for grid in (0, 3, 64, 256, 511, 513, 2000):
+        with sk.sk_plan_create(problems, sk.sk_plan_params_default(host_only=1, grid_limit=grid)) as plan:
+            got, n = _slices(plan)
+            assert n == 2 * sk.sk_plan_num_tiles(plan)
+            assert got == {i: {(0, 512), (512, 512)} for i in range(16)}, grid
 
 
 # Few operators with long reductions: the launch would wait for single records, so the list slices them (LDS tiles from 32 stages

@@ -45,6 +45,18 @@ def test_static_launch_matches_the_allocating_one_twice_in_a_row():
     _both_ways(bs, {"xcd_part": 1, "grid_limit": 11}, "sixth call, per-die lists, eleven workgroups")
 
 
+def test_static_launch_slices_like_the_allocating_one_beyond_the_scratch_of_a_table():
+    """A table of 0.1 MiB whose list (two slices of every product) needs 32.2: still the same bits, and on another grid too."""
+    from test_work_list import BEYOND
+    b = H.Batch(BEYOND, seed=7)
+    bits = []
+    for prm in ({}, {"grid_limit": 200}):
+        _both_ways(b, prm, f"list beyond the table's scratch {prm}")
+        bits.append(b.all_output_bits())
+    for x, y in zip(*bits):
+        assert np.array_equal(x, y)
+
+
 def test_static_launch_refuses_what_it_cannot_hold_or_serve():
     specs = workloads.config(2, seed=1)[:3]
     b = H.Batch(specs, seed=1)
