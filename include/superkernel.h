@@ -147,7 +147,9 @@ typedef struct {
                           /* decides: lists, with an eighth of the plan's rectangles per     */
                           /* part, if every operator is in the LDS-tile classes and the sum  */
                           /* of flops / peak exceeds the sum of operand bytes / bandwidth    */
-                          /* (datasheet ratios, no device query); none otherwise             */
+                          /* (datasheet ratios, no device query); none otherwise.  Lists     */
+                          /* that the planner chose itself give way where all operators run  */
+                          /* as runs of pixels (sk_launch), those asked for never do         */
   int32_t reserved;       /* 0                                                               */
 } sk_plan_params;
 
@@ -279,7 +281,9 @@ int32_t sk_plan_grid(const sk_plan *plan);
 /* Which die takes which LDS tile (sk_plan_params.xcd_part; Section 1 item (c): the shape of the execution
  * blocks is the runtime's to choose): offsets[9] and, if `tiles` is not null, at most `cap` table indices:
  * tiles[offsets[x] .. offsets[x+1]) are the records die x takes, in order.  offsets[8] is the number of
- * LDS tiles of the plan, 0 if the plan has no lists.  Host memory, caller-owned. */
+ * LDS tiles of the plan, 0 if the plan has no lists.  (The lists of the table: a plan that launches its
+ * operators as runs of pixels instead of the table's tiles, see sk_launch, does not use those that xcd_part = -1
+ * gave it.)  Host memory, caller-owned. */
 sk_status sk_plan_get_xcd_lists(const sk_plan *plan, uint32_t *offsets, uint32_t *tiles, int64_t cap);
 
 /*

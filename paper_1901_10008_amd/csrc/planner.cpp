@@ -867,8 +867,9 @@ bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile>
     some = some || window[i];
     all = all && window[i];
   }
-  // (the per-die lists of other operators name tiles of the table)
-  if (!some || (!all && !hp.xorder.empty())) return false;
+  // (the per-die lists of other operators name tiles of the table; lists that the caller has asked for are kept: only the planner's own give
+  // way)
+  if (!some || (!hp.xorder.empty() && (!all || hp.params.xcd_part > 0))) return false;
   auto steps_of = [&](size_t i) { return (hp.dev[i].Mg + STEP - 1) / STEP; };
   int64_t per = MOST;
   if (all) {

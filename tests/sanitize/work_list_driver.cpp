@@ -232,6 +232,13 @@ int main() {
       if (next[i] != hp.dev[i].Mg) return fail("pixels missing", seed);
     if (count != w.count || w.ws_f32x4 != 0 || w.ws_off.size() < 1) return fail("counts of the records of pixels", seed);
     std::vector<sk_problem> bad = ps;
+    // lists that were asked for stay: no runs
+    sk_plan_params asked = prm;
+    asked.xcd_part = pick({1, 2, 32});
+    sk::HostPlan kept;
+    if (sk::plan_host(ps.data(), (int)ps.size(), &asked, kept, err) != SK_OK || kept.xorder.empty()) return fail("lists asked for", seed);
+    sk::WorkList k;
+    if (sk::device_list(kept, 1, g() % 2, k) && (k.window || k.xorder.size() < kept.xorder.size())) return fail("lists asked for are dropped", seed);
     sk_problem &b = bad[g() % bad.size()];
     switch (g() % 9) {
       case 0: b.Cin = 128; break;
