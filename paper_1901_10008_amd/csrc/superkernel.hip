@@ -268,12 +268,17 @@ struct sk_plan {
   bool narrow = false;
   int64_t longest_stages = 0;  // stages of the reduction of the longest such tile
   int cus = 0;                 // compute units of the plan's device
-  // (for a launch of the table: one of runs of pixels goes to the general kernel)
-  bool narrow_launch(int64_t tiles) const { return narrow && sk::narrow_pays(only_dtype == SK_F32, longest_stages, tiles, cus); }
   int64_t general_workgroups() const { return host.params.grid_limit > 0 ? host.params.grid_limit : 2 * (int64_t)cus; }
-  int64_t most_workgroups(int64_t tiles) const {
-    if (host.run.window) return general_workgroups();
-    return host.params.grid_limit > 0 ? host.params.grid_limit : (narrow_launch(tiles) ? 3 : 2) * (int64_t)cus;
+  // Kernel and grid of a launch of that many records: of what the device runs in the table's place (`whole`; runs of pixels go to the
+  // general kernel), or of an operator's own table in the baseline (never runs of pixels).
+  struct Shape {
+    bool narrow;
+    int grid;
+  };
+  Shape shape(int64_t records, bool whole) const {
+    const bool three = narrow && !(whole && host.run.window) && sk::narrow_pays(only_dtype == SK_F32, longest_stages, records, cus);
+    const int64_t limit = three && host.params.grid_limit == 0 ? 3 * (int64_t)cus : general_workgroups();
+    return Shape{three, (int)std::min(records, limit)};
   }
   // Every tile is short (at most 64 KB of operands): sk_launch gives workgroup b the tiles b, b + grid, ...
   // instead of running the queue.  A queue claim is an atomic round trip before the next record can be
@@ -489,8 +494,7 @@ sk_status sk_plan_create(const sk_problem *problems, int32_t n, const sk_plan_pa
       delete plan;
       return st;
     }
-    const int64_t ntiles = (int64_t)plan->host.records().size(), limit = plan->most_workgroups(ntiles);
-    plan->grid = (int)(ntiles < limit ? ntiles : limit);
+    plan->grid = plan->shape((int64_t)plan->host.records().size(), true).grid;
     st = upload_tables(plan->host, plan->device, plan->dev);
     if (st != SK_OK) {
       delete plan;
@@ -562,8 +566,9 @@ sk_status sk_release_cached_memory(void) {
 
 // `behind`: an event to complete with the launch (null: none); `packet`: recorded behind it.
 static sk_status launch_range(sk_plan *plan, const DeviceTables &dt, hipStream_t stream, uint32_t begin, uint32_t end,
-                              int grid, bool dynamic, bool write_start, bool whole_table = false, hipEvent_t behind = nullptr, bool packet = false) {
-  if (end <= begin || grid <= 0) return SK_OK;
+                              bool dynamic, bool write_start, bool whole_table = false, hipEvent_t behind = nullptr, bool packet = false) {
+  if (end <= begin) return SK_OK;
+  const sk_plan::Shape shape = plan->shape((int64_t)end - begin, whole_table);
   sk::KernelArgs a;
   // the per-die lists cover the LDS tiles of the whole table, and only the queue hands them out
   const bool lists = whole_table && dynamic && dt.xwork != nullptr;
@@ -580,9 +585,9 @@ static sk_status launch_range(sk_plan *plan, const DeviceTables &dt, hipStream_t
   a.ws = dt.ws;
   a.ws_off = dt.ws_off;
   a.arrive = dt.arrive;
-  const dim3 g((unsigned)grid), b(sk::WG_THREADS);
+  const dim3 g((unsigned)shape.grid), b(sk::WG_THREADS);
   void (*kernel)(const sk::TileWork *, sk::KernelArgs) = nullptr;
-  if (!(whole_table && plan->host.run.window) && plan->narrow_launch((int64_t)end - begin)) {
+  if (shape.narrow) {
     switch (plan->only_dtype) {
       case SK_F32: kernel = sk::sk_superkernel<SK_F32, false, true>; break;
       case SK_BF16: kernel = sk::sk_superkernel<SK_BF16, false, true>; break;
@@ -686,8 +691,8 @@ static sk_status launch_whole(sk_plan *plan, void *hip_stream, bool packet_first
   st = arm_start_stamp(plan, stream, capturing);
   if (st != SK_OK) return st;
   const hipEvent_t behind = launch_event(plan, capturing);
-  st = launch_range(plan, plan->dev, stream, 0u, (uint32_t)plan->host.records().size(), plan->grid,
-                    !plan->fixed_assignment, true, true, behind, packet_first && !plan->launched);
+  st = launch_range(plan, plan->dev, stream, 0u, (uint32_t)plan->host.records().size(), !plan->fixed_assignment, true, true, behind,
+                    packet_first && !plan->launched);
   plan->ledger.after_launch((uintptr_t)stream, capturing, behind && st == SK_OK);
   plan->launched = plan->launched || !capturing;
   return st;
@@ -712,8 +717,8 @@ sk_status sk_launch_sequential(sk_plan *plan, void *hip_stream) {
   if (!plan->seq_ready) {
     std::string err;
     try {
-      st = sk::plan_host_each_alone(plan->host, plan->most_workgroups(1), plan->seq_host, err);
-      if (st == SK_OK && !plan->narrow) (void)sk::balance_each_alone(plan->seq_host, plan->most_workgroups(1));
+      st = sk::plan_host_each_alone(plan->host, plan->general_workgroups(), plan->seq_host, err);
+      if (st == SK_OK && !plan->narrow) (void)sk::balance_each_alone(plan->seq_host, plan->general_workgroups());
     } catch (const std::bad_alloc &) {
       return set_error(SK_ERR_ALLOC, "host allocation failed while planning");
     }
@@ -733,9 +738,7 @@ sk_status sk_launch_sequential(sk_plan *plan, void *hip_stream) {
   const hipEvent_t behind = launch_event(plan, capturing);
   for (size_t i = 0; i < n && st == SK_OK; ++i) {
     const int64_t first = plan->seq_host.first[i], count = plan->seq_host.count[i];
-    const int64_t limit = plan->most_workgroups(count);
-    const int grid = (int)(count < limit ? count : limit);
-    st = launch_range(plan, plan->seq_dev, stream, (uint32_t)first, (uint32_t)(first + count), grid, false, i == 0, false,
+    st = launch_range(plan, plan->seq_dev, stream, (uint32_t)first, (uint32_t)(first + count), false, i == 0, false,
                       i + 1 == n ? behind : nullptr);
   }
   plan->ledger.after_launch((uintptr_t)stream, capturing, behind && st == SK_OK);  // also after a failure: some launches may be out
@@ -769,9 +772,8 @@ sk_status sk_launch_static(sk_plan *plan, void *hip_stream) {
   bind_tables(dt, base, l);
   plan->cus = cus;
   const int64_t ntiles = (int64_t)plan->host.records().size();
-  const int64_t limit = plan->most_workgroups(ntiles);
-  plan->grid = (int)(ntiles < limit ? ntiles : limit);
-  return launch_range(plan, dt, stream, 0u, (uint32_t)ntiles, plan->grid, !plan->fixed_assignment, false, true);
+  plan->grid = plan->shape(ntiles, true).grid;
+  return launch_range(plan, dt, stream, 0u, (uint32_t)ntiles, !plan->fixed_assignment, false, true);
 }
 
 // For tests, not part of the boundary (so not in include/superkernel.h): what the device runs in place of the plan's table; at most `cap`
@@ -781,6 +783,13 @@ int64_t sk_diag_plan_records(const sk_plan *plan, sk_tile *dst, int64_t cap) {
   const std::vector<sk_tile> &r = plan->host.records();
   if (dst && cap > 0) std::memcpy(dst, r.data(), std::min<size_t>((size_t)cap, r.size()) * sizeof(sk_tile));
   return (int64_t)r.size();
+}
+
+// As well: the workgroups of a launch of `records` records of a plan (a host-only one: on 256 compute units), negative if
+// the narrow kernel runs them; `whole` as in sk_plan::shape.
+int32_t sk_diag_plan_shape(const sk_plan *plan, int64_t records, int32_t whole) {
+  const sk_plan::Shape s = plan->shape(records, whole != 0);
+  return s.narrow ? -s.grid : s.grid;
 }
 
 int64_t sk_plan_num_tiles(const sk_plan *plan) { return plan ? (int64_t)plan->host.tiles.size() : -1; }

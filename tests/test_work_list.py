@@ -52,6 +52,25 @@ def test_slices_do_not_depend_on_the_grid_or_the_scratch():
             assert got == {i: {(0, 512), (512, 512)} for i in range(16)}, grid
 
 
+def test_baseline_grid_of_plans_with_runs_of_pixels():
+    """The one-launch-per-operator baseline of such a plan launches tiles: where the kernel of which three workgroups share a compute unit
+    runs them, on three per compute unit, as in a plan of tiles."""
+    L = sk.lib()
+    L.sk_diag_plan_shape.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32]
+    conv = Problem(op="conv", dtype="bf16", Nb=1, H=56, W=56, Cin=64, Cout=64, R=3, S=3, pad_h=1, pad_w=1)
+    problems = [sk.make_problem(conv, (1 << 40) + (i << 32), (1 << 40) + (i << 32) + (1 << 30), (1 << 40) + (i << 32) + (2 << 30))
+                for i in range(64)]
+    with sk.sk_plan_create(problems[:20], sk.sk_plan_params_default(host_only=1)) as tiles, \
+            sk.sk_plan_create(problems, sk.sk_plan_params_default(host_only=1)) as runs, \
+            sk.sk_plan_create(problems, sk.sk_plan_params_default(host_only=1, grid_limit=600)) as limited:
+        assert _slices(tiles)[1] == 500 and _slices(runs)[1] < sk.sk_plan_num_tiles(runs) == 1600
+        for n in (1, 100, 400, 600, 640, 5000):
+            assert L.sk_diag_plan_shape(runs.handle, n, 0) == L.sk_diag_plan_shape(tiles.handle, n, 0)
+            assert 0 < L.sk_diag_plan_shape(runs.handle, n, 1) <= 512
+            assert abs(L.sk_diag_plan_shape(limited.handle, n, 0)) == min(n, 600)
+        assert L.sk_diag_plan_shape(runs.handle, 600, 0) == -600 and L.sk_diag_plan_shape(runs.handle, 5000, 0) == -768
+
+
 # Few operators with long reductions: the launch would wait for single records, so the list slices them (LDS tiles from 32 stages
 # on, blocks of any alignment from 12), and cuts wide weight-streaming records by columns.
 def _cases():
