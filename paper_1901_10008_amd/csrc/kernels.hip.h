@@ -186,10 +186,22 @@ __device__ __forceinline__ uint32_t cvt_bits(float f) {
   return __builtin_bit_cast(uint32_t, f);
 }
 
-// Outputs of whole tiles are stored past the caches (this bit of a buffer store, nontemporal stores elsewhere): the launch does not read them
-// again, and what it does read stays (main workload 1028 -> 1000 us, ResNet layers x16 69.0 -> 67.5, channel-major x8 101 -> 97).  Not
+// Outputs of whole tiles are stored past the caches (this bit of a buffer store, nontemporal stores elsewhere) if FLAG_PAST_CACHES is
+// set: the launch does not read them again, and what it does read stays (main workload 1028 -> 1000 us).  Not
 // the eight-byte stores of the weight-streaming classes: main workload 1002 -> 1019 us.
 constexpr int NONTEMPORAL = 2;
+
+// N pieces of 16 bytes, `step` bytes apart.  (One branch around all of them.)
+template <int N>
+__device__ __forceinline__ void store_out(const u32x4 (&v)[N], __amdgpu_buffer_rsrc_t desc, uint32_t at, uint32_t step, bool past_caches) {
+  if (past_caches) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) __builtin_amdgcn_raw_buffer_store_b128(v[i], desc, at + (uint32_t)i * step, 0, NONTEMPORAL);
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) __builtin_amdgcn_raw_buffer_store_b128(v[i], desc, at + (uint32_t)i * step, 0, 0);
+  }
+}
 
 // Store four consecutive outputs of one row (columns n .. n+3, clipped to n_end).
 template <int DT>
@@ -1044,8 +1056,7 @@ __device__ __forceinline__ void finish_tile(const DevProblem &P, const sk_tile &
       u32x4 v[BM / RPI];
 #pragma unroll
       for (int i = 0; i < BM / RPI; ++i) v[i] = *(const u32x4 *)(lds + pr * OROW + pc * 16 + i * (RPI * OROW));
-#pragma unroll
-      for (int i = 0; i < BM / RPI; ++i) __builtin_amdgcn_raw_buffer_store_b128(v[i], desc, voff + (uint32_t)(i * RPI) * ld, 0, NONTEMPORAL);
+      store_out(v, desc, voff, (uint32_t)RPI * ld, (P.flags & FLAG_PAST_CACHES) != 0);
       return;
     }
 #pragma unroll 1
@@ -1759,8 +1770,7 @@ __device__ __forceinline__ void run_window(const DevProblem &P, const sk_tile &T
 #pragma unroll
     for (int q = 0; q < 4; ++q) v[q] = *(const u32x4 *)(out + (r + 16 * q) * WIN_OROW + (l & 3) * 16);
     const uint32_t at = n < P.Ng ? (uint32_t)(((i * WIN_BLOCK + 64 * wm + r) * P.Ng + n) * 2) : NOWHERE;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) __builtin_amdgcn_raw_buffer_store_b128(v[q], descC, at + (uint32_t)(q * 16 * P.Ng * 2), 0, NONTEMPORAL);
+    store_out(v, descC, at, (uint32_t)(16 * P.Ng * 2), true);
   };
 
   // this lane's two pixels of a step, counted within their image, and how far these move from one step to the next
@@ -2339,7 +2349,11 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         const u32x4 v = *(const u32x4 *)(lds + r * OROW + col * ES);
         if (whole) {
           const int64_t o = NCHW ? pixel0 + (int64_t)(nb + r) * hw : (int64_t)(mb + r) * P.ldc + nb + col;
-          __builtin_nontemporal_store(v, (u32x4_any SK_GLOBAL *)((uintptr_t)P.C + (uintptr_t)(o * ES)));
+          u32x4_any SK_GLOBAL *const dst = (u32x4_any SK_GLOBAL *)((uintptr_t)P.C + (uintptr_t)(o * ES));
+          if ((P.flags & FLAG_PAST_CACHES) != 0)
+            __builtin_nontemporal_store(v, dst);
+          else
+            *dst = v;
         } else {
           const piece_t ev = __builtin_bit_cast(piece_t, v);
 #pragma unroll

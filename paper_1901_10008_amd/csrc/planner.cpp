@@ -205,6 +205,25 @@ static void build_xcd_lists(HostPlan &out, const std::vector<Canon> &canon) {
   out.xoff[8] = (uint32_t)out.xorder.size();
 }
 
+// Whether the outputs of the plan's tiles go past the caches.  The launch itself gains by that, whatever its size (0 to 10 % where it
+// finds its own operands there, as on a relaunch); the launch that reads the outputs loses where they would have been there for it.  With a launch
+// of twice this and more nothing is left of either (256 MB of last-level cache).  Pairs and triples of layers that read each other's
+// outputs in turn, us, in the caches / past them: sixteen 1024-cubed products (101 MB a launch) 88 / 102, four layers of 128 rows from 768 to 3072 and
+// back 36.8 / 40.9, 16 bottlenecks of 14x14x1024 49.8 / 52.5, 64 of 56x56x256 (131 MB) 92.7 / 96.9, channel-major
+// 28x28x128 x64 122.7 / 130.8; above the line 3x3 28x28x128 x256 (178 MB) 175.9 / 168.2, bottlenecks 56x56x256 x96 (196 MB) 132.5 / 129.4, x256
+// 329 / 307, 3x3 56x56x64 x512 269 / 263 (but x256, 224 MB of which half are outputs, 135 / 144).
+static bool past_caches(const HostPlan &hp) {
+  constexpr double LINE = 160.0 * 1024 * 1024;
+  double bytes = 0;
+  for (size_t i = 0; i < hp.dev.size(); ++i) {
+    const DevProblem &d = hp.dev[i];
+    const sk_problem &p = hp.problems[i];
+    const double a = p.op == SK_GEMM ? (double)d.Mg * d.Kg : (double)p.Nb * p.H * p.Wd * p.Cin;
+    bytes += elem_size(d.dtype) * (a + (double)d.Ng * d.Kg + (double)d.Mg * d.Ng);
+  }
+  return bytes > LINE;
+}
+
 sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params *params, HostPlan &out,
                     std::string &err) {
   if (n < 0 || (n > 0 && !problems)) {
@@ -434,6 +453,8 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
     out.dev[i].tile_count = (int32_t)out.count[i];
   }
   build_xcd_lists(out, canon);
+  if (past_caches(out))
+    for (DevProblem &d : out.dev) d.flags |= FLAG_PAST_CACHES;
   return SK_OK;
 }
 

@@ -268,6 +268,26 @@ int main() {
     for (size_t i = 0; i < bad.size(); ++i)
       if (area[i] != (int64_t)hp.dev[i].Mg * hp.dev[i].Ng) return fail("outputs beside runs of pixels", seed);
   }
+  // outputs past the caches: all operators of a plan of more than 160 MiB, or none
+  for (int n : {1, 3, 40}) {
+    for (int k : {1000, 27279, 27280, 80000}) {  // n operators of 2 x (1024 k + k + 1024) bytes
+      std::vector<sk_problem> ps((size_t)n);
+      for (int i = 0; i < n; ++i) {
+        ps[(size_t)i] = sk_problem{};
+        ps[(size_t)i].op = SK_GEMM, ps[(size_t)i].dtype = SK_BF16, ps[(size_t)i].M = 1, ps[(size_t)i].N = 1024, ps[(size_t)i].K = k;
+        ps[(size_t)i].A = (const void *)0x1000, ps[(size_t)i].B = (const void *)0x100000, ps[(size_t)i].C = (void *)(0x100000000 + 4096 * (uintptr_t)i);
+      }
+      sk_plan_params prm;
+      sk_plan_params_default(&prm);
+      prm.host_only = 1;
+      sk::HostPlan hp;
+      std::string err;
+      if (sk::plan_host(ps.data(), n, &prm, hp, err) != SK_OK) return fail(err.c_str(), n);
+      const bool want = (int64_t)n * 2 * (1024LL * k + k + 1024) > (160LL << 20);
+      for (const sk::DevProblem &d : hp.dev)
+        if (((d.flags & sk::FLAG_PAST_CACHES) != 0) != want) return fail("outputs past the caches", n);
+    }
+  }
   if (cut < 100 || sliced < 100 || moved < 100) return fail("too few plans with a list of their own", cut);
   std::puts("work_list_driver: ok");
   return 0;

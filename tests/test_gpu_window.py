@@ -59,6 +59,30 @@ def test_window_plans(name, dtype):
             assert np.array_equal(x, y)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_outputs_past_the_caches(dtype):
+    """Runs of pixels, tiles and blocks for any alignment beside an operator that makes the plan large: their outputs then leave past the
+    caches, with the bits they have in a plan whose outputs do not."""
+    t = torch.bfloat16 if dtype == "bf16" else torch.float16
+    weights, x, y = torch.zeros(90000 * 1024, dtype=t, device="cuda"), torch.ones(1024, dtype=t, device="cuda"), torch.empty(90000, dtype=t, device="cuda")
+    large = sk.make_problem(g(1, 90000, 1024, dtype), x.data_ptr(), weights.data_ptr(), y.data_ptr())
+    nchw = c(14, 14, 64, 60, 3, 3, 1, 1)
+    nchw = dataclasses.replace(nchw, op="conv_nchw")
+    for specs in (CASES["edges"][:5], [g(130, 200, 256), g(200, 64, 136), c(12, 12, 64, 130, 3, 3, 1, 1)],
+                  [g(130, 129, 131), nchw, c(20, 20, 3, 64, 7, 7, 3, 3, st=2), g(70, 64, 128)]):
+        b = H.Batch([dataclasses.replace(s, dtype=dtype) for s in specs], seed=63)
+        bits = []
+        for problems in (b.problems, b.problems + [large]):
+            with sk.sk_plan_create(problems, sk.sk_plan_params_default(grid_limit=3, tail_div=0)) as plan:
+                b.reset_outputs()
+                sk.sk_launch(plan, H.stream_handle())
+                torch.cuda.synchronize()
+                H.check_against_oracle(b, f"{len(problems)} operators")
+                bits.append(b.all_output_bits())
+        for i, (p, q) in enumerate(zip(*bits)):
+            assert np.array_equal(p, q), i
+
+
 @pytest.mark.parametrize("other", [g(70, 64, 128), c(14, 14, 128, 64, 3, 3, 1, 1), c(14, 14, 64, 64, 3, 3, 1, 1, st=2), c(14, 14, 64, 64, 3, 3, 0, 0),
                                    c(14, 14, 64, 60, 3, 3, 1, 1), c(3, 64, 64, 64, 3, 3, 1, 1), c(14, 14, 64, 64, 3, 3, 1, 1, "f16")],
                          ids=["gemm", "channels", "stride", "padding", "columns", "width", "types"])
