@@ -187,7 +187,7 @@ __device__ __forceinline__ uint32_t cvt_bits(float f) {
 }
 
 // Outputs of whole tiles are stored past the caches (this bit of a buffer store, nontemporal stores elsewhere) if FLAG_PAST_CACHES is
-// set: the launch does not read them again, and what it does read stays (main workload 1028 -> 1000 us).  Not
+// set (past_caches in planner.cpp): the launch does not read them again, and what it does read stays (main workload 1028 -> 1000 us).  Not
 // the eight-byte stores of the weight-streaming classes: main workload 1002 -> 1019 us.
 constexpr int NONTEMPORAL = 2;
 
@@ -1680,7 +1680,7 @@ __device__ __forceinline__ void run_lds_tile(const DevProblem &P, const sk_tile 
 //     the ring (a tap outside the image reads a row of zeros instead: one bit per pixel and tap);
 //   * one barrier per 128 pixels (72 MFMAs a wave): the block read next has landed, the one before last is free;
 //   * a step's outputs are staged by the wave itself and stored at the next step's top, so that the wait there is for loads and stores a
-//     whole step old; past the caches, which leaves room there for the pixels (2 to 5 %).
+//     whole step old; in large plans past the caches, which leaves room there for the pixels (2 to 5 %).
 // The sums are taken in the tiles' order: the same bits.
 // 512 tenants of 56x56, 64 to 64 (0.45 GB, 118 GFLOP), every launch on other operands: 214 to 230 us in the kernel for tiles
 // alone, 132 here: 3.4 TB/s of operands and outputs against the 4.8 of a large copy.  Without its MFMAs it takes 107, without its
@@ -1770,7 +1770,7 @@ __device__ __forceinline__ void run_window(const DevProblem &P, const sk_tile &T
 #pragma unroll
     for (int q = 0; q < 4; ++q) v[q] = *(const u32x4 *)(out + (r + 16 * q) * WIN_OROW + (l & 3) * 16);
     const uint32_t at = n < P.Ng ? (uint32_t)(((i * WIN_BLOCK + 64 * wm + r) * P.Ng + n) * 2) : NOWHERE;
-    store_out(v, descC, at, (uint32_t)(16 * P.Ng * 2), true);
+    store_out(v, descC, at, (uint32_t)(16 * P.Ng * 2), (P.flags & FLAG_PAST_CACHES) != 0);
   };
 
   // this lane's two pixels of a step, counted within their image, and how far these move from one step to the next

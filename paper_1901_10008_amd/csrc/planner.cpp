@@ -205,13 +205,13 @@ static void build_xcd_lists(HostPlan &out, const std::vector<Canon> &canon) {
   out.xoff[8] = (uint32_t)out.xorder.size();
 }
 
-// Whether the outputs of the plan's tiles go past the caches.  The launch itself gains by that, whatever its size (0 to 10 % where it
-// finds its own operands there, as on a relaunch); the launch that reads the outputs loses where they would have been there for it.  With a launch
-// of twice this and more nothing is left of either (256 MB of last-level cache).  Pairs and triples of layers that read each other's
+// Whether the outputs of the plan's tiles go past the caches.  The launch itself gains by that (up to 10 % where it finds operands of its
+// own in the caches, as on a relaunch), the launch that reads the outputs loses where they would have been there for it, and in a launch
+// beyond the 256 MB last-level cache most of what it writes is gone when it ends.  Pairs and triples of layers that read each other's
 // outputs in turn, us, in the caches / past them: sixteen 1024-cubed products (101 MB a launch) 88 / 102, four layers of 128 rows from 768 to 3072 and
-// back 36.8 / 40.9, 16 bottlenecks of 14x14x1024 49.8 / 52.5, 64 of 56x56x256 (131 MB) 92.7 / 96.9, channel-major
-// 28x28x128 x64 122.7 / 130.8; above the line 3x3 28x28x128 x256 (178 MB) 175.9 / 168.2, bottlenecks 56x56x256 x96 (196 MB) 132.5 / 129.4, x256
-// 329 / 307, 3x3 56x56x64 x512 269 / 263 (but x256, 224 MB of which half are outputs, 135 / 144).
+// back 36.8 / 40.9, 16 bottlenecks of 14x14x1024 49.8 / 52.5, 3x3 56x56x64 x128 (112 MB) 88.0 / 92.4, 64 bottlenecks of 56x56x256
+// (131 MB) 95.0 / 98.2, channel-major 3x3 28x28x128 x64 122.7 / 130.8; above the line 3x3 28x28x128 x256 (178 MB) 175.9 / 168.2, bottlenecks 56x56x256 x96 (196
+// MB) 132.5 / 129.4, x256 329 / 307, 3x3 56x56x64 x512 269 / 263 (but x256, 224 MB of which half are outputs, 136 / 144).
 static bool past_caches(const HostPlan &hp) {
   constexpr double LINE = 160.0 * 1024 * 1024;
   double bytes = 0;
