@@ -877,8 +877,14 @@ bool window_operator(const HostPlan &hp, size_t i) {
 // round for some workgroups, 20.3 and 18.6, 1600 tiles 37.5 and 28.6, 12800 tiles 214 and 132.
 // How long a run is: in a plan of nothing else, what takes the fewest steps over the rounds of runs; beside other operators, half
 // a workgroup's share of the launch, as for weight streaming.
+// In a plan of several deadlines a run is a fifth of a share at most, so that the first deadlines' operators are not done with the launch's
+// middle, and where that is less than three steps (of a plan of nothing else: with a share of less than twelve) the tiles stay.  512 operators
+// of 56x56 with deadlines of their own, us until the first tenth of them in that order are done, all of them in the mean, the
+// last: as tiles 28.6, 122.9 and 223.8, in the longest runs 90.8, 102.1 and 132.8, in a fifth of a share 28.6, 86.3 and 142.7 (a third 34.8 in the first place, a sixth
+// and an eighth 99 and 100 in the mean); 256: 23.9, 63.6 and 105.8, 50.4, 56.5 and 65.3, three steps 22.8, 57.7 and 90.9; 128: 16.1, 37.5 and 62.2, 34.2, 37.8 and 43.8.
 bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &records, std::vector<int64_t> &count) {
   constexpr int64_t STEP = 128, START = 3, MOST = 500;  // pixels; steps that a start costs; steps of a run (its pixels fit 16 bits)
+  constexpr int64_t DATED_LEAST = 3;
   if (workgroups < 1 || (int64_t)hp.tiles.size() <= workgroups) return false;
   std::vector<char> window(hp.dev.size(), 0);
   bool some = false, all = true;
@@ -891,9 +897,17 @@ bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile>
   // (the per-die lists of other operators name tiles of the table; lists that the caller has asked for are kept: only the planner's own give
   // way)
   if (!some || (!hp.xorder.empty() && (!all || hp.params.xcd_part > 0))) return false;
+  bool dated = false;  // the order of the operators means something
+  for (const sk_problem &p : hp.problems)
+    dated = dated || (hp.params.edf && deadline_key(p.deadline_ms) != deadline_key(hp.problems[0].deadline_ms));
   auto steps_of = [&](size_t i) { return (hp.dev[i].Mg + STEP - 1) / STEP; };
   int64_t per = MOST;
-  if (all) {
+  if (all && dated) {
+    int64_t steps = 0;
+    for (size_t i = 0; i < hp.dev.size(); ++i) steps += steps_of(i);
+    if (steps / workgroups < 4 * DATED_LEAST) return false;
+    per = std::min(MOST, std::max(DATED_LEAST, steps / workgroups / 5));
+  } else if (all) {
     int64_t best = 0, longest = 1;
     for (size_t i = 0; i < hp.dev.size(); ++i) longest = std::max<int64_t>(longest, steps_of(i));
     for (int64_t len = std::min(longest, MOST); len >= 1; len = len > 8 ? len * 7 / 8 : len - 1) {
@@ -918,7 +932,8 @@ bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile>
       const int64_t kb = 128 / elem_size(hp.dev[i].dtype), cols = t.cls < CLS_TILE_128x128 ? (t.n_len + 127) / 128 : 1;
       total += hp.count[i] * (rt.start + (t.k_len + kb - 1) / kb * cols * rt.step);
     }
-    per = std::max<int64_t>(2, std::min(MOST, (total / workgroups / 2 - WINDOW_START) / WINDOW_STEP));
+    per = std::max<int64_t>(2, std::min(MOST, (total / workgroups / (dated ? 5 : 2) - WINDOW_START) / WINDOW_STEP));
+    if (dated && per < DATED_LEAST) return false;
   }
   records.clear();
   count.assign(hp.dev.size(), 0);

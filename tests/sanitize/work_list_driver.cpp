@@ -232,6 +232,30 @@ int main() {
       if (next[i] != hp.dev[i].Mg) return fail("pixels missing", seed);
     if (count != w.count || w.ws_f32x4 != 0 || w.ws_off.size() < 1) return fail("counts of the records of pixels", seed);
     std::vector<sk_problem> bad = ps;
+    // deadlines of their own: no run longer than a fifth of a workgroup's share (but three steps), or tiles
+    std::vector<sk_problem> dated = ps;
+    for (size_t i = 0; i < dated.size(); ++i) dated[i].deadline_ms = (double)(dated.size() - i);
+    const int64_t grid = std::min<int64_t>(tiles - 1, pick({1, 4, 16, 512}));
+    for (int edf : {1, 0}) {
+      sk_plan_params by = prm;
+      by.edf = edf;
+      sk::HostPlan dp;
+      if (sk::plan_host(dated.data(), (int)dated.size(), &by, dp, err) != SK_OK) return fail(err.c_str(), seed);
+      int64_t steps = 0;
+      for (const sk::DevProblem &d : dp.dev) steps += (d.Mg + 127) / 128;
+      sk::WorkList dw;
+      const bool runs = sk::device_list(dp, grid, true, dw) && dw.window;
+      if (edf == 0 || dated.size() == 1) {
+        if (!runs) return fail("no runs of pixels where no order is asked for", seed);
+        continue;
+      }
+      if (runs != (steps / grid >= 12)) return fail("runs of pixels by deadline", seed);
+      if (!runs) continue;
+      for (size_t i = 0; i < dw.work.size(); ++i) {
+        if (dw.work[i].m_len > 128 * std::max<int64_t>(3, steps / grid / 5)) return fail("a run that is long for its deadline", seed);
+        if (i && dated[dw.work[i - 1].problem].deadline_ms > dated[dw.work[i].problem].deadline_ms) return fail("runs out of order", seed);
+      }
+    }
     // lists that were asked for stay: no runs
     sk_plan_params asked = prm;
     asked.xcd_part = pick({1, 2, 32});
