@@ -634,9 +634,12 @@ static RecordTime record_time(const DevProblem &d, const sk_tile &t, bool any) {
 //     workgroup's share of the whole launch: LSTM cells 64 230 -> 215 us, a quarter no better; not those of
 //     operators with deadlines, which run where the table puts them and shrink towards its end: 52 mixed operators 215 -> 217), the others, if they outlast an
 //     even share by a quarter (LDS tiles of 16-bit types: twice that share, a compute unit's that runs one of them at a time: six 45x45 convolutions of
-//     256 channels 35.7 us whole, 43.7 in two slices), into slices of the reduction, of at least 16 stages (blocks of any alignment six), because a slice writes its
-//     sums to memory and the last one reads all of them (with 6 stages nine 15x15 convolutions of 256 channels 24.7 -> 32.6 us,
-//     with 16 24.5).  Weight-streaming records are not sliced any further: 16 low-batch layers 32 -> 39 us.
+//     256 channels 35.7 us whole, 43.7 in two slices), into equal slices of the reduction, as many as
+//     slices that take an even share, and of 16 stages or more (blocks of any alignment eight), cover it: 36 stages 12/12/12, 40 stages 16/16/8, 17 stages
+//     12/5.  All but the last have twelve stages (eight) at least, because a slice writes its
+//     sums to memory and the last one reads all of them (in slices of 6 stages eleven 20x20 convolutions of 192 channels 24.7 -> 32.6 us, by this
+//     rule 24.5).  Holding every slice to 16 (six) by making fewer is slower: nine 14x14 convolutions of 256 channels 19.9 -> 22.7,
+//     three 18.3 -> 21.1, twenty 23.2 -> 24.4, 96 odd-sized operators 69 -> 83.  Weight-streaming records are not sliced any further: 16 low-batch layers 32 -> 39 us.
 //   * Nothing is cut below 14 us: 10 and 18 measure the same.
 // Before / after, us: channel-major ResNet layers x8 140 -> 96, odd-sized operators 134 -> 73, ResNet layers x16 80 -> 70, x3 34 -> 28,
 // BERT layers x8 173 -> 156, stride-2 layers x3 43 -> 33; mixes whose operators all have deadlines of their own as before.
@@ -748,7 +751,7 @@ static bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &reco
         } else if (!impose && t.cls != CLS_WINDOW && hp.params.tail_div > 0 && t.m_len <= 128 && t.n_len <= 128) {
           constexpr int64_t GRAIN = 4;  // stages
           const int64_t kb = 128 / elem_size(d.dtype), k = t.S > 1 ? d.Kg : (int64_t)t.k_len, all = (k + kb - 1) / kb;
-          const int64_t fits = (std::max<int64_t>((most - rt.start - rt.hand) / rt.step, any ? 6 : 16) + GRAIN - 1) / GRAIN * GRAIN;
+          const int64_t fits = (std::max<int64_t>((most - rt.start - rt.hand) / rt.step, any ? 8 : 16) + GRAIN - 1) / GRAIN * GRAIN;
           const int64_t want = std::min<int64_t>((all + fits - 1) / fits, 255);
           const int64_t per = ((all + want - 1) / want + GRAIN - 1) / GRAIN * GRAIN, n = (all + per - 1) / per;
           const int64_t time = rt.start + per * rt.step + rt.hand;

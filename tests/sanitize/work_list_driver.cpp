@@ -134,6 +134,13 @@ int main() {
       if (prm.tail_div == 0)
         for (const sk_tile &t : w.work)
           if (t.S != hp.tiles[(size_t)hp.first[t.problem]].S) return fail("slices without the tail rule", seed);
+      // slices that only the list makes: all but the last of twelve stages at least (blocks of any alignment eight), and equal
+      for (const sk_tile &t : w.work) {
+        const sk::DevProblem &d = hp.dev[t.problem];
+        if (t.S == hp.tiles[(size_t)hp.first[t.problem]].S || t.ks_idx + 1 == t.S) continue;
+        const int64_t stages = t.k_len / (128 / sk::elem_size(d.dtype));
+        if (stages < ((d.flags & 3) == 3 ? 12 : 8) || stages % 4 != 0 || t.k0 != (uint64_t)t.ks_idx * t.k_len) return fail("a short slice", seed);
+      }
       // the slices are those of a launch that fills the chip, whatever the grid; without new ones they are the table's
       for (int64_t other : {(int64_t)512, (int64_t)33}) {
         sk::WorkList o;
