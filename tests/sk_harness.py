@@ -7,6 +7,9 @@ sides consume exactly the same operand values.
 """
 from __future__ import annotations
 
+import ctypes
+import struct
+
 import numpy as np
 import torch
 
@@ -36,6 +39,22 @@ def _to_dev_bits(bits: np.ndarray, dtype: str, device, byte_offset: int = 0, ld:
     signed = host.view(np.int16 if es == 2 else np.int32)
     buf = torch.from_numpy(signed.copy()).to(device)
     return buf, buf.data_ptr() + byte_offset
+
+
+def device_records(plan):
+    """What the device runs in place of the plan's table: (operator, class, slice, slices, m0, n0, rows, columns, k0, k_len, rectangle) of
+    every record; class 11 is a run of pixels."""
+    fn = sk.lib().sk_diag_plan_records
+    fn.restype, fn.argtypes = ctypes.c_int64, [ctypes.c_void_p, ctypes.c_char_p, ctypes.c_int64]
+    n = fn(plan.handle, None, 0)
+    buf = ctypes.create_string_buffer(32 * n)
+    assert fn(plan.handle, buf, n) == n
+    return list(struct.iter_unpack("<IHBBIIHHIII", buf.raw))
+
+
+def runs_of_pixels(plan):
+    """The operators of the plan that the device runs as runs of pixels."""
+    return sorted({r[0] for r in device_records(plan) if r[1] == 11})
 
 
 class Batch:

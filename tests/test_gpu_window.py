@@ -39,13 +39,14 @@ def test_window_plans(name, dtype):
         return b.all_output_bits()
 
     with b.plan() as plan:  # fewer tiles than workgroups: the tile kernels
-        assert sk.sk_plan_num_tiles(plan) < 500
+        assert sk.sk_plan_num_tiles(plan) < 500 and not H.runs_of_pixels(plan)
         tiles = launch(plan)
         H.check_against_oracle(b, f"tiles {name}")
         n = sk.sk_plan_num_tiles(plan)
     for prm in ({"grid_limit": 1}, {"grid_limit": 3}, {"grid_limit": n - 1}, {"grid_limit": 7, "stamps": 1}):
         with b.plan(**prm) as plan:
             assert sk.sk_plan_grid(plan) <= prm["grid_limit"]
+            assert H.runs_of_pixels(plan) == list(range(len(specs)))
             first = launch(plan)
             H.check_against_oracle(b, f"window {name} {prm}")
             again = launch(plan)
@@ -55,6 +56,7 @@ def test_window_plans(name, dtype):
                 done, start, rate = sk.sk_plan_get_stamps(plan)
                 assert rate > 0 and all(d > start for d in done)
     with b.plan(grid_limit=3, host_only=1) as plan:
+        assert H.runs_of_pixels(plan) == list(range(len(specs)))
         for x, y in zip(tiles, launch(plan, sk.sk_launch_static)):
             assert np.array_equal(x, y)
 
@@ -74,6 +76,7 @@ def test_outputs_past_the_caches(dtype):
         bits = []
         for problems in (b.problems, b.problems + [large]):
             with sk.sk_plan_create(problems, sk.sk_plan_params_default(grid_limit=3, tail_div=0)) as plan:
+                assert bool(H.runs_of_pixels(plan)) == (specs[0].Cin == 64)
                 b.reset_outputs()
                 sk.sk_launch(plan, H.stream_handle())
                 torch.cuda.synchronize()
@@ -90,6 +93,7 @@ def test_plans_with_other_operators(other):
     """An operator that keeps its tiles beside runs of pixels (another element type: no runs at all)."""
     b = H.Batch(CASES["edges"][:5] + [other], seed=62)
     with b.plan(grid_limit=3) as plan:
+        assert H.runs_of_pixels(plan) == ([] if other.dtype == "f16" else list(range(5)))
         b.reset_outputs()
         sk.sk_launch(plan, H.stream_handle())
         torch.cuda.synchronize()

@@ -3,11 +3,11 @@ the sanitizers, and results of records that only the list cuts, on the GPU."""
 import ctypes
 import os
 import shutil
-import struct
 
 import pytest
 
 import paper_1901_10008_amd as sk
+import sk_harness as H
 from workloads import Problem
 
 from test_sanitizers import ENV, ROOT, SAN, _run
@@ -25,17 +25,10 @@ def test_work_list_under_sanitizers(tmp_path):
 
 def _slices(plan):
     """{operator: the reduction ranges of its outputs} of what the device runs, and the number of records."""
-    L = sk.lib()
-    L.sk_diag_plan_records.restype = ctypes.c_int64
-    L.sk_diag_plan_records.argtypes = [ctypes.c_void_p, ctypes.c_char_p, ctypes.c_int64]
-    n = L.sk_diag_plan_records(plan.handle, None, 0)
-    buf = ctypes.create_string_buffer(32 * n)
-    assert L.sk_diag_plan_records(plan.handle, buf, n) == n
-    got = {}
-    for r in range(n):
-        problem, _cls, _ks, _S, _m0, _n0, _ml, _nl, k0, k_len, _id = struct.unpack_from("<IHBBIIHHIII", buf.raw, 32 * r)
-        got.setdefault(problem, set()).add((k0, k_len))
-    return got, n
+    records, got = H.device_records(plan), {}
+    for r in records:
+        got.setdefault(r[0], set()).add((r[8], r[9]))
+    return got, len(records)
 
 
 # Sixteen fp32 products whose list needs more than the 32 MiB that a table may have: two slices each for a chip of 512 workgroups.
