@@ -204,19 +204,21 @@ sk_status sk_release_cached_memory(void);
 
 /*
  * Run every operator of the plan in ONE kernel launch on `hip_stream`
- * (Sections 1 and 5.3: the superkernel).  Persistent workgroups take tiles
- * from the table in order, so operators with earlier deadlines start first:
- * workgroup b starts on tile b and takes further tiles through a single atomic
- * counter; a plan whose tiles are all short (at most 64 KB of operands each)
- * skips the counter and gives workgroup b the tiles b, b + grid, ...  With
- * (Operators of one deadline, so all that have none, may start in another
- * order than the table's, those with the longest tiles first, and long tiles
- * may run in parts: the table is the contract of what is computed and of the
- * deadlines' order.)  With
- * per-die lists (params.xcd_part) a position of the table that holds an LDS tile only says
- * that one LDS tile is due: the workgroup runs the next tile of its die's list
- * (sk_plan_get_xcd_lists), so operators still start in table order, and every
- * tile runs exactly once with the same result bits.
+ * (Sections 1 and 5.3: the superkernel).  The launch runs a list of records that
+ * is made from the table with the plan: the table says what is computed and in
+ * which order of deadlines.  Operators of one deadline, so all that have none,
+ * may stand in another order than the table's, those with the longest tiles
+ * first; long tiles may be cut, by columns or along the reduction; and 3x3
+ * convolutions of 64 channels may run as longer runs of pixels.  Persistent
+ * workgroups take records from the list in order, so operators with earlier
+ * deadlines start first: workgroup b starts on record b and takes further ones
+ * through a single atomic counter; a plan whose tiles are all short (at most
+ * 64 KB of operands each) skips the counter and gives workgroup b the records
+ * b, b + grid, ...  With per-die lists (params.xcd_part) a position of the list
+ * that holds an LDS tile only says that one LDS tile is due: the workgroup runs
+ * the next tile of its die's list (sk_plan_get_xcd_lists), so operators still
+ * start in that order, and every tile runs exactly once with the same result
+ * bits.
  * Asynchronous.  Needs a device-resident plan (SK_ERR_STATE otherwise).
  * A plan has one tile queue and one set of split-reduction counters, which the
  * kernel re-arms itself when it ends: launches of ONE plan must not overlap
@@ -224,8 +226,9 @@ sk_status sk_release_cached_memory(void);
  * if the plan's previous launch went to another stream and still runs.
  * The call makes no allocation, copy, memset or host synchronisation, so it may
  * be captured into a HIP graph; the plan must then outlive the graph's
- * replays.  (A plan with stamps enabled launches one more, one-thread kernel
- * that resets the start stamp.)
+ * replays.  (A plan with stamps enabled launches one more, small kernel ahead,
+ * which resets the start stamp; its first launch, if not captured, does
+ * without.)
  */
 sk_status sk_launch(sk_plan *plan, void *hip_stream);
 
@@ -251,14 +254,15 @@ sk_status sk_launch_sequential(sk_plan *plan, void *hip_stream);
  * queue, split-reduction counters and workspace) placed in a fixed array inside
  * the library's code objects (one per GPU, and a larger one for plans whose
  * slices need it) instead of an allocated block.  The call enqueues one copy of
- * the plan's table image from
- * host memory to that array and one kernel launch on `hip_stream`, and calls no
- * hipMalloc, hipFree or other allocating routine; the first call on a device
- * looks up the array's address and the device's size.  Same results as
- * sk_launch, bit for bit (same kernel, same slices of every reduction).
- * SK_ERR_UNSUPPORTED if the plan's table and its workspace exceed SK_STATIC_SCRATCH_BYTES,
- * SK_ERR_STATE for a plan that is not host-only or has stamps enabled.
- * The calls on a GPU share its arrays: calls that overlap on one GPU
+ * the plan's table image from host memory to that array and one kernel launch
+ * on `hip_stream`, and calls no hipMalloc, hipFree or other allocating routine;
+ * the first call on a device looks up the array's address and the device's size.
+ * Same results as sk_launch, bit for bit (same kernel, same slices of every
+ * reduction).
+ * SK_ERR_UNSUPPORTED if the plan's table and its workspace exceed
+ * SK_STATIC_SCRATCH_BYTES, SK_ERR_STATE for a plan that is not host-only or has
+ * stamps enabled.
+ * All calls on a GPU share its arrays: calls that overlap on one GPU
  * (different streams, or different host threads without ordering) race and give
  * wrong results; calls on one stream are ordered by the stream.  The plan must
  * stay alive until the call has returned; A, B and C as for sk_launch.
@@ -272,7 +276,8 @@ int64_t sk_plan_num_tiles(const sk_plan *plan);    /* < 0 on error */
 int32_t sk_plan_num_problems(const sk_plan *plan); /* < 0 on error */
 /* Copies the flat table (num_tiles * 32 bytes) to host memory `dst`. */
 sk_status sk_plan_get_tiles(const sk_plan *plan, void *dst, int64_t dst_bytes);
-/* Execution order: order[i] = index of the i-th operator to start (n entries). */
+/* The table's order: order[i] = index of its i-th operator (n entries).  Operators start in it, but for those of
+ * one deadline, which may change places (sk_launch). */
 sk_status sk_plan_get_order(const sk_plan *plan, int32_t *order);
 /* Per operator (by index): first record and number of records in the table. */
 sk_status sk_plan_get_ranges(const sk_plan *plan, int64_t *first_tile, int64_t *tile_count);
