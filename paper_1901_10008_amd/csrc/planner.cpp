@@ -670,9 +670,8 @@ static bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &reco
   std::vector<Op> ops;
   ops.reserve(hp.dev.size());
   auto any_of = [&](const sk_tile &t) { return runs_in_any_blocks(hp.dev[t.problem], t); };
-  auto stages_of = [&](const sk_tile &t) {
-    const int64_t kb = 128 / elem_size(hp.dev[t.problem].dtype);
-    return ((int64_t)t.k_len + kb - 1) / kb;
+  auto stages_of = [&](const sk_tile &t) -> int64_t {  // (shifts: this runs for every record)
+    return hp.dev[t.problem].dtype == SK_F32 ? ((int64_t)t.k_len + 31) >> 5 : ((int64_t)t.k_len + 63) >> 6;
   };
   auto columns_of = [](const sk_tile &t, bool any) -> int64_t {  // blocks of 128 that a weight-streaming record walks one after the other
     return t.cls < CLS_TILE_128x128 && !any ? (t.n_len + 127) / 128 : 1;
@@ -683,7 +682,7 @@ static bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &reco
     return rt.start + stages_of(t) * columns_of(t, any) * rt.step + (t.S > 1 ? rt.hand : 0);
   };
   auto imposed = [&](const sk_tile &t) { return impose && t.out_tile_id < impose->size() ? (*impose)[t.out_tile_id] : Slicing{}; };
-  auto alike = [](const sk_tile &a, const sk_tile &b) { return a.m_len == b.m_len && a.n_len == b.n_len && a.k_len == b.k_len; };
+  auto alike = [](const sk_tile &a, const sk_tile &b) { return a.m_len == b.m_len && a.n_len == b.n_len && a.k_len == b.k_len && a.S == b.S; };
   int64_t total = 0;
   for (size_t i = 0; i < records.size();) {
     Op op{(int32_t)records[i].problem, i, 0, 0, 0, 0, false};
@@ -705,23 +704,46 @@ static bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &reco
 
   bool changed = false;
   std::vector<Slicing> slicing;
+  auto slice_anew = [&](const sk_tile &t, const Rect &x) {
+    if (slicing.size() <= t.out_tile_id) slicing.resize(t.out_tile_id + 1);
+    slicing[t.out_tile_id] = Slicing{x.S, x.slice};
+  };
   for (Op &op : ops) {
     if (op.longest * 10 <= std::max(SHORTEST, share / 2) * 11 && !op.sliced) continue;
     const bool dated = hp.params.edf && std::isfinite(deadline_key(hp.problems[op.problem].deadline_ms));
     op.rect = rects.size();
+    const sk_tile *timed = nullptr;
+    int64_t time = 0;
     for (size_t i = op.first; i < op.first + op.count; ++i) {
       const sk_tile &t = records[i];
+      if (!timed || !alike(*timed, t)) {
+        timed = &t;
+        time = time_of(t);
+      }
       if (i == op.first || t.out_tile_id != records[i - 1].out_tile_id) rects.push_back(Rect{i, 0, 0, t.n_len, t.S, t.k_len});
       Rect &x = rects.back();
       ++x.count;
-      x.time = std::max(x.time, time_of(t));
+      x.time = std::max(x.time, time);
       x.width = std::max<int64_t>(x.width, t.n_len);
     }
     op.rects = rects.size() - op.rect;
     op.longest = 0;
+    const Rect *last = nullptr;  // the rectangle before, settled, and what its time was
+    int64_t last_time = 0;
     for (size_t r = op.rect; r < op.rect + op.rects; ++r) {
       Rect &x = rects[r];
       const sk_tile &t = records[x.first];
+      if (last && !impose && last_time == x.time && alike(records[last->first], t)) {  // settled alike
+        x.time = last->time;
+        x.width = std::min(x.width, last->width);
+        x.S = last->S;
+        x.slice = last->slice;
+        if (x.S != t.S) slice_anew(t, x);
+        last = &x;
+        continue;
+      }
+      last = &x;
+      last_time = x.time;
       const DevProblem &d = hp.dev[t.problem];
       const bool any = any_of(t), stream = !any && t.cls < CLS_TILE_128x128;
       const int64_t most = std::max<int64_t>(SHORTEST, stream ? share / 2 : any || d.dtype == SK_F32 ? share * 5 / 4 : share * 2);
@@ -760,8 +782,7 @@ static bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &reco
             x.slice = per * kb;
             x.time = time;
             changed = true;
-            if (slicing.size() <= t.out_tile_id) slicing.resize(t.out_tile_id + 1);
-            slicing[t.out_tile_id] = Slicing{x.S, x.slice};
+            slice_anew(t, x);
           }
         }
       }
@@ -939,6 +960,7 @@ bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile>
     if (dated && per < DATED_LEAST) return false;
   }
   records.clear();
+  records.reserve(hp.tiles.size());  // (there are fewer runs than tiles)
   count.assign(hp.dev.size(), 0);
   uint32_t id = 0x80000000u;  // (rectangles are numbered anew later; here they only have to differ)
   for (const int32_t o : hp.order) {
