@@ -102,7 +102,7 @@ sk_status get_stamps(sk_queue *q, size_t n, StampBuffer *out) {
   size_t cap = 1024;
   while (cap < n) cap *= 2;
   void *p = nullptr;
-  const hipError_t e = hipHostMalloc(&p, cap * sizeof(uint64_t), hipHostMallocDefault);
+  const hipError_t e = hipHostMalloc(&p, cap * sizeof(uint64_t), hipHostMallocPortable);  // (whichever device is current when it is used)
   if (e != hipSuccess) return hip_fail("hipHostMalloc", e);
   *out = StampBuffer{(uint64_t *)p, cap};
   return SK_OK;
@@ -316,10 +316,16 @@ sk_status sk_queue_create(const sk_queue_params *params, void *hip_stream, sk_qu
   if (prm.policy != SK_QUEUE_SEQUENTIAL) {
     // (not in the first launch: pinning memory takes some 20 us; where there is none to be had that launch says so)
     StampBuffer b;
-    if (get_stamps(q, 1, &b) == SK_OK)
-      q->spare_stamps.push_back(b);
-    else
-      (void)hipGetLastError();
+    try {
+      q->spare_stamps.reserve(1);
+      if (get_stamps(q, 1, &b) == SK_OK)
+        q->spare_stamps.push_back(b);
+      else
+        (void)hipGetLastError();
+    } catch (const std::bad_alloc &) {
+      delete q;
+      return sk::set_last_error(SK_ERR_ALLOC, "host allocation failed");
+    }
   }
   *out = q;
   return SK_OK;
