@@ -1742,6 +1742,10 @@ __device__ __forceinline__ void run_window(const DevProblem &P, const sk_tile &T
     dma_pixels(desc, v[0], v[1], v[2], v[3], lds_base + (uint32_t)slot * (WIN_BLOCK * 128u) + (uint32_t)wave * 4096u);
   };
   const int blocks = (pixels + WIN_BLOCK - 1) / WIN_BLOCK;
+#ifdef SK_DIAG_CLOCKS
+  const int diag_tile = pf.diag_tile;
+#endif
+  SK_DIAG(1);
   if (tid < 8) ((u32x4 *)(lds + WIN_ZERO))[tid] = u32x4{0u, 0u, 0u, 0u};
   load_block(0, 0);
   if (blocks > 1) load_block(1, 1);
@@ -1858,8 +1862,11 @@ __device__ __forceinline__ void run_window(const DevProblem &P, const sk_tile &T
         *(u32x2 *)(out + (32 * f + (l & 31)) * WIN_OROW + (8 * j + 4 * (l >> 5)) * 2) = o;
       }
     slot = slot == 2 ? 0 : slot + 1;
+    if (i == 0) SK_DIAG(2);
   }
+  SK_DIAG(3);
   store_step(steps - 1);
+  SK_DIAG(4);
 }
 
 // ---------------------------------------------------------------------------

@@ -25,7 +25,7 @@ import os
 import sys
 
 PHASES = ("set-up", "first step", "main loop", "outputs", "hand-over", "whole tile")
-CLASS_NAMES = {0: "skinny, 16 rows", 3: "skinny, 32 rows", 6: "skinny, 64 rows", 9: "LDS tile 128x128", 10: "LDS tile 128x64"}
+CLASS_NAMES = {0: "skinny, 16 rows", 3: "skinny, 32 rows", 6: "skinny, 64 rows", 9: "LDS tile 128x128", 10: "LDS tile 128x64", 11: "run of pixels"}
 
 
 def end_summary(stamps) -> str:
@@ -50,7 +50,7 @@ def end_summary(stamps) -> str:
     if any(x[3] for x in last):
         lines.append("(some workgroups ran more tiles than are stamped: their end is that of the last stamped tile)")
     lines.append("last to finish (workgroup, class and length of its last tile, end): " + "  ".join(
-        f"{last[i][0]} {'LDS tile' if last[i][1] >= 9 else 'skinny'} {last[i][2]:.0f} us, {e[i]:.0f}" for i in np.argsort(-e)[:8]))
+        f"{last[i][0]} {'run' if last[i][1] == 11 else 'LDS tile' if last[i][1] >= 9 else 'skinny'} {last[i][2]:.0f} us, {e[i]:.0f}" for i in np.argsort(-e)[:8]))
     return "\n".join(lines)
 
 
