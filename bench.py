@@ -326,7 +326,8 @@ def measured_ceilings(torch, achieved_gbs, achieved_tflops):
             return {"error": f"sk_ceiling_lds_read status {st}"}
         res["lds_fragment_read_GBs"] = round(g.value, 1)
         res["lds_fragment_read_bytes_per_clk_per_cu"] = round(bpc.value, 1)
-        # the LDS-tile stage loop by itself on sixteen 2048-cubed products: whole, without operand loads, loads only
+        # an earlier form of the LDS-tile stage loop by itself on sixteen 2048-cubed products: whole (the superkernel is past that by now), without
+        # operand loads, loads only
         del buf
         lib.sk_ceiling_tile_loop.argtypes = [C.c_int, C.c_void_p, C.c_void_p, C.c_void_p, C.POINTER(C.c_double)]
         ta = (torch.randn(16 * 2048 * 2048, device="cuda") * 0.5).to(torch.bfloat16)

@@ -1684,8 +1684,8 @@ __device__ __forceinline__ void run_lds_tile(const DevProblem &P, const sk_tile 
 // The sums are taken in the tiles' order: the same bits.
 // 512 tenants of 56x56, 64 to 64 (0.45 GB, 118 GFLOP), every launch on other operands: 214 to 230 us in the kernel for tiles
 // alone, 132 here: 3.4 TB/s of operands and outputs against the 4.8 of a large copy.  Without its MFMAs it takes 107, without its
-// fragment reads 120, without storing the outputs 112 (of 130, operands the same every time): bound by memory, with the
-// MFMAs (46 % of the cycles) not quite beside it.  Fragments two or three steps ahead measure the same.
+// fragment reads 120, without storing the outputs 112 (of 130, operands the same every time): bound by memory (1.11 times the algorithmic
+// bytes), with the MFMAs (42 % of the SIMD cycles by SQ_VALU_MFMA_BUSY_CYCLES) not quite beside it.  Fragments two or three steps ahead measure the same.
 constexpr int WIN_BLOCK = 128;                          // pixels per step and ring block
 constexpr int WIN_RING = 3 * WIN_BLOCK;                 // pixels in the ring
 constexpr int WIN_OROW = 80;                            // bytes of 32 outputs in LDS, padded
