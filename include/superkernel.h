@@ -256,7 +256,9 @@ sk_status sk_launch_sequential(sk_plan *plan, void *hip_stream);
  * slices need it) instead of an allocated block.  The call enqueues one copy of
  * the plan's table image from host memory to that array and one kernel launch
  * on `hip_stream`, and calls no hipMalloc, hipFree or other allocating routine;
- * the first call on a device looks up the array's address and the device's size.
+ * the first call on a device looks up the array's address and the device's size
+ * (the first plan that needs the larger array that one's: make it outside a
+ * stream capture, as the first call).
  * Same results as sk_launch, bit for bit (same kernel, same slices of every
  * reduction).
  * SK_ERR_UNSUPPORTED if the plan's table and its workspace exceed
