@@ -1941,7 +1941,7 @@ __device__ __forceinline__ void run_generic(const DevProblem *P_mem, const sk_ti
 //     of contiguous elements (a GEMM row; for an NHWC convolution the S * Cin elements under one filter row),
 //     each padded to whole 16-byte pieces.  A piece that reaches beyond the run, or beyond the part of it that
 //     lies in the image, is read from the nearest place inside and shifted, with zeros behind it.
-//   * a channel-major image has no contiguous runs along the reduction.  There the lanes of a wave take
+//   * a channel-major image has no contiguous runs along the reduction.  There (where run_tile_planes does not serve it) the lanes of a wave take
 //     64 consecutive pixels under one reduction index (channel and tap are scalar; whether a pixel's tap lies in
 //     the image is one bit each of a row and a column mask), so a load of single elements is one
 //     coalesced access and costs three vector instructions beside it.  The block is computed transposed (output
@@ -1961,6 +1961,173 @@ __device__ __forceinline__ bool holds_a_piece(const DevProblem &P) {
   constexpr int CE = 16 / ES;
   const int64_t a = P.gather ? (int64_t)P.H * P.W * P.Cin : (int64_t)(P.Mg - 1) * P.lda + P.Kg;
   return (P.nchw || a >= CE) && (int64_t)(P.Ng - 1) * P.ldb + P.Kg >= CE;
+}
+
+// A slice of a split reduction of run_tile_any or run_tile_planes (see below) hands its partial sums over; true in the workgroup that
+// arrived last, with the sum of all slices in `acc`.
+template <bool NCHW, int FM, int FN>
+__device__ __forceinline__ bool any_handover(const sk_tile &T, const SplitK &sp, unsigned char *lds, uint32_t *s_flag, int tid,
+                                             f32x16 (&acc)[FN][FM]) {
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wm = wave & 1, wn = wave >> 1;
+  const int l32 = lane & 31, half = lane >> 5;
+  // A slice of a split reduction (such a rectangle is a single block here: at most 128 x 128, or
+  // 16, 32 or 64 rows x 128 columns in the skinny classes).  Partial sums go to the rectangle's
+  // workspace, which holds per slice `rows` x 128 (64 for the 64-column class) floats, as 16-byte
+  // pieces indexed by (quad of consecutive outputs, MFMA row); the last slice to arrive adds
+  // all of them in slice order and stores the result.  Same hand-over as in run_tile.
+  // The accumulator quads of a thread wait in LDS meanwhile (free by now: the last stage
+  // ended with a barrier; a slot per thread and quad), so that the loops below can run rolled up:
+  // unrolled over the accumulators they cost this kernel forty registers it does not have.
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  static_assert(FN * FM * 4 * WG_THREADS * 16 <= LDS_TILE_BYTES, "the accumulators do not fit the LDS buffer");
+  f32x4 *slot = (f32x4 *)lds + tid;  // quad p of this thread: slot[p * WG_THREADS]
+#pragma unroll
+  for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        slot[((fn * FM + fm) * 4 + q) * WG_THREADS] =
+            f32x4{acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1], acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]};
+  const int rows = T.cls >= CLS_TILE_128x128 ? 128 : 16 << (T.cls / 3);
+  const int cols = T.cls == CLS_TILE_128x64 ? 64 : 128;
+  const int lrows = NCHW ? cols : rows, quads = (NCHW ? rows : cols) / 4;
+  const size_t per_slice = (size_t)lrows * quads;  // f32x4 units
+  unsigned long long *mine = (unsigned long long *)(sp.ws + sp.ws_off[T.out_tile_id]);
+  // where quad p = (fn*FM + fm)*4 + q of this thread lies in slice 0, or null if outside the rectangle's rows / columns
+  auto place = [&](int p) -> unsigned long long * {
+    const int fn = p / (4 * FM), fm = (p >> 2) % FM, q = p & 3;
+    const int r = (wm * FM + fm) * 32 + l32, g = (wn * FN + fn) * 8 + q * 2 + half;
+    if (r >= lrows || g >= quads) return nullptr;
+    return mine + 2 * ((size_t)g * lrows + r);
+  };
+#pragma unroll 1
+  for (int p = 0; p < FN * FM * 4; ++p) {
+    unsigned long long *q = place(p);
+    if (q) {
+      q += 2 * (size_t)T.ks_idx * per_slice;
+      const f32x4 v = slot[p * WG_THREADS];
+      __hip_atomic_store(q, __builtin_bit_cast(unsigned long long, f32x2{v.x, v.y}), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(q + 1, __builtin_bit_cast(unsigned long long, f32x2{v.z, v.w}), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0);  // all counters to zero: the stores above have completed
+  __syncthreads();
+  if (tid == 0)
+    *s_flag = __hip_atomic_fetch_add(&sp.arrive[T.out_tile_id], 1u, SK_ARRIVE_ORDER, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (*s_flag != (uint32_t)T.S - 1) return false;
+#pragma unroll 1
+  for (int p = 0; p < FN * FM * 4; ++p) {
+    unsigned long long *q = place(p);
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    if (q) {
+      for (int s2 = 0; s2 < T.S; ++s2, q += 2 * per_slice) {
+        const f32x2 lo = __builtin_bit_cast(f32x2, __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const f32x2 hi = __builtin_bit_cast(f32x2, __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        sum += f32x4{lo.x, lo.y, hi.x, hi.y};
+      }
+    }
+    slot[p * WG_THREADS] = sum;
+  }
+  if (tid == 0)  // re-arm for the next launch
+    __hip_atomic_store(&sp.arrive[T.out_tile_id], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+    for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 v = slot[((fn * FM + fm) * 4 + q) * WG_THREADS];
+        acc[fn][fm][4 * q] = v.x;
+        acc[fn][fm][4 * q + 1] = v.y;
+        acc[fn][fm][4 * q + 2] = v.z;
+        acc[fn][fm][4 * q + 3] = v.w;
+      }
+  __syncthreads();  // the slots have been read: the outputs are staged in the same LDS next
+  return true;
+}
+
+// Outputs of a block of run_tile_any or run_tile_planes (rows mb .., columns nb ..): through LDS, so that they leave as runs of consecutive places.
+template <int DT, bool NCHW, int ROWS, int COLS>
+__device__ __forceinline__ void any_outputs(const DevProblem *P_mem, const sk_tile *T_mem, int mb, int nb, unsigned char *lds, int tid,
+                                            f32x16 (&acc)[COLS / 64][ROWS / 64]) {
+  constexpr int ES = Elem<DT>::ES;
+  constexpr int CE = 16 / ES;
+  constexpr int FM = ROWS / 64, FN = COLS / 64;
+  using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
+  typedef elem_t piece_t __attribute__((ext_vector_type(CE)));
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wm = wave & 1, wn = wave >> 1;
+  const int l32 = lane & 31, half = lane >> 5;
+  // (the record is read again: kept through the stages, what the outputs need of it costs the mixed-type kernel a quarter
+  // more spilled scalars)
+  const DevProblem P = load_record(P_mem);
+  const sk_tile T = load_record(T_mem);
+  const int m_end = (int)T.m0 + (int)T.m_len, n_end = (int)T.n0 + (int)T.n_len, hw = P.Ho * P.Wo;
+  // lane holds, per (fn, fm): MFMA row l32, columns 8*(i/4) + 4*half + (i%4)
+  constexpr int OROW = COLS * ES + 16;
+  static_assert(ROWS * OROW <= LDS_TILE_BYTES, "output tile does not fit the LDS buffer");
+#pragma unroll
+  for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+    for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        unsigned char *d = lds + ((wm * FM + fm) * 32 + l32) * OROW + ((wn * FN + fn) * 32 + 8 * q + 4 * half) * ES;
+        if constexpr (ES == 4) {
+          *(f32x4 *)d = f32x4{acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1], acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]};
+        } else {
+          u32x2 o;
+          o.x = cvt_pack<DT>(acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1]);
+          o.y = cvt_pack<DT>(acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]);
+          *(u32x2 *)d = o;
+        }
+      }
+  __syncthreads();
+  constexpr int PIECES = COLS / CE, RPI = WG_THREADS / PIECES;
+  const int col = (tid % PIECES) * CE;
+  const int row_end = NCHW ? n_end - nb : m_end - mb, col_end = NCHW ? m_end - mb : n_end - nb;
+  // NCHW: the piece's pixels (its first one, and whether they lie in one image)
+  int64_t pixel0 = 0;
+  bool whole = col + CE <= col_end;
+  if constexpr (NCHW) {
+    if (col < col_end) {
+      pixel0 = nchw_out_base(P, mb + col);
+      whole = whole && nchw_out_base(P, mb + col + CE - 1) == pixel0 + CE - 1;
+    }
+  }
+  // (the rule for the caches outside the loop: beside each store it cost stride-2 layers x4 to x16 1 to 2 %)
+  auto store_rows = [&](auto past_caches) {
+#pragma unroll 1
+    for (int r = tid / PIECES; r < row_end && r < ROWS; r += RPI) {
+      if (col >= col_end) break;
+      const u32x4 v = *(const u32x4 *)(lds + r * OROW + col * ES);
+      if (whole) {
+        const int64_t o = NCHW ? pixel0 + (int64_t)(nb + r) * hw : (int64_t)(mb + r) * P.ldc + nb + col;
+        u32x4_any SK_GLOBAL *const dst = (u32x4_any SK_GLOBAL *)((uintptr_t)P.C + (uintptr_t)(o * ES));
+        if constexpr (decltype(past_caches)::value)
+          __builtin_nontemporal_store(v, dst);
+        else
+          *dst = v;
+      } else {
+        const piece_t ev = __builtin_bit_cast(piece_t, v);
+#pragma unroll
+        for (int e = 0; e < CE; ++e)
+          if (col + e < col_end) {
+            const int64_t o = NCHW ? nchw_out_base(P, mb + col + e) + (int64_t)(nb + r) * hw : (int64_t)(mb + r) * P.ldc + nb + col + e;
+            *(elem_t SK_GLOBAL *)((uintptr_t)P.C + (uintptr_t)(o * ES)) = ev[e];
+          }
+      }
+    }
+  };
+  if ((P.flags & FLAG_PAST_CACHES) != 0)
+    store_rows(std::true_type{});
+  else
+    store_rows(std::false_type{});
 }
 
 template <int DT, bool NCHW, int BM, int BN>
@@ -2231,154 +2398,251 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
         __syncthreads();  // stage s+1 is written, and everyone has read stage s
       }
 
-      if (T.S > 1) {
-        // A slice of a split reduction (such a rectangle is a single block here: at most 128 x 128, or
-        // 16, 32 or 64 rows x 128 columns in the skinny classes).  Partial sums go to the rectangle's
-        // workspace, which holds per slice `rows` x 128 (64 for the 64-column class) floats, as 16-byte
-        // pieces indexed by (quad of consecutive outputs, MFMA row); the last slice to arrive adds
-        // all of them in slice order and stores the result.  Same hand-over as in run_tile.
-        // The accumulator quads of a thread wait in LDS meanwhile (free by now: the last stage
-        // ended with a barrier; a slot per thread and quad), so that the loops below can run rolled up:
-        // unrolled over the accumulators they cost this kernel forty registers it does not have.
-        typedef float f32x2 __attribute__((ext_vector_type(2)));
-        static_assert(FN * FM * 4 * WG_THREADS * 16 <= LDS_TILE_BYTES, "the accumulators do not fit the LDS buffer");
-        f32x4 *slot = (f32x4 *)lds + tid;  // quad p of this thread: slot[p * WG_THREADS]
-#pragma unroll
-        for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-          for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              slot[((fn * FM + fm) * 4 + q) * WG_THREADS] =
-                  f32x4{acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1], acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]};
-        const int rows = T.cls >= CLS_TILE_128x128 ? 128 : 16 << (T.cls / 3);
-        const int cols = T.cls == CLS_TILE_128x64 ? 64 : 128;
-        const int lrows = NCHW ? cols : rows, quads = (NCHW ? rows : cols) / 4;
-        const size_t per_slice = (size_t)lrows * quads;  // f32x4 units
-        unsigned long long *mine = (unsigned long long *)(sp.ws + sp.ws_off[T.out_tile_id]);
-        // where quad p = (fn*FM + fm)*4 + q of this thread lies in slice 0, or null if outside the rectangle's rows / columns
-        auto place = [&](int p) -> unsigned long long * {
-          const int fn = p / (4 * FM), fm = (p >> 2) % FM, q = p & 3;
-          const int r = (wm * FM + fm) * 32 + l32, g = (wn * FN + fn) * 8 + q * 2 + half;
-          if (r >= lrows || g >= quads) return nullptr;
-          return mine + 2 * ((size_t)g * lrows + r);
-        };
-#pragma unroll 1
-        for (int p = 0; p < FN * FM * 4; ++p) {
-          unsigned long long *q = place(p);
-          if (q) {
-            q += 2 * (size_t)T.ks_idx * per_slice;
-            const f32x4 v = slot[p * WG_THREADS];
-            __hip_atomic_store(q, __builtin_bit_cast(unsigned long long, f32x2{v.x, v.y}), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(q + 1, __builtin_bit_cast(unsigned long long, f32x2{v.z, v.w}), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-          }
-        }
-        __builtin_amdgcn_s_waitcnt(0);  // all counters to zero: the stores above have completed
-        __syncthreads();
-        if (tid == 0)
-          *s_flag = __hip_atomic_fetch_add(&sp.arrive[T.out_tile_id], 1u, SK_ARRIVE_ORDER, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        if (*s_flag != (uint32_t)T.S - 1) return;
-#pragma unroll 1
-        for (int p = 0; p < FN * FM * 4; ++p) {
-          unsigned long long *q = place(p);
-          f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-          if (q) {
-            for (int s2 = 0; s2 < T.S; ++s2, q += 2 * per_slice) {
-              const f32x2 lo = __builtin_bit_cast(f32x2, __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-              const f32x2 hi = __builtin_bit_cast(f32x2, __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-              sum += f32x4{lo.x, lo.y, hi.x, hi.y};
-            }
-          }
-          slot[p * WG_THREADS] = sum;
-        }
-        if (tid == 0)  // re-arm for the next launch
-          __hip_atomic_store(&sp.arrive[T.out_tile_id], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-          for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const f32x4 v = slot[((fn * FM + fm) * 4 + q) * WG_THREADS];
-              acc[fn][fm][4 * q] = v.x;
-              acc[fn][fm][4 * q + 1] = v.y;
-              acc[fn][fm][4 * q + 2] = v.z;
-              acc[fn][fm][4 * q + 3] = v.w;
-            }
-        __syncthreads();  // the slots have been read: the outputs are staged in the same LDS next
-      }
+      if (T.S > 1 && !any_handover<NCHW, FM, FN>(T, sp, lds, s_flag, tid, acc)) return;
+      any_outputs<DT, NCHW, ROWS, COLS>(P_mem, T_mem, mb, nb, lds, tid, acc);
+      __syncthreads();  // the output tile has been read before the next block's stages are written
+    }
+  }
+}
 
-      // ---- outputs: through LDS, so that they leave as runs of consecutive places ----
-      {
-      // (the record is read again: kept through the stages, what the outputs need of it costs the mixed-type kernel a quarter
-      // more spilled scalars)
-      const DevProblem P = load_record(P_mem);
-      const sk_tile T = load_record(T_mem);
-      const int m_end = (int)T.m0 + (int)T.m_len, n_end = (int)T.n0 + (int)T.n_len, hw = P.Ho * P.Wo;
-      // lane holds, per (fn, fm): MFMA row l32, columns 8*(i/4) + 4*half + (i%4)
-      constexpr int OROW = COLS * ES + 16;
-      static_assert(ROWS * OROW <= LDS_TILE_BYTES, "output tile does not fit the LDS buffer");
+// ---------------------------------------------------------------------------
+// channel-major convolutions whose pixels lie in the order of their outputs
+// ---------------------------------------------------------------------------
+// Under one reduction index (channel and tap) of a convolution that keeps its images' width, consecutive outputs read
+// consecutive places of one channel plane, from row to row as well.  So (planes_form) instead of single elements:
+//   * a thread reads 16 bytes (8 pixels; 4 in fp32) under one reduction index, at whatever address they start, and clears the pixels whose
+//     tap lies outside the image (a byte of bits per filter column and row, worked out once per block);
+//   * the LDS image of a stage holds a row of pixels per reduction index, pieces turned over (^ 4 per row) so that the rows a fragment
+//     takes lie in different banks, and 16-bit fragments are read with the hardware's transposing LDS load (a lane gets four
+//     reduction indices of its pixel), fp32 ones element by element.
+// The sums are those of run_tile_any: the same bits.  What a stage cost there were the instructions for its single elements (32 loads of
+// two bytes a lane and stage, and as many masks and packs; here four loads, and two dozen instructions for each): channel-major
+// ResNet layers for eight 98.1 -> 70.1 us.
+template <int ES>
+__device__ __forceinline__ bool planes_tile(const DevProblem &P, const sk_tile &T) {
+  constexpr int CE = 16 / ES;
+  if (!planes_form(P, ES)) return false;
+  const int b0 = fast_div((int)T.m0, P.div_hw), b1 = fast_div((int)T.m0 + (int)T.m_len - 1, P.div_hw);
+  // (a piece of pixels lies in one image, and all offsets within 2^31 bytes)
+  return (b0 == b1 || (P.Ho * P.Wo) % CE == 0) && offsets_below(P, b1 - b0, ES, (int64_t)1 << 31);
+}
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+// Four 16-bit elements of this lane's column out of four rows of a group of 16 lanes.
+__device__ __forceinline__ u32x2 read_transposed(const unsigned char *p) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(unsigned char *)p));
+}
+// One bit per element to all its bits.
+template <int ES>
+__device__ __forceinline__ u32x4 keep_elements(const u32x4 &v, uint32_t bits) {
+  u32x4 r;
 #pragma unroll
-      for (int fm = 0; fm < FM; ++fm)
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (ES == 4) {
+      r[i] = v[i] & (uint32_t)__builtin_amdgcn_sbfe((int)bits, i, 1);
+    } else {
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 2 * i, 1), hi = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 2 * i + 1, 1);
+      r[i] = v[i] & __builtin_amdgcn_perm(hi, lo, 0x07060100u);
+    }
+  }
+  return r;
+}
+
+template <int DT, int BM, int BN>
+__device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const sk_tile *T_mem, const SplitK &sp, unsigned char *lds,
+                                                uint32_t *s_flag, int tid) {
+  constexpr int ES = Elem<DT>::ES;
+  constexpr int CE = 16 / ES;
+  constexpr int KB = 8 * CE;              // reduction elements per stage
+  constexpr int PROW = BM * ES;           // bytes of an LDS row of pixels
+  constexpr int PPR = BM / CE;            // pieces of such a row
+  constexpr int RPP = WG_THREADS / PPR;   // rows that the workgroup fills at a time
+  constexpr int NA = KB / RPP, NBW = BN / 32;
+  constexpr int WEIGHTS = KB * PROW;      // where the weight rows start
+  constexpr int STAGE = WEIGHTS + BN * LDS_ROW;
+  constexpr int FM = BN / 64, FN = BM / 64;  // 32x32 blocks per wave: output channels, pixels
+  constexpr uint32_t ALL = (1u << CE) - 1u;
+  static_assert(2 * STAGE <= LDS_TILE_BYTES, "two stages do not fit the LDS buffer");
+  const DevProblem P = load_record(P_mem);
+  const sk_tile T = load_record(T_mem);
+  const int m_end = (int)T.m0 + (int)T.m_len, n_end = (int)T.n0 + (int)T.n_len;
+  const int hw = P.Ho * P.Wo, plane = P.H * P.W, taps = P.R * P.S;
+  const int k_stop = (int)T.k0 + (int)T.k_len;
+  const int p_begin = ((int)T.k0 + CE - 1) / CE, p_stop = (k_stop + CE - 1) / CE;
+  const int nstages = (p_stop - p_begin + 7) >> 3;
+  const int stage_c = KB / taps, stage_t = KB - stage_c * taps;  // channels and taps from one stage to the next ...
+  const int pass_c = RPP / taps, pass_t = RPP - pass_c * taps;   // ... and from one of a thread's rows to the next
+  const int row_of_tap = P.S == 3 ? 11 : 32;                     // tap / S = tap * this / 32, for at most twelve taps
+  const bool ragged = P.Kg % CE != 0;                            // the last piece of a weight row reaches beyond it
+
+  for (int mb = (int)T.m0; mb < m_end; mb += BM) {
+    // (what depends on the thread is worked out again for every block: kept over all of them it would not fit the registers)
+    asm volatile("" : "+v"(tid));
+    const int pc = tid & (PPR - 1);
+    // ---- this thread's piece of pixels ----
+    const int b0 = fast_div(mb, P.div_hw), b1 = fast_div(min(mb + BM, m_end) - 1, P.div_hw);
+    const char SK_GLOBAL *image = as_global<char>(P.A) + (int64_t)b0 * P.Cin * plane * ES;
+    const int a_last = (((b1 - b0 + 1) * P.Cin) * plane - CE) * ES;  // last place a piece may be read from
+    int a_off;                 // its place under tap (0, 0) of channel 0, in bytes from `image` (may lie in front of it)
+    uint32_t cols = 0, rows = 0;  // bit e of byte s: pixel e's tap in filter column s lies in the image; the same for the filter rows
+    {
+      const int m = min(mb + pc * CE, m_end - 1);
+      const int b = fast_div(m, P.div_hw), rem = m - b * hw;
+      int ho = fast_div(rem, P.div_wo), wo = rem - ho * P.Wo;
+      a_off = ((b - b0) * P.Cin * plane + rem - P.pad_h * P.W - P.pad_w) * ES;
+      const int inside = m_end - (mb + pc * CE);
 #pragma unroll
-        for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            unsigned char *d = lds + ((wm * FM + fm) * 32 + l32) * OROW + ((wn * FN + fn) * 32 + 8 * q + 4 * half) * ES;
-            if constexpr (ES == 4) {
-              *(f32x4 *)d = f32x4{acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1], acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]};
-            } else {
-              u32x2 o;
-              o.x = cvt_pack<DT>(acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1]);
-              o.y = cvt_pack<DT>(acc[fn][fm][4 * q + 2], acc[fn][fm][4 * q + 3]);
-              *(u32x2 *)d = o;
-            }
-          }
-      __syncthreads();
-      constexpr int PIECES = COLS / CE, RPI = WG_THREADS / PIECES;
-      const int col = (tid % PIECES) * CE;
-      const int row_end = NCHW ? n_end - nb : m_end - mb, col_end = NCHW ? m_end - mb : n_end - nb;
-      // NCHW: the piece's pixels (its first one, and whether they lie in one image)
-      int64_t pixel0 = 0;
-      bool whole = col + CE <= col_end;
-      if constexpr (NCHW) {
-        if (col < col_end) {
-          pixel0 = nchw_out_base(P, mb + col);
-          whole = whole && nchw_out_base(P, mb + col + CE - 1) == pixel0 + CE - 1;
+      for (int e = 0; e < CE; ++e) {
+        if (e < inside) {
+          for (int s = 0; s < P.S; ++s) cols |= ((unsigned)(wo - P.pad_w + s) < (unsigned)P.W ? 1u : 0u) << (8 * s + e);
+          for (int r = 0; r < P.R; ++r) rows |= ((unsigned)(ho - P.pad_h + r) < (unsigned)P.H ? 1u : 0u) << (8 * r + e);
+        }
+        if (++wo == P.Wo) {
+          wo = 0;
+          if (++ho == P.Ho) ho = 0;
         }
       }
-      // (the rule for the caches outside the loop: beside each store it cost stride-2 layers x4 to x16 1 to 2 %)
-      auto store_rows = [&](auto past_caches) {
-#pragma unroll 1
-        for (int r = tid / PIECES; r < row_end && r < ROWS; r += RPI) {
-          if (col >= col_end) break;
-          const u32x4 v = *(const u32x4 *)(lds + r * OROW + col * ES);
-          if (whole) {
-            const int64_t o = NCHW ? pixel0 + (int64_t)(nb + r) * hw : (int64_t)(mb + r) * P.ldc + nb + col;
-            u32x4_any SK_GLOBAL *const dst = (u32x4_any SK_GLOBAL *)((uintptr_t)P.C + (uintptr_t)(o * ES));
-            if constexpr (decltype(past_caches)::value)
-              __builtin_nontemporal_store(v, dst);
-            else
-              *dst = v;
-          } else {
-            const piece_t ev = __builtin_bit_cast(piece_t, v);
+    }
+    const int p_swz = ES == 4 ? 8 : BM == 128 ? 4 : 4;
+    auto swizzle = [&](int r) { return (ES == 4 ? (r >> 2) & 1 : BM == 128 ? r & 3 : (r >> 1) & 1) * p_swz; };
+
+    for (int nb = (int)T.n0; nb < n_end; nb += BN) {
+      asm volatile("" : "+v"(tid));
+      const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+      const int wm = wave & 1, wn = wave >> 1;
+      const int l32 = lane & 31, half = lane >> 5;
+      const int c8 = tid & 7, srow = tid >> 3;  // weights: piece c8 of rows srow + 32 i
+      const int kr = tid / PPR;                 // pixels: piece pc of rows kr + RPP i
+      f32x16 acc[FN][FM];
 #pragma unroll
-            for (int e = 0; e < CE; ++e)
-              if (col + e < col_end) {
-                const int64_t o = NCHW ? nchw_out_base(P, mb + col + e) + (int64_t)(nb + r) * hw : (int64_t)(mb + r) * P.ldc + nb + col + e;
-                *(elem_t SK_GLOBAL *)((uintptr_t)P.C + (uintptr_t)(o * ES)) = ev[e];
-              }
+      for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[fn][fm][i] = 0.f;
+
+      // ---- the next stage to load ----
+      int ks = p_begin * CE;  // its first reduction index
+      int k_tap[NA];          // this thread's rows of it: tap, and ...
+      int k_off[NA];          // ... a_off plus its channel's place
+      {
+        int c = (ks + kr) / taps, t = ks + kr - c * taps;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+          k_tap[i] = t;
+          k_off[i] = a_off + c * plane * ES;
+          c += pass_c;
+          t += pass_t;
+          if (t >= taps) {
+            t -= taps;
+            ++c;
           }
+          // (opaque, so that the first stage's positions are not worked out apart)
+          asm volatile("" : "+v"(k_tap[i]), "+v"(k_off[i]));
+        }
+      }
+      const char SK_GLOBAL *weights = as_global<char>(P.B) + (int64_t)nb * P.ldb * ES;
+      uint32_t w_off[NBW];
+#pragma unroll
+      for (int i = 0; i < NBW; ++i) w_off[i] = (uint32_t)(min(srow + 32 * i, n_end - 1 - nb) * (int)P.ldb) * ES;
+      u32x4 ra[NA], rb[NBW];
+      uint32_t a_bits[NA];  // of the stage loaded last: which pixels to keep; ...
+      int a_sh[NA];         // ... how far its pieces were read from their places, ...
+      int w_at = 0;         // ... the reduction index of its weight piece
+      auto gload = [&]() {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+          const int r = (k_tap[i] * row_of_tap) >> 5, s = k_tap[i] - r * P.S;
+          const int off = k_off[i] + (r * P.W + s) * ES, at = min(max(off, 0), a_last);
+          a_sh[i] = (off - at) / ES;
+          a_bits[i] = ks + kr + RPP * i < k_stop ? (cols >> (8 * s)) & (rows >> (8 * r)) & ALL : 0u;
+          ra[i] = *(const u32x4_any SK_GLOBAL *)(image + (uint32_t)at);
+          k_tap[i] += stage_t;
+          k_off[i] += stage_c * plane * ES;
+          if (k_tap[i] >= taps) {
+            k_tap[i] -= taps;
+            k_off[i] += plane * ES;
+          }
+        }
+        w_at = ks + c8 * CE;
+        const uint32_t at = (uint32_t)(min(w_at, P.Kg - CE) * ES);
+#pragma unroll
+        for (int i = 0; i < NBW; ++i) rb[i] = *(const u32x4_any SK_GLOBAL *)(weights + (w_off[i] + at));
+        ks += KB;
+      };
+      auto lstore = [&](int buf) {
+        unsigned char *s = lds + buf * STAGE;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+          u32x4 v = ra[i];
+          if (__any(a_sh[i] != 0)) v = shift_piece<ES>(v, a_sh[i]);
+          if (__any(a_bits[i] != ALL)) v = keep_elements<ES>(v, a_bits[i]);
+          const int r = kr + RPP * i;
+          *(u32x4 *)(s + r * PROW + ((pc ^ swizzle(r)) << 4)) = v;
+        }
+        // (the last stage: zeros beyond the slice, and beyond the row)
+        const bool last = ks >= p_stop * CE;
+#pragma unroll
+        for (int i = 0; i < NBW; ++i) {
+          u32x4 v = rb[i];
+          if (last) {
+            if (ragged) v = shift_piece<ES>(v, max(w_at - (P.Kg - CE), 0));
+            if (w_at >= p_stop * CE) v = u32x4{0u, 0u, 0u, 0u};
+          }
+          *(u32x4 *)(s + WEIGHTS + (srow + 32 * i) * LDS_ROW + c8 * 16) = v;
         }
       };
-      if ((P.flags & FLAG_PAST_CACHES) != 0)
-        store_rows(std::true_type{});
-      else
-        store_rows(std::false_type{});
+      // fragment addresses: of block f of this wave's pixels, reduction indices 0 .. of the stage
+      int px_at[FN];
+#pragma unroll
+      for (int f = 0; f < FN; ++f) {
+        if constexpr (ES == 2) {
+          const int i = lane & 15, r = 8 * half + (i >> 2), px = (wn * FN + f) * 32 + 16 * ((lane >> 4) & 1) + 4 * (i & 3);
+          px_at[f] = r * PROW + (((px >> 3) ^ swizzle(r)) << 4) + (px & 7) * 2;
+        } else {
+          const int px = (wn * FN + f) * 32 + l32;
+          px_at[f] = 4 * half * PROW + (((px >> 2) ^ swizzle(4 * half)) << 4) + (px & 3) * 4;
+        }
       }
+      const int w_frag = WEIGHTS + (wm * FM * 32 + l32) * LDS_ROW + half * 16;
+
+      // (step -1 only loads; an empty slice delivers zeros)
+      for (int s = -1; s < nstages; ++s) {
+        if (s + 1 < nstages) gload();
+        if (s >= 0) {
+          const unsigned char *l = lds + (s & 1) * STAGE;
+          u32x4 fa[2][FM], fb[2][FN];
+          auto frag = [&](int kk, u32x4(&xa)[FM], u32x4(&xb)[FN]) {
+#pragma unroll
+            for (int f = 0; f < FM; ++f) xa[f] = *(const u32x4 *)(l + w_frag + f * 32 * LDS_ROW + kk * 32);
+#pragma unroll
+            for (int f = 0; f < FN; ++f) {
+              if constexpr (ES == 2) {
+                const u32x2 lo = read_transposed(l + px_at[f] + kk * 16 * PROW), hi = read_transposed(l + px_at[f] + (kk * 16 + 4) * PROW);
+                xb[f] = u32x4{lo.x, lo.y, hi.x, hi.y};
+              } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) xb[f][j] = *(const uint32_t *)(l + px_at[f] + (kk * 8 + j) * PROW);
+              }
+            }
+          };
+          frag(0, fa[0], fb[0]);
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) {
+            if (kk < 3) frag(kk + 1, fa[(kk + 1) & 1], fb[(kk + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);  // (a step ahead and no further: the registers)
+#pragma unroll
+            for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+              for (int fm = 0; fm < FM; ++fm) mma32<DT>(fb[kk & 1][fn], fa[kk & 1][fm], acc[fn][fm]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        if (s + 1 < nstages) lstore((s + 1) & 1);
+        __syncthreads();  // stage s+1 is written, and everyone has read stage s
+      }
+      if (T.S > 1 && !any_handover<true, FM, FN>(T, sp, lds, s_flag, tid, acc)) return;
+      any_outputs<DT, true, BN, BM>(P_mem, T_mem, mb, nb, lds, tid, acc);
       __syncthreads();  // the output tile has been read before the next block's stages are written
     }
   }
@@ -2387,17 +2651,25 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
 // (A slice of a split reduction must be a single block, so a shape may only be wider than its rectangle.  64 x 128 and 128 x 64
 // beside the square ones: without them the channel-major ResNet layers for eight take 173 instead of 152 us, the stride-2
 // layers for sixteen 123 instead of 113.)
-template <int DT, bool NCHW>
+template <int DT, bool NCHW, bool PLANES, int BM, int BN>
+__device__ __forceinline__ void run_block_shape(const DevProblem *P_mem, const sk_tile *T_mem, const SplitK &sp, unsigned char *lds,
+                                                uint32_t *s_flag, int tid) {
+  if constexpr (PLANES)
+    run_tile_planes<DT, BM, BN>(P_mem, T_mem, sp, lds, s_flag, tid);
+  else
+    run_tile_any<DT, NCHW, BM, BN>(P_mem, T_mem, sp, lds, s_flag, tid);
+}
+template <int DT, bool NCHW, bool PLANES>
 __device__ __forceinline__ void run_block_any(const DevProblem *P_mem, const sk_tile *T_mem, int m_len, int n_len, const SplitK &sp,
                                               unsigned char *lds, uint32_t *s_flag, int tid) {
   if (m_len <= 64 && n_len <= 64)
-    run_tile_any<DT, NCHW, 64, 64>(P_mem, T_mem, sp, lds, s_flag, tid);
+    run_block_shape<DT, NCHW, PLANES, 64, 64>(P_mem, T_mem, sp, lds, s_flag, tid);
   else if (m_len <= 64)
-    run_tile_any<DT, NCHW, 64, 128>(P_mem, T_mem, sp, lds, s_flag, tid);
+    run_block_shape<DT, NCHW, PLANES, 64, 128>(P_mem, T_mem, sp, lds, s_flag, tid);
   else if (n_len <= 64)
-    run_tile_any<DT, NCHW, 128, 64>(P_mem, T_mem, sp, lds, s_flag, tid);
+    run_block_shape<DT, NCHW, PLANES, 128, 64>(P_mem, T_mem, sp, lds, s_flag, tid);
   else
-    run_tile_any<DT, NCHW, 128, 128>(P_mem, T_mem, sp, lds, s_flag, tid);
+    run_block_shape<DT, NCHW, PLANES, 128, 128>(P_mem, T_mem, sp, lds, s_flag, tid);
 }
 
 template <int DT, bool ANY_ALIGNMENT, bool NARROW, bool WINDOW>
@@ -2428,10 +2700,12 @@ __device__ __forceinline__ void run_class(const DevProblem &P, const sk_tile &T,
           // (an operand of less than one piece also goes the first way: the others read whole pieces from inside it)
           if (small || !holds_a_piece<Elem<DT>::ES>(P))
             run_generic<DT>(P_mem, T_mem, pf.tid);
+          else if (P.nchw && planes_tile<Elem<DT>::ES>(P, T))
+            run_block_any<DT, true, true>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag, pf.tid);
           else if (P.nchw)
-            run_block_any<DT, true>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag, pf.tid);
+            run_block_any<DT, true, false>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag, pf.tid);
           else
-            run_block_any<DT, false>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag, pf.tid);
+            run_block_any<DT, false, false>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag, pf.tid);
         }
       }
     }

@@ -64,6 +64,14 @@ SK_HOST_DEVICE bool offsets_below(const DevProblem &d, int64_t later, int64_t es
   return (uint64_t)(later * ((int64_t)d.H * d.W * d.Cin * es) + (int64_t)d.reach + (((int64_t)1 << 31) - limit)) >> 31 == 0;
 }
 
+// Whether a channel-major convolution's outputs lie in the order of the pixels under each of its taps (run_tile_planes): stride 1, one or
+// three filter columns that keep the images' width, at most four filter rows (a byte of bits each), images and weight rows of at least a piece.
+SK_HOST_DEVICE bool planes_form(const DevProblem &d, int64_t es) {
+  const int64_t piece = 16 / es;
+  return d.nchw && d.stride == 1 && (d.S == 1 || d.S == 3) && 2 * d.pad_w == d.S - 1 && d.R <= 4 && d.Kg >= piece &&
+         (int64_t)d.H * d.W * d.Cin >= piece && (uint64_t)(128 * d.ldb * es) >> 31 == 0;
+}
+
 // n / d for 0 <= n < 2^31 as (n * mul) >> shift with mul = floor(2^(31+l) / d) + 1, l = ceil(log2 d), shift = 31 + l:
 // mul * d = 2^(31+l) + e with 0 < e <= d <= 2^l, so the quotient is off by less than n / (d * 2^31) < 1 / d.
 struct FastDiv {
