@@ -2411,13 +2411,14 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
 // Under one reduction index (channel and tap) of a convolution that keeps its images' width, consecutive outputs read
 // consecutive places of one channel plane, from row to row as well.  So (planes_form) instead of single elements:
 //   * a thread reads 16 bytes (8 pixels; 4 in fp32) under one reduction index, at whatever address they start, and clears the pixels whose
-//     tap lies outside the image (a byte of bits per filter column and row, worked out once per block);
+//     tap lies outside the image (a table in LDS of what each tap keeps of each piece, worked out once per block);
 //   * the LDS image of a stage holds a row of pixels per reduction index, pieces turned over (^ 4 per row) so that the rows a fragment
 //     takes lie in different banks, and 16-bit fragments are read with the hardware's transposing LDS load (a lane gets four
 //     reduction indices of its pixel), fp32 ones element by element.
 // The sums are those of run_tile_any: the same bits.  What a stage cost there were the instructions for its single elements (32 loads of
 // two bytes a lane and stage, and as many masks and packs; here four loads, and two dozen instructions for each): channel-major
 // ResNet layers for eight 98.1 -> 70.1 us.
+constexpr int PLANES_TAPS = 12;  // the most planes_form lets through
 template <int ES>
 __device__ __forceinline__ bool planes_tile(const DevProblem &P, const sk_tile &T) {
   constexpr int CE = 16 / ES;
@@ -2432,21 +2433,18 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32x2 read_transposed(const unsigned char *p) {
   return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(unsigned char *)p));
 }
-// One bit per element to all its bits.
+// Which pixels of a piece to keep under a tap: their bits as the AND of a 16-bit piece takes them, or (fp32) one bit each.
 template <int ES>
-__device__ __forceinline__ u32x4 keep_elements(const u32x4 &v, uint32_t bits) {
-  u32x4 r;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if constexpr (ES == 4) {
-      r[i] = v[i] & (uint32_t)__builtin_amdgcn_sbfe((int)bits, i, 1);
-    } else {
-      const uint32_t lo = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 2 * i, 1), hi = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 2 * i + 1, 1);
-      r[i] = v[i] & __builtin_amdgcn_perm(hi, lo, 0x07060100u);
-    }
+struct Keep {
+  using type = typename std::conditional<ES == 4, uint32_t, u32x4>::type;
+  static __device__ __forceinline__ u32x4 apply(const u32x4 &v, const type &k) {
+    if constexpr (ES == 4)
+      return u32x4{v[0] & (uint32_t)__builtin_amdgcn_sbfe((int)k, 0, 1), v[1] & (uint32_t)__builtin_amdgcn_sbfe((int)k, 1, 1),
+                   v[2] & (uint32_t)__builtin_amdgcn_sbfe((int)k, 2, 1), v[3] & (uint32_t)__builtin_amdgcn_sbfe((int)k, 3, 1)};
+    else
+      return v & k;
   }
-  return r;
-}
+};
 
 template <int DT, int BM, int BN>
 __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const sk_tile *T_mem, const SplitK &sp, unsigned char *lds,
@@ -2461,8 +2459,6 @@ __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const s
   constexpr int WEIGHTS = KB * PROW;      // where the weight rows start
   constexpr int STAGE = WEIGHTS + BN * LDS_ROW;
   constexpr int FM = BN / 64, FN = BM / 64;  // 32x32 blocks per wave: output channels, pixels
-  constexpr uint32_t ALL = (1u << CE) - 1u;
-  static_assert(2 * STAGE <= LDS_TILE_BYTES, "two stages do not fit the LDS buffer");
   const DevProblem P = load_record(P_mem);
   const sk_tile T = load_record(T_mem);
   const int m_end = (int)T.m0 + (int)T.m_len, n_end = (int)T.n0 + (int)T.n_len;
@@ -2472,39 +2468,44 @@ __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const s
   const int nstages = (p_stop - p_begin + 7) >> 3;
   const int stage_c = KB / taps, stage_t = KB - stage_c * taps;  // channels and taps from one stage to the next ...
   const int pass_c = RPP / taps, pass_t = RPP - pass_c * taps;   // ... and from one of a thread's rows to the next
-  const int row_of_tap = P.S == 3 ? 11 : 32;                     // tap / S = tap * this / 32, for at most twelve taps
   const bool ragged = P.Kg % CE != 0;                            // the last piece of a weight row reaches beyond it
+  const bool masked = taps > 1 || P.pad_h > 0;                   // some taps lie outside the image
+  using keep_t = typename Keep<ES>::type;
+  keep_t *const keep = (keep_t *)(lds + 2 * STAGE);  // [tap][piece of pixels]
+  static_assert(2 * STAGE + PLANES_TAPS * PPR * (int)sizeof(keep_t) <= LDS_TILE_BYTES, "the table of taps does not fit the LDS buffer");
 
   for (int mb = (int)T.m0; mb < m_end; mb += BM) {
     // (what depends on the thread is worked out again for every block: kept over all of them it would not fit the registers)
     asm volatile("" : "+v"(tid));
-    const int pc = tid & (PPR - 1);
-    // ---- this thread's piece of pixels ----
     const int b0 = fast_div(mb, P.div_hw), b1 = fast_div(min(mb + BM, m_end) - 1, P.div_hw);
     const char SK_GLOBAL *image = as_global<char>(P.A) + (int64_t)b0 * P.Cin * plane * ES;
     const int a_last = (((b1 - b0 + 1) * P.Cin) * plane - CE) * ES;  // last place a piece may be read from
-    int a_off;                 // its place under tap (0, 0) of channel 0, in bytes from `image` (may lie in front of it)
-    uint32_t cols = 0, rows = 0;  // bit e of byte s: pixel e's tap in filter column s lies in the image; the same for the filter rows
-    {
-      const int m = min(mb + pc * CE, m_end - 1);
-      const int b = fast_div(m, P.div_hw), rem = m - b * hw;
-      int ho = fast_div(rem, P.div_wo), wo = rem - ho * P.Wo;
-      a_off = ((b - b0) * P.Cin * plane + rem - P.pad_h * P.W - P.pad_w) * ES;
-      const int inside = m_end - (mb + pc * CE);
+    if (masked)
+      for (int i = tid; i < taps * PPR; i += WG_THREADS) {
+        const int t = i / PPR, r = P.S == 3 ? (t * 11) >> 5 : t, s = t - r * P.S;
+        const int m = min(mb + (i & (PPR - 1)) * CE, m_end - 1);
+        const int rem = m - fast_div(m, P.div_hw) * hw;
+        int ho = fast_div(rem, P.div_wo), w = rem - ho * P.Wo + s - P.pad_w, h = ho + r - P.pad_h;
+        uint32_t in[CE];  // (of pixels past the edge, which are never stored, whatever follows)
 #pragma unroll
-      for (int e = 0; e < CE; ++e) {
-        if (e < inside) {
-          for (int s = 0; s < P.S; ++s) cols |= ((unsigned)(wo - P.pad_w + s) < (unsigned)P.W ? 1u : 0u) << (8 * s + e);
-          for (int r = 0; r < P.R; ++r) rows |= ((unsigned)(ho - P.pad_h + r) < (unsigned)P.H ? 1u : 0u) << (8 * r + e);
+        for (int e = 0; e < CE; ++e) {
+          in[e] = (unsigned)w < (unsigned)P.W && (unsigned)h < (unsigned)P.H ? ~0u : 0u;
+          if (++w == P.Wo + s - P.pad_w) {
+            w = s - P.pad_w;
+            ++h;
+            if (++ho == P.Ho) {
+              ho = 0;
+              h = r - P.pad_h;
+            }
+          }
         }
-        if (++wo == P.Wo) {
-          wo = 0;
-          if (++ho == P.Ho) ho = 0;
-        }
+        if constexpr (ES == 4)
+          keep[i] = (in[0] & 1u) | (in[1] & 2u) | (in[2] & 4u) | (in[3] & 8u);
+        else
+#pragma unroll
+          for (int e = 0; e < 4; ++e) keep[i][e] = (in[2 * e] & 0xffffu) | (in[2 * e + 1] & 0xffff0000u);
       }
-    }
-    const int p_swz = ES == 4 ? 8 : BM == 128 ? 4 : 4;
-    auto swizzle = [&](int r) { return (ES == 4 ? (r >> 2) & 1 : BM == 128 ? r & 3 : (r >> 1) & 1) * p_swz; };
+    auto swizzle = [&](int r) { return ES == 4 ? (r << 1) & 8 : BM == 128 ? (r & 3) << 2 : (r << 1) & 4; };
 
     for (int nb = (int)T.n0; nb < n_end; nb += BN) {
       asm volatile("" : "+v"(tid));
@@ -2512,7 +2513,7 @@ __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const s
       const int wm = wave & 1, wn = wave >> 1;
       const int l32 = lane & 31, half = lane >> 5;
       const int c8 = tid & 7, srow = tid >> 3;  // weights: piece c8 of rows srow + 32 i
-      const int kr = tid / PPR;                 // pixels: piece pc of rows kr + RPP i
+      const int pc = tid & (PPR - 1), kr = tid / PPR;  // pixels: piece pc of rows kr + RPP i
       f32x16 acc[FN][FM];
 #pragma unroll
       for (int fn = 0; fn < FN; ++fn)
@@ -2523,14 +2524,19 @@ __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const s
 
       // ---- the next stage to load ----
       int ks = p_begin * CE;  // its first reduction index
-      int k_tap[NA];          // this thread's rows of it: tap, and ...
-      int k_off[NA];          // ... a_off plus its channel's place
+      uint32_t k_tap[NA];     // this thread's rows of it: tap, and ...
+      int k_off[NA];          // ... place under tap (0, 0), in bytes from `image` (may lie in front of it)
+      int tap_off;            // lane t: tap t's, from that under tap (0, 0)
       {
+        const int tr = P.S == 3 ? (lane * 11) >> 5 : lane;  // (at most PLANES_TAPS taps)
+        tap_off = (tr * P.W + lane - tr * P.S) * ES;
+        const int m = min(mb + pc * CE, m_end - 1), b = fast_div(m, P.div_hw);
+        const int a_off = (b - b0) * P.Cin * plane + m - b * hw - P.pad_h * P.W - P.pad_w;
         int c = (ks + kr) / taps, t = ks + kr - c * taps;
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
-          k_tap[i] = t;
-          k_off[i] = a_off + c * plane * ES;
+          k_tap[i] = (uint32_t)t;
+          k_off[i] = (a_off + c * plane) * ES;
           c += pass_c;
           t += pass_t;
           if (t >= taps) {
@@ -2546,23 +2552,23 @@ __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const s
 #pragma unroll
       for (int i = 0; i < NBW; ++i) w_off[i] = (uint32_t)(min(srow + 32 * i, n_end - 1 - nb) * (int)P.ldb) * ES;
       u32x4 ra[NA], rb[NBW];
-      uint32_t a_bits[NA];  // of the stage loaded last: which pixels to keep; ...
-      int a_sh[NA];         // ... how far its pieces were read from their places, ...
-      int w_at = 0;         // ... the reduction index of its weight piece
+      uint32_t a_tap[NA];  // of the stage loaded last: its rows' taps; ...
+      int a_sh[NA];        // ... how many bytes from their places its pieces were read, ...
+      int w_at = 0;        // ... the reduction index of its weight piece
+      const int plane_bytes = plane * ES, stage_off = stage_c * plane_bytes;
       auto gload = [&]() {
+        int under[NA];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) under[i] = __builtin_amdgcn_ds_bpermute((int)(k_tap[i] << 2), tap_off);
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
-          const int r = (k_tap[i] * row_of_tap) >> 5, s = k_tap[i] - r * P.S;
-          const int off = k_off[i] + (r * P.W + s) * ES, at = min(max(off, 0), a_last);
-          a_sh[i] = (off - at) / ES;
-          a_bits[i] = ks + kr + RPP * i < k_stop ? (cols >> (8 * s)) & (rows >> (8 * r)) & ALL : 0u;
+          const int off = k_off[i] + under[i], at = min(max(off, 0), a_last);
+          a_sh[i] = off - at;
+          a_tap[i] = k_tap[i];
           ra[i] = *(const u32x4_any SK_GLOBAL *)(image + (uint32_t)at);
-          k_tap[i] += stage_t;
-          k_off[i] += stage_c * plane * ES;
-          if (k_tap[i] >= taps) {
-            k_tap[i] -= taps;
-            k_off[i] += plane * ES;
-          }
+          const uint32_t t = k_tap[i] + (uint32_t)stage_t, u = t - (uint32_t)taps;
+          k_off[i] += stage_off + (t >= (uint32_t)taps ? plane_bytes : 0);
+          k_tap[i] = min(t, u);  // (t - taps wraps where t < taps)
         }
         w_at = ks + c8 * CE;
         const uint32_t at = (uint32_t)(min(w_at, P.Kg - CE) * ES);
@@ -2572,25 +2578,42 @@ __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const s
       };
       auto lstore = [&](int buf) {
         unsigned char *s = lds + buf * STAGE;
+        const bool last = ks >= p_stop * CE;  // (zeros beyond the slice, and beyond the weight rows)
+        if (masked) {
+          keep_t k[NA];
+#pragma unroll
+          for (int i = 0; i < NA; ++i) k[i] = keep[a_tap[i] * PPR + pc];
+          int any = 0;
+#pragma unroll
+          for (int i = 0; i < NA; ++i) any |= a_sh[i];
+          if (__any(any != 0)) {
+#pragma unroll
+            for (int i = 0; i < NA; ++i) ra[i] = shift_piece<ES>(ra[i], a_sh[i] / ES);
+          }
+#pragma unroll
+          for (int i = 0; i < NA; ++i) ra[i] = Keep<ES>::apply(ra[i], k[i]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < NA; ++i)
+            if (__any(a_sh[i] != 0)) ra[i] = shift_piece<ES>(ra[i], a_sh[i] / ES);
+        }
+        if (last) {
+#pragma unroll
+          for (int i = 0; i < NA; ++i)
+            if (ks - KB + kr + RPP * i >= k_stop) ra[i] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+          for (int i = 0; i < NBW; ++i) {
+            if (ragged) rb[i] = shift_piece<ES>(rb[i], max(w_at - (P.Kg - CE), 0));
+            if (w_at >= p_stop * CE) rb[i] = u32x4{0u, 0u, 0u, 0u};
+          }
+        }
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
-          u32x4 v = ra[i];
-          if (__any(a_sh[i] != 0)) v = shift_piece<ES>(v, a_sh[i]);
-          if (__any(a_bits[i] != ALL)) v = keep_elements<ES>(v, a_bits[i]);
           const int r = kr + RPP * i;
-          *(u32x4 *)(s + r * PROW + ((pc ^ swizzle(r)) << 4)) = v;
+          *(u32x4 *)(s + r * PROW + ((pc ^ swizzle(r)) << 4)) = ra[i];
         }
-        // (the last stage: zeros beyond the slice, and beyond the row)
-        const bool last = ks >= p_stop * CE;
 #pragma unroll
-        for (int i = 0; i < NBW; ++i) {
-          u32x4 v = rb[i];
-          if (last) {
-            if (ragged) v = shift_piece<ES>(v, max(w_at - (P.Kg - CE), 0));
-            if (w_at >= p_stop * CE) v = u32x4{0u, 0u, 0u, 0u};
-          }
-          *(u32x4 *)(s + WEIGHTS + (srow + 32 * i) * LDS_ROW + c8 * 16) = v;
-        }
+        for (int i = 0; i < NBW; ++i) *(u32x4 *)(s + WEIGHTS + (srow + 32 * i) * LDS_ROW + c8 * 16) = rb[i];
       };
       // fragment addresses: of block f of this wave's pixels, reduction indices 0 .. of the stage
       int px_at[FN];
@@ -2609,6 +2632,7 @@ __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const s
       // (step -1 only loads; an empty slice delivers zeros)
       for (int s = -1; s < nstages; ++s) {
         if (s + 1 < nstages) gload();
+        if (s < 0 && masked) __syncthreads();  // the table of taps is written
         if (s >= 0) {
           const unsigned char *l = lds + (s & 1) * STAGE;
           u32x4 fa[2][FM], fb[2][FN];

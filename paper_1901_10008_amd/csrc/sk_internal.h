@@ -65,7 +65,7 @@ SK_HOST_DEVICE bool offsets_below(const DevProblem &d, int64_t later, int64_t es
 }
 
 // Whether a channel-major convolution's outputs lie in the order of the pixels under each of its taps (run_tile_planes): stride 1, one or
-// three filter columns that keep the images' width, at most four filter rows (a byte of bits each), images and weight rows of at least a piece.
+// three filter columns that keep the images' width, at most four filter rows, images and weight rows of at least a piece.
 SK_HOST_DEVICE bool planes_form(const DevProblem &d, int64_t es) {
   const int64_t piece = 16 / es;
   return d.nchw && d.stride == 1 && (d.S == 1 || d.S == 3) && 2 * d.pad_w == d.S - 1 && d.R <= 4 && d.Kg >= piece &&
