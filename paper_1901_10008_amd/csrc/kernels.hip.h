@@ -1679,18 +1679,19 @@ __device__ __forceinline__ void run_lds_tile(const DevProblem &P, const sk_tile 
 //   * pixels pass through a ring of three blocks of 128 in LDS, each read once; the nine taps are nine places in
 //     the ring (a tap outside the image reads a row of zeros instead: one bit per pixel and tap);
 //   * one barrier per 128 pixels (72 MFMAs a wave): the block read next has landed, the one before last is free;
-//   * a step's outputs are staged by the wave itself and stored at the next step's top, so that the wait there is for loads and stores a
-//     whole step old; in large plans past the caches, which leaves room there for the pixels (2 to 5 %).
+//   * a step's outputs are staged in LDS and stored at the next step's top, so that the wait there is for loads and stores a
+//     whole step old; in large plans past the caches, which leaves room there for the pixels (2 to 5 %).  As whole lines of 64
+//     channels, out of two waves each (and a barrier in a step's middle, so that their place is free by its end): half lines, a wave's
+//     own, made 258 MB of the 206 written to memory (131.7 -> 124.4 us).
 // The sums are taken in the tiles' order: the same bits.
 // 512 tenants of 56x56, 64 to 64 (0.45 GB, 118 GFLOP), every launch on other operands: 214 to 230 us in the kernel for tiles
-// alone, 132 here: 3.4 TB/s of operands and outputs against the 4.8 of a large copy.  Without its MFMAs it takes 107, without its
-// fragment reads 120, without storing the outputs 112 (of 130, operands the same every time): bound by memory (1.11 times the algorithmic
-// bytes), with the MFMAs (42 % of the SIMD cycles by SQ_VALU_MFMA_BUSY_CYCLES) not quite beside it.  Fragments two or three steps ahead measure the same.
+// alone, 124 here: 3.6 TB/s of operands and outputs against the 4.8 of a large copy.  (Of 130, with half lines stored and operands the same every
+// time, it took 107 without its MFMAs, 120 without its fragment reads, 112 without storing the outputs.)  Bound by memory, with the MFMAs (42 % of the SIMD cycles by SQ_VALU_MFMA_BUSY_CYCLES) not quite beside it.  Fragments two or three steps ahead measure the same.
 constexpr int WIN_BLOCK = 128;                          // pixels per step and ring block
 constexpr int WIN_RING = 3 * WIN_BLOCK;                 // pixels in the ring
-constexpr int WIN_OROW = 80;                            // bytes of 32 outputs in LDS, padded
-constexpr int WIN_OUT = WIN_RING * 128;                 // where the waves' outputs are staged
-constexpr int WIN_ZERO = WIN_OUT + 4 * 64 * WIN_OROW;   // the row of zeros
+constexpr int WIN_OROW = 144;                              // bytes of a pixel's outputs in LDS, padded
+constexpr int WIN_OUT = WIN_RING * 128;                    // where a step's outputs are staged
+constexpr int WIN_ZERO = WIN_OUT + WIN_BLOCK * WIN_OROW;   // the row of zeros
 static_assert(WIN_ZERO + 128 <= LDS_TILE_BYTES, "the ring, the outputs and the row of zeros do not fit the LDS buffer");
 static_assert(WIN_ZERO % 128 == 0, "places in the row of zeros are told apart by the low seven bits");
 
@@ -1764,17 +1765,17 @@ __device__ __forceinline__ void run_window(const DevProblem &P, const sk_tile &T
 
   __builtin_amdgcn_s_waitcnt(0);  // (the builtin: the compiler, too, takes the weights as arrived and waits for nothing in the loop)
 
-  unsigned char *out = lds + WIN_OUT + wave * (64 * WIN_OROW);
+  unsigned char *const out = lds + WIN_OUT;
   const __amdgpu_buffer_rsrc_t descC = __builtin_amdgcn_make_buffer_rsrc(
       (void *)((uintptr_t)P.C + (uintptr_t)((int64_t)m0 * P.Ng * 2)), 0, m_len * P.Ng * 2, 0x00020000);
-  // a step's outputs, staged by the wave itself: 64 rows of 64 bytes (rows past the record's end lie outside the descriptor)
+  // a step's outputs: this wave's 32 pixels, whole lines of 64 channels (pixels past the record's end lie outside the descriptor)
   auto store_step = [&](int i) {
-    const int l = lane_again(), r = l >> 2, n = 32 * wn + (l & 3) * 8;
+    const int l = lane_again(), r = 32 * wave + (l >> 3), n = (l & 7) * 8;
     u32x4 v[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = *(const u32x4 *)(out + (r + 16 * q) * WIN_OROW + (l & 3) * 16);
-    const uint32_t at = n < P.Ng ? (uint32_t)(((i * WIN_BLOCK + 64 * wm + r) * P.Ng + n) * 2) : NOWHERE;
-    store_out(v, descC, at, (uint32_t)(16 * P.Ng * 2), (P.flags & FLAG_PAST_CACHES) != 0);
+    for (int q = 0; q < 4; ++q) v[q] = *(const u32x4 *)(out + (r + 8 * q) * WIN_OROW + n * 2);
+    const uint32_t at = n < P.Ng ? (uint32_t)(((i * WIN_BLOCK + r) * P.Ng + n) * 2) : NOWHERE;
+    store_out(v, descC, at, (uint32_t)(8 * P.Ng * 2), (P.flags & FLAG_PAST_CACHES) != 0);
   };
 
   // this lane's two pixels of a step, counted within their image, and how far these move from one step to the next
@@ -1849,6 +1850,7 @@ __device__ __forceinline__ void run_window(const DevProblem &P, const sk_tile &T
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int f = 0; f < 2; ++f) mma32<DT>(w[z >> 2][z & 3], x[z % (AHEAD + 1)][f], acc[f]);
+      if (z == 17) __builtin_amdgcn_s_barrier();  // every wave has stored its part of the step before: its place is free
     }
     // lane holds, per f: pixel l32, channels 8 j + 4 half + (0 .. 3)
 #pragma unroll
@@ -1859,12 +1861,13 @@ __device__ __forceinline__ void run_window(const DevProblem &P, const sk_tile &T
         o.x = cvt_pack<DT>(acc[f][4 * j], acc[f][4 * j + 1]);
         o.y = cvt_pack<DT>(acc[f][4 * j + 2], acc[f][4 * j + 3]);
         const int l = lane_again();
-        *(u32x2 *)(out + (32 * f + (l & 31)) * WIN_OROW + (8 * j + 4 * (l >> 5)) * 2) = o;
+        *(u32x2 *)(out + (64 * wm + 32 * f + (l & 31)) * WIN_OROW + (32 * wn + 8 * j + 4 * (l >> 5)) * 2) = o;
       }
     slot = slot == 2 ? 0 : slot + 1;
     if (i == 0) SK_DIAG(2);
   }
   SK_DIAG(3);
+  __syncthreads();
   store_step(steps - 1);
   SK_DIAG(4);
 }

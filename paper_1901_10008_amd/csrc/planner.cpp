@@ -898,7 +898,7 @@ bool window_operator(const HostPlan &hp, size_t i) {
 // The table with such operators' tiles replaced by runs of pixels; false: none.
 // Only where the tiles are more than the workgroups: with a tile for each at most, a run is a single block of 128 pixels, and its
 // start (weights to registers, 36 loads a wave) is what it takes.  500 tiles of 56x56 images 18.8 us as tiles, 20.0 as runs; 525 tiles, a second
-// round for some workgroups, 20.3 and 18.6, 1600 tiles 37.5 and 28.6, 12800 tiles 214 and 132.
+// round for some workgroups, 20.3 and 18.6, 1600 tiles 37.5 and 28.6, 12800 tiles 214 and 124.
 // How long a run is: in a plan of nothing else, what takes the fewest steps over the rounds of runs; beside other operators, half
 // a workgroup's share of the launch, as for weight streaming.
 // In a plan of several deadlines a run is a fifth of a share at most, so that the first deadlines' operators are not done with the launch's
