@@ -304,6 +304,11 @@ __device__ __forceinline__ u32x4 mask_piece(const u32x4 &v, int lo, int hi) {
   }
   return r;
 }
+// The four dwords that start `shift` bits (0 or 16) into v, `end` behind them.
+__device__ __forceinline__ u32x4 join_dwords(const u32x4 &v, uint32_t end, uint32_t shift) {
+  return u32x4{__builtin_amdgcn_alignbit(v[1], v[0], shift), __builtin_amdgcn_alignbit(v[2], v[1], shift),
+               __builtin_amdgcn_alignbit(v[3], v[2], shift), __builtin_amdgcn_alignbit(end, v[3], shift)};
+}
 __device__ __forceinline__ u32x4 load_any(uintptr_t p) { return *(const u32x4_any SK_GLOBAL *)p; }
 
 // n / d with d given as multiplier and shift (FastDiv), 0 <= n < 2^31.
@@ -2055,16 +2060,17 @@ __device__ __forceinline__ bool any_handover(const sk_tile &T, const SplitK &sp,
 }
 
 // Outputs of a block of run_tile_any or run_tile_planes (rows mb .., columns nb ..): through LDS, so that they leave as runs of consecutive places.
-template <int DT, bool NCHW, int ROWS, int COLS>
+// (WM waves side by side along the rows, 4 / WM along the columns.)
+template <int DT, bool NCHW, int ROWS, int COLS, int WM>
 __device__ __forceinline__ void any_outputs(const DevProblem *P_mem, const sk_tile *T_mem, int mb, int nb, unsigned char *lds, int tid,
-                                            f32x16 (&acc)[COLS / 64][ROWS / 64]) {
+                                            f32x16 (&acc)[COLS * WM / 128][ROWS / (32 * WM)]) {
   constexpr int ES = Elem<DT>::ES;
   constexpr int CE = 16 / ES;
-  constexpr int FM = ROWS / 64, FN = COLS / 64;
+  constexpr int FM = ROWS / (32 * WM), FN = COLS * WM / 128;
   using elem_t = typename std::conditional<ES == 4, uint32_t, uint16_t>::type;
   typedef elem_t piece_t __attribute__((ext_vector_type(CE)));
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int wm = wave & 1, wn = wave >> 1;
+  const int wm = wave % WM, wn = wave / WM;
   const int l32 = lane & 31, half = lane >> 5;
   // (the record is read again: kept through the stages, what the outputs need of it costs the mixed-type kernel a quarter
   // more spilled scalars)
@@ -2402,7 +2408,7 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
       }
 
       if (T.S > 1 && !any_handover<NCHW, FM, FN>(T, sp, lds, s_flag, tid, acc)) return;
-      any_outputs<DT, NCHW, ROWS, COLS>(P_mem, T_mem, mb, nb, lds, tid, acc);
+      any_outputs<DT, NCHW, ROWS, COLS, 2>(P_mem, T_mem, mb, nb, lds, tid, acc);
       __syncthreads();  // the output tile has been read before the next block's stages are written
     }
   }
@@ -2669,8 +2675,206 @@ __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const s
         __syncthreads();  // stage s+1 is written, and everyone has read stage s
       }
       if (T.S > 1 && !any_handover<true, FM, FN>(T, sp, lds, s_flag, tid, acc)) return;
-      any_outputs<DT, true, BN, BM>(P_mem, T_mem, mb, nb, lds, tid, acc);
+      any_outputs<DT, true, BN, BM, 2>(P_mem, T_mem, mb, nb, lds, tid, acc);
       __syncthreads();  // the output tile has been read before the next block's stages are written
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// NHWC convolutions of few channels: a window of the image in LDS
+// ---------------------------------------------------------------------------
+// A convolution on an image of few channels (the 7x7 stem on RGB) has runs of S * Cin elements under a filter row that pieces of 16 bytes do not
+// divide, and brings every element into LDS once per tap: as patches that was 11.5 us a tile of three stages, nearly all of it vector
+// instructions for shifts and addresses and loads at places that are no multiples of a dword.  Here (rows_form):
+//   * the rows of the image that a block of 128 output pixels needs are loaded once, with zeros for the padding, 16 bytes a thread wherever they
+//     start, and a pixel's patch is read out of them by the MFMA fragments themselves: piece j of filter row r lies r rows and 16 j bytes
+//     on from where the patch starts, at a dword's address or (odd strides of odd channel counts of 16 bits) half a dword past one;
+//   * what a piece holds beyond its run is cleared (it is some other pixel's);
+//   * the weights (at most 64 channels) stay in LDS for all blocks of the record, and the next block's rows are on their way while one
+//     is multiplied;
+//   * a wave makes 32 pixels x 64 channels, so that each pixel's fragments are read and cleared once.
+// Pieces and their order are those of run_tile_any: the same sums, the same bits.
+template <int ES>
+__device__ __forceinline__ bool rows_tile(const DevProblem &P, const sk_tile &T) {
+  if (T.cls < CLS_TILE_128x128 || T.S != 1 || !rows_form(P, ES).ok) return false;
+  return fast_div((int)T.m0, P.div_hw) == fast_div((int)T.m0 + (int)T.m_len - 1, P.div_hw);
+}
+
+// The products of a block: PR pieces per run, `patch` where this lane's starts, `w` this lane's pieces of the weights.
+template <int DT, int PR, bool ODD>
+__device__ __forceinline__ void multiply_rows(const unsigned char *patch, const unsigned char *w, int R, int image_row, int weight_row, int half,
+                                              uint32_t shift, const uint32_t (&tail)[4], f32x16 (&acc)[2][1]) {
+  typedef u32x4 u32x4_dword __attribute__((aligned(4)));
+  // what this lane keeps where the last piece of a run is that of lanes 0 to 31 (1: of the others, 2: of both; 3: and the others' is none)
+  auto keep = [&](int which, int i) { return which == 2 || (which == 1) == (half != 0) ? tail[i] : which == 3 ? 0u : ~0u; };
+  auto step = [&](const unsigned char *src, int which) {
+    u32x4 x = *(const u32x4_dword *)src;
+    if constexpr (ODD) x = join_dwords(x, *(const uint32_t *)(src + 16), shift);
+    const u32x4 w0 = *(const u32x4 *)w, w1 = *(const u32x4 *)(w + 32 * weight_row);
+    w += 32;
+    if (which >= 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[i] &= keep(which, i);
+    }
+    mma32<DT>(w0, x, acc[0][0]);
+    mma32<DT>(w1, x, acc[1][0]);
+  };
+  if constexpr (PR % 2 == 0) {
+    patch += 16 * half;
+    for (int r = 0; r < R; ++r, patch += image_row) {
+#pragma unroll
+      for (int j = 0; j < PR; j += 2) step(patch + 16 * j, j + 2 == PR ? 1 : -1);
+    }
+  } else {
+    // two runs at a time: the middle step has the last piece of one and the first of the other
+    const unsigned char *at = patch + 16 * half, *middle = patch + (half ? image_row : 16 * (PR - 1));
+    for (int r = 0; r + 1 < R; r += 2, at += 2 * image_row, middle += 2 * image_row) {
+#pragma unroll
+      for (int j = 0; j < PR - 1; j += 2) step(at + 16 * j, -1);
+      step(middle, PR == 1 ? 2 : 0);
+#pragma unroll
+      for (int j = 1; j < PR; j += 2) step(at + image_row + 16 * j, j + 2 == PR ? 1 : -1);
+    }
+    if (R & 1) {
+#pragma unroll
+      for (int j = 0; j < PR - 1; j += 2) step(at + 16 * j, -1);
+      step(half ? patch : middle, 3);  // (the weights end with a piece of zeros)
+    }
+  }
+}
+
+template <int DT>
+__device__ __forceinline__ void run_tile_rows(const DevProblem *P_mem, const sk_tile *T_mem, unsigned char *lds, Prefetch &pf) {
+  constexpr int ES = Elem<DT>::ES;
+  constexpr int CE = 16 / ES;
+  constexpr int BM = 128;
+  static_assert(ROWS_LDS == LDS_TILE_BYTES, "the size rows_form goes by");
+  const int tid = pf.tid;
+  const DevProblem P = load_record(P_mem);
+  const sk_tile T = load_record(T_mem);
+  const RowsForm F = rows_form(P, ES);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int l32 = lane & 31, half = lane >> 5;
+  const int m_end = (int)T.m0 + (int)T.m_len, hw = P.Ho * P.Wo;
+  const int b = fast_div((int)T.m0, P.div_hw), image_m = b * hw;  // (the record lies in one image)
+  const int run_len = P.S * P.Cin, row_len = P.W * P.Cin;
+  const int row_pieces = F.image_row / 16;
+  const int np = P.R * F.pieces;  // pieces of a patch, and of a weight row
+  unsigned char *const window = lds + 64 * F.weight_row;
+  const char SK_GLOBAL *const image = as_global<char>(P.A) + (int64_t)b * P.H * row_len * ES;
+
+  // ---- the rows of a block: this thread's pieces tid + 256 i, each always at one place of one of the rows ----
+  u32x4 win[ROWS_LOADS];
+  int win_row[ROWS_LOADS], win_at[ROWS_LOADS], win_sh[ROWS_LOADS];  // row, byte of an image row it is read from, how far from its place that is
+  {
+    const uint32_t inv = 0xffffffffu / (uint32_t)row_pieces + 1u;  // i / row_pieces
+#pragma unroll
+    for (int i = 0; i < ROWS_LOADS; ++i) {
+      const int idx = tid + i * WG_THREADS, r = (int)__umulhi((uint32_t)idx, inv), e0 = (idx - r * row_pieces) * CE - P.pad_w * P.Cin;
+      const int at = min(max(e0, 0), row_len - CE);
+      win_row[i] = r;
+      win_at[i] = at * ES;
+      win_sh[i] = e0 - at;
+    }
+  }
+  auto first_row = [&](int mb) { return fast_div(mb - image_m, P.div_wo); };
+  auto load_window = [&](int mb) {
+    const int h0 = first_row(mb) * P.stride - P.pad_h;
+#pragma unroll
+    for (int i = 0; i < ROWS_LOADS; ++i) {
+      const int h = min(max(h0 + win_row[i], 0), P.H - 1);  // (rows outside the image are cleared when stored)
+      win[i] = *(const u32x4_any SK_GLOBAL *)(image + (uint32_t)(h * (row_len * ES) + win_at[i]));
+    }
+  };
+  auto store_window = [&](int mb) {
+    const int r0 = first_row(mb), h0 = r0 * P.stride - P.pad_h, rows = (first_row(min(mb + BM, m_end) - 1) - r0) * P.stride + P.R;
+#pragma unroll
+    for (int i = 0; i < ROWS_LOADS; ++i) {
+      u32x4 v = win[i];
+      if (__any(win_sh[i] != 0)) v = shift_piece<ES>(v, win_sh[i]);
+      const bool in = (unsigned)(h0 + win_row[i]) < (unsigned)P.H;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = in ? v[e] : 0u;
+      if (win_row[i] < rows) *(u32x4 *)(window + (tid + i * WG_THREADS) * 16) = v;
+    }
+  };
+  load_window((int)T.m0);
+  pf.issue();
+
+  // ---- the weights: row n's pieces side by side, and a piece of zeros where they are odd in number ----
+  {
+    const int per_row = (np + 1) & ~1, n_len = (int)T.n_len;
+    const uint32_t inv = 0xffffffffu / (uint32_t)per_row + 1u, inv_run = 0xffffffffu / (uint32_t)F.pieces + 1u;
+    const char SK_GLOBAL *const base = as_global<char>(P.B) + (int64_t)T.n0 * P.ldb * ES;
+    for (int i0 = 0; i0 < 64 * per_row; i0 += 4 * WG_THREADS) {
+      u32x4 v[4];
+      int sh[4], to[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int idx = i0 + tid + i * WG_THREADS, n = (int)__umulhi((uint32_t)idx, inv), p = idx - n * per_row, q = min(p, np - 1);
+        const int r = F.pieces == 1 ? q : (int)__umulhi((uint32_t)q, inv_run), e0 = (q - r * F.pieces) * CE, at = min(e0, run_len - CE);
+        sh[i] = p < np ? e0 - at : CE;  // (shifted by a whole piece: zeros)
+        to[i] = n < 64 ? n * F.weight_row + p * 16 : -1;
+        // (rows past the edge repeat the last one; never stored)
+        v[i] = *(const u32x4_any SK_GLOBAL *)(base + (uint32_t)((min(n, n_len - 1) * (int)P.ldb + r * run_len + at) * ES));
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (__any(sh[i] != 0)) v[i] = shift_piece<ES>(v[i], sh[i]);
+        if (to[i] >= 0) *(u32x4 *)(lds + to[i]) = v[i];
+      }
+    }
+  }
+  store_window((int)T.m0);
+  __syncthreads();
+
+  // what the last piece of a run keeps
+  uint32_t tail[4];
+  {
+    const int keep = run_len - (F.pieces - 1) * CE;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      tail[i] = ES == 4 ? (i < keep ? ~0u : 0u) : (2 * i < keep ? 0xffffu : 0u) | (2 * i + 1 < keep ? 0xffff0000u : 0u);
+  }
+  const bool odd = ES == 2 && ((P.stride * P.Cin) & 1) != 0;  // some patches start half a dword past one
+
+  for (int mb = (int)T.m0; mb < m_end; mb += BM) {
+    const bool more = mb + BM < m_end;
+    if (more) load_window(mb + BM);
+    // this lane's pixel, and where its patch starts
+    const int m = min(mb + 32 * wave + l32, m_end - 1) - image_m, ho = fast_div(m, P.div_wo), wo = m - ho * P.Wo;
+    const int start = ((ho - first_row(mb)) * F.image_row + wo * P.Cin * ES) * P.stride;
+    const uint32_t shift = (uint32_t)(start & 2) << 3;
+    f32x16 acc[2][1];
+#pragma unroll
+    for (int fn = 0; fn < 2; ++fn)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[fn][0][i] = 0.f;
+    const unsigned char *const patch = window + (start & ~3), *const w = lds + l32 * F.weight_row + half * 16;
+    auto go = [&](auto odd_c) {
+      constexpr bool ODD = decltype(odd_c)::value;
+      if (F.pieces == 3)
+        multiply_rows<DT, 3, ODD>(patch, w, P.R, F.image_row, F.weight_row, half, shift, tail, acc);
+      else if (F.pieces == 2)
+        multiply_rows<DT, 2, ODD>(patch, w, P.R, F.image_row, F.weight_row, half, shift, tail, acc);
+      else if (F.pieces == 1)
+        multiply_rows<DT, 1, ODD>(patch, w, P.R, F.image_row, F.weight_row, half, shift, tail, acc);
+      else if (F.pieces == 4)
+        multiply_rows<DT, 4, ODD>(patch, w, P.R, F.image_row, F.weight_row, half, shift, tail, acc);
+      else
+        multiply_rows<DT, 6, ODD>(patch, w, P.R, F.image_row, F.weight_row, half, shift, tail, acc);
+    };
+    if (ES == 2 && odd)
+      go(std::integral_constant<bool, ES == 2>{});
+    else
+      go(std::false_type{});
+    __syncthreads();  // everyone is done with the window: the outputs are staged in its place
+    any_outputs<DT, false, BM, 64, 4>(P_mem, T_mem, mb, (int)T.n0, window, tid, acc);
+    if (more) {
+      __syncthreads();  // the outputs have been read
+      store_window(mb + BM);
+      __syncthreads();
     }
   }
 }
@@ -2723,10 +2927,13 @@ __device__ __forceinline__ void run_class(const DevProblem &P, const sk_tile &T,
           pieces = true;
         } else {
           pf.claim();
-          pf.issue();
+          const bool rows = !small && rows_tile<Elem<DT>::ES>(P, T);
+          if (!rows) pf.issue();
           // (an operand of less than one piece also goes the first way: the others read whole pieces from inside it)
           if (small || !holds_a_piece<Elem<DT>::ES>(P))
             run_generic<DT>(P_mem, T_mem, pf.tid);
+          else if (rows)
+            run_tile_rows<DT>(P_mem, T_mem, lds, pf);
           else if (P.nchw && planes_tile<Elem<DT>::ES>(P, T))
             run_block_any<DT, true, true>(P_mem, T_mem, (int)T.m_len, (int)T.n_len, sp, lds, s_flag, pf.tid);
           else if (P.nchw)

@@ -475,6 +475,15 @@ static bool runs_in_any_blocks(const DevProblem &d, const sk_tile &t) {
   return !(t.cls < CLS_TILE_128x128 && !d.nchw && d.Kg >= ce && (!d.gather || d.Cin % ce == 0));
 }
 
+// Whether run_tile_rows runs the record: an LDS tile, or a run of them, of an operator that rows_form takes, not split, in one image.
+static bool runs_in_rows(const DevProblem &d, const sk_tile &t) {
+  if (t.cls < CLS_TILE_128x128 || t.cls == CLS_WINDOW || t.S != 1 || !runs_in_any_blocks(d, t) || !rows_form(d, elem_size(d.dtype)).ok) return false;
+  const int64_t hw = (int64_t)d.Ho * d.Wo;
+  return t.m0 / hw == (t.m0 + t.m_len - 1) / hw && ((int64_t)t.m_len * t.n_len + 255) / 256 * d.Kg > 64;
+}
+// ... and what that takes, in nanoseconds on a compute unit that two workgroups share: around the blocks of 128 pixels, a block.
+constexpr int64_t ROWS_START = 6000, ROWS_BLOCK = 3000;
+
 // A record of m_len x n_len outputs in blocks of any alignment, `stages` of 128 bytes of the reduction.
 static RecordCost any_block_cost(const DevProblem &d, int64_t m_len, int64_t n_len, int64_t stages) {
   const bool m64 = m_len <= 64, n64 = n_len <= 64;
@@ -493,6 +502,10 @@ static RecordCost any_block_cost(const DevProblem &d, int64_t m_len, int64_t n_l
 static RecordCost record_cost(const DevProblem &d, const sk_tile &t) {
   const int64_t es = elem_size(d.dtype), kb = 128 / es, stages = ((int64_t)t.k_len + kb - 1) / kb;
   const bool f32 = d.dtype == SK_F32;
+  if (runs_in_rows(d, t)) {
+    const int64_t blocks = (t.m_len + 127) / 128;
+    return RecordCost{ROWS_START + blocks * ROWS_BLOCK, ROWS_START / 2 + blocks * ROWS_BLOCK / 2};
+  }
   if (runs_in_any_blocks(d, t)) return any_block_cost(d, t.m_len, t.n_len, stages);
   if (t.cls < CLS_TILE_128x128) {
     const int64_t steps = stages * ((t.n_len + 127) / 128);
@@ -543,7 +556,7 @@ static bool refine_blocks(const HostPlan &hp, int64_t workgroups, std::vector<sk
     if (any) stages += stages_of(t);
     // (up to 64 reduction elements a small rectangle may go the one-output-per-thread way, whose sums round differently: a
     // part must not where its record does not)
-    if (t.S != 1 || (t.m_len <= 64 && t.n_len <= 64) || d.Kg <= 64 || !any) {
+    if (t.S != 1 || (t.m_len <= 64 && t.n_len <= 64) || d.Kg <= 64 || !any || runs_in_rows(d, t)) {
       whole = std::max(whole, c.time);
       continue;
     }
@@ -615,6 +628,7 @@ struct RecordTime {
 constexpr int64_t WINDOW_START = 6000, WINDOW_STEP = 3000;
 static RecordTime record_time(const DevProblem &d, const sk_tile &t, bool any) {
   const bool f32 = d.dtype == SK_F32;
+  if (any && runs_in_rows(d, t)) return RecordTime{ROWS_START + (t.m_len + 127) / 128 * ROWS_BLOCK, 0, 0};
   if (any) {
     const int64_t one = any_block_cost(d, t.m_len, t.n_len, 1).time, step = any_block_cost(d, t.m_len, t.n_len, 2).time - one;
     return RecordTime{one - step, f32 ? step * 13 / 10 : step, 8000};
@@ -987,6 +1001,43 @@ bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile>
 // A launch that fills a whole MI355X: two workgroups on each of its 256 compute units.
 constexpr int64_t CHIP_WORKGROUPS = 512;
 
+// Tiles that run_tile_rows runs, side by side along the rows, as runs of a third of a workgroup's share of the launch: a run loads its weights
+// once, and a block's rows while the one before is multiplied.  Only where they are a fifth of the work at least: elsewhere longer records
+// cost the launch's end more than they save.  Down-sampling layers with the 7x7 stem, us, in single tiles / in runs of half, a third and a quarter of a
+// share: for sixteen tenants 102.6 / 91.6, 85.4, 91.9, for eleven 70.1 / 65.3, 66.1, 63.8, for eight 54.0 / 53.8, 47.7, 51.1, for six 44.5 / 40.9, 39.9, 44.2;
+// 96 odd-sized operators, of which they are a seventh, 70.5 / 75.7, 75.3, 70.1.  False: nothing changed.
+static bool rows_runs(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &records, std::vector<int64_t> &count) {
+  constexpr int64_t MOST = 16, BLOCK = 4500;  // blocks; nanoseconds of one, with its part of what is around them
+  if (workgroups < 1) return false;
+  int64_t total = 0, rows = 0;
+  for (const sk_tile &t : records) {
+    const DevProblem &d = hp.dev[t.problem];
+    const int64_t time = record_cost(d, t).work * 2;
+    total += time;
+    if (runs_in_rows(d, t)) rows += time;
+  }
+  const int64_t blocks = std::min<int64_t>(MOST, total / workgroups / 3 / BLOCK);
+  if (rows * 5 < total || blocks < 2) return false;
+  std::vector<sk_tile> runs;
+  runs.reserve(records.size());
+  for (const sk_tile &t : records) {
+    if (!runs.empty() && runs.back().problem == t.problem && runs.back().n0 == t.n0 && runs.back().m0 + runs.back().m_len == t.m0 &&
+        runs.back().m_len % 128 == 0 && runs.back().m_len + t.m_len <= 128 * blocks && runs_in_rows(hp.dev[t.problem], t)) {
+      sk_tile u = runs.back();
+      u.m_len = (uint16_t)(u.m_len + t.m_len);
+      if (runs_in_rows(hp.dev[t.problem], runs.back()) && runs_in_rows(hp.dev[t.problem], u)) {
+        runs.back() = u;
+        --count[t.problem];
+        continue;
+      }
+    }
+    runs.push_back(t);
+  }
+  const bool changed = runs.size() != records.size();
+  if (changed) records.swap(runs);
+  return changed;
+}
+
 // The list of tiles, and with `runs` of runs of pixels where they pay, for a launch of that many workgroups.
 static bool list_records(const HostPlan &hp, int64_t workgroups, bool runs, bool tiles_only, const std::vector<Slicing> *impose, WorkList &out) {
   std::vector<sk_tile> cut;
@@ -1009,7 +1060,14 @@ static bool list_records(const HostPlan &hp, int64_t workgroups, bool runs, bool
     return true;
   }
   if (tiles_only) return false;
-  const bool refined = refine_blocks(hp, workgroups, cut, count);
+  bool refined = refine_blocks(hp, workgroups, cut, count);
+  if (hp.xorder.empty()) {
+    if (!refined) {
+      cut = hp.tiles;
+      count = hp.count;
+    }
+    refined = rows_runs(hp, workgroups, cut, count) || refined;
+  }
   if (balance_records(hp, refined ? cut : hp.tiles, workgroups, false, impose, out)) return true;
   if (!refined || !hp.xorder.empty()) return false;
   as_cut();

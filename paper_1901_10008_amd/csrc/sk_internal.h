@@ -72,6 +72,31 @@ SK_HOST_DEVICE bool planes_form(const DevProblem &d, int64_t es) {
          (int64_t)d.H * d.W * d.Cin >= piece && (uint64_t)(128 * d.ldb * es) >> 31 == 0;
 }
 
+// How run_tile_rows holds an NHWC convolution of few channels in LDS: `pieces` of 16 bytes per filter row's run of S * Cin elements, a weight row of
+// `weight_row` bytes, a row of the image (its padding included) of `image_row`, of which a tile needs `rows` at most.  ok: it serves the
+// operator (filters and images small enough, at most 64 output channels, runs of one to four or six pieces, image rows of at least one).
+struct RowsForm {
+  bool ok;
+  int32_t pieces, weight_row, image_row, rows;
+};
+constexpr int32_t ROWS_LOADS = 6;               // pieces of an image window per thread
+constexpr int32_t ROWS_LDS = 512 * 144;         // LDS_TILE_BYTES of the kernels
+SK_HOST_DEVICE RowsForm rows_form(const DevProblem &d, int32_t es) {
+  const int32_t ce = 16 / es;
+  RowsForm f{false, 0, 0, 0, 0};
+  if (!d.gather || d.nchw || d.Ng > 64 || d.R > 16 || d.S > 16 || d.Cin > 16 || d.Wo > 4096 || d.stride > 16) return f;
+  const int32_t run = d.S * d.Cin;
+  if (run < ce || (int64_t)d.W * d.Cin < ce || ((uint64_t)d.H * (uint64_t)d.W * (uint64_t)(d.Cin * es)) >> 31 != 0 || ((uint64_t)64 * (uint64_t)d.ldb * (uint64_t)es) >> 31 != 0) return f;
+  f.pieces = (run + ce - 1) / ce;
+  if (f.pieces == 5 || f.pieces > 6) return f;
+  f.weight_row = ((d.R * f.pieces + 1) / 2 * 2 + 1) * 16;  // (an odd number of pieces: the rows' banks)
+  f.image_row = (((d.Wo - 1) * d.stride * d.Cin + f.pieces * ce) * es + 31) / 16 * 16;
+  f.rows = (126 + d.Wo) / d.Wo * d.stride + d.R;
+  const int32_t window = f.rows * f.image_row, outputs = 128 * (64 * es + 16);
+  f.ok = window <= ROWS_LOADS * 256 * 16 && 64 * f.weight_row + (window > outputs ? window : outputs) <= ROWS_LDS;
+  return f;
+}
+
 // n / d for 0 <= n < 2^31 as (n * mul) >> shift with mul = floor(2^(31+l) / d) + 1, l = ceil(log2 d), shift = 31 + l:
 // mul * d = 2^(31+l) + e with 0 < e <= d <= 2^l, so the quotient is off by less than n / (d * 2^31) < 1 / d.
 struct FastDiv {
