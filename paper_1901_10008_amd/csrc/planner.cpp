@@ -224,6 +224,8 @@ static bool past_caches(const HostPlan &hp) {
   return bytes > LINE;
 }
 
+static void mark_rows(HostPlan &hp);
+
 sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params *params, HostPlan &out,
                     std::string &err) {
   if (n < 0 || (n > 0 && !problems)) {
@@ -455,6 +457,7 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
   build_xcd_lists(out, canon);
   if (past_caches(out))
     for (DevProblem &d : out.dev) d.flags |= FLAG_PAST_CACHES;
+  mark_rows(out);
   return SK_OK;
 }
 
@@ -476,8 +479,10 @@ static bool runs_in_any_blocks(const DevProblem &d, const sk_tile &t) {
 }
 
 // Whether run_tile_rows runs the record: an LDS tile, or a run of them, of an operator that rows_form takes, not split, in one image.
+// (Only in plans where such operators are marked, mark_rows: in others they are planned as blocks of any alignment, as before; they run no slower than
+// those.)
 static bool runs_in_rows(const DevProblem &d, const sk_tile &t) {
-  if (t.cls < CLS_TILE_128x128 || t.cls == CLS_WINDOW || t.S != 1 || !runs_in_any_blocks(d, t) || !rows_form(d, elem_size(d.dtype)).ok) return false;
+  if (!(d.flags & FLAG_ROWS) || t.cls < CLS_TILE_128x128 || t.cls == CLS_WINDOW || t.S != 1 || !runs_in_any_blocks(d, t) || !rows_form(d, elem_size(d.dtype)).ok) return false;
   const int64_t hw = (int64_t)d.Ho * d.Wo;
   return t.m0 / hw == (t.m0 + t.m_len - 1) / hw && ((int64_t)t.m_len * t.n_len + 255) / 256 * d.Kg > 64;
 }
@@ -616,6 +621,27 @@ static bool refine_blocks(const HostPlan &hp, int64_t workgroups, std::vector<sk
 
 bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &work, std::vector<int64_t> &count) {
   return hp.xorder.empty() && refine_blocks(hp, workgroups, work, count);
+}
+
+// Marks the operators that run_tile_rows serves where they are a fifth of the work of a plan of one element type.  (In the kernels for mixed types, which
+// spill more scalars than any, it gains nothing: three plans of 70 to 95 operators in three types, a fifth to a quarter of their work such, took 4 to 7 %
+// longer planned by its times.)
+static void mark_rows(HostPlan &hp) {
+  bool some = false;
+  for (const DevProblem &d : hp.dev)
+    if (d.dtype != hp.dev[0].dtype) return;
+  for (DevProblem &d : hp.dev)
+    if (rows_form(d, elem_size(d.dtype)).ok) d.flags |= FLAG_ROWS, some = true;
+  if (!some) return;
+  int64_t total = 0, rows = 0;
+  for (const sk_tile &t : hp.tiles) {
+    const DevProblem &d = hp.dev[t.problem];
+    const int64_t work = record_cost(d, t).work;
+    total += work;
+    if (runs_in_rows(d, t)) rows += work;
+  }
+  if (rows * 5 < total)
+    for (DevProblem &d : hp.dev) d.flags &= ~FLAG_ROWS;
 }
 
 // What a record takes on a chip whose compute units hold two workgroups each, in nanoseconds: `start` around its steps (set-up, first
@@ -1002,22 +1028,18 @@ bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile>
 constexpr int64_t CHIP_WORKGROUPS = 512;
 
 // Tiles that run_tile_rows runs, side by side along the rows, as runs of a third of a workgroup's share of the launch: a run loads its weights
-// once, and a block's rows while the one before is multiplied.  Only where they are a fifth of the work at least: elsewhere longer records
-// cost the launch's end more than they save.  Down-sampling layers with the 7x7 stem, us, in single tiles / in runs of half, a third and a quarter of a
+// once, and a block's rows while the one before is multiplied.  (Not where they are less than a fifth of the work, FLAG_ROWS: longer records
+// cost the launch's end more than they save there.)  Down-sampling layers with the 7x7 stem, us, in single tiles / in runs of half, a third and a quarter of a
 // share: for sixteen tenants 102.6 / 91.6, 85.4, 91.9, for eleven 70.1 / 65.3, 66.1, 63.8, for eight 54.0 / 53.8, 47.7, 51.1, for six 44.5 / 40.9, 39.9, 44.2;
 // 96 odd-sized operators, of which they are a seventh, 70.5 / 75.7, 75.3, 70.1.  False: nothing changed.
 static bool rows_runs(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &records, std::vector<int64_t> &count) {
   constexpr int64_t MOST = 16, BLOCK = 4500;  // blocks; nanoseconds of one, with its part of what is around them
   if (workgroups < 1) return false;
-  int64_t total = 0, rows = 0;
-  for (const sk_tile &t : records) {
-    const DevProblem &d = hp.dev[t.problem];
-    const int64_t time = record_cost(d, t).work * 2;
-    total += time;
-    if (runs_in_rows(d, t)) rows += time;
-  }
+  if (std::none_of(hp.dev.begin(), hp.dev.end(), [](const DevProblem &d) { return (d.flags & FLAG_ROWS) != 0; })) return false;
+  int64_t total = 0;
+  for (const sk_tile &t : records) total += record_cost(hp.dev[t.problem], t).work * 2;
   const int64_t blocks = std::min<int64_t>(MOST, total / workgroups / 3 / BLOCK);
-  if (rows * 5 < total || blocks < 2) return false;
+  if (blocks < 2) return false;
   std::vector<sk_tile> runs;
   runs.reserve(records.size());
   for (const sk_tile &t : records) {

@@ -15,6 +15,7 @@ enum : int32_t {
   FLAG_VEC_A = 1,  // activation rows can be read in aligned 16-byte pieces
   FLAG_VEC_B = 2,  // weight rows can be read in aligned 16-byte pieces
   FLAG_VEC_C = 4,  // four consecutive outputs of a row can be stored as one vector
+  FLAG_ROWS = 16,  // the host plans the operator as one of run_tile_rows (which runs it in either case)
   FLAG_PAST_CACHES = 8,  // outputs of whole tiles go past the caches (of every operator of the plan, or of none)
 };
 
