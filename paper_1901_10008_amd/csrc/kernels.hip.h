@@ -2028,18 +2028,37 @@ __device__ __forceinline__ bool any_handover(const sk_tile &T, const SplitK &sp,
     *s_flag = __hip_atomic_fetch_add(&sp.arrive[T.out_tile_id], 1u, SK_ARRIVE_ORDER, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   if (*s_flag != (uint32_t)T.S - 1) return false;
+  // Four quads at a time: their partial sums of a slice are requested together (one by one, each quad and slice was a memory round trip).  Quads
+  // outside the rectangle read its first one.
+  constexpr int TOGETHER = 4;
 #pragma unroll 1
-  for (int p = 0; p < FN * FM * 4; ++p) {
-    unsigned long long *q = place(p);
-    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-    if (q) {
-      for (int s2 = 0; s2 < T.S; ++s2, q += 2 * per_slice) {
-        const f32x2 lo = __builtin_bit_cast(f32x2, __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        const f32x2 hi = __builtin_bit_cast(f32x2, __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        sum += f32x4{lo.x, lo.y, hi.x, hi.y};
+  for (int p0 = 0; p0 < FN * FM * 4; p0 += TOGETHER) {
+    unsigned long long *q[TOGETHER];
+    f32x4 sum[TOGETHER];
+#pragma unroll
+    for (int u = 0; u < TOGETHER; ++u) {
+      q[u] = place(p0 + u);
+      if (!q[u]) q[u] = mine;
+      sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll 1
+    for (int s2 = 0; s2 < T.S; ++s2) {
+      unsigned long long part[TOGETHER][2];
+#pragma unroll
+      for (int u = 0; u < TOGETHER; ++u) {
+        part[u][0] = __hip_atomic_load(q[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        part[u][1] = __hip_atomic_load(q[u] + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        q[u] += 2 * per_slice;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < TOGETHER; ++u) {
+        const f32x2 lo = __builtin_bit_cast(f32x2, part[u][0]), hi = __builtin_bit_cast(f32x2, part[u][1]);
+        sum[u] += f32x4{lo.x, lo.y, hi.x, hi.y};
       }
     }
-    slot[p * WG_THREADS] = sum;
+#pragma unroll
+    for (int u = 0; u < TOGETHER; ++u) slot[(p0 + u) * WG_THREADS] = sum[u];
   }
   if (tid == 0)  // re-arm for the next launch
     __hip_atomic_store(&sp.arrive[T.out_tile_id], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
