@@ -461,6 +461,9 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
   return SK_OK;
 }
 
+// A launch that fills a whole MI355X: two workgroups on each of its 256 compute units.
+constexpr int64_t CHIP_WORKGROUPS = 512;
+
 // What a record costs, in nanoseconds: `time` by itself on a compute unit, and `work`, its share of a compute unit that two
 // workgroups keep busy.  Measured on plans of one kind of record each, 1 to 1024 of them, over 3 to 27 stages (fp32 blocks that
 // read rows: 1.2 times that time, which is what they take among other records).  They decide which records are cut
@@ -626,8 +629,10 @@ bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &
 // Marks the operators that run_tile_rows serves where they are a fifth of the work of a plan of one element type.  (In the kernels for mixed types, which
 // spill more scalars than any, it gains nothing: three plans of 70 to 95 operators in three types, a fifth to a quarter of their work such, took 4 to 7 %
 // longer planned by its times.)
+// (Nor in plans whose tiles all start at once: 30 odd bf16 operators 29.4 -> 30.4 us.)
 static void mark_rows(HostPlan &hp) {
   bool some = false;
+  if ((int64_t)hp.tiles.size() <= CHIP_WORKGROUPS) return;
   for (const DevProblem &d : hp.dev)
     if (d.dtype != hp.dev[0].dtype) return;
   for (DevProblem &d : hp.dev)
@@ -1024,9 +1029,6 @@ bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile>
   return true;
 }
 
-// A launch that fills a whole MI355X: two workgroups on each of its 256 compute units.
-constexpr int64_t CHIP_WORKGROUPS = 512;
-
 // Tiles that run_tile_rows runs, side by side along the rows, as runs of a third of a workgroup's share of the launch: a run loads its weights
 // once, and a block's rows while the one before is multiplied.  (Not where they are less than a fifth of the work, FLAG_ROWS: longer records
 // cost the launch's end more than they save there.)  Down-sampling layers with the 7x7 stem, us, in single tiles / in runs of half, a third and a quarter of a
@@ -1055,9 +1057,9 @@ static bool rows_runs(const HostPlan &hp, int64_t workgroups, std::vector<sk_til
     }
     runs.push_back(t);
   }
-  const bool changed = runs.size() != records.size();
-  if (changed) records.swap(runs);
-  return changed;
+  if (runs.size() == records.size()) return false;
+  records.swap(runs);
+  return true;
 }
 
 // The list of tiles, and with `runs` of runs of pixels where they pay, for a launch of that many workgroups.
@@ -1082,13 +1084,21 @@ static bool list_records(const HostPlan &hp, int64_t workgroups, bool runs, bool
     return true;
   }
   if (tiles_only) return false;
-  bool refined = refine_blocks(hp, workgroups, cut, count);
+  const bool refined = refine_blocks(hp, workgroups, cut, count);
   if (hp.xorder.empty()) {
-    if (!refined) {
-      cut = hp.tiles;
-      count = hp.count;
+    std::vector<sk_tile> joined = refined ? cut : hp.tiles;
+    std::vector<int64_t> joined_count = refined ? count : hp.count;
+    if (rows_runs(hp, workgroups, joined, joined_count)) {
+      // (the slices are those of the tiles, with and without lists; order and cuts go by the runs)
+      std::vector<Slicing> own;
+      WorkList plain;
+      if (!impose && balance_records(hp, refined ? cut : hp.tiles, workgroups, false, nullptr, plain)) own = std::move(plain.slicing);
+      cut = std::move(joined);
+      count = std::move(joined_count);
+      if (!balance_records(hp, cut, workgroups, false, impose ? impose : &own, out)) as_cut();
+      out.slicing = std::move(own);
+      return true;
     }
-    refined = rows_runs(hp, workgroups, cut, count) || refined;
   }
   if (balance_records(hp, refined ? cut : hp.tiles, workgroups, false, impose, out)) return true;
   if (!refined || !hp.xorder.empty()) return false;
