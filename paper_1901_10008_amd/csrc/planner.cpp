@@ -629,10 +629,11 @@ bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &
 // Marks the operators that run_tile_rows serves where they are a fifth of the work of a plan of one element type.  (In the kernels for mixed types, which
 // spill more scalars than any, it gains nothing: three plans of 70 to 95 operators in three types, a fifth to a quarter of their work such, took 4 to 7 %
 // longer planned by its times.)
-// (Nor in plans whose tiles all start at once: 30 odd bf16 operators 29.4 -> 30.4 us.)
+// (Nor in plans of less than two rounds of tiles, where runs leave too few records to even the launch's end out: 67 odd bf16 operators 35.9 -> 37.5 us, 30
+// of them 29.4 -> 30.4, ten such plans 0.97 to 1.02; stride-2 layers for five, 885 tiles, would gain 3 %, for six, 1062 tiles, 10 %.)
 static void mark_rows(HostPlan &hp) {
   bool some = false;
-  if ((int64_t)hp.tiles.size() <= CHIP_WORKGROUPS) return;
+  if ((int64_t)hp.tiles.size() <= 2 * CHIP_WORKGROUPS) return;
   for (const DevProblem &d : hp.dev)
     if (d.dtype != hp.dev[0].dtype) return;
   for (DevProblem &d : hp.dev)
