@@ -1,0 +1,50 @@
+"""The device's records of few-channel convolutions (runs of tiles): on the CPU, that they cover every output once, that tiles are joined where that
+pays and nowhere else, and that plans with per-die lists keep the same slices."""
+import pytest
+
+import paper_1901_10008_amd as sk
+import sk_harness as H
+from workloads import Problem
+
+
+def _conv(hw, cin, cout, r, pad, stride=2, dtype="bf16", nb=1):
+    return Problem(op="conv", dtype=dtype, Nb=nb, H=hw, W=hw, Cin=cin, Cout=cout, R=r, S=r, pad_h=pad, pad_w=pad, stride=stride)
+
+
+LAYERS = [_conv(224, 3, 64, 7, 3), _conv(56, 128, 128, 3, 1), _conv(28, 256, 256, 3, 1), _conv(28, 512, 1024, 1, 0), _conv(14, 512, 512, 3, 1)]
+
+
+def _records(specs, **prm):
+    at = 1 << 40
+    problems = [sk.make_problem(s, at + (i << 32), at + (i << 32) + (1 << 30), at + (i << 32) + (2 << 30)) for i, s in enumerate(specs)]
+    with sk.sk_plan_create(problems, sk.sk_plan_params_default(host_only=1, **prm)) as plan:
+        return H.device_records(plan), sk.sk_plan_num_tiles(plan)
+
+
+@pytest.mark.parametrize("specs,joined", [
+    (LAYERS * 16, True),
+    ([_conv(224, 3, 64, 7, 3, nb=2)] * 8 + LAYERS * 4, True),                        # (tiles of two images stay single)
+    (LAYERS * 2, False),                                                             # too few tiles
+    (LAYERS[:1] * 8 + LAYERS[1:] * 40, False),                                       # not a fifth of the work
+    (LAYERS * 12 + [_conv(28, 512, 1024, 1, 0, dtype="f16")], False),                # two types
+], ids=["downsampling", "images", "few", "share", "types"])
+def test_runs_cover_every_output_once(specs, joined):
+    records, tiles = _records(specs)
+    assert any(r[6] > 128 for r in records) == joined
+    rows = {}
+    for p, cls, ks, S, m0, n0, m_len, n_len, k0, k_len, rect in records:
+        if specs[p].Cin == 3:
+            assert (ks, S, n0, n_len, k0, k_len) == (0, 1, 0, 64, 0, 147)
+            rows.setdefault(p, []).append((m0, m0 + m_len))
+            assert m_len <= 128 or m0 // 12544 == (m0 + m_len - 1) // 12544
+    for p, s in enumerate(specs):
+        if s.Cin == 3:
+            spans = sorted(rows[p])
+            assert spans[0][0] == 0 and spans[-1][1] == s.Nb * 12544 and all(a[1] == b[0] for a, b in zip(spans, spans[1:]))
+    assert (len(records) < tiles) == joined or not joined
+
+
+def test_lists_keep_the_slices():
+    specs = LAYERS * 16
+    slices = [{(r[0], r[4] if specs[r[0]].Cin != 3 else 0, r[8], r[9]) for r in _records(specs, xcd_part=part)[0]} for part in (0, 32)]
+    assert slices[0] == slices[1]
