@@ -25,7 +25,9 @@
 //     contiguous: one output per thread for small rectangles; MFMA blocks whose
 //     pieces are read at any address and shifted into place (images in channel
 //     planes: element by element, lanes along pixels) for larger ones; only in
-//     the kernel instantiations for plans that need them.
+//     the kernel instantiations for plans that need them.  Two forms of these have
+//     paths of their own: channel-major convolutions that keep the images' width
+//     (run_tile_planes) and NHWC ones of few channels, stems (run_tile_rows).
 //   * 3x3 convolutions of 64 channels in plans that fill the chip (run_window): weights in registers, pixels through a
 //     ring in LDS, every pixel read once for its nine taps.
 #pragma once
@@ -2078,7 +2080,7 @@ __device__ __forceinline__ bool any_handover(const sk_tile &T, const SplitK &sp,
   return true;
 }
 
-// Outputs of a block of run_tile_any or run_tile_planes (rows mb .., columns nb ..): through LDS, so that they leave as runs of consecutive places.
+// Outputs of a block of run_tile_any, run_tile_planes or run_tile_rows (rows mb .., columns nb ..): through LDS, so that they leave as runs of consecutive places.
 // (WM waves side by side along the rows, 4 / WM along the columns.)
 template <int DT, bool NCHW, int ROWS, int COLS, int WM>
 __device__ __forceinline__ void any_outputs(const DevProblem *P_mem, const sk_tile *T_mem, int mb, int nb, unsigned char *lds, int tid,
@@ -2445,7 +2447,8 @@ __device__ __forceinline__ void run_tile_any(const DevProblem *P_mem, const sk_t
 //     reduction indices of its pixel), fp32 ones element by element.
 // The sums are those of run_tile_any: the same bits.  What a stage cost there were the instructions for its single elements (32 loads of
 // two bytes a lane and stage, and as many masks and packs; here four loads, and two dozen instructions for each): channel-major
-// ResNet layers for eight 98.1 -> 70.1 us.
+// ResNet layers for eight 98.1 -> 67.6 us (61.8 with the partial sums of slices read together, any_handover).  What binds it now is the
+// loads: at places that are no multiples of a dword 16 bytes a lane run one lane a clock (67 clocks for 1 KB, 21 to 24 from any dword's address).
 constexpr int PLANES_TAPS = 12;  // the most planes_form lets through
 template <int ES>
 __device__ __forceinline__ bool planes_tile(const DevProblem &P, const sk_tile &T) {
@@ -2713,7 +2716,9 @@ __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const s
 //   * the weights (at most 64 channels) stay in LDS for all blocks of the record, and the next block's rows are on their way while one
 //     is multiplied;
 //   * a wave makes 32 pixels x 64 channels, so that each pixel's fragments are read and cleared once.
-// Pieces and their order are those of run_tile_any: the same sums, the same bits.
+// Pieces and their order are those of run_tile_any: the same sums, the same bits.  7x7 stems on 224x224x3 of 64 tenants 146 -> 80 us, of 16 beside the
+// other down-sampling layers of a residual network 100.4 -> 74.2; with the positions worked out piece by piece in the loop, a hundred scalar
+// instructions a step, 127 of 146.
 template <int ES>
 __device__ __forceinline__ bool rows_tile(const DevProblem &P, const sk_tile &T) {
   if (T.cls < CLS_TILE_128x128 || T.S != 1 || !rows_form(P, ES).ok) return false;
