@@ -816,7 +816,8 @@ static bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &reco
             x.time = rt.start + stages_of(t) * wide * rt.step;
             changed = changed || x.width < t.n_len;
           }
-        } else if (!impose && t.cls != CLS_WINDOW && hp.params.tail_div > 0 && t.m_len <= 128 && t.n_len <= 128) {
+        } else if (!impose && rt.step > 0 && hp.params.tail_div > 0 && t.m_len <= 128 && t.n_len <= 128) {
+          // (a step of no time: a run of pixels or of tiles, timed by its pixels; never sliced)
           constexpr int64_t GRAIN = 4;  // stages
           const int64_t kb = 128 / elem_size(d.dtype), k = t.S > 1 ? d.Kg : (int64_t)t.k_len, all = (k + kb - 1) / kb;
           const int64_t fits = (std::max<int64_t>((most - rt.start - rt.hand) / rt.step, any ? 8 : 16) + GRAIN - 1) / GRAIN * GRAIN;

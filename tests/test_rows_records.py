@@ -1,5 +1,9 @@
 """The device's records of few-channel convolutions (runs of tiles): on the CPU, that they cover every output once, that tiles are joined where that
-pays and nowhere else, and that plans with per-die lists keep the same slices."""
+pays and nowhere else, that plans with per-die lists keep the same slices, and that no cost of such a tile makes the planner slice it."""
+import os
+import shutil
+import subprocess
+
 import pytest
 
 import paper_1901_10008_amd as sk
@@ -48,3 +52,56 @@ def test_lists_keep_the_slices():
     specs = LAYERS * 16
     slices = [{(r[0], r[4] if specs[r[0]].Cin != 3 else 0, r[8], r[9]) for r in _records(specs, xcd_part=part)[0]} for part in (0, 32)]
     assert slices[0] == slices[1]
+
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1901_10008_amd", "csrc")
+
+# A plan of few stems beside many short tiles, where a long record would be sliced: none of the stems' is.
+SLICES_CPP = r"""
+#include <cstdio>
+#include <limits>
+#include <string>
+#include "sk_internal.h"
+int main() {
+  std::vector<sk_problem> ps;
+  for (int i = 0; i < 47; ++i) {
+    const bool stem = i < 5;  // 64x64x3, 7x7, stride 2: eight tiles each; 56x56x64, 1x1: 25
+    sk_problem p{};
+    p.op = SK_CONV2D_NHWC, p.dtype = SK_BF16, p.Nb = 1, p.H = p.Wd = stem ? 64 : 56, p.Cin = stem ? 3 : 64, p.Cout = 64;
+    p.R = p.S = stem ? 7 : 1, p.pad_h = p.pad_w = stem ? 3 : 0, p.stride = stem ? 2 : 1;
+    p.deadline_ms = std::numeric_limits<double>::infinity();
+    const uintptr_t at = ((uintptr_t)1 << 44) + ((uintptr_t)i << 32);
+    p.A = (void *)at, p.B = (void *)(at + (1u << 30)), p.C = (void *)(at + (2ull << 30));
+    ps.push_back(p);
+  }
+  sk_plan_params prm;
+  sk_plan_params_default(&prm);
+  prm.host_only = 1;
+  sk::HostPlan hp;
+  std::string err;
+  if (sk::plan_host(ps.data(), (int32_t)ps.size(), &prm, hp, err) != SK_OK) return 1;
+  if (!(hp.dev[0].flags & sk::FLAG_ROWS)) return 2;
+  sk::WorkList w;
+  if (!sk::device_list(hp, 512, false, w, true)) return 3;
+  for (const sk_tile &t : w.work)
+    if (t.problem < 5 && t.S != 1) return 4;
+  std::puts("slices: ok");
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host C++ compiler")
+def test_tiles_of_few_channels_are_never_sliced(tmp_path):
+    """Whatever the planner takes such a tile's start to cost: here so much that it outlasts what other records are sliced from."""
+    with open(os.path.join(CSRC, "planner.cpp")) as f:
+        text = f.read()
+    assert text.count("ROWS_START = 6000") == 1
+    (tmp_path / "planner.cpp").write_text(text.replace("ROWS_START = 6000", "ROWS_START = 40000"))
+    (tmp_path / "main.cpp").write_text(SLICES_CPP)
+    exe = str(tmp_path / "slices")
+    res = subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", CSRC, str(tmp_path / "main.cpp"),
+                          str(tmp_path / "planner.cpp"), "-o", exe], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+    res = subprocess.run([exe], capture_output=True, text=True)
+    assert res.returncode == 0 and "slices: ok" in res.stdout, (res.returncode, res.stderr)
