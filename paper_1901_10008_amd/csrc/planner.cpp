@@ -481,13 +481,22 @@ static bool runs_in_any_blocks(const DevProblem &d, const sk_tile &t) {
   return !(t.cls < CLS_TILE_128x128 && !d.nchw && d.Kg >= ce && (!d.gather || d.Cin % ce == 0));
 }
 
-// Whether run_tile_rows runs the record: an LDS tile, or a run of them, of an operator that rows_form takes, not split, in one image.
+static bool in_one_image(const DevProblem &d, const sk_tile &t) {
+  const uint32_t hw = (uint32_t)(d.Ho * d.Wo);
+  return hw == (uint32_t)d.Mg || t.m0 / hw == (t.m0 + t.m_len - 1) / hw;
+}
+// Whether run_tile_rows runs the record: an LDS tile, or a run of them, of an operator that rows_form takes (only such are marked), not split, in one image.
 // (Only in plans where such operators are marked, mark_rows: in others they are planned as blocks of any alignment, as before; they run no slower than
 // those.)
 static bool runs_in_rows(const DevProblem &d, const sk_tile &t) {
-  if (!(d.flags & FLAG_ROWS) || t.cls < CLS_TILE_128x128 || t.cls == CLS_WINDOW || t.S != 1 || !runs_in_any_blocks(d, t) || !rows_form(d, elem_size(d.dtype)).ok) return false;
-  const int64_t hw = (int64_t)d.Ho * d.Wo;
-  return t.m0 / hw == (t.m0 + t.m_len - 1) / hw && ((int64_t)t.m_len * t.n_len + 255) / 256 * d.Kg > 64;
+  if (!(d.flags & FLAG_ROWS) || t.cls < CLS_TILE_128x128 || t.cls == CLS_WINDOW || t.S != 1 || !runs_in_any_blocks(d, t)) return false;
+  return in_one_image(d, t) && ((int64_t)t.m_len * t.n_len + 255) / 256 * d.Kg > 64;
+}
+// Whether b, which follows a, takes what a takes: records of an operator are mostly alike.  (Which tiles of several images lie in one is asked of
+// each.)
+static bool alike(const DevProblem &d, const sk_tile &a, const sk_tile &b) {
+  return a.problem == b.problem && a.m_len == b.m_len && a.n_len == b.n_len && a.k_len == b.k_len && a.S == b.S &&
+         (!(d.flags & FLAG_ROWS) || d.Mg == d.Ho * d.Wo);
 }
 // ... and what that takes, in nanoseconds on a compute unit that two workgroups share: around the blocks of 128 pixels, a block.
 constexpr int64_t ROWS_START = 6000, ROWS_BLOCK = 3000;
@@ -524,6 +533,25 @@ static RecordCost record_cost(const DevProblem &d, const sk_tile &t) {
   return RecordCost{5000 + stages * (f32 ? 2000 : 700), 2500 + stages * (f32 ? 1800 : 1000)};
 }
 
+// The work of all records; `rows`: of those that run_tile_rows runs.
+static int64_t work_of(const HostPlan &hp, const std::vector<sk_tile> &records, int64_t *rows) {
+  int64_t total = 0, of_rows = 0, work = 0;
+  bool in_rows = false;
+  const sk_tile *last = nullptr;
+  for (const sk_tile &t : records) {
+    const DevProblem &d = hp.dev[t.problem];
+    if (!last || !alike(d, *last, t)) {
+      work = record_cost(d, t).work;
+      in_rows = runs_in_rows(d, t);
+    }
+    last = &t;
+    total += work;
+    if (in_rows) of_rows += work;
+  }
+  if (rows) *rows = of_rows;
+  return total;
+}
+
 // A launch lasts at least as long as its longest record, and as long as the work of all records spread over the compute
 // units.  Where a record without 16-byte pieces is what it would wait for, such records are cut into parts of at most 64 x 64
 // outputs.  A part takes 0.4 (fp32) to 0.7 (16-bit types) of the time of a 128 x 128 block, but the parts together 1.4 to 2.6
@@ -555,16 +583,23 @@ static bool refine_blocks(const HostPlan &hp, int64_t workgroups, std::vector<sk
   int64_t longest = 0, whole = 0, part = 0, total = 0;  // cuttable; not cuttable; a part of the longest; work of all
   int64_t stages = 0;                                   // of all records in such blocks
   bool fp32 = false;                                    // one of those that can be cut is
+  RecordCost c{0, 0};
+  int64_t steps = 0;
+  bool any = false, rows = false;
   for (size_t i = 0; i < hp.tiles.size(); ++i) {
     const sk_tile &t = hp.tiles[i];
     const DevProblem &d = hp.dev[t.problem];
-    const RecordCost c = record_cost(d, t);
-    const bool any = runs_in_any_blocks(d, t);
+    if (i == 0 || !alike(d, hp.tiles[i - 1], t)) {
+      c = record_cost(d, t);
+      any = runs_in_any_blocks(d, t);
+      rows = runs_in_rows(d, t);
+      steps = any ? stages_of(t) : 0;
+    }
     total += c.work;
-    if (any) stages += stages_of(t);
+    stages += steps;
     // (up to 64 reduction elements a small rectangle may go the one-output-per-thread way, whose sums round differently: a
     // part must not where its record does not)
-    if (t.S != 1 || (t.m_len <= 64 && t.n_len <= 64) || d.Kg <= 64 || !any || runs_in_rows(d, t)) {
+    if (t.S != 1 || (t.m_len <= 64 && t.n_len <= 64) || d.Kg <= 64 || !any || rows) {
       whole = std::max(whole, c.time);
       continue;
     }
@@ -632,22 +667,18 @@ bool refine_tiles(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &
 // (Nor in plans of less than two rounds of tiles, where runs leave too few records to even the launch's end out: 67 odd bf16 operators 35.9 -> 37.5 us, 30
 // of them 29.4 -> 30.4, ten such plans 0.97 to 1.02; stride-2 layers for five, 885 tiles, would gain 3 %, for six, 1062 tiles, 10 %.)
 static void mark_rows(HostPlan &hp) {
-  bool some = false;
   if ((int64_t)hp.tiles.size() <= 2 * CHIP_WORKGROUPS) return;
   for (const DevProblem &d : hp.dev)
     if (d.dtype != hp.dev[0].dtype) return;
   for (DevProblem &d : hp.dev)
-    if (rows_form(d, elem_size(d.dtype)).ok) d.flags |= FLAG_ROWS, some = true;
-  if (!some) return;
-  int64_t total = 0, rows = 0;
-  for (const sk_tile &t : hp.tiles) {
-    const DevProblem &d = hp.dev[t.problem];
-    const int64_t work = record_cost(d, t).work;
-    total += work;
-    if (runs_in_rows(d, t)) rows += work;
-  }
-  if (rows * 5 < total)
+    if (rows_form(d, elem_size(d.dtype)).ok) d.flags |= FLAG_ROWS, hp.rows = true;
+  if (!hp.rows) return;
+  int64_t rows = 0;
+  const int64_t total = work_of(hp, hp.tiles, &rows);
+  if (rows * 5 < total) {
     for (DevProblem &d : hp.dev) d.flags &= ~FLAG_ROWS;
+    hp.rows = false;
+  }
 }
 
 // What a record takes on a chip whose compute units hold two workgroups each, in nanoseconds: `start` around its steps (set-up, first
@@ -693,8 +724,9 @@ static RecordTime record_time(const DevProblem &d, const sk_tile &t, bool any) {
 // else is in the plan, get none.  Plans with per-die lists get the same slices as without (the bits of a result do not depend on who
 // runs a tile) and stay otherwise as they are.  Nor do they depend on the number of workgroups: `impose` names the slices of a launch that
 // fills a whole MI355X (null: this is that launch, they are settled here).
+// (`slices_only`: out.slicing is all that is wanted of the list.)
 static bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &records, int64_t workgroups, bool drop_lists,
-                            const std::vector<Slicing> *impose, WorkList &out) {
+                            const std::vector<Slicing> *impose, WorkList &out, bool slices_only = false) {
   constexpr int64_t SHORTEST = 14000;
   if (workgroups < 1 || records.empty()) return false;
   const bool lists = !hp.xorder.empty() && !drop_lists;
@@ -835,6 +867,10 @@ static bool balance_records(const HostPlan &hp, const std::vector<sk_tile> &reco
       }
       op.longest = std::max(op.longest, x.time);
     }
+  }
+  if (slices_only) {
+    out.slicing = std::move(slicing);
+    return changed;
   }
   if (hp.params.edf && !lists) {
     auto before = [&](const Op &a, const Op &b) {
@@ -1036,32 +1072,36 @@ bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile>
 // cost the launch's end more than they save there.)  Down-sampling layers with the 7x7 stem, us, in single tiles / in runs of half, a third and a quarter of a
 // share: for sixteen tenants 102.6 / 91.6, 85.4, 91.9, for eleven 70.1 / 65.3, 66.1, 63.8, for eight 54.0 / 53.8, 47.7, 51.1, for six 44.5 / 40.9, 39.9, 44.2;
 // 96 odd-sized operators, of which they are a seventh, 70.5 / 75.7, 75.3, 70.1.  False: nothing changed.
-static bool rows_runs(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile> &records, std::vector<int64_t> &count) {
+static bool rows_runs(const HostPlan &hp, int64_t workgroups, const std::vector<sk_tile> &records, std::vector<sk_tile> &joined,
+                      std::vector<int64_t> &count) {
   constexpr int64_t MOST = 16, BLOCK = 4500;  // blocks; nanoseconds of one, with its part of what is around them
-  if (workgroups < 1) return false;
-  if (std::none_of(hp.dev.begin(), hp.dev.end(), [](const DevProblem &d) { return (d.flags & FLAG_ROWS) != 0; })) return false;
-  int64_t total = 0;
-  for (const sk_tile &t : records) total += record_cost(hp.dev[t.problem], t).work * 2;
-  const int64_t blocks = std::min<int64_t>(MOST, total / workgroups / 3 / BLOCK);
+  if (workgroups < 1 || !hp.rows || !hp.xorder.empty()) return false;
+  const int64_t blocks = std::min<int64_t>(MOST, work_of(hp, records, nullptr) * 2 / workgroups / 3 / BLOCK);
   if (blocks < 2) return false;
-  std::vector<sk_tile> runs;
-  runs.reserve(records.size());
+  joined.clear();
+  joined.reserve(records.size());
+  count.assign(hp.dev.size(), 0);
+  bool open = false, rows = false;  // whether run_tile_rows runs the last of `joined`, this record
+  const sk_tile *last = nullptr;
   for (const sk_tile &t : records) {
-    if (!runs.empty() && runs.back().problem == t.problem && runs.back().n0 == t.n0 && runs.back().m0 + runs.back().m_len == t.m0 &&
-        runs.back().m_len % 128 == 0 && runs.back().m_len + t.m_len <= 128 * blocks && runs_in_rows(hp.dev[t.problem], t)) {
-      sk_tile u = runs.back();
-      u.m_len = (uint16_t)(u.m_len + t.m_len);
-      if (runs_in_rows(hp.dev[t.problem], runs.back()) && runs_in_rows(hp.dev[t.problem], u)) {
-        runs.back() = u;
-        --count[t.problem];
-        continue;
+    const DevProblem &d = hp.dev[t.problem];
+    if (!last || !alike(d, *last, t)) rows = runs_in_rows(d, t);
+    last = &t;
+    if (open && rows) {
+      sk_tile u = joined.back();
+      if (u.problem == t.problem && u.n0 == t.n0 && u.m0 + u.m_len == t.m0 && u.m_len % 128 == 0 && u.m_len + t.m_len <= 128 * blocks) {
+        u.m_len = (uint16_t)(u.m_len + t.m_len);
+        if (in_one_image(d, u)) {
+          joined.back() = u;
+          continue;
+        }
       }
     }
-    runs.push_back(t);
+    open = rows;
+    joined.push_back(t);
+    ++count[t.problem];
   }
-  if (runs.size() == records.size()) return false;
-  records.swap(runs);
-  return true;
+  return joined.size() != records.size();
 }
 
 // The list of tiles, and with `runs` of runs of pixels where they pay, for a launch of that many workgroups.
@@ -1087,22 +1127,23 @@ static bool list_records(const HostPlan &hp, int64_t workgroups, bool runs, bool
   }
   if (tiles_only) return false;
   const bool refined = refine_blocks(hp, workgroups, cut, count);
-  if (hp.xorder.empty()) {
-    std::vector<sk_tile> joined = refined ? cut : hp.tiles;
-    std::vector<int64_t> joined_count = refined ? count : hp.count;
-    if (rows_runs(hp, workgroups, joined, joined_count)) {
-      // (the slices are those of the tiles, with and without lists; order and cuts go by the runs)
-      std::vector<Slicing> own;
-      WorkList plain;
-      if (!impose && balance_records(hp, refined ? cut : hp.tiles, workgroups, false, nullptr, plain)) own = std::move(plain.slicing);
-      cut = std::move(joined);
-      count = std::move(joined_count);
-      if (!balance_records(hp, cut, workgroups, false, impose ? impose : &own, out)) as_cut();
+  const std::vector<sk_tile> &records = refined ? cut : hp.tiles;
+  std::vector<sk_tile> joined;
+  std::vector<int64_t> joined_count;
+  if (rows_runs(hp, workgroups, records, joined, joined_count)) {
+    // (the slices are those of the tiles, with and without lists; order and cuts go by the runs)
+    std::vector<Slicing> own;
+    WorkList plain;
+    if (!impose && balance_records(hp, records, workgroups, false, nullptr, plain, true)) own = std::move(plain.slicing);
+    cut = std::move(joined);
+    count = std::move(joined_count);
+    if (balance_records(hp, cut, workgroups, false, impose ? impose : &own, out))
       out.slicing = std::move(own);
-      return true;
-    }
+    else
+      as_cut();
+    return true;
   }
-  if (balance_records(hp, refined ? cut : hp.tiles, workgroups, false, impose, out)) return true;
+  if (balance_records(hp, records, workgroups, false, impose, out)) return true;
   if (!refined || !hp.xorder.empty()) return false;
   as_cut();
   return true;

@@ -152,6 +152,7 @@ struct HostPlan {
   uint32_t xoff[9] = {};
   sk_plan_params params;
   int64_t target_tile_bytes = 0;
+  bool rows = false;  // some operators are planned as ones of run_tile_rows (FLAG_ROWS)
   // what the device runs in place of the table (see device_list); without records: the table itself
   WorkList run;
   const std::vector<sk_tile> &records() const { return run.work.empty() ? tiles : run.work; }
