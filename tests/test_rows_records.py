@@ -1,7 +1,9 @@
 """The device's records of few-channel convolutions (runs of tiles): on the CPU, that they cover every output once, that tiles are joined where that
 pays and nowhere else, that plans with per-die lists keep the same slices, and that no cost of such a tile makes the planner slice it."""
 import os
+import random
 import shutil
+import struct
 import subprocess
 
 import pytest
@@ -19,39 +21,59 @@ LAYERS = [_conv(224, 3, 64, 7, 3), _conv(56, 128, 128, 3, 1), _conv(28, 256, 256
 
 
 def _records(specs, **prm):
+    """The device's records, how many slices the table gives every operator, and its tiles."""
     at = 1 << 40
     problems = [sk.make_problem(s, at + (i << 32), at + (i << 32) + (1 << 30), at + (i << 32) + (2 << 30)) for i, s in enumerate(specs)]
     with sk.sk_plan_create(problems, sk.sk_plan_params_default(host_only=1, **prm)) as plan:
-        return H.device_records(plan), sk.sk_plan_num_tiles(plan)
+        table = struct.iter_unpack("<IHBBIIHHIII", sk.sk_plan_get_tiles(plan))
+        return H.device_records(plan), {t[0]: t[3] for t in table}, sk.sk_plan_num_tiles(plan)
 
 
 @pytest.mark.parametrize("specs,joined", [
     (LAYERS * 16, True),
-    ([_conv(224, 3, 64, 7, 3, nb=2)] * 8 + LAYERS * 4, True),                        # (tiles of two images stay single)
+    ([_conv(224, 3, 64, 7, 3, nb=2)] * 8 + LAYERS * 4, True),                        # (images of whole tiles)
+    ([_conv(220, 3, 64, 7, 3, nb=3)] * 6 + LAYERS * 4, True),                        # (tiles of two images stay single)
     (LAYERS * 2, False),                                                             # too few tiles
     (LAYERS[:1] * 8 + LAYERS[1:] * 40, False),                                       # not a fifth of the work
     (LAYERS * 12 + [_conv(28, 512, 1024, 1, 0, dtype="f16")], False),                # two types
-], ids=["downsampling", "images", "few", "share", "types"])
+], ids=["downsampling", "images", "across", "few", "share", "types"])
 def test_runs_cover_every_output_once(specs, joined):
-    records, tiles = _records(specs)
+    records, _, tiles = _records(specs)
     assert any(r[6] > 128 for r in records) == joined
     rows = {}
     for p, cls, ks, S, m0, n0, m_len, n_len, k0, k_len, rect in records:
         if specs[p].Cin == 3:
             assert (ks, S, n0, n_len, k0, k_len) == (0, 1, 0, 64, 0, 147)
             rows.setdefault(p, []).append((m0, m0 + m_len))
-            assert m_len <= 128 or m0 // 12544 == (m0 + m_len - 1) // 12544
     for p, s in enumerate(specs):
         if s.Cin == 3:
+            hw = (s.H // 2) ** 2
             spans = sorted(rows[p])
-            assert spans[0][0] == 0 and spans[-1][1] == s.Nb * 12544 and all(a[1] == b[0] for a, b in zip(spans, spans[1:]))
+            assert spans[0][0] == 0 and spans[-1][1] == s.Nb * hw and all(a[1] == b[0] for a, b in zip(spans, spans[1:]))
+            across = [(a, b) for a, b in spans if a // hw != (b - 1) // hw]
+            assert len(across) >= (s.Nb - 1 if hw % 128 else 0) and all(a % 64 == 0 and b - a <= 128 for a, b in across)
     assert (len(records) < tiles) == joined or not joined
 
 
-def test_lists_keep_the_slices():
-    specs = LAYERS * 16
-    slices = [{(r[0], r[4] if specs[r[0]].Cin != 3 else 0, r[8], r[9]) for r in _records(specs, xcd_part=part)[0]} for part in (0, 32)]
-    assert slices[0] == slices[1]
+def _mix(seed):
+    """Stems, whose tiles are joined, beside a few long reductions, which are sliced."""
+    r = random.Random(seed)
+    stems = [_conv(r.randint(150, 270), 3, 64, 7, 3, nb=r.choice([1, 1, 2])) for _ in range(r.randint(5, 24))]
+    return stems + [_conv(r.randint(7, 26), r.randint(128, 2048), r.randint(128, 512), 3, 1, stride=1) for _ in range(r.randint(1, 6))]
+
+
+@pytest.mark.parametrize("seed", [8, 46, 59, 72, 76])
+def test_lists_and_grids_keep_the_slices(seed):
+    """The reduction ranges of every 128 x 128 outputs, in a plan whose tiles are joined and some of whose rectangles only the list slices."""
+    specs = _mix(seed)
+    slices = []
+    for prm in (dict(xcd_part=0), dict(xcd_part=32), dict(xcd_part=0, grid_limit=300)):
+        records, table, _ = _records(specs, **prm)
+        slices.append({(r[0], r[4] // 128 if specs[r[0]].Cin != 3 else 0, r[5] // 128, r[8], r[9]) for r in records})
+        if not prm["xcd_part"]:
+            assert any(r[6] > 128 for r in records)
+            assert any(r[3] != table[r[0]] for r in records)
+    assert slices[0] == slices[1] == slices[2]
 
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
