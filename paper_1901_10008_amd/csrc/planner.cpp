@@ -978,6 +978,13 @@ bool window_operator(const HostPlan &hp, size_t i) {
   return t.cls == CLS_TILE_128x64 && t.S == 1;
 }
 
+// The order of the operators means something.
+static bool several_deadlines(const HostPlan &hp) {
+  return hp.params.edf && std::any_of(hp.problems.begin(), hp.problems.end(), [&](const sk_problem &p) {
+    return deadline_key(p.deadline_ms) != deadline_key(hp.problems[0].deadline_ms);
+  });
+}
+
 // The table with such operators' tiles replaced by runs of pixels; false: none.
 // Only where the tiles are more than the workgroups: with a tile for each at most, a run is a single block of 128 pixels, and its
 // start (weights to registers, 36 loads a wave) is what it takes.  500 tiles of 56x56 images 18.8 us as tiles, 20.0 as runs; 525 tiles, a second
@@ -1004,9 +1011,7 @@ bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile>
   // (the per-die lists of other operators name tiles of the table; lists that the caller has asked for are kept: only the planner's own give
   // way)
   if (!some || (!hp.xorder.empty() && (!all || hp.params.xcd_part > 0))) return false;
-  bool dated = false;  // the order of the operators means something
-  for (const sk_problem &p : hp.problems)
-    dated = dated || (hp.params.edf && deadline_key(p.deadline_ms) != deadline_key(hp.problems[0].deadline_ms));
+  const bool dated = several_deadlines(hp);
   auto steps_of = [&](size_t i) { return (hp.dev[i].Mg + STEP - 1) / STEP; };
   int64_t per = MOST;
   if (all && dated) {
@@ -1071,12 +1076,16 @@ bool window_records(const HostPlan &hp, int64_t workgroups, std::vector<sk_tile>
 // once, and a block's rows while the one before is multiplied.  (Not where they are less than a fifth of the work, FLAG_ROWS: longer records
 // cost the launch's end more than they save there.)  Down-sampling layers with the 7x7 stem, us, in single tiles / in runs of half, a third and a quarter of a
 // share: for sixteen tenants 102.6 / 91.6, 85.4, 91.9, for eleven 70.1 / 65.3, 66.1, 63.8, for eight 54.0 / 53.8, 47.7, 51.1, for six 44.5 / 40.9, 39.9, 44.2;
-// 96 odd-sized operators, of which they are a seventh, 70.5 / 75.7, 75.3, 70.1.  False: nothing changed.
+// 96 odd-sized operators, of which they are a seventh, 70.5 / 75.7, 75.3, 70.1.
+// In a plan of several deadlines of an eighth of a share, so that the first deadlines' operators are not done with the launch's middle: 64 stems with deadlines of
+// their own, us until the first tenth of them in that order are done, all of them in the mean, the last: as tiles 25.5, 76.1 and 138.2, in runs of a
+// third 43.6, 59.9 and 89.2, a fifth 28.2, 54.3 and 87.9, an eighth 24.4, 55.1 and 89.6; stride-2 layers for sixteen 61.5, 61.6 and 97, 65.4, 60.5 and 100,
+// 64, 58.6 and 92, 62.6, 57.4 and 90; sixteen stems 16.4, 28.1 and 42.1, 20.8, 26.4 and 37.2, 16.6, 28.4 and 42.5, as a fifth (tiles).  False: nothing changed.
 static bool rows_runs(const HostPlan &hp, int64_t workgroups, const std::vector<sk_tile> &records, std::vector<sk_tile> &joined,
                       std::vector<int64_t> &count) {
   constexpr int64_t MOST = 16, BLOCK = 4500;  // blocks; nanoseconds of one, with its part of what is around them
   if (workgroups < 1 || !hp.rows || !hp.xorder.empty()) return false;
-  const int64_t blocks = std::min<int64_t>(MOST, work_of(hp, records, nullptr) * 2 / workgroups / 3 / BLOCK);
+  const int64_t blocks = std::min<int64_t>(MOST, work_of(hp, records, nullptr) * 2 / workgroups / (several_deadlines(hp) ? 8 : 3) / BLOCK);
   if (blocks < 2) return false;
   joined.clear();
   joined.reserve(records.size());

@@ -1,5 +1,6 @@
 """The device's records of few-channel convolutions (runs of tiles): on the CPU, that they cover every output once, that tiles are joined where that
 pays and nowhere else, that plans with per-die lists keep the same slices, and that no cost of such a tile makes the planner slice it."""
+import dataclasses
 import os
 import random
 import shutil
@@ -53,6 +54,22 @@ def test_runs_cover_every_output_once(specs, joined):
             across = [(a, b) for a, b in spans if a // hw != (b - 1) // hw]
             assert len(across) >= (s.Nb - 1 if hw % 128 else 0) and all(a % 64 == 0 and b - a <= 128 for a, b in across)
     assert (len(records) < tiles) == joined or not joined
+
+
+def test_runs_of_operators_with_deadlines_are_short():
+    """The first operators in the order of deadlines are not done with the launch's middle: an eighth of a workgroup's share of the launch at most, a third
+    where nothing has a deadline or all have the same."""
+    stem = _conv(224, 3, 64, 7, 3)
+    deadlines = list(range(64, 0, -1))
+    share = 64 * 98 * 9000 // 512 // 4500  # blocks
+    longest = {}
+    for name, at in (("none", [float("inf")] * 64), ("one", [2.0] * 64), ("own", deadlines)):
+        records, _, _ = _records([dataclasses.replace(stem, deadline_ms=d) for d in at])
+        longest[name] = max(r[6] for r in records) // 128
+        order = [r[0] for r in records]
+        assert order == sorted(order, key=lambda p: at[p])
+    assert longest["none"] == longest["one"] == share // 3
+    assert 1 < longest["own"] == share // 8
 
 
 def _mix(seed):
