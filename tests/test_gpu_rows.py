@@ -35,9 +35,36 @@ def test_rows(name, off):
 
 
 def test_the_stem_of_a_residual_network():
-    """7x7 on 224x224x3, alone and for three tenants: one type a plan, as it is used."""
+    """7x7 on 224x224x3, two of them in one plan of their type (in fp32 as patches: their window does not fit LDS)."""
     for dt in ("bf16", "f16", "f32"):
         run_all_modes([c(224, 224, 3, 64, 7, 7, 3, 3, dt, st=2)] * 2, seed=62, label=dt)
+
+
+# Enough tiles of few-channel operators for runs of several blocks: last blocks of 8 to 126 pixels, blocks of several rows of the image and within one,
+# images whose tiles are joined only within each, steps between patches that are even and odd, runs of one to four and six pieces.
+RUNS = {
+    "bf16": [c(220, 220, 3, 8, 7, 7, 3, 3, st=2), c(111, 111, 5, 12, 5, 5, 2, 2), c(140, 70, 5, 9, 3, 3, 1, 1, nb=2), c(10, 1203, 1, 16, 3, 8, 1, 4)] * 6,
+    "f16": [c(113, 113, 1, 7, 5, 9, 2, 4, "f16"), c(128, 100, 3, 64, 3, 3, 1, 1, "f16"), c(200, 63, 9, 10, 5, 5, 2, 2, "f16"), c(225, 227, 3, 5, 7, 7, 0, 0, "f16", st=2)] * 6,
+    "f32": [c(111, 111, 3, 8, 5, 5, 2, 2, "f32"), c(158, 80, 1, 12, 3, 4, 1, 2, "f32"), c(94, 129, 2, 33, 3, 3, 1, 1, "f32"), c(70, 91, 5, 6, 3, 3, 1, 1, "f32", nb=2)] * 6,
+}
+
+
+@pytest.mark.parametrize("dtype", sorted(RUNS))
+def test_runs_of_several_blocks(dtype):
+    """One record takes several blocks of 128 pixels, the next one's rows on their way while one is multiplied.  run_all_modes compares them with the oracle
+    and bit for bit with plans that have lists, where nothing is joined."""
+    specs = RUNS[dtype]
+    b = H.Batch(specs, seed=64)
+    with b.plan() as plan:
+        records = H.device_records(plan)
+        blocks = {p: max(-(-r[6] // 128) for r in records if r[0] == p) for p in range(len(specs))}
+        assert all(n >= 2 for n in blocks.values()), blocks
+        partial = {r[6] % 128 for r in records if r[6] > 128}
+        assert len(partial) > 1, partial
+    with b.plan(xcd_part=32) as plan:
+        assert max(r[6] for r in H.device_records(plan)) <= 128
+    del b
+    run_all_modes(specs, seed=64, label=dtype)
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
