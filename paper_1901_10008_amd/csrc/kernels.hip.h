@@ -2453,7 +2453,13 @@ constexpr int PLANES_TAPS = 12;  // the most planes_form lets through
 template <int ES>
 __device__ __forceinline__ bool planes_tile(const DevProblem &P, const sk_tile &T) {
   constexpr int CE = 16 / ES;
-  if (!planes_form(P, ES)) return false;
+  // (fp32: the host's answer.  The 16-bit kernels ask again: with the flags their other paths took 1 to 2 % longer, see rows_tile.)
+  if constexpr (ES == 4) {
+    if (!(P.flags & FLAG_PLANES_FORM)) return false;
+    if (P.Mg == P.Ho * P.Wo) return true;  // one image
+  } else {
+    if (!planes_form(P, ES)) return false;
+  }
   const int b0 = fast_div((int)T.m0, P.div_hw), b1 = fast_div((int)T.m0 + (int)T.m_len - 1, P.div_hw);
   // (a piece of pixels lies in one image, and all offsets within 2^31 bytes)
   return (b0 == b1 || (P.Ho * P.Wo) % CE == 0) && offsets_below(P, b1 - b0, ES, (int64_t)1 << 31);
@@ -2719,9 +2725,16 @@ __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const s
 // Pieces and their order are those of run_tile_any: the same sums, the same bits.  7x7 stems on 224x224x3 of 64 tenants 146 -> 80 us, of 16 beside the
 // other down-sampling layers of a residual network 100.4 -> 74.2; with the positions worked out piece by piece in the loop, a hundred scalar
 // instructions a step, 127 of 146.
+// Parts of 64 rows, as refine_tiles cuts them where the operators are not marked, go the way of all others in 16-bit types: half a block's waves would
+// repeat the last pixel, and every part loads the weights (one, two and four 7x7 stems 10.4, 12.6 and 22.3 us in half blocks, 9.9, 12.0 and 21.1 so, 9.9, 12.0 and 21.1
+// before there was this path).  fp32 parts gain either way (3x3 on 60x60 11.6 us as patches, 9.2 here).
+// Whether the form serves is the host's answer in fp32, worked out per tile it was 0.4 us of each (the same stem 9.8 us); the 16-bit kernels ask the form itself: with
+// the flag the compiler kept 27 scalars more in vector lanes and the paths beside this one took 1 to 2 % longer (odd products of 200 rows x12 59.1 and 60.3 us).
 template <int ES>
 __device__ __forceinline__ bool rows_tile(const DevProblem &P, const sk_tile &T) {
-  if (T.cls < CLS_TILE_128x128 || T.S != 1 || !rows_form(P, ES).ok) return false;
+  if (T.cls < CLS_TILE_128x128 || T.S != 1) return false;
+  if (ES == 2 && !(P.flags & FLAG_ROWS) && (int)T.m_len <= 64) return false;
+  if (!(ES == 4 ? (P.flags & FLAG_ROWS_FORM) != 0 : rows_form(P, ES).ok)) return false;
   return fast_div((int)T.m0, P.div_hw) == fast_div((int)T.m0 + (int)T.m_len - 1, P.div_hw);
 }
 
@@ -2785,6 +2798,9 @@ __device__ __forceinline__ void run_tile_rows(const DevProblem *P_mem, const sk_
   const int run_len = P.S * P.Cin, row_len = P.W * P.Cin;
   const int row_pieces = F.image_row / 16;
   const int np = P.R * F.pieces;  // pieces of a patch, and of a weight row
+  // pieces of a block's rows per thread, ROWS_LOADS at most; loaded, shifted and cleared in pairs (all six always: 3x3 stems on 112x112 x16 10.8 us, so 9.9; each
+  // asked for by itself costs the kernel 40 scalars more in vector lanes, and its other paths 1 to 4 %)
+  const int loads = (F.rows * row_pieces + WG_THREADS - 1) / WG_THREADS;
   unsigned char *const window = lds + 64 * F.weight_row;
   const char SK_GLOBAL *const image = as_global<char>(P.A) + (int64_t)b * P.H * row_len * ES;
 
@@ -2807,6 +2823,7 @@ __device__ __forceinline__ void run_tile_rows(const DevProblem *P_mem, const sk_
     const int h0 = first_row(mb) * P.stride - P.pad_h;
 #pragma unroll
     for (int i = 0; i < ROWS_LOADS; ++i) {
+      if (i % 2 == 0 && i >= loads) break;
       const int h = min(max(h0 + win_row[i], 0), P.H - 1);  // (rows outside the image are cleared when stored)
       win[i] = *(const u32x4_any SK_GLOBAL *)(image + (uint32_t)(h * (row_len * ES) + win_at[i]));
     }
@@ -2815,6 +2832,7 @@ __device__ __forceinline__ void run_tile_rows(const DevProblem *P_mem, const sk_
     const int r0 = first_row(mb), h0 = r0 * P.stride - P.pad_h, rows = (first_row(min(mb + BM, m_end) - 1) - r0) * P.stride + P.R;
 #pragma unroll
     for (int i = 0; i < ROWS_LOADS; ++i) {
+      if (i % 2 == 0 && i >= loads) break;
       u32x4 v = win[i];
       if (__any(win_sh[i] != 0)) v = shift_piece<ES>(v, win_sh[i]);
       const bool in = (unsigned)(h0 + win_row[i]) < (unsigned)P.H;

@@ -315,6 +315,8 @@ sk_status plan_host(const sk_problem *problems, int32_t n, const sk_plan_params 
     }
     if (aligned16(p.B) && d.ldb % ce == 0 && c.Kg % ce == 0) flags |= FLAG_VEC_B;
     if (!d.nchw && (reinterpret_cast<uintptr_t>(p.C) % (4 * es)) == 0 && d.ldc % 4 == 0) flags |= FLAG_VEC_C;
+    if (planes_form(d, es) && offsets_below(d, 0, es, (int64_t)1 << 31)) flags |= FLAG_PLANES_FORM;
+    if (rows_form(d, es).ok) flags |= FLAG_ROWS_FORM;
     d.flags = flags;
     out.dev[i] = d;
     total_w += stream_bytes(c.Mg, c.Ng, c.Kg, es, prm);
@@ -671,7 +673,7 @@ static void mark_rows(HostPlan &hp) {
   for (const DevProblem &d : hp.dev)
     if (d.dtype != hp.dev[0].dtype) return;
   for (DevProblem &d : hp.dev)
-    if (rows_form(d, elem_size(d.dtype)).ok) d.flags |= FLAG_ROWS, hp.rows = true;
+    if (d.flags & FLAG_ROWS_FORM) d.flags |= FLAG_ROWS, hp.rows = true;
   if (!hp.rows) return;
   int64_t rows = 0;
   const int64_t total = work_of(hp, hp.tiles, &rows);

@@ -15,7 +15,9 @@ enum : int32_t {
   FLAG_VEC_A = 1,  // activation rows can be read in aligned 16-byte pieces
   FLAG_VEC_B = 2,  // weight rows can be read in aligned 16-byte pieces
   FLAG_VEC_C = 4,  // four consecutive outputs of a row can be stored as one vector
-  FLAG_ROWS = 16,  // the host plans the operator as one of run_tile_rows (which runs it in either case)
+  FLAG_ROWS = 16,         // the host plans the operator as one of run_tile_rows (mark_rows)
+  FLAG_ROWS_FORM = 32,    // run_tile_rows serves the operator's form (rows_form)
+  FLAG_PLANES_FORM = 64,  // run_tile_planes does (planes_form)
   FLAG_PAST_CACHES = 8,  // outputs of whole tiles go past the caches (of every operator of the plan, or of none)
 };
 

@@ -22,6 +22,9 @@ FORMS = {
     # padding on one side only, beyond the filter, and none; one row, one column, images no wider than a filter
     "padding": [c(13, 17, 3, 20, 5, 5, 0, 0), c(13, 17, 3, 20, 5, 5, 4, 1), c(12, 12, 3, 20, 3, 3, 5, 6, st=2), c(1, 200, 3, 16, 1, 3, 0, 1),
                 c(200, 3, 3, 16, 3, 3, 1, 1), c(150, 5, 3, 33, 7, 7, 3, 3, "f16"), c(3, 100, 6, 64, 5, 5, 2, 2), c(129, 3, 5, 8, 3, 3, 1, 1, "f32")],
+    # windows of five and six pieces a thread (all others here take one to four)
+    "windows": [c(40, 260, 3, 16, 5, 5, 2, 2, st=3), c(40, 190, 9, 16, 3, 3, 1, 1, st=2), c(40, 130, 9, 24, 5, 5, 2, 2, "f16", st=2),
+                c(40, 260, 3, 16, 5, 5, 2, 2, "f32"), c(40, 75, 7, 16, 3, 3, 1, 1, "f32", st=2)],
     # several images: blocks in one each, and blocks that would not be (patches)
     "images": [c(16, 8, 3, 24, 3, 3, 1, 1, nb=3), c(15, 15, 3, 64, 3, 3, 1, 1, nb=2), c(32, 16, 5, 30, 5, 5, 2, 2, st=2, nb=4, dtype="f16"), c(16, 16, 3, 24, 3, 3, 1, 1, "f32", nb=3)],
 }
