@@ -4,7 +4,8 @@ A measuring aid, not part of the boundary.  It uses a second build of the librar
 `-DSK_DIAG_CLOCKS`, libsuperkernel_diag.so) in which thread 0 of the first workgroups stamps the device clock at
 the phase boundaries of every tile it runs: tile taken up, set-up done, first main-loop step multiplied, main
 loop done, outputs stored, next tile's record handed to all waves.  The stamps of one launch are read back and
-averaged per tile class:
+averaged per tile class (of tiles in the paths for operands of any alignment, runs of them and channel-major images among them, the whole
+tile's time alone, ", any"):
 
     python -m paper_1901_10008_amd.tile_phases --config 5
     python -m paper_1901_10008_amd.tile_phases --config 8 --replicate 16
@@ -63,15 +64,17 @@ def phase_table(stamps) -> str:
     for wg in range(stamps.shape[0]):
         for t in range(stamps.shape[1]):
             x = stamps[wg, t]
-            if x[6] == 0 or x[1] == 0 or x[5] == 0:  # no tile, a tile of the element-wise paths, or not finished
+            if x[6] == 0 or x[5] == 0:  # no tile, or not finished
                 continue
-            key = (int(x[6] - 1) % 100, int(x[6] - 1) // 100 > 1)
-            by.setdefault(key, []).append([x[1] - x[0], x[2] - x[1], x[3] - x[2], x[4] - x[3], x[5] - x[4], x[5] - x[0]])
+            inner = x[1] != 0  # (the paths for operands of any alignment have no stamps inside: the whole tile's time alone)
+            key = (int(x[6] - 1) % 100, int(x[6] - 1) // 100 > 1, not inner)
+            by.setdefault(key, []).append([x[1] - x[0], x[2] - x[1], x[3] - x[2], x[4] - x[3], x[5] - x[4], x[5] - x[0]] if inner else
+                                          [0, 0, 0, 0, 0, x[5] - x[0]])
     lines = [f"{'tile class':28s} {'tiles':>6s} " + " ".join(f"{p:>11s}" for p in PHASES) + "   (mean, us)"]
     for key in sorted(by):
         r = np.array(by[key], dtype=np.float64) / 100.0
-        name = CLASS_NAMES.get(key[0], f"class {key[0]}") + (", slice" if key[1] else "")
-        lines.append(f"{name:28s} {len(r):6d} " + " ".join(f"{r[:, i].mean():11.2f}" for i in range(len(PHASES))))
+        name = CLASS_NAMES.get(key[0], f"class {key[0]}") + (", slice" if key[1] else "") + (", any" if key[2] else "")
+        lines.append(f"{name:28s} {len(r):6d} " + " ".join(f"{'-':>11s}" if key[2] and i < 5 else f"{r[:, i].mean():11.2f}" for i in range(len(PHASES))))
     return "\n".join(lines)
 
 
