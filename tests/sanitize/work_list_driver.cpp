@@ -299,6 +299,72 @@ int main() {
     for (size_t i = 0; i < bad.size(); ++i)
       if (area[i] != (int64_t)hp.dev[i].Mg * hp.dev[i].Ng) return fail("outputs beside runs of pixels", seed);
   }
+  // Runs of few-channel tiles: in plans of one type, beside long reductions and channel counts of any kind.  Every output once, a run in one image and of
+  // one operator that the form takes, never sliced, slices as without lists and on other grids, the operators in the order of their deadlines.
+  int joined = 0, beside = 0;
+  for (int seed = 0; seed < 150; ++seed) {
+    std::mt19937 g(seed);
+    auto pick = [&](std::initializer_list<int> v) { return *(v.begin() + g() % v.size()); };
+    std::vector<sk_problem> ps((size_t)(8 + g() % 30));
+    uintptr_t addr = 0x10000000;
+    const int dt = pick({SK_BF16, SK_F16, SK_F32}), deadlines = (int)(g() % 2);
+    for (size_t i = 0; i < ps.size(); ++i) {
+      sk_problem &p = ps[i];
+      p = sk_problem{};
+      p.op = SK_CONV2D_NHWC, p.dtype = dt, p.Nb = pick({1, 1, 1, 2}), p.deadline_ms = deadlines * (double)(1 + g() % 4);
+      if (i % 4 != 3) {
+        p.H = 40 + (int)(g() % 190), p.Wd = 40 + (int)(g() % 190), p.Cin = pick({1, 3, 3, 5}), p.Cout = pick({5, 32, 64, 64, 65});
+        p.R = p.S = pick({3, 5, 7}), p.pad_h = p.pad_w = p.R / 2, p.stride = pick({1, 2, 2});
+      } else {
+        p.op = pick({SK_CONV2D_NHWC, SK_CONV2D_NHWC, SK_CONV2D_NCHW}), p.H = p.Wd = 7 + (int)(g() % 20), p.Cin = 128 + (int)(g() % 1900);
+        p.Cout = 128 + (int)(g() % 400), p.R = p.S = 3, p.pad_h = p.pad_w = 1, p.stride = 1;
+      }
+      p.A = (const void *)addr, p.B = (const void *)(addr + (1u << 28)), p.C = (void *)(addr + (2u << 28));
+      addr += (uintptr_t)3 << 28;
+    }
+    std::map<std::tuple<uint32_t, uint32_t, uint32_t>, Slices> plain;
+    for (int part : {0, 4}) {
+      sk_plan_params prm;
+      sk_plan_params_default(&prm);
+      prm.host_only = 1;
+      prm.xcd_part = part;
+      sk::HostPlan hp;
+      std::string err;
+      if (sk::plan_host(ps.data(), (int)ps.size(), &prm, hp, err) != SK_OK) return fail(err.c_str(), seed);
+      bool marked = false;
+      for (const sk::DevProblem &d : hp.dev) marked = marked || (d.flags & sk::FLAG_ROWS) != 0;
+      if (marked != hp.rows || (marked && hp.tiles.size() <= 1024)) return fail("marked operators", seed);
+      for (int64_t wgs : {(int64_t)512, (int64_t)200, (int64_t)33}) {
+        sk::WorkList w;
+        if (!sk::device_list(hp, wgs, false, w)) {
+          w.work = hp.tiles, w.count = hp.count, w.ws_off = hp.ws_off, w.ws_f32x4 = hp.ws_f32x4, w.xorder = hp.xorder;
+          std::copy(std::begin(hp.xoff), std::end(hp.xoff), std::begin(w.xoff));
+        }
+        std::map<std::tuple<uint32_t, uint32_t, uint32_t>, Slices> slices;
+        if (const char *what = check(hp, w, slices)) return fail(what, seed);
+        bool run = false, anew = false;
+        for (size_t i = 0; i < w.work.size(); ++i) {
+          const sk_tile &t = w.work[i];
+          const sk::DevProblem &d = hp.dev[t.problem];
+          anew = anew || t.S != hp.tiles[(size_t)hp.first[t.problem]].S;
+          if (prm.edf && i && ps[w.work[i - 1].problem].deadline_ms > ps[t.problem].deadline_ms) return fail("runs of tiles out of order", seed);
+          if (t.m_len <= 128) continue;
+          run = true;
+          const uint32_t hw = (uint32_t)(d.Ho * d.Wo);
+          if (!(d.flags & sk::FLAG_ROWS) || !sk::rows_form(d, (int32_t)sk::elem_size(d.dtype)).ok || part != 0 || t.S != 1 || t.m0 % 128 != 0 ||
+              t.m0 / hw != (t.m0 + t.m_len - 1) / hw)
+            return fail("a run of tiles", seed);
+        }
+        joined += run;
+        beside += run && anew;
+        if (plain.empty()) plain = slices;
+        if (plain.size() != slices.size()) return fail("blocks beside runs of tiles", seed);
+        for (const auto &s : slices)
+          if (same(s.second) != same(plain[s.first])) return fail("slices beside runs of tiles", seed);
+      }
+    }
+  }
+  if (joined < 50 || beside < 5) return fail("too few plans with runs of tiles", joined * 1000 + beside);
   // outputs past the caches: all operators of a plan of more than 160 MiB, or none
   for (int n : {1, 3, 40}) {
     for (int k : {1000, 27279, 27280, 80000}) {  // n operators of 2 x (1024 k + k + 1024) bytes
