@@ -1693,7 +1693,7 @@ __device__ __forceinline__ void run_lds_tile(const DevProblem &P, const sk_tile 
 // The sums are taken in the tiles' order: the same bits.
 // 512 tenants of 56x56, 64 to 64 (0.45 GB, 118 GFLOP), every launch on other operands: 214 to 230 us in the kernel for tiles
 // alone, 124 here: 3.6 TB/s of operands and outputs against the 4.8 of a large copy.  (Of 130, with half lines stored and operands the same every
-// time, it took 107 without its MFMAs, 120 without its fragment reads, 112 without storing the outputs.)  Bound by memory, with the MFMAs (42 % of the SIMD cycles by SQ_VALU_MFMA_BUSY_CYCLES) not quite beside it.  Fragments two or three steps ahead measure the same.
+// time, it took 107 without its MFMAs, 120 without its fragment reads, 112 without storing the outputs.)  Bound by memory, with the MFMAs (46 % of the SIMD cycles by SQ_VALU_MFMA_BUSY_CYCLES) not quite beside it.  Fragments two or three steps ahead measure the same.
 constexpr int WIN_BLOCK = 128;                          // pixels per step and ring block
 constexpr int WIN_RING = 3 * WIN_BLOCK;                 // pixels in the ring
 constexpr int WIN_OROW = 144;                              // bytes of a pixel's outputs in LDS, padded
@@ -2722,9 +2722,10 @@ __device__ __forceinline__ void run_tile_planes(const DevProblem *P_mem, const s
 //   * the weights (at most 64 channels) stay in LDS for all blocks of the record, and the next block's rows are on their way while one
 //     is multiplied;
 //   * a wave makes 32 pixels x 64 channels, so that each pixel's fragments are read and cleared once.
-// Pieces and their order are those of run_tile_any: the same sums, the same bits.  7x7 stems on 224x224x3 of 64 tenants 146 -> 80 us, of 16 beside the
-// other down-sampling layers of a residual network 100.4 -> 74.2; with the positions worked out piece by piece in the loop, a hundred scalar
-// instructions a step, 127 of 146.
+// Pieces and their order are those of run_tile_any: the same sums, the same bits.  7x7 stems on 224x224x3 of 64 tenants 140 -> 72 us, of 16 beside the
+// other down-sampling layers of a residual network 100.4 -> 73.7; with the positions worked out piece by piece in the loop, a hundred scalar
+// instructions a step, it gained 19 us of the 66 then.  Not where there is little else in a launch to gain it from: 5x5 filters on one channel (runs shorter than a
+// piece, patches as before) 8.7 -> 9.1 us, by what this path costs the kernel's others in scalars.
 // Parts of 64 rows, as refine_tiles cuts them where the operators are not marked, go the way of all others in 16-bit types: half a block's waves would
 // repeat the last pixel, and every part loads the weights (one, two and four 7x7 stems 10.4, 12.6 and 22.3 us in half blocks, 9.9, 12.0 and 21.1 so, 9.9, 12.0 and 21.1
 // before there was this path).  fp32 parts gain either way (3x3 on 60x60 11.6 us as patches, 9.2 here).

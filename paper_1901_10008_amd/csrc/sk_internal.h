@@ -78,11 +78,14 @@ SK_HOST_DEVICE bool planes_form(const DevProblem &d, int64_t es) {
 // How run_tile_rows holds an NHWC convolution of few channels in LDS: `pieces` of 16 bytes per filter row's run of S * Cin elements, a weight row of
 // `weight_row` bytes, a row of the image (its padding included) of `image_row`, of which a tile needs `rows` at most.  ok: it serves the
 // operator (filters and images small enough, at most 64 output channels, runs of one to four or six pieces, image rows of at least one).
+// What it leaves out, which runs as patches: windows of more than ROWS_LOADS pieces a thread, which wait in registers for a block (7x7 on 224x224 RGB in fp32,
+// 30.6 KB against 24, and on 448 columns in 16 bits); more channels than the two fragments a wave multiplies a pixel by; runs of five pieces (11x11 on
+// RGB in 16 bits), an instantiation of the products more per type.
 struct RowsForm {
   bool ok;
   int32_t pieces, weight_row, image_row, rows;
 };
-constexpr int32_t ROWS_LOADS = 6;               // pieces of an image window per thread
+constexpr int32_t ROWS_LOADS = 6;               // pieces of an image window per thread, at most
 constexpr int32_t ROWS_LDS = 512 * 144;         // LDS_TILE_BYTES of the kernels
 SK_HOST_DEVICE RowsForm rows_form(const DevProblem &d, int32_t es) {
   const int32_t ce = 16 / es;
